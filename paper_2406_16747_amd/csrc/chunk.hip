@@ -14,10 +14,8 @@
 // evaluated) and compacts the survivors back into the state.  Inside the virtual sequence
 // distances of at most w are preserved (the last w retained entries are the true window), and
 // dropped keys cannot change any threshold or selection, so every chunk query sees exactly the
-// keys and gates of the unchunked run.  The padding carries scores 2 below every real one: it
-// never enters a support once k real keys exist; while fewer exist the real gates are all 1, as
-// they must be, and the padding itself is kept out of every query's key set (lifetimes cleared,
-// and the attention kernel is told the first real position, so its window stops there).
+// keys and gates of the unchunked run.  The mask and attention kernels are told the first real
+// position: rows start there, and the padding is kept out of every query's key set (lifetimes cleared).
 #include "common.hpp"
 
 namespace spk {
@@ -96,32 +94,20 @@ __global__ void chunk_init_kernel(int32_t* count, int32_t* flags, int rows)
     if (i < rows) { count[i] = 0; flags[i] = 0; }
 }
 
-// Scores of the virtual sequence of one row: padding (min - 2), retained, chunk.
+// Scores of the virtual sequence of one row: padding (-inf, nobody looks at it), retained, chunk.
 __global__ __launch_bounds__(1024) void chunk_assemble_scores_kernel(const int32_t* __restrict__ count,
                                                                      const float* __restrict__ ret_u,
                                                                      const float* __restrict__ u_chunk, int rcap,
                                                                      int clen, float* __restrict__ u_v,
                                                                      int32_t* __restrict__ first_valid)
 {
-    __shared__ float red[16];
-    const int row = blockIdx.x, tid = threadIdx.x;
-    const int R = count[row];
-    const int pad = rcap - R, nv = rcap + clen;
-    if (tid == 0) first_valid[row] = pad;
-    const float* ru = ret_u + (size_t)row * rcap;
-    const float* cu = u_chunk + (size_t)row * clen;
-    float mn = INFINITY;
-    for (int i = tid; i < R; i += 1024) mn = fminf(mn, ru[i]);
-    for (int i = tid; i < clen; i += 1024) mn = fminf(mn, cu[i]);
-    mn = wave_min_f32(mn);
-    if ((tid & 63) == 0) red[tid >> 6] = mn;
-    __syncthreads();
-    float m = red[0];
-#pragma unroll
-    for (int i = 1; i < 16; i++) m = fminf(m, red[i]);
-    const float dummy = m - 2.0f;
-    float* out = u_v + (size_t)row * nv;
-    for (int e = tid; e < nv; e += 1024) out[e] = e < pad ? dummy : e < rcap ? ru[e - pad] : cu[e - rcap];
+    const int row = blockIdx.y;
+    const int pad = rcap - count[row], nv = rcap + clen;
+    const int e = blockIdx.x * 1024 + threadIdx.x;
+    if (e == 0) first_valid[row] = pad;
+    if (e < nv)
+        u_v[(size_t)row * nv + e] = e < pad ? -INFINITY : e < rcap ? ret_u[(size_t)row * rcap + (e - pad)]
+                                                                   : u_chunk[(size_t)row * clen + (e - rcap)];
 }
 
 // K and V rows of the virtual sequence of one head (16 bytes per thread and step).  Padding rows
@@ -316,13 +302,13 @@ int launch_chunk_prefill(const sparsek_chunk_cfg& c, void* state, int clen, cons
     uint4* v_v = (uint4*)(w + W.v);
     const sparsek_cfg cv = virtual_cfg(c, nv);
 
-    hipLaunchKernelGGL(chunk_assemble_scores_kernel, dim3(rows), dim3(1024), 0, st, count, ret_u, u, L.rcap, clen, u_v,
+    hipLaunchKernelGGL(chunk_assemble_scores_kernel, dim3((nv + 1023) / 1024, rows), dim3(1024), 0, st, count, ret_u, u, L.rcap, clen, u_v,
                        first_valid);
     const int gx = (int)std::min<size_t>(((size_t)nv * row16 + 255) / 256, 2048);
     hipLaunchKernelGGL(chunk_assemble_rows_kernel, dim3(gx, BH), dim3(256), 0, st, count, ret_k, ret_v, (const uint4*)k,
                        (const uint4*)v, c.H, c.Gu, L.rcap, clen, row16, k_v, v_v);
     // thresholds are needed from prefix R_cap - w - 1 on (the last one the previous call used)
-    int rc = launch_mask(cv, u_v, tau_v, death_v, w + W.mask, st, std::max(0, L.rcap - c.w - 1));
+    int rc = launch_mask(cv, u_v, tau_v, death_v, w + W.mask, st, std::max(0, L.rcap - c.w - 1), first_valid);
     if (rc) return rc;
     hipLaunchKernelGGL(chunk_clear_padding_kernel, dim3((L.rcap + 255) / 256, rows), dim3(256), 0, st, count,
                        (const int32_t*)(s + L.ret_sel), L.rcap, nv, death_v);
@@ -392,7 +378,7 @@ int launch_chunk_bwd(const sparsek_chunk_cfg& c, int clen, const void* q, const 
     cv.gate_mode = c.gate_mode;  // the straight-through mode has its own score gradient
     float* du_v = (float*)(b + Bw.du);
     rc = launch_mask_bwd(cv, q, k_v, v_v, u_v, tau_v, death_v, o, lse, dO, du_v, b + Bw.mask, st, L.rcap, clen,
-                         std::max(0, L.rcap - c.w - 1));
+                         std::max(0, L.rcap - c.w - 1), first_valid);
     if (rc) return rc;
     hipLaunchKernelGGL(chunk_slice_du_kernel, dim3((clen + 255) / 256, rows), dim3(256), 0, st, du_v, nv, L.rcap, clen, du);
     return launch_status();
@@ -422,13 +408,13 @@ int launch_chunk_to_decode(const sparsek_chunk_cfg& c, void* state, void* ws, co
     uint4* k_v = (uint4*)(w + W.k);
     uint4* v_v = (uint4*)(w + W.v);
     const sparsek_cfg cv = virtual_cfg(c, nv);
-    hipLaunchKernelGGL(chunk_assemble_scores_kernel, dim3(rows), dim3(1024), 0, st, count, (const float*)(s + L.ret_u),
+    hipLaunchKernelGGL(chunk_assemble_scores_kernel, dim3((nv + 1023) / 1024, rows), dim3(1024), 0, st, count, (const float*)(s + L.ret_u),
                        (const float*)nullptr, L.rcap, 0, u_v, (int32_t*)(w + W.first));
     const int gx = (int)std::min<size_t>(((size_t)nv * row16 + 255) / 256, 2048);
     hipLaunchKernelGGL(chunk_assemble_rows_kernel, dim3(gx, BH), dim3(256), 0, st, count, (const uint4*)(s + L.ret_k),
                        (const uint4*)(s + L.ret_v), (const uint4*)nullptr, (const uint4*)nullptr, c.H, c.Gu, L.rcap, 0,
                        row16, k_v, v_v);
-    int rc = launch_mask(cv, u_v, tau_v, death_v, w + W.mask, st, std::max(0, L.rcap - c.w - 1));
+    int rc = launch_mask(cv, u_v, tau_v, death_v, w + W.mask, st, std::max(0, L.rcap - c.w - 1), (const int32_t*)(w + W.first));
     if (rc) return rc;
     hipLaunchKernelGGL(chunk_clear_padding_kernel, dim3((L.rcap + 255) / 256, rows), dim3(256), 0, st, count,
                        (const int32_t*)(s + L.ret_sel), L.rcap, nv, death_v);

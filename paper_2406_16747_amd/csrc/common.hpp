@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "../../include/sparsek.h"
 
 #define SPK_WAVE 64
@@ -10,10 +12,11 @@
 namespace spk {
 
 // Launch wrappers implemented in the .hip files; all return a SPARSEK_* code.
-// t_begin > 0: thresholds of prefixes before t_begin are not needed and deaths that fall before it are left at
-// their preset (chunked prefill); the 128-prefix blocks that end at or before t_begin are skipped.
+// t_begin > 0 (chunked prefill): the 128-prefix blocks that end at or before t_begin are skipped; their thresholds and
+// the lifetimes of the keys that die there are not written.  first_valid: row r starts at position first_valid[r] (what
+// lies before does not exist and nothing is written for it).
 int launch_mask(const sparsek_cfg& c, const float* u, float* tau, int32_t* death, void* ws,
-                hipStream_t st, int t_begin = 0);
+                hipStream_t st, int t_begin = 0, const int32_t* first_valid = nullptr);
 size_t mask_ws_bytes(const sparsek_cfg& c);
 // copies the status word that the last launch_mask on `ws` left (bit 0: a threshold solve hit its iteration cap) and waits
 int mask_status(const sparsek_cfg& c, const void* ws, int32_t* host_flag, hipStream_t st);
@@ -29,9 +32,9 @@ size_t attn_fwd_ws_bytes(const sparsek_cfg& c);
 int launch_mask_bwd(const sparsek_cfg& c, const void* q, const void* k, const void* v,
                     const float* u, const float* tau, const int32_t* death, const void* o,
                     const float* lse, const void* dO, float* du, void* ws, hipStream_t st, int q_begin = 0,
-                    int q_rows = 0, int t_min = 0);
-// (q_begin, q_rows as in launch_attn_fwd, for q, o, dO and lse; thresholds of prefixes before t_min are not read;
-//  bf16 with d = 64 or 128 only when any of them is set)
+                    int q_rows = 0, int t_min = 0, const int32_t* first_valid = nullptr);
+// (q_begin, q_rows as in launch_attn_fwd, for q, o, dO and lse; thresholds of prefixes before t_min are not read, row r
+//  starts at position first_valid[r]; bf16 with d = 64 or 128 only when any of them is set)
 size_t mask_bwd_ws_bytes(const sparsek_cfg& c);
 int launch_attn_bwd(const sparsek_cfg& c, const void* q, const void* k, const void* v, const float* u,
                     const float* tau, const int32_t* death, const void* o, const float* lse, const void* dO,

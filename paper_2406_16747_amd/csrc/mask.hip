@@ -1,197 +1,54 @@
 // Stages 1+2: SPARSEK thresholds tau_t for every causal prefix and per-key lifetimes.
 //
-// The paper evaluates the prefixes one after another with two heaps on the CPU
-// (Sec. 3.3, incremental algorithm; App. B.3).  Here the sequence is cut into chunks of
-// CHUNK prefixes that are solved independently, one workgroup each:
-//   * tau_t and the k-th largest score theta_t never decrease once the prefix holds k
-//     entries (Sec. 3.2, irreversibility), so for a chunk starting at t0 only the scores
-//     above a lower bound lo <= tau_{t0-1} can matter; a first kernel finds such a bound
-//     at coarse boundaries, the chunk kernel compacts those candidates into LDS, sorts them
-//     once (selection order, bitonic) and takes fp64 prefix sums of the sorted scores;
-//   * inside a chunk every wave owns a few consecutive prefixes.  tau_t is the root of
-//     f_t(x) = sum clip(z - x, 0, 1) = k, found by repeating the closed form of the
-//     solution equation (tau from u*, w* and the fractional sum) until the pair (u*, w*)
-//     reproduces itself -- exact, not an iteration to a tolerance; a bracket guards it.
-//     One evaluation of (u*, w*, fractional sum) is two searches in the sorted list plus a
-//     difference of prefix sums for the older scores, and a direct pass over the chunk's own
-//     (at most CHUNK) scores, which enter one by one.  theta_t follows by "newcomer in,
-//     smallest out" with a pointer into the sorted list;
-//   * death[j] is the first t with sel_key(j) < theta_t: a binary search in the chunk.
+// The paper evaluates the prefixes one after another with two heaps on the CPU (Sec. 3.3, incremental
+// algorithm; App. B.3).  Here the sequence is cut into chunks of CHUNK prefixes that are solved
+// independently, one workgroup each, in one launch (mask_kernel):
+//   * tau_t and the k-th largest selection key never decrease once the prefix holds k entries (Sec. 3.2,
+//     irreversibility), so inside a chunk only the scores between two bounds can change anything.
+//     Both bounds come from one histogram of the prefix: f_t(x) = sum clip(z - x, 0, 1) is the integral
+//     over [x, x + 1] of #{z > y}, so windowed sums of the bin counts bound f_t at every bin edge --
+//     in integers, without a search.  A second pass adds up the scores that are saturated or fractional
+//     whatever the threshold does inside the bounds and collects the few others (about 120 of 32768
+//     scores of unit variance at k = 1024);
+//   * every wave then solves a few consecutive prefixes: tau_t is the root of f_t(x) = k, found by
+//     repeating the closed form of the solution equation (tau from u*, w* and the fractional sum) until
+//     no breakpoint lies between two iterates -- exact, not an iteration to a tolerance; a bracket
+//     guards it;
+//   * key j dies at the first prefix that holds k larger keys: with c older keys above it, at the
+//     (k - c)-th newcomer of the chunk that is larger -- a rank and two ballots per key.
+// Chunks whose scores do not suit this (clusters of equal scores, k-th largest score outside the
+// histogram's range of 16) take the sorted path below it: the candidates above theta - 1 are
+// compacted into LDS, sorted once, and the same iteration runs on searches in the sorted list.
 #include "common.hpp"
 
 namespace spk {
 
 constexpr int CHUNK = 128;        // prefixes per workgroup of the chunk kernel
-constexpr int NT_CHUNK = 1024;    // threads of the chunk kernel (16 waves, 8 prefixes each)
+constexpr int NT_CHUNK = 1024;    // threads per workgroup (16 waves, 8 prefixes each)
 constexpr int NW_CHUNK = NT_CHUNK / 64;
-constexpr int SUPER = 2048;       // spacing of the coarse lower bounds
-constexpr int CAP = 8192;         // candidate capacity in LDS (64-bit keys: 64 KB, fp64 prefix sums: 64 KB);
-                                  // CAP_SMALL halves it so that two workgroups share a compute unit
-constexpr int NT_COARSE = 1024;
-constexpr int NPROBE = 15;
-constexpr int NPASS = 3;
+constexpr int CAP = 8192;         // sorted path: candidate capacity in LDS (64 KB of 64-bit keys, 8 KB of prefix sums)
 constexpr int MAX_ITERS = 4096;
+constexpr size_t STATUS_WORDS = 2048;   // up to this many chunks, each has a status word of its own
 
+static size_t mask_chunks(const sparsek_cfg& c) { return (size_t)c.B * c.Gu * (((size_t)c.n + CHUNK - 1) / CHUNK); }
+static bool mask_shared_status(const sparsek_cfg& c) { return mask_chunks(c) > STATUS_WORDS; }
+
+// Status words (see mask_kernel), never less than one bit per chunk and 4 bytes per 2048 positions of every row.
 size_t mask_ws_bytes(const sparsek_cfg& c)
 {
-    size_t rows = (size_t)c.B * c.Gu;
-    size_t nsuper = ((size_t)c.n + SUPER - 1) / SUPER;
-    // lower bounds, the status word, one bit per 128-prefix chunk (chunks that the half-capacity kernel hands on)
-    size_t nchunks = ((size_t)c.n + CHUNK - 1) / CHUNK;
-    return align_up(rows * nsuper * sizeof(float), 256) + 256 + align_up((rows * nchunks + 31) / 32 * 4, 256);
-}
-
-// ---------------------------------------------------------------------------------
-// Coarse kernel, grid (nsuper, rows), 1024 threads.
-//  * every block presets death[] = n on its slice of SUPER positions;
-//  * block s == 0 also writes the thresholds of the prefixes with at most k entries:
-//    tau_t = min(u[0..t]) - 1 (k == 0: tau_t = max(u[0..t]) and death[j] = j) -- a block scan;
-//  * block s >= 1 looks at the prefix of length L = s*SUPER and, if L >= k, narrows a bracket
-//    around the root of f_L(x) = k with NPASS passes of NPROBE probes; lo_out = a point with
-//    f(lo) >= k + 1/4 (so lo <= tau of that prefix despite fp32 partial sums).
-// Scores are read once into registers (COARSE_REG per thread), in segments for very long rows.
-// ---------------------------------------------------------------------------------
-constexpr int COARSE_REG = 32;
-
-__device__ void short_prefix_scan(const float* __restrict__ ur, float* __restrict__ tr, int32_t* __restrict__ dr,
-                                  int n, int k, float* part /* [1024] LDS */)
-{
-    const int tid = threadIdx.x;
-    const bool use_max = (k == 0);
-    const int upto = use_max ? n : (k < n ? k : n);
-    const int per = (upto + 1023) / 1024;
-    const int b = tid * per, e = min(b + per, upto);
-    float acc = use_max ? -INFINITY : INFINITY;
-    for (int i = b; i < e; i++) acc = use_max ? fmaxf(acc, ur[i]) : fminf(acc, ur[i]);
-    part[tid] = acc;
-    __syncthreads();
-    // inclusive Hillis-Steele scan of the 1024 partial extrema
-    for (int off = 1; off < 1024; off <<= 1) {
-        float other = (tid >= off) ? part[tid - off] : acc;
-        __syncthreads();
-        acc = use_max ? fmaxf(acc, other) : fminf(acc, other);
-        part[tid] = acc;
-        __syncthreads();
-    }
-    float run = (tid == 0) ? (use_max ? -INFINITY : INFINITY) : part[tid - 1];
-    for (int i = b; i < e; i++) {
-        run = use_max ? fmaxf(run, ur[i]) : fminf(run, ur[i]);
-        tr[i] = use_max ? run : run - 1.0f;
-    }
-    if (use_max)
-        for (int i = tid; i < n; i += 1024) dr[i] = i;
-}
-
-__global__ __launch_bounds__(NT_COARSE) void mask_coarse_kernel(const float* __restrict__ u,
-                                                                 float* __restrict__ lo_out,
-                                                                 float* __restrict__ tau,
-                                                                 int32_t* __restrict__ death, int n,
-                                                                 int k, int nsuper, int* __restrict__ status,
-                                                                 unsigned* __restrict__ handed_on, int nwords)
-{
-    __shared__ double red[NT_COARSE / 64][NPROBE + 1];
-    __shared__ double ftot[NPROBE];
-    __shared__ float bracket[2];
-    __shared__ float part[1024];
-    const int s = blockIdx.x, row = blockIdx.y;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const float* ur = u + (size_t)row * n;
-    int32_t* dr = death + (size_t)row * n;
-    // the call's status word starts at 0; the chunk kernel, which sets bits in it, runs after this one on the stream
-    if (s == 0 && row == 0 && tid == 0) *status = 0;
-    for (int i = (row * gridDim.x + s) * NT_COARSE + tid; i < nwords; i += gridDim.x * gridDim.y * NT_COARSE)
-        handed_on[i] = 0u;
-    if (k > 0)
-        for (int i = s * SUPER + tid; i < min(n, (s + 1) * SUPER); i += NT_COARSE) dr[i] = n;
-    const int L = s * SUPER;
-    float* out = lo_out + (size_t)row * nsuper + s;
-    if (s == 0) {
-        short_prefix_scan(ur, tau + (size_t)row * n, dr, n, k, part);
-        if (tid == 0) *out = -INFINITY;
-        return;
-    }
-    if (L < k || k == 0) {
-        if (tid == 0) *out = -INFINITY;
-        return;
-    }
-    const int nseg = (L + NT_COARSE * COARSE_REG - 1) / (NT_COARSE * COARSE_REG);
-    float z[COARSE_REG];
-    auto load_seg = [&](int seg) {
-#pragma unroll
-        for (int r = 0; r < COARSE_REG; r++) {
-            const int i = (seg * COARSE_REG + r) * NT_COARSE + tid;
-            z[r] = (i < L) ? ur[i] : -INFINITY;  // -inf never counts in f; excluded from the min below
-        }
-    };
-    load_seg(0);
-    // pass 0: range of the prefix
-    float mn = INFINITY, mx = -INFINITY;
-    for (int seg = 0; seg < nseg; seg++) {
-        if (nseg > 1) load_seg(seg);
-#pragma unroll
-        for (int r = 0; r < COARSE_REG; r++) {
-            mx = fmaxf(mx, z[r]);
-            mn = (z[r] > -INFINITY) ? fminf(mn, z[r]) : mn;
-        }
-    }
-    mn = wave_min_f32(mn);
-    mx = wave_max_f32(mx);
-    if (lane == 0) { red[wv][0] = mn; red[wv][1] = mx; }
-    __syncthreads();
-    if (tid == 0) {
-        float a = INFINITY, b = -INFINITY;
-        for (int i = 0; i < NT_COARSE / 64; i++) { a = fminf(a, (float)red[i][0]); b = fmaxf(b, (float)red[i][1]); }
-        bracket[0] = a - 1.0f;  // f = L >= k here
-        bracket[1] = b;         // f = 0 < k here
-    }
-    __syncthreads();
-    for (int pass = 0; pass < NPASS; pass++) {
-        const float lo = bracket[0], hi = bracket[1];
-        const float step = (hi - lo) / (float)(NPROBE + 1);
-        float acc[NPROBE];
-#pragma unroll
-        for (int p = 0; p < NPROBE; p++) acc[p] = 0.0f;
-        for (int seg = 0; seg < nseg; seg++) {
-            if (nseg > 1) load_seg(seg);
-#pragma unroll
-            for (int r = 0; r < COARSE_REG; r++) {
-#pragma unroll
-                for (int p = 0; p < NPROBE; p++) acc[p] += clip01(z[r] - (lo + step * (float)(p + 1)));
-            }
-        }
-#pragma unroll
-        for (int p = 0; p < NPROBE; p++) {
-            double t = wave_sum_f64((double)acc[p]);
-            if (lane == 0) red[wv][p] = t;
-        }
-        __syncthreads();
-        if (tid < NPROBE) {  // one thread per probe adds the 16 wave totals
-            double f = 0.0;
-            for (int i = 0; i < NT_COARSE / 64; i++) f += red[i][tid];
-            ftot[tid] = f;
-        }
-        __syncthreads();
-        if (tid == 0) {
-            float nlo = lo, nhi = hi;
-            for (int p = 0; p < NPROBE; p++) {
-                float x = lo + step * (float)(p + 1);
-                if (ftot[p] >= (double)k + 0.25) nlo = x;
-                else { nhi = x; break; }
-            }
-            bracket[0] = nlo;
-            bracket[1] = nhi;
-        }
-        __syncthreads();
-    }
-    if (tid == 0) *out = bracket[0];
+    const size_t rows = (size_t)c.B * c.Gu, chunks = mask_chunks(c);
+    const size_t bytes = align_up(rows * (((size_t)c.n + 2047) / 2048) * sizeof(float), 256) + 256 +
+                         align_up((chunks + 31) / 32 * 4, 256);
+    return mask_shared_status(c) ? bytes : std::max(bytes, align_up(chunks * sizeof(int), 256));
 }
 
 // ---------------------------------------------------------------------------------
 // Candidate lists: compacted in LDS, or (overflow fallback) the raw prefix in global memory.
 // ---------------------------------------------------------------------------------
 // Sorted list: key[0, m_old) = selection keys (score, then older position) of the older
-// candidates in descending order, pref[i] = sum of the scores of key[0, i) in fp64; the chunk's
+// candidates in descending order, pref[i] = sum of the scores of key[0, PSTRIDE * i) in fp64; the chunk's
 // own scores live in registers, two per lane (entries `lane` and `lane + 64` of the chunk).
+constexpr int PSTRIDE = 8;
 struct ListSorted {
     const unsigned long long* key;
     const double* pref;
@@ -293,7 +150,9 @@ __device__ __forceinline__ Piece eval_sorted(const ListSorted& L, int t, double 
     if (b - a <= 64) {
         if (lane < b - a) part += (double)key_score(L.key[a + lane]);
     } else {
-        base = L.pref[b] - L.pref[a];
+        base = L.pref[b / PSTRIDE] - L.pref[a / PSTRIDE];   // in whole strides, corrected at both ends
+        if (lane < b % PSTRIDE) part += (double)key_score(L.key[b / PSTRIDE * PSTRIDE + lane]);
+        if (lane < a % PSTRIDE) part -= (double)key_score(L.key[a / PSTRIDE * PSTRIDE + lane]);
     }
     const unsigned long long packed = wave_sum_u64(((unsigned long long)f << 32) | (unsigned long long)sc);
     P.F = a + (int)(packed >> 32);
@@ -501,7 +360,7 @@ __device__ void wave_tau(const List& L, const float* __restrict__ ur, float* __r
     bool have_prev = false;
     double tau_prev = 0.0;
     for (int t = ta; t < tb; t++) {
-        if (t + 1 <= k) continue;  // written by the coarse kernel's short-prefix scan
+        if (t + 1 <= k) continue;  // at most k entries: written by short_prefix_tau
         const double ut = (double)readlane_f32(my_u, t - ta);
         double tau;
         if (have_prev && !(ut > tau_prev)) {
@@ -535,7 +394,7 @@ __device__ void wave_tau(const ListSorted& L, const float* __restrict__ ur, floa
     double x = 0.0;
     Piece P;
     for (int t = ta; t < tb; t++) {
-        if (t + 1 <= k) continue;  // written by the coarse kernel's short-prefix scan
+        if (t + 1 <= k) continue;  // at most k entries: written by short_prefix_tau
         const float utf = readlane_f32(my_u, t - ta);
         const double ut = (double)utf;
         if (started && !(ut > x)) {  // the new score is below the threshold: nothing changes
@@ -718,10 +577,12 @@ __device__ void wave_theta(const ListSorted& L, const float* __restrict__ ur, in
     }
 }
 
-// death of one list entry given the chunk's theta sequence (non-decreasing).
+// death of one list entry given the chunk's theta sequence (non-decreasing).  Positions count from the row's first
+// valid key, lifetimes from the row's start (j0 = the difference); survivor != 0: the lifetime of a key that outlives
+// the chunk (written by the row's last chunk).
 __device__ __forceinline__ void write_death(unsigned long long key, int j, int t0, int t1, int k,
                                             const unsigned long long* th, unsigned long long th_start,
-                                            int32_t* __restrict__ dr)
+                                            int32_t* __restrict__ dr, int j0, int survivor)
 {
     int first;
     if (j < t0) {
@@ -737,7 +598,8 @@ __device__ __forceinline__ void write_death(unsigned long long key, int j, int t
         if (th[m] > key) b = m;
         else a = m + 1;
     }
-    if (a < t1 - t0) dr[j] = t0 + a;
+    if (a < t1 - t0) dr[j] = j0 + t0 + a;
+    else if (survivor) dr[j] = survivor;
 }
 
 constexpr int NW_TAU = NW_CHUNK - 1;                     // waves solving tau; the last wave walks theta
@@ -747,7 +609,7 @@ constexpr int SLICE_REG = 8;                             // compaction: scores c
 template <class List>
 __device__ void chunk_body(const List& L, const float* __restrict__ ur, float* __restrict__ tr,
                            int32_t* __restrict__ dr, int t0, int t1, int k, float lo, unsigned* hist,
-                           unsigned long long* bc, unsigned long long* th, int* status)
+                           unsigned long long* bc, unsigned long long* th, int* status, int j0, int survivor)
 {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     // theta at the chunk start, by the whole workgroup
@@ -765,14 +627,14 @@ __device__ void chunk_body(const List& L, const float* __restrict__ ur, float* _
     __syncthreads();
     for (int i = tid; i < L.M; i += NT_CHUNK) {
         const int p = L.pos(i);
-        if (p < t1) write_death(sel_key(L.val(i), p), p, t0, t1, k, th, th_start, dr);
+        if (p < t1) write_death(sel_key(L.val(i), p), p, t0, t1, k, th, th_start, dr, j0, survivor);
     }
 }
 
 // The same for the sorted list: theta at the chunk start is the k-th sorted key.
 __device__ void chunk_body_sorted(const ListSorted& L, const float* __restrict__ ur, float* __restrict__ tr,
                                   int32_t* __restrict__ dr, int t0, int t1, int k, float lo,
-                                  unsigned long long* th, int* status)
+                                  unsigned long long* th, int* status, int j0, int survivor)
 {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const unsigned long long th_start = (t0 >= k) ? L.key[k - 1] : 0ull;
@@ -788,9 +650,9 @@ __device__ void chunk_body_sorted(const ListSorted& L, const float* __restrict__
     __syncthreads();
     for (int i = tid; i < L.m_old; i += NT_CHUNK) {
         const unsigned long long key = L.key[i];
-        write_death(key, key_pos(key), t0, t1, k, th, th_start, dr);
+        write_death(key, key_pos(key), t0, t1, k, th, th_start, dr, j0, survivor);
     }
-    if (tid < t1 - t0) write_death(sel_key(ur[t0 + tid], t0 + tid), t0 + tid, t0, t1, k, th, th_start, dr);
+    if (tid < t1 - t0) write_death(sel_key(ur[t0 + tid], t0 + tid), t0 + tid, t0, t1, k, th, th_start, dr, j0, survivor);
 }
 
 // Bitonic sort of key[0, N) in descending order, N a power of two >= 2048 (one or more pairs per
@@ -820,140 +682,58 @@ __device__ void bitonic_sort_desc(unsigned long long* key, int N)
     __syncthreads();
 }
 
-// Sort key[0, m) in descending order by distribution: NB value buckets between the smallest and
-// the largest score (one counting pass, one scan, one scatter into `tmp`), then every element
-// finds its rank inside its bucket by reading the bucket (a handful of elements for spread-out
-// scores) and goes to its final place in key[].  Returns false, with key[] untouched, when some
-// bucket holds more than BUCKET_MAX elements (many equal or clustered scores): the caller then
-// sorts by comparison.  The result depends on the keys only, not on the order of the atomics.
-constexpr int NB = 2048;
-constexpr int CAP_SMALL = 4096, NB_SMALL = 1024;   // the variant for k small enough that 4096 candidates suffice
-constexpr int BUCKET_MAX = 96;
-
-template <int NB>
-__device__ bool bucket_sort_desc(unsigned long long* key, unsigned long long* tmp, int m, float vmin, float vmax,
-                                 int* bcount /* [NB] */, int* boff /* [NB + 1] */, int* flag, int* wsum /* [NW_CHUNK] */)
-{
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const float scale = (float)NB / (vmax - vmin);
-    auto bucket = [&](unsigned long long kk) {
-        const float v = key_score(kk);
-        int b = (int)((v - vmin) * scale);
-        b = max(0, min(NB - 1, b));
-        return NB - 1 - b;  // larger scores first
-    };
-    for (int i = tid; i < NB; i += NT_CHUNK) bcount[i] = 0;
-    if (tid == 0) *flag = 0;
-    __syncthreads();
-    for (int i = tid; i < m; i += NT_CHUNK) atomicAdd(&bcount[bucket(key[i])], 1);
-    __syncthreads();
-    // exclusive scan of the NB counts (NB / NT_CHUNK consecutive buckets per thread)
-    constexpr int BPT = NB / NT_CHUNK;
-    int c[BPT], tot = 0, big = 0;
-#pragma unroll
-    for (int r = 0; r < BPT; r++) {
-        c[r] = bcount[tid * BPT + r];
-        tot += c[r];
-        big |= c[r] > BUCKET_MAX ? 1 : 0;
-    }
-    int inc = tot;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += y;
-    }
-    if (lane == 63) wsum[wv] = inc;
-    if (big) *flag = 1;
-    __syncthreads();
-    if (*flag) return false;
-    int before = inc - tot;
-    for (int i = 0; i < wv; i++) before += wsum[i];
-#pragma unroll
-    for (int r = 0; r < BPT; r++) {
-        boff[tid * BPT + r] = before;
-        bcount[tid * BPT + r] = before;  // scatter cursor
-        before += c[r];
-    }
-    if (tid == NT_CHUNK - 1) boff[NB] = before;
-    __syncthreads();
-    for (int i = tid; i < m; i += NT_CHUNK) {
-        const unsigned long long kk = key[i];
-        tmp[atomicAdd(&bcount[bucket(kk)], 1)] = kk;
-    }
-    __syncthreads();
-    for (int i = tid; i < m; i += NT_CHUNK) {
-        const unsigned long long kk = tmp[i];
-        const int b = bucket(kk);
-        const int b0 = boff[b], b1 = boff[b + 1];
-        int rank = 0;
-        for (int j = b0; j < b1; j++) rank += tmp[j] > kk ? 1 : 0;
-        key[b0 + rank] = kk;
-    }
-    __syncthreads();
-    return true;
-}
-
-// pref[i] = sum of the scores of key[0, i), i = 0..N, in fp64 (N a multiple of NT_CHUNK).
+// pref[i] = sum of the scores of key[0, PSTRIDE * i), i = 0..N / PSTRIDE, in fp64 (N a multiple of NT_CHUNK * 2).
 __device__ void sorted_prefix_sums(const unsigned long long* key, double* pref, int N, int m_old, double* wtot)
 {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int per = N / NT_CHUNK;
-    double run = 0.0;
-    for (int r = 0; r < per; r++) {
-        const int i = tid * per + r;
-        run += (i < m_old) ? (double)key_score(key[i]) : 0.0;
-    }
-    // inclusive scan of the thread totals across the wave, then across the waves
-    double inc = run;
+    double carry = 0.0;
+    for (int base = 0; base < N; base += NT_CHUNK * PSTRIDE) {
+        double run = 0.0;
+        for (int r = 0; r < PSTRIDE; r++) {
+            const int i = base + tid * PSTRIDE + r;
+            run += (i < m_old) ? (double)key_score(key[i]) : 0.0;
+        }
+        // inclusive scan of the thread totals across the wave, then across the waves
+        double inc = run;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const double y = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += y;
+        for (int o = 1; o < 64; o <<= 1) {
+            const double y = __shfl_up(inc, o, 64);
+            if (lane >= o) inc += y;
+        }
+        __syncthreads();
+        if (lane == 63) wtot[wv] = inc;
+        __syncthreads();
+        double before = carry + inc - run;
+        for (int i = 0; i < wv; i++) before += wtot[i];
+        for (int i = 0; i < NW_CHUNK; i++) carry += wtot[i];
+        if (base + tid * PSTRIDE <= N) pref[base / PSTRIDE + tid] = before;
     }
-    if (lane == 63) wtot[wv] = inc;
-    __syncthreads();
-    double before = inc - run;
-    for (int i = 0; i < wv; i++) before += wtot[i];
-    for (int r = 0; r < per; r++) {
-        const int i = tid * per + r;
-        pref[i] = before;
-        before += (i < m_old) ? (double)key_score(key[i]) : 0.0;
-    }
-    if (tid == NT_CHUNK - 1) pref[N] = before;
+    if (tid == 0) pref[N / PSTRIDE] = carry;
     __syncthreads();
 }
 
-template <int CAP, int NB>
-__global__ __launch_bounds__(NT_CHUNK, CAP <= CAP_SMALL ? 8 : 4) void mask_chunk_kernel(
-    const float* __restrict__ u, const float* __restrict__ lo_in, float* __restrict__ tau,
-    int32_t* __restrict__ death, int n, int k, int nsuper, int* __restrict__ status, int t_begin,
-    unsigned* __restrict__ handed_on, int only_handed_on)
+// LDS of the sorted path.
+struct SortedSmem {
+    unsigned long long skey[CAP];
+    double pref[CAP / PSTRIDE + 1];
+    unsigned long long th[CHUNK];
+    unsigned hist[256];
+    double wtot[NW_CHUNK];
+    int count;
+    unsigned long long bc;
+};
+
+// One chunk by sorting its candidates (whole workgroup).  Positions count from the row's first valid key.
+__device__ __noinline__ void mask_chunk_sorted(SortedSmem& sm, const float* __restrict__ ur, float* __restrict__ tr,
+                                  int32_t* __restrict__ dr, int t0, int t1, int k, int* status, int j0, int survivor)
 {
-    __shared__ __align__(16) unsigned long long skey[CAP];
-    __shared__ __align__(16) double pref[CAP + 1];
-    __shared__ unsigned long long th[CHUNK];
-    __shared__ unsigned hist[256];
-    __shared__ double wtot[NW_CHUNK];
-    __shared__ int wcount[NW_CHUNK + 1];
-    __shared__ float wmin[NW_CHUNK], wmax[NW_CHUNK];
-    __shared__ int bcount[NB], boff[NB + 1], bflag, wsum[NW_CHUNK];
-    __shared__ unsigned long long bc;
-
-    const int c = blockIdx.x, row = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int t0 = c * CHUNK, t1 = min(n, t0 + CHUNK);
-    if (t1 <= k) return;  // no prefix here is longer than k: tau is written elsewhere, nothing dies
-    if (t1 <= t_begin) return;  // the caller needs neither these thresholds nor the deaths that fall here
-    // Two launches share the chunks when there are many: the half-capacity kernel (two workgroups per compute unit)
-    // takes them all and hands on, through one bit each, those whose candidates do not fit its lists; the
-    // full-capacity kernel then runs those alone.
-    const int chunk_id = row * gridDim.x + c;
-    if (only_handed_on && !((handed_on[chunk_id >> 5] >> (chunk_id & 31)) & 1u)) return;
-    const float* ur = u + (size_t)row * n;
-    float* tr = tau + (size_t)row * n;
-    int32_t* dr = death + (size_t)row * n;
-    const float lo = lo_in[(size_t)row * nsuper + t0 / SUPER];
-
+    // tau lies in [z_(k) - 1, z_(k)) and both ends only rise: theta_{t0-1} - 1 bounds every threshold of the chunk
+    float lo = -INFINITY;
+    if (t0 >= k) {
+        const unsigned long long th_start = block_kth_largest(ListGlobal{ur, t0}, t0, k, sm.hist, &sm.bc);
+        lo = __double2float_rd((double)key_score(th_start) - 1.0);
+    }
     // ---- compaction of {j < t0 : u_j > lo} as selection keys, in one pass: each wave owns a contiguous slice, read
     // in segments of 64*SLICE_REG scores held in registers (independent loads, one latency); a segment reserves
     // its room in the list with one LDS atomic.  The order in which the segments land does not matter: the list
@@ -961,9 +741,8 @@ __global__ __launch_bounds__(NT_CHUNK, CAP <= CAP_SMALL ? 8 : 4) void mask_chunk
     const int per = ((t0 + NW_CHUNK - 1) / NW_CHUNK + 63) / 64 * 64;
     const int sb = min(t0, wv * per), se = min(t0, sb + per);
     constexpr int SEGN = 64 * SLICE_REG;
-    if (tid == 0) wcount[NW_CHUNK] = 0;
+    if (tid == 0) sm.count = 0;
     __syncthreads();
-    float cmin = INFINITY, cmax = -INFINITY;  // range of the candidates
     for (int g0 = sb; g0 < se; g0 += SEGN) {
         float z[SLICE_REG];
 #pragma unroll
@@ -976,52 +755,853 @@ __global__ __launch_bounds__(NT_CHUNK, CAP <= CAP_SMALL ? 8 : 4) void mask_chunk
         for (int r = 0; r < SLICE_REG; r++) {
             const bool p = z[r] > lo;
             seg_cnt += __popcll(__ballot(p));
-            cmin = p ? fminf(cmin, z[r]) : cmin;
-            cmax = p ? fmaxf(cmax, z[r]) : cmax;
         }
         int off = 0;
-        if (lane == 0 && seg_cnt > 0) off = atomicAdd(&wcount[NW_CHUNK], seg_cnt);
+        if (lane == 0 && seg_cnt > 0) off = atomicAdd(&sm.count, seg_cnt);
         off = __builtin_amdgcn_readfirstlane(off);
 #pragma unroll
         for (int r = 0; r < SLICE_REG; r++) {
             const bool p = z[r] > lo;
             const unsigned long long ball = __ballot(p);
             const int pos = off + __popcll(ball & ((1ull << lane) - 1ull));
-            if (p && pos < CAP) skey[pos] = sel_key(z[r], g0 + r * 64 + lane);   // beyond CAP: the slow path below
+            if (p && pos < CAP) sm.skey[pos] = sel_key(z[r], g0 + r * 64 + lane);   // beyond CAP: the slow path below
             off += __popcll(ball);
         }
     }
-    cmin = wave_min_f32(cmin);
-    cmax = wave_max_f32(cmax);
-    if (lane == 0) { wmin[wv] = cmin; wmax[wv] = cmax; }
     __syncthreads();
-    const int m_old = wcount[NW_CHUNK];
+    const int m_old = sm.count;
     // the list must hold the whole top-k of every prefix of the chunk (it does when lo is a lower
     // bound of tau; checked, not assumed)
     const bool fits = (m_old <= CAP) && (t0 < k || m_old >= k);
     if (fits) {
         int npad = 2 * NT_CHUNK;
         while (npad < m_old) npad <<= 1;
-        for (int i = m_old + tid; i < npad; i += NT_CHUNK) skey[i] = 0ull;  // below every real key
+        for (int i = m_old + tid; i < npad; i += NT_CHUNK) sm.skey[i] = 0ull;  // below every real key
         __syncthreads();
         if (m_old > 0) {
-            float vmin = INFINITY, vmax = -INFINITY;
-            for (int i = 0; i < NW_CHUNK; i++) { vmin = fminf(vmin, wmin[i]); vmax = fmaxf(vmax, wmax[i]); }
-            // pref[] is free until the prefix sums are taken: scratch of the distribution sort
-            if (!bucket_sort_desc<NB>(skey, (unsigned long long*)pref, m_old, vmin, vmax, bcount, boff, &bflag, wsum))
-                bitonic_sort_desc(skey, npad);
-            sorted_prefix_sums(skey, pref, npad, m_old, wtot);
+            bitonic_sort_desc(sm.skey, npad);
+            sorted_prefix_sums(sm.skey, sm.pref, npad, m_old, sm.wtot);
         }
         const int cn = t1 - t0;
-        ListSorted L{skey, pref, m_old, t0, (lane < cn) ? ur[t0 + lane] : -INFINITY,
+        ListSorted L{sm.skey, sm.pref, m_old, t0, (lane < cn) ? ur[t0 + lane] : -INFINITY,
                      (lane + 64 < cn) ? ur[t0 + lane + 64] : -INFINITY};
-        chunk_body_sorted(L, ur, tr, dr, t0, t1, k, lo, th, status);
-    } else if (CAP <= CAP_SMALL && !only_handed_on) {
-        if (tid == 0) atomicOr(&handed_on[chunk_id >> 5], 1u << (chunk_id & 31));
+        chunk_body_sorted(L, ur, tr, dr, t0, t1, k, lo, sm.th, status, j0, survivor);
     } else {
         ListGlobal L{ur, t1};
-        chunk_body(L, ur, tr, dr, t0, t1, k, -INFINITY, hist, &bc, th, status);
+        chunk_body(L, ur, tr, dr, t0, t1, k, -INFINITY, sm.hist, &sm.bc, sm.th, status, j0, survivor);
     }
+}
+
+// ---------------------------------------------------------------------------------
+// The histogram path.  Bounded by latency -- two passes over the prefix, a dozen workgroup barriers, the searches and
+// the newcomers of a wave -- not by bandwidth or arithmetic.  One row of 32768 scores at k = 1024 takes 35 us (late
+// chunks 22 us: histogram 3.9, bounds 2.2, second pass 7.2, sorting the two short lists 3.5, thresholds 4.3, lifetimes
+// 0.9), 32 rows of 16384 take 262 us.  Before, with a lower bound from a 45-point bracket search in a kernel of its own
+// and a sort of all candidates per chunk: 85 us and 390 us.
+// ---------------------------------------------------------------------------------
+constexpr int HBINS = 2048;      // bins of width 1 / HRES: a window of 16 around the scores
+constexpr int HRES = 128;
+constexpr int TL_WAVE = 64;      // per wave: scores with a breakpoint between the bounds
+constexpr int TL_CAP = NW_CHUNK * TL_WAVE;
+constexpr int QL_CAP = 1024;     // keys between the bounds of theta
+constexpr int CP_CAP = 64 + 128 + 64;   // what is left of the last 64, two groups of a wave, slack for reads past the end
+constexpr int BP_REG = 5;
+constexpr int BP_CAP = 64 * BP_REG;     // breakpoints between the bounds, for the parallel solution
+
+struct HistSmem {
+    union {
+        struct {
+            unsigned hist[HBINS], own[HBINS];   // older scores, the chunk's own scores
+            unsigned cum[2][HBINS];             // twice-cumulated counts, from the top bin down: older, all
+        } h;
+        struct {
+            float v[NW_CHUNK][CP_CAP];          // per wave: older scores above the lower bound
+            int pos[NW_CHUNK][CP_CAP];
+        } c;
+        struct {
+            float v[TL_CAP + 64];               // the scores between the bounds and their breakpoints, unordered,
+            double bp[BP_CAP];
+            int tie[TL_CAP], btie[BP_CAP];      // and how many of each rank have been placed
+        } s;
+        double gain[NW_CHUNK][BP_CAP];          // what a wave's newcomers add to f at every breakpoint
+    } x;
+    float raw[NW_CHUNK][TL_WAVE];       // per wave: scores between the bounds
+    float tl[TL_CAP];                   // the same in descending order
+    double pref[BP_CAP + 1];            // sums of the first i of them
+    double bps[BP_CAP];                 // breakpoints, ascending
+    double bsum[BP_CAP];                // at a breakpoint (ascending): sum of the fractional older scores,
+    int bF[BP_CAP], bS[BP_CAP];         // older scores above it + 1, above it
+    unsigned long long qk[QL_CAP];      // selection keys between the bounds of theta
+    float own[CHUNK];
+    unsigned long long ownkey[CHUNK];
+    unsigned wscan[4][NW_CHUNK];
+    float wmm[2][NW_CHUNK];
+    double wsum[NW_CHUNK];
+    int wF[NW_CHUNK], wC[NW_CHUNK], wM[NW_CHUNK];
+    int jlo, jhi, jl, jh, above, jmin, nq, nbp, full;
+};
+
+// Inclusive sum over the lanes of a wave (DPP row shifts, then the row totals are broadcast).
+__device__ __forceinline__ unsigned wave_scan_u32(unsigned x)
+{
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true);
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true);
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true);
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true);
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);  // row_bcast15 into rows 1 and 3
+    x += (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);  // row_bcast31 into rows 2 and 3
+    return x;
+}
+
+// Exclusive sums of two counters over the workgroup's threads; barriers inside (two arrays w, distinct per call).
+__device__ __forceinline__ void block_scan2(unsigned a, unsigned b, unsigned* wa, unsigned* wb, unsigned& ea, unsigned& eb)
+{
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const unsigned ia = wave_scan_u32(a), ib = wave_scan_u32(b);
+    if (lane == 63) { wa[wv] = ia; wb[wv] = ib; }
+    __syncthreads();
+    // lane l of every wave holds wave l's total; the sum over the waves before this one is a ballot-free wave scan
+    const unsigned ta = wave_scan_u32(lane < NW_CHUNK ? wa[lane] : 0u), tb = wave_scan_u32(lane < NW_CHUNK ? wb[lane] : 0u);
+    const unsigned pa = wv > 0 ? (unsigned)__builtin_amdgcn_readlane((int)ta, wv - 1) : 0u;
+    const unsigned pb = wv > 0 ? (unsigned)__builtin_amdgcn_readlane((int)tb, wv - 1) : 0u;
+    ea = pa + ia - a;
+    eb = pb + ib - b;
+}
+
+// The scores a prefix of the chunk is made of, for thresholds between the bounds: Fb scores that are saturated and Cb
+// (sum sumb) that are fractional at every such threshold, a short list in a fixed order, and the chunk's own scores, two
+// per lane.  The first 64 * TL_REG entries of the list live in registers, widened once, so that a comparison with a
+// threshold or a threshold + 1 is one instruction; -inf fills up.
+constexpr int TL_REG = 3;
+struct ListBounded {
+    const float* v;
+    int M, Fb, Cb;
+    double sumb;
+    int t0, lane;
+    double own[2];
+    double reg[TL_REG];
+};
+
+// A condition that is the same in every lane, as a scalar branch.
+__device__ __forceinline__ bool uniform(bool c) { return __ballot(c) != 0ull; }
+
+template <typename F>
+__device__ __forceinline__ void each_bounded(const ListBounded& L, int t, F&& f)
+{
+#pragma unroll
+    for (int r = 0; r < TL_REG; r++)
+        if (64 * r < L.M) f(L.reg[r]);
+    for (int i = 64 * TL_REG; i < L.M; i += 64) f(i + L.lane < L.M ? (double)L.v[i + L.lane] : -INFINITY);
+    const int nc = t - L.t0 + 1;
+    f(L.lane < nc ? L.own[0] : -INFINITY);
+    if (nc > 64) f(L.lane + 64 < nc ? L.own[1] : -INFINITY);
+}
+
+struct PieceB {
+    int F, S;
+    double fsum;
+};
+
+// Right-limit counts of the linear piece of f_t that contains x.  A sum of one fractional score is exact (no
+// differences of sums), which the flat case -- root exactly on a breakpoint, sup rule -- relies on.
+__device__ __forceinline__ PieceB eval_bounded(const ListBounded& L, int t, double x)
+{
+    const double x1 = x + 1.0;
+    int F = L.Fb, S = L.Fb + L.Cb;
+    double part = 0.0;
+    each_bounded(L, t, [&](double v) {
+        const unsigned long long a = __ballot(v > x), b = __ballot(v > x1);
+        S += (int)__popcll(a);
+        F += (int)__popcll(b);
+        part += ((a & ~b) >> L.lane) & 1ull ? v : 0.0;
+    });
+    return PieceB{F, S, L.sumb + wave_sum_f64(part)};
+}
+
+// True if no score of prefix t has a breakpoint (z or z - 1) in (lo, hi], both between the bounds.
+__device__ __forceinline__ bool clear_bounded(const ListBounded& L, int t, double lo, double hi)
+{
+    const double lo1 = lo + 1.0, hi1 = hi + 1.0;
+    unsigned long long hit = 0ull;
+    each_bounded(L, t, [&](double v) {
+        hit |= (__ballot(v > lo) & ~__ballot(v > hi)) | (__ballot(v > lo1) & ~__ballot(v > hi1));
+    });
+    return hit == 0ull;
+}
+
+// Smallest listed or own score above x + 1 in prefix t.
+__device__ __forceinline__ double min_saturated(const ListBounded& L, int t, double x)
+{
+    const double x1 = x + 1.0;
+    float mf = INFINITY;
+    each_bounded(L, t, [&](double v) { mf = fminf(mf, v > x1 ? (float)v : INFINITY); });
+    return (double)wave_min_f32(mf);
+}
+
+// One wave, thresholds of prefixes [ta, tb), tb - ta <= 64 (those longer than k), all roots in [lo, hi).  The iteration
+// is that of wave_tau(ListSorted): the piece is carried from prefix to prefix and only evaluated again when a breakpoint
+// was crossed; prefixes whose newcomer is not above the threshold are passed over.
+__device__ __forceinline__ void wave_tau(const ListBounded& L, float* __restrict__ tr, int ta, int tb, int k, double lo,
+                                         double hi, int* status)
+{
+    const int first = max(ta, k);   // prefixes of at most k entries: written by short_prefix_tau
+    if (first >= tb) return;
+    bool have = false;
+    double x = lo;
+    float res = 0.0f;               // lane l: threshold of prefix ta + l
+    PieceB P{0, 0, 0.0};
+    for (int t = first; t < tb;) {
+        const int c = t - L.t0;
+        if (have) {
+            const float utf = c < 64 ? readlane_f32((float)L.own[0], c) : readlane_f32((float)L.own[1], c - 64);
+            const double ut = (double)utf;
+            P.S++;
+            if (uniform(ut > x + 1.0)) P.F++;
+            else P.fsum += ut;
+        } else {
+            P = eval_bounded(L, t, x);
+            have = true;
+        }
+        double lo_b = x, hi_b = hi;
+        int it = 0;
+        for (; it < MAX_ITERS; it++) {
+            const double f = (double)P.F + P.fsum - (double)(P.S - P.F) * x;
+            const bool left = uniform(!(f < (double)k));
+            double xn = (P.fsum + (double)P.F - (double)k) / (double)(P.S - P.F);
+            bool step = false;
+            if (!left) {
+                hi_b = x;
+                if (P.S > P.F) {
+                    if (uniform(xn >= lo_b && xn < x) && clear_bounded(L, t, xn, x)) { x = xn; break; }
+                    step = uniform(xn > lo_b && xn < hi_b);
+                }
+            } else {
+                lo_b = x;
+                if (P.S == P.F) {  // flat to the right of x, f == F there
+                    const double nb = min_saturated(L, t, x) - 1.0;  // next breakpoint
+                    if (P.F == k && uniform(nb < hi)) {  // sup of the level set f == k; the piece changes there
+                        x = nb;
+                        have = false;
+                        break;
+                    }
+                    xn = nb;  // F > k: still left of the root
+                } else {
+                    if (!uniform(xn > x)) break;  // f(x) == k up to rounding
+                    if (uniform(xn < hi_b) && clear_bounded(L, t, x, xn)) { x = xn; break; }
+                }
+                step = uniform(xn < hi_b);
+            }
+            if (!step) {
+                const double mid = 0.5 * (lo_b + hi_b);
+                if (!uniform(mid > lo_b && mid < hi_b)) { x = lo_b; have = false; break; }
+                xn = mid;
+            }
+            x = xn;
+            P = eval_bounded(L, t, x);
+        }
+        if (it == MAX_ITERS && L.lane == 0) atomicOr(status, 1);
+        // the next prefix whose newcomer is above the threshold
+        const int nc = t + 1 - L.t0;
+        unsigned long long m0 = __ballot(L.own[0] > x), m1 = __ballot(L.own[1] > x);
+        m0 = nc < 64 ? m0 >> nc << nc : 0ull;
+        m1 = nc <= 64 ? m1 : nc < 128 ? m1 >> (nc - 64) << (nc - 64) : 0ull;
+        const int next = min(tb, m0 ? L.t0 + __builtin_ctzll(m0) : m1 ? L.t0 + 64 + __builtin_ctzll(m1) : tb);
+        res = ta + L.lane >= t && ta + L.lane < next ? (float)x : res;
+        t = next;
+    }
+    if (ta + L.lane >= first && ta + L.lane < tb) tr[ta + L.lane] = res;
+}
+
+// Thresholds of the chunk's prefixes with at most k entries: tau_t = min(u[0..t]) - 1 (k == 0: max(u[0..t])).
+// `before`: the extremum of u[0, t0).  One wave.
+__device__ __forceinline__ void short_prefix_tau(float before, float nv0, float nv1, int t0, int t1, int k, int lane,
+                                                 float* __restrict__ tr)
+{
+    const bool use_max = k == 0;
+    const float none = use_max ? -INFINITY : INFINITY;
+    const int cn = t1 - t0;
+    float a = lane < cn ? nv0 : none, b = lane + 64 < cn ? nv1 : none;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const float ya = __shfl_up(a, o, 64), yb = __shfl_up(b, o, 64);
+        if (lane >= o) {
+            a = use_max ? fmaxf(a, ya) : fminf(a, ya);
+            b = use_max ? fmaxf(b, yb) : fminf(b, yb);
+        }
+    }
+    const float top = readlane_f32(a, 63);
+    a = use_max ? fmaxf(a, before) : fminf(a, before);
+    b = use_max ? fmaxf(fmaxf(b, top), before) : fminf(fminf(b, top), before);
+    const int upto = use_max ? t1 : min(t1, k);
+    if (t0 + lane < upto) tr[t0 + lane] = use_max ? a : a - 1.0f;
+    if (t0 + lane + 64 < upto) tr[t0 + lane + 64] = use_max ? b : b - 1.0f;
+}
+
+// f(score, position, is one) for the older scores, NT_CHUNK of them at a time in a fixed order, four groups in flight;
+// after() follows every two groups.
+template <typename F, typename G>
+__device__ __forceinline__ void each_older(const float* __restrict__ ur, int t0, F&& f, G&& after)
+{
+    const int tid = threadIdx.x;
+    auto get = [&](int base) { return base + tid < t0 ? ur[base + tid] : -INFINITY; };
+    float z[4];
+#pragma unroll
+    for (int r = 0; r < 4; r++) z[r] = get(r * NT_CHUNK);
+    for (int base = 0; base < t0; base += 4 * NT_CHUNK) {
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int b = base + r * NT_CHUNK;
+            if (b < t0) f(z[r], b + tid, b + tid < t0);
+            z[r] = get(b + 4 * NT_CHUNK);
+            if (r & 1) after();
+        }
+    }
+}
+
+__device__ __forceinline__ int tM_before(int inclusive, int wv) { return wv > 0 ? __builtin_amdgcn_readlane(inclusive, wv - 1) : 0; }
+
+// Inclusive sum over the lanes of a wave, fp64 (in lane order).
+__device__ __forceinline__ double wave_scan_f64(double x)
+{
+#define SPK_SCAN_STEP(ctrl, rows)                                                                                       \
+    {                                                                                                                   \
+        const unsigned long long b = (unsigned long long)__double_as_longlong(x);                                       \
+        const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)b, ctrl, rows, 0xF, rows == 0xF);                  \
+        const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(b >> 32), ctrl, rows, 0xF, rows == 0xF);          \
+        x += __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));                \
+    }
+    SPK_SCAN_STEP(0x111, 0xF)
+    SPK_SCAN_STEP(0x112, 0xF)
+    SPK_SCAN_STEP(0x114, 0xF)
+    SPK_SCAN_STEP(0x118, 0xF)
+    SPK_SCAN_STEP(0x142, 0xA)
+    SPK_SCAN_STEP(0x143, 0xC)
+#undef SPK_SCAN_STEP
+    return x;
+}
+
+// Thresholds of all prefixes of the chunk at once (whole workgroup; wave w owns the prefixes [ta, tb)).  f_t is linear
+// between neighbouring breakpoints and does not increase, so the root lies right of the last breakpoint at which f_t
+// is still at least k:
+//   1. f_{t0-1} at every breakpoint: two searches in the sorted list and a difference of its prefix sums;
+//   2. every wave adds up what its own newcomers contribute at every breakpoint;
+//   3. every wave takes the sum over the waves before it, adds its newcomers one by one and counts the breakpoints
+//      with f >= k after each;
+//   4. eight lanes per prefix form the piece right of that breakpoint and its root.
+// A misjudged f (rounding, about 1e-13) only matters where the root is that close to the breakpoint, or where f equals
+// k on a flat stretch: a piece without fractional scores has its root at its right end (sup rule).
+__device__ __forceinline__ void solve_parallel(HistSmem& sm, const ListBounded& L, float* __restrict__ tr, int ta, int tb,
+                                               int k, double lo, double hi)
+{
+    const int tid = threadIdx.x, lane = L.lane, wv = tid >> 6;
+    const int M = L.M, B = sm.nbp;
+    // prefix sums of the sorted list
+    if (wv == 0) {
+        double carry = 0.0;
+        if (lane == 0) sm.pref[0] = 0.0;
+        for (int m = 0; m < M; m += 64) {
+            const double z = m + lane < M ? (double)sm.tl[m + lane] : 0.0;
+            const double inc = wave_scan_f64(z);
+            if (m + lane < M) sm.pref[m + lane + 1] = carry + inc;
+            carry += __longlong_as_double((long long)readlane_u64((unsigned long long)__double_as_longlong(inc), 63));
+        }
+    }
+    __syncthreads();
+    auto above = [&](double x) {   // listed scores above x
+        int a = 0, b = M;
+        while (a < b) {
+            const int m = (a + b) >> 1;
+            if ((double)sm.tl[m] > x) a = m + 1;
+            else b = m;
+        }
+        return a;
+    };
+    if (tid < B) {
+        const double b = sm.bps[tid];
+        const int S = above(b), F = above(b + 1.0);
+        sm.bS[tid] = S;
+        sm.bF[tid] = F;
+        sm.bsum[tid] = sm.pref[S] - sm.pref[F];
+    }
+    // 2. (registers: breakpoint 64 r + lane)
+    double b[BP_REG];
+#pragma unroll
+    for (int r = 0; r < BP_REG; r++) b[r] = 64 * r + lane < B ? sm.bps[64 * r + lane] : INFINITY;
+    auto clip = [](double x) { return fmin(fmax(x, 0.0), 1.0); };
+    const int c0 = ta - L.t0, cn = tb - ta;
+    double g[BP_REG];
+#pragma unroll
+    for (int r = 0; r < BP_REG; r++) g[r] = 0.0;
+    for (int s = 0; s < cn; s++) {
+        const double us = (double)sm.own[c0 + s];
+        if (!uniform(us > lo)) continue;
+#pragma unroll
+        for (int r = 0; r < BP_REG; r++)
+            if (64 * r < B) g[r] += clip(us - b[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < BP_REG; r++)
+        if (64 * r < B) sm.x.gain[wv][64 * r + lane] = g[r];
+    __syncthreads();
+    // 3.
+    double f[BP_REG];
+#pragma unroll
+    for (int r = 0; r < BP_REG; r++) {
+        f[r] = -INFINITY;
+        if (64 * r >= B) continue;
+        if (64 * r + lane < B) {
+            const int F = L.Fb + sm.bF[64 * r + lane], S = L.Fb + L.Cb + sm.bS[64 * r + lane];
+            f[r] = (double)F + (L.sumb + sm.bsum[64 * r + lane]) - (double)(S - F) * b[r];
+        }
+        for (int w = 0; w < wv; w++) f[r] += sm.x.gain[w][64 * r + lane];
+    }
+    int seg = 0;      // lanes 8 p .. 8 p + 7: breakpoints with f >= k after the wave's newcomer p
+    int count = -1;
+    for (int s = 0; s < cn; s++) {
+        const double us = (double)sm.own[c0 + s];
+        if (uniform(us > lo)) {
+#pragma unroll
+            for (int r = 0; r < BP_REG; r++)
+                if (64 * r < B) f[r] += clip(us - b[r]);
+            count = -1;
+        }
+        if (count < 0) {
+            count = 0;
+#pragma unroll
+            for (int r = 0; r < BP_REG; r++)
+                if (64 * r < B) count += (int)__popcll(__ballot(f[r] >= (double)k));
+        }
+        seg = (lane >> 3) == s ? count : seg;
+    }
+    // 4.
+    const int t = ta + (lane >> 3);
+    const double x0 = seg > 0 ? sm.bps[seg - 1] : lo, x1 = seg < B ? sm.bps[seg] : hi;
+    int F, S;
+    double sum;
+    if (seg > 0) {
+        F = sm.bF[seg - 1];
+        S = sm.bS[seg - 1];
+        sum = sm.bsum[seg - 1];
+    } else {
+        S = above(x0);
+        F = above(x0 + 1.0);
+        sum = sm.pref[S] - sm.pref[F];
+    }
+    int fs = 0;       // own scores of prefix t: saturated, above x0 (two counters)
+    double part = 0.0;
+    for (int s = lane & 7; s <= t - L.t0 && s < CHUNK; s += 8) {
+        const double v = (double)sm.own[s];
+        const bool a = v > x0, c = v > x0 + 1.0;
+        fs += (c ? 1 : 0) + (a ? 1 << 16 : 0);
+        part += a && !c ? v : 0.0;
+    }
+#pragma unroll
+    for (int st = 0; st < 3; st++) {   // within groups of 8 lanes: swap neighbours, swap pairs, mirror
+        fs += dpp_i32(fs, st);
+        part += dpp_f64(part, st);
+    }
+    F += L.Fb + (fs & 0xFFFF);
+    S += L.Fb + L.Cb + (fs >> 16);
+    const double fsum = L.sumb + sum + part;
+    double x = S > F ? (fsum + (double)F - (double)k) / (double)(S - F) : x1;
+    x = fmin(fmax(x, x0), x1);
+    if ((lane & 7) == 0 && t < tb && t >= k) tr[t] = (float)x;
+}
+
+// One chunk (t0 < t1, k >= 1) by its histogram; false, with nothing written but the thresholds of prefixes of at most k
+// entries (and lifetimes that are written again), when the chunk does not suit it.
+__device__ bool mask_chunk_hist(HistSmem& sm, const float* __restrict__ ur, float* __restrict__ tr,
+                                int32_t* __restrict__ dr, int t0, int t1, int k, int* status, int j0, int survivor)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int cn = t1 - t0;
+    const float nv0 = lane < cn ? ur[t0 + lane] : -INFINITY, nv1 = lane + 64 < cn ? ur[t0 + lane + 64] : -INFINITY;
+    if (wv == 0) {
+        sm.ownkey[lane] = sel_key(nv0, t0 + lane);
+        sm.ownkey[lane + 64] = sel_key(nv1, t0 + lane + 64);
+        sm.own[lane] = nv0;
+        sm.own[lane + 64] = nv1;
+    }
+    if (t0 < k) {
+        float mn = INFINITY;
+        each_older(ur, t0, [&](float v, int, bool in) { mn = fminf(mn, in ? v : INFINITY); }, [] {});
+        mn = wave_min_f32(mn);
+        if (lane == 0) sm.wmm[0][wv] = mn;
+        __syncthreads();
+        if (wv == 0)
+            short_prefix_tau(wave_min_f32(lane < NW_CHUNK ? sm.wmm[0][lane] : INFINITY), nv0, nv1, t0, t1, k, lane, tr);
+        if (t1 <= k) return true;
+        __syncthreads();
+    }
+    float origin = -8.0f;
+    bool ok = false;
+    int jlo = 0, jhi = 0;
+    double lo = 0.0, hi = 0.0;
+    for (int attempt = 0; attempt < 2; attempt++) {
+        const float shift = -origin * (float)HRES;  // exact: the origin is a whole number
+        auto bin = [&](float v) { return (int)__builtin_amdgcn_fmed3f(fmaf(v, (float)HRES, shift), 0.0f, (float)(HBINS - 1)); };
+        *(uint2*)&sm.x.h.hist[2 * tid] = make_uint2(0, 0);
+        *(uint2*)&sm.x.h.own[2 * tid] = make_uint2(0, 0);
+        if (tid == 0) { sm.jlo = -1; sm.jhi = -1; sm.jl = t0 >= k ? -1 : 0; sm.jh = -1; sm.above = 0; sm.jmin = 0; sm.nq = 0; sm.nbp = 0; sm.full = 0; }
+        __syncthreads();
+        each_older(ur, t0, [&](float v, int, bool in) { if (in) atomicAdd(&sm.x.h.hist[bin(v)], 1u); }, [] {});
+        if (tid < cn) atomicAdd(&sm.x.h.own[bin(tid < 64 ? nv0 : nv1)], 1u);  // (waves 0 and 1)
+        __syncthreads();
+        // Suffix counts N_i = #{bin >= i} of the older and of all scores: thread t owns the bins 2047 - 2t, 2046 - 2t.
+        const int b0 = HBINS - 1 - 2 * tid;
+        const uint2 ho = *(const uint2*)&sm.x.h.hist[b0 - 1], hn = *(const uint2*)&sm.x.h.own[b0 - 1];
+        const unsigned o0 = ho.y, o1 = ho.x, a0 = o0 + hn.y, a1 = o1 + hn.x;
+        unsigned eo, ea;
+        block_scan2(o0 + o1, a0 + a1, sm.wscan[0], sm.wscan[1], eo, ea);
+        const unsigned No0 = eo + o0, No1 = No0 + o1, Na0 = ea + a0, Na1 = Na0 + a1;
+        if (No0 >= (unsigned)k && eo < (unsigned)k) sm.jl = b0;
+        if (No1 >= (unsigned)k && No0 < (unsigned)k) sm.jl = b0 - 1;
+        if (Na0 >= (unsigned)k && ea < (unsigned)k) { sm.jh = b0; sm.above = (int)eo; }
+        if (Na1 >= (unsigned)k && Na0 < (unsigned)k) { sm.jh = b0 - 1; sm.above = (int)No0; }
+        if (Na0 == (unsigned)t1 && ea < (unsigned)t1) sm.jmin = b0;
+        if (Na1 == (unsigned)t1 && Na0 < (unsigned)t1) sm.jmin = b0 - 1;
+        // Cumulate once more, so that windowed sums of N are differences.  Sums over a window stay below 2^32 up to
+        // 2^24 scores; beyond, the counts are scaled down (older: rounded down, all: rounded up).
+        int s = 0;
+        while ((t1 >> s) > (1 << 24)) s++;
+        const unsigned up = (1u << s) - 1u;
+        unsigned co, ca;
+        const unsigned so0 = No0 >> s, so1 = No1 >> s, sa0 = (Na0 + up) >> s, sa1 = (Na1 + up) >> s;
+        block_scan2(so0 + so1, sa0 + sa1, sm.wscan[2], sm.wscan[3], co, ca);
+        *(uint2*)&sm.x.h.cum[0][2 * tid] = make_uint2(co + so0, co + so0 + so1);
+        *(uint2*)&sm.x.h.cum[1][2 * tid] = make_uint2(ca + sa0, ca + sa0 + sa1);
+        __syncthreads();
+        // f(edge_j) >= (sum of N_{j+1} .. N_{j+HRES} of the older scores) / HRES: the last j with a sum of at least
+        // k * HRES is a lower bound of every threshold from prefix t0 - 1 on.  f(edge_j) <= (N_j + .. + N_{j+HRES-1}
+        // of all scores) / HRES: the first j with a sum below k * HRES bounds every threshold of the chunk from above.
+        auto wsum = [&](int which, int d_hi, int d_lo) { return sm.x.h.cum[which][d_hi] - (d_lo >= 0 ? sm.x.h.cum[which][d_lo] : 0u); };
+        const unsigned want = (unsigned)(((unsigned long long)k * HRES + up) >> s);
+        auto low = [&](int j) { return wsum(0, HBINS - 2 - j, HBINS - 2 - HRES - j) >= want; };  // j <= HBINS - 1 - HRES
+        auto high = [&](int j) { return wsum(1, HBINS - 1 - j, HBINS - 1 - HRES - j) < want; };
+        constexpr int JTOP = HBINS - 1 - HRES;
+        if (b0 - 1 >= 1 && b0 < JTOP) {
+            const bool l0 = low(b0 - 1), l1 = low(b0), l2 = low(b0 + 1);
+            if (l0 && !l1) sm.jlo = b0 - 1;
+            if (l1 && !l2) sm.jlo = b0;
+            const bool h0 = high(b0 - 1), h1 = high(b0), h2 = high(b0 + 1);
+            if (!h0 && h1) sm.jhi = b0;
+            if (!h1 && h2) sm.jhi = b0 + 1;
+        }
+        __syncthreads();
+        jlo = sm.jlo;
+        jhi = sm.jhi;
+        if (t0 < k) jlo = sm.jmin - HRES;  // the first threshold is that of prefix k: at least min - 1
+        // bin() rounds: a score may lie 2^-21 beyond its bin's edges
+        constexpr double EPS = 1.0 / (1 << 20);
+        ok = jhi > 0 && (t0 < k ? sm.jmin > 0 : jlo > 0);
+        lo = (double)origin + (double)jlo / HRES - EPS;
+        hi = (double)origin + (double)jhi / HRES + EPS;
+        if (ok || attempt == 1) break;
+        // another window: over the whole range if it fits, else below the largest score
+        float a = INFINITY, b = -INFINITY;
+        each_older(ur, t0, [&](float v, int, bool in) { a = fminf(a, in ? v : INFINITY); b = fmaxf(b, v); }, [] {});
+        a = wave_min_f32(fminf(a, fminf(lane < cn ? nv0 : INFINITY, lane + 64 < cn ? nv1 : INFINITY)));
+        b = wave_max_f32(fmaxf(b, fmaxf(nv0, nv1)));
+        if (lane == 0) { sm.wmm[0][wv] = a; sm.wmm[1][wv] = b; }
+        __syncthreads();
+        a = wave_min_f32(lane < NW_CHUNK ? sm.wmm[0][lane] : INFINITY);
+        b = wave_max_f32(lane < NW_CHUNK ? sm.wmm[1][lane] : -INFINITY);
+        origin = (b - a <= 12.0f) ? floorf(0.5f * (a + b)) - 8.0f : floorf(b) - 13.0f;
+        if (!(fabsf(origin) < 65536.0f)) break;  // (uniform) the edges would not be exact
+    }
+    if (!ok) return false;
+
+    // ---- second pass: count and sum what is certain between the bounds, collect what is not ----
+    // (for an fp32 score v: v > x <=> v > rd(x))
+    const float lof = __double2float_rd(lo), hif = __double2float_rd(hi);
+    const float lo1f = __double2float_rd(lo + 1.0), hi1f = __double2float_rd(hi + 1.0);
+    const float shift = -origin * (float)HRES;
+    // bins jl .. jh as limits of the value that bin() truncates
+    const int jl = sm.jl, jh = sm.jh, above = sm.above;
+    const float ql = jl == 0 ? -INFINITY : (float)jl, qh = jh == HBINS - 1 ? INFINITY : (float)(jh + 1);
+    // nothing below this matters (a score in bin jl may lie 2^-21 below its edge)
+    const float least = jl == 0 ? -INFINITY : __double2float_rd(fmin(lo, (double)origin + (double)jl / HRES - 1.0 / (1 << 20)));
+    double csum = 0.0;
+    int nF = 0, nC = 0, nM = 0;
+    auto classify = [&](float v, int i, bool in) {
+        const float tb = fmaf(v, (float)HRES, shift);
+        const bool sat = in && v > hi1f;
+        const bool frac = in && v > hif && v <= lo1f;
+        const bool open = in && v > lof && !sat && !frac;
+        const bool sel = in && tb >= ql;
+        const bool q = sel && tb < qh;
+        nF += (int)__popcll(__ballot(sat && !frac));
+        nC += (int)__popcll(__ballot(frac));
+        csum += (double)(frac ? v : 0.0f);
+        if (survivor && sel && !q) dr[i] = survivor;
+        const unsigned long long bo = __ballot(open), bq = __ballot(q);
+        const unsigned long long below = (1ull << lane) - 1ull;
+        if (bo) {
+            const int at = nM + (int)__popcll(bo & below);
+            if (open && at < TL_WAVE) sm.raw[wv][at] = v;
+            nM += (int)__popcll(bo);
+        }
+        if (bq) {
+            int off = 0;
+            if (lane == 0) off = atomicAdd(&sm.nq, (int)__popcll(bq));
+            off = __builtin_amdgcn_readfirstlane(off) + (int)__popcll(bq & below);
+            if (q && off < QL_CAP) sm.qk[off] = sel_key(v, i);
+        }
+    };
+    __syncthreads();  // the histograms are no longer needed
+    // Only a few per cent of the scores lie above the lower bound.  Every wave collects its own and looks at them 64 at
+    // a time, in an order that does not depend on timing (the sum is taken in that order).
+    {
+        float* const cv = sm.x.c.v[wv];
+        int* const cp = sm.x.c.pos[wv];
+        int have = 0;
+        auto flush = [&](int least) {
+            int at = 0;
+            __builtin_amdgcn_wave_barrier();   // (a wave's LDS accesses are performed in program order)
+            while (have - at >= least && have > at) {
+                const bool in = at + lane < have;
+                classify(in ? cv[at + lane] : 0.0f, in ? cp[at + lane] : 0, in);
+                at = min(at + 64, have);
+            }
+            if (at > 0 && at < have) {   // fewer than 64 are left: to the front
+                const float v = cv[at + lane];
+                const int i = cp[at + lane];
+                __builtin_amdgcn_wave_barrier();
+                if (lane < have - at) { cv[lane] = v; cp[lane] = i; }
+            }
+            __builtin_amdgcn_wave_barrier();
+            have -= at;
+        };
+        each_older(ur, t0, [&](float v, int i, bool in) {
+            const bool p = in && v > least;
+            const unsigned long long m = __ballot(p);
+            const int at = have + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+            if (p) { cv[at] = v; cp[at] = i; }
+            have += (int)__popcll(m);
+        }, [&] { if (have >= 64) flush(64); });
+        flush(1);
+    }
+    csum = wave_sum_f64(csum);
+    if (lane == 0) {
+        sm.wsum[wv] = csum;
+        sm.wF[wv] = nF;
+        sm.wC[wv] = nC;
+        sm.wM[wv] = nM;
+        if (nM > TL_WAVE) sm.full = 1;
+    }
+    __syncthreads();
+    const int MQ = sm.nq;
+    if (sm.full || MQ > QL_CAP) return false;
+    // totals over the waves, and this wave's place in the list
+    const int tM = (int)wave_scan_u32(lane < NW_CHUNK ? (unsigned)sm.wM[lane] : 0u);
+    const int M = __builtin_amdgcn_readlane(tM, NW_CHUNK - 1);
+    ListBounded L;
+    L.v = sm.tl;
+    L.M = M;
+    L.Fb = wave_sum_i32(lane < NW_CHUNK ? sm.wF[lane] : 0);
+    L.Cb = wave_sum_i32(lane < NW_CHUNK ? sm.wC[lane] : 0);
+    L.sumb = 0.0;
+    for (int i = 0; i < NW_CHUNK; i++) L.sumb += sm.wsum[i];
+    L.t0 = t0;
+    L.lane = lane;
+    L.own[0] = (double)nv0;
+    L.own[1] = (double)nv1;
+    {
+        // The list in descending order, by rank (equal scores are interchangeable): sums over it then do not depend on
+        // the order in which the scores arrived.  Its breakpoints (z and z - 1, where they lie between the bounds) are
+        // collected at the same time, those of the chunk's own scores by waves 0 and 1, and ranked in the same way.
+        if (lane < nM) sm.x.s.v[tM_before(tM, wv) + lane] = sm.raw[wv][lane];
+        if (tid < 64) sm.x.s.v[M + tid] = -INFINITY;
+        for (int i = tid; i < TL_CAP; i += NT_CHUNK) sm.x.s.tie[i] = 0;
+        auto add = [&](bool on, double b) {
+            const unsigned long long m = __ballot(on);
+            if (!m) return;
+            int off = 0;
+            if (lane == 0) off = atomicAdd(&sm.nbp, (int)__popcll(m));
+            off = __builtin_amdgcn_readfirstlane(off) + (int)__popcll(m & ((1ull << lane) - 1ull));
+            if (on && off < BP_CAP) sm.x.s.bp[off] = b;
+        };
+        auto add_both = [&](bool real, float v) {
+            add(real && v > lof && v <= hif, (double)v);
+            add(real && v > lo1f && v <= hi1f, (double)v - 1.0);
+        };
+        if (nM > 0) add_both(lane < nM, sm.raw[wv][lane]);
+        if (wv < 2) add_both(64 * wv + lane < cn, wv ? nv1 : nv0);
+        if (tid < BP_CAP) sm.x.s.btie[tid] = 0;
+        __syncthreads();
+        // G lanes share the counting for one element: each takes a run of q others
+        if (M > 0) {
+            int G = 1;
+            while (G < 16 && 2 * G * M <= NT_CHUNK) G *= 2;   // M <= NT_CHUNK: every element has its G lanes
+            const int g = tid & (G - 1), e = tid / G, q = (M + 4 * G - 1) / (4 * G) * 4;
+            const float v = sm.x.s.v[min(e, M - 1)];
+            int rank = 0;
+            for (int j = g * q; j < min(g * q + q, M); j += 4) {
+                const float4 y = *(const float4*)&sm.x.s.v[j];
+                rank += (y.x > v ? 1 : 0) + (y.y > v ? 1 : 0) + (y.z > v ? 1 : 0) + (y.w > v ? 1 : 0);
+            }
+            for (int o = 1; o < G; o <<= 1) rank += __shfl_xor(rank, o, 64);
+            if (e < M && g == 0) sm.tl[rank + atomicAdd(&sm.x.s.tie[rank], 1)] = v;
+        }
+    }
+    const int B = sm.nbp;
+    if (B > 0 && B <= BP_CAP) {
+        int G = 1;
+        while (G < 16 && 2 * G * B <= NT_CHUNK) G *= 2;
+        const int g = tid & (G - 1), e = tid / G, q = (B + 2 * G - 1) / (2 * G) * 2;
+        const double v = sm.x.s.bp[min(e, B - 1)];
+        int rank = 0;
+        for (int j = g * q; j < min(g * q + q, B); j += 2) {
+            const double2 y = *(const double2*)&sm.x.s.bp[j];
+            rank += (y.x < v ? 1 : 0) + (y.y < v && j + 1 < B ? 1 : 0);
+        }
+        for (int o = 1; o < G; o <<= 1) rank += __shfl_xor(rank, o, 64);
+        if (e < B && g == 0) sm.bps[rank + atomicAdd(&sm.x.s.btie[rank], 1)] = v;
+    }
+    __syncthreads();
+    const int TPW = CHUNK / NW_CHUNK;
+    const int ta = min(t1, t0 + wv * TPW), tb_ = min(t1, ta + TPW);
+    if (B <= BP_CAP && M <= BP_CAP) {
+        solve_parallel(sm, L, tr, ta, tb_, k, lo, hi);
+    } else {
+#pragma unroll
+        for (int r = 0; r < TL_REG; r++) L.reg[r] = 64 * r + lane < M ? (double)sm.tl[64 * r + lane] : -INFINITY;
+        wave_tau(L, tr, ta, tb_, k, lo, hi, status);
+    }
+    // ---- lifetimes: key j dies at the first prefix that holds k larger keys ----
+    // Own keys outside the bins of theta need no counting: below them they are dead on arrival, above they outlive the chunk.
+    const unsigned long long k0 = sm.ownkey[lane], k1 = sm.ownkey[lane + 64];
+    const bool r0 = lane < cn, r1 = lane + 64 < cn;
+    const float tb0 = fmaf(nv0, (float)HRES, shift), tb1 = fmaf(nv1, (float)HRES, shift);
+    if (wv == NW_CHUNK - 1) {
+        if (r0 && tb0 < ql) dr[t0 + lane] = j0 + t0 + lane;
+        if (r1 && tb1 < ql) dr[t0 + lane + 64] = j0 + t0 + lane + 64;
+        if (survivor) {
+            if (r0 && tb0 >= qh) dr[t0 + lane] = survivor;
+            if (r1 && tb1 >= qh) dr[t0 + lane + 64] = survivor;
+        }
+    }
+    unsigned long long o0 = __ballot(r0 && tb0 >= ql && tb0 < qh), o1 = __ballot(r1 && tb1 >= ql && tb1 < qh);
+    const int no0 = (int)__popcll(o0), no = no0 + (int)__popcll(o1);
+    auto nth_bit = [&](unsigned long long m, int want) {   // position of the want-th set bit, counted from 1
+        const int bef = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+        return (int)__builtin_ctzll(__ballot(((m >> lane) & 1ull) && bef == want - 1));
+    };
+    for (int i = wv; i < MQ + no; i += NW_CHUNK) {
+        const bool own = i >= MQ;
+        int c = -1;
+        if (own) c = i - MQ < no0 ? nth_bit(o0, i - MQ + 1) : 64 + nth_bit(o1, i - MQ - no0 + 1);
+        const unsigned long long key = readlane_u64(own ? sm.ownkey[c] : sm.qk[i], 0);
+        const int j = key_pos(key);
+        int older = above;           // older keys above this one
+        for (int m = 0; m < MQ; m += 64) older += (int)__popcll(__ballot(m + lane < MQ && sm.qk[min(m + lane, MQ - 1)] > key));
+        const int need = k - older;  // the newcomer that pushes it out: the need-th larger one
+        int d = -1;                  // chunk entry at which it dies
+        if (need <= 0) {
+            if (!own) continue;      // out before this chunk
+            d = c;
+        } else {
+            const unsigned long long m0 = __ballot(r0 && k0 > key), m1 = __ballot(r1 && k1 > key);
+            const int n0 = (int)__popcll(m0);
+            if (need <= n0) d = nth_bit(m0, need);
+            else if (need <= n0 + (int)__popcll(m1)) d = 64 + nth_bit(m1, need - n0);
+            if (d >= 0 && own) d = max(d, c);
+        }
+        if (lane == 0) {
+            if (d >= 0) dr[j] = j0 + t0 + d;
+            else if (survivor) dr[j] = survivor;
+        }
+    }
+    return true;
+}
+
+union MaskSmem {
+    HistSmem h;
+    SortedSmem s;
+};
+
+// What a workgroup of both kernels does first: its chunk [t0, t1) of row `row`, in positions that count from the row's
+// first valid key (the pointers are moved there; lifetimes count from the row's start, j0 being the difference).
+struct ChunkArgs {
+    const float* u;
+    float* tau;
+    int32_t* death;
+    int n, k, t_begin;
+    const int32_t* first_valid;
+};
+struct ChunkJob {
+    const float* ur;
+    float* tr;
+    int32_t* dr;
+    int t0, t1, j0, survivor;
+};
+__device__ __forceinline__ bool chunk_job(const ChunkArgs& a, int c, int row, ChunkJob& J)
+{
+    const int j0 = a.first_valid ? a.first_valid[row] : 0;
+    const int t1 = min(a.n, (c + 1) * CHUNK);
+    if (t1 <= a.t_begin) return false;  // nobody asks for these thresholds and lifetimes
+    if (j0 > c * CHUNK) {               // entries before the row's start: never selected, and a finite threshold
+        const int e = c * CHUNK + threadIdx.x;
+        if (e < min(t1, j0)) {
+            a.tau[(size_t)row * a.n + e] = 0.0f;
+            a.death[(size_t)row * a.n + e] = e;
+        }
+        if (t1 <= j0) return false;
+    }
+    J.ur = a.u + (size_t)row * a.n + j0;
+    J.tr = a.tau + (size_t)row * a.n + j0;
+    J.dr = a.death + (size_t)row * a.n + j0;
+    J.t0 = max(c * CHUNK - j0, 0);
+    J.t1 = t1 - j0;
+    J.j0 = j0;
+    // every key's lifetime is written once: by the chunk in which it dies or, if it outlives the row, by the last chunk
+    J.survivor = t1 == a.n ? a.n : 0;
+    return true;
+}
+
+// k == 0 or k >= the row's length: nothing is ever selected, or nothing ever dies.  (The first chunk that is not
+// skipped also writes the lifetimes of the chunks before it.)
+__device__ __forceinline__ void trivial_deaths(const ChunkArgs& a, const ChunkJob& J)
+{
+    const int first = a.t_begin > 0 && J.t0 + J.j0 <= a.t_begin ? 0 : J.t0;
+    for (int t = first + threadIdx.x; t < J.t1; t += NT_CHUNK) J.dr[t] = a.k == 0 ? J.j0 + t : a.n;
+}
+
+__device__ void window_only_chunk(float* red, const ChunkJob& J)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, cn = J.t1 - J.t0;
+    float mx = -INFINITY;
+    for (int i = tid; i < J.t0; i += NT_CHUNK) mx = fmaxf(mx, J.ur[i]);
+    mx = wave_max_f32(mx);
+    if (lane == 0) red[wv] = mx;
+    __syncthreads();
+    if (wv == 0)
+        short_prefix_tau(wave_max_f32(lane < NW_CHUNK ? red[lane] : -INFINITY), lane < cn ? J.ur[J.t0 + lane] : -INFINITY,
+                         lane + 64 < cn ? J.ur[J.t0 + lane + 64] : -INFINITY, J.t0, J.t1, 0, lane, J.tr);
+}
+
+// Few chunks: status has one word per chunk, which the chunk's workgroup sets.  Many (shared_status): one word, cleared
+// ahead of this kernel, because a word per chunk would make the workspace grow.  Two workgroups share a compute unit
+// (76 KB of LDS, 64 registers): 256 chunks of one row run at once wherever they land.
+__global__ void mask_clear_status_kernel(int* __restrict__ status) { *status = 0; }
+
+__global__ __launch_bounds__(NT_CHUNK, 8) void mask_kernel(ChunkArgs a, int* __restrict__ status, int shared_status)
+{
+    __shared__ __align__(16) MaskSmem sm;
+    // late chunks have the longest prefixes: they go first
+    const int c = gridDim.x - 1 - blockIdx.x, row = blockIdx.y;
+    int* st = status;
+    if (!shared_status) {
+        st += (size_t)row * gridDim.x + c;
+        if (threadIdx.x == 0) *st = 0;
+    }
+    ChunkJob J;
+    if (!chunk_job(a, c, row, J)) return;
+    if (a.k == 0 || a.n - J.j0 <= a.k) trivial_deaths(a, J);
+    if (a.k == 0) { window_only_chunk((float*)&sm, J); return; }
+    if (mask_chunk_hist(sm.h, J.ur, J.tr, J.dr, J.t0, J.t1, a.k, st, J.j0, J.survivor)) return;
+    __syncthreads();
+    mask_chunk_sorted(sm.s, J.ur, J.tr, J.dr, J.t0, J.t1, a.k, st, J.j0, J.survivor);
 }
 
 // ---------------------------------------------------------------------------------
@@ -1070,42 +1650,26 @@ __global__ __launch_bounds__(256) void materialize_kernel(const float* __restric
 }
 
 int launch_mask(const sparsek_cfg& c, const float* u, float* tau, int32_t* death, void* ws,
-                hipStream_t st, int t_begin)
+                hipStream_t st, int t_begin, const int32_t* first_valid)
 {
-    const int rows = c.B * c.Gu;
-    const int nsuper = (c.n + SUPER - 1) / SUPER;
     const int nchunks = (c.n + CHUNK - 1) / CHUNK;
-    const size_t lo_bytes = align_up((size_t)rows * nsuper * sizeof(float), 256);
-    float* lo = (float*)ws;
-    int* status = (int*)((char*)ws + lo_bytes);
-    unsigned* handed_on = (unsigned*)((char*)ws + lo_bytes + 256);
-    const int nwords = (int)(((size_t)rows * nchunks + 31) / 32);
-    hipLaunchKernelGGL(mask_coarse_kernel, dim3(c.k == 0 ? 1 : nsuper, rows), dim3(NT_COARSE), 0, st, u, lo, tau,
-                       death, c.n, c.k, nsuper, status, handed_on, nwords);
-    if (c.k == 0) return launch_status();
-    if (c.k < c.n) {
-        // The candidates of a chunk number about 2.5 k for scores of unit variance (the support of the threshold), so
-        // up to k = 1280 the half-size lists usually do, and two workgroups then fit a compute unit: worth it when
-        // the chunks outnumber the compute units several times (many score rows).  Chunks whose candidates do not
-        // fit are handed on to the full-capacity kernel.  Not for the virtual sequences of the chunked prefill
-        // (t_begin > 0), whose padding scores all count as candidates at first.
-        const bool two_stage = c.k <= 1280 && t_begin == 0 && (long long)rows * nchunks >= 2048;
-        if (two_stage)
-            hipLaunchKernelGGL((mask_chunk_kernel<CAP_SMALL, NB_SMALL>), dim3(nchunks, rows), dim3(NT_CHUNK), 0, st, u, lo,
-                               tau, death, c.n, c.k, nsuper, status, t_begin, handed_on, 0);
-        hipLaunchKernelGGL((mask_chunk_kernel<CAP, NB>), dim3(nchunks, rows), dim3(NT_CHUNK), 0, st, u, lo, tau,
-                           death, c.n, c.k, nsuper, status, t_begin, handed_on, two_stage ? 1 : 0);
-    }
+    const ChunkArgs a{u, tau, death, c.n, c.k, t_begin, first_valid};
+    const bool shared = mask_shared_status(c);
+    if (shared) hipLaunchKernelGGL(mask_clear_status_kernel, dim3(1), dim3(1), 0, st, (int*)ws);
+    hipLaunchKernelGGL(mask_kernel, dim3(nchunks, c.B * c.Gu), dim3(NT_CHUNK), 0, st, a, (int*)ws, shared ? 1 : 0);
     return launch_status();
 }
 
 int mask_status(const sparsek_cfg& c, const void* ws, int32_t* host_flag, hipStream_t st)
 {
-    const size_t rows = (size_t)c.B * c.Gu, nsuper = ((size_t)c.n + SUPER - 1) / SUPER;
-    const int* status = (const int*)((const char*)ws + align_up(rows * nsuper * sizeof(float), 256));
-    if (hipMemcpyAsync(host_flag, status, sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess)
+    int32_t words[STATUS_WORDS];
+    const size_t count = mask_shared_status(c) ? 1 : mask_chunks(c);
+    if (hipMemcpyAsync(words, ws, count * sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess)
         return SPARSEK_ERR_LAUNCH;
-    return hipStreamSynchronize(st) == hipSuccess ? SPARSEK_OK : SPARSEK_ERR_LAUNCH;
+    if (hipStreamSynchronize(st) != hipSuccess) return SPARSEK_ERR_LAUNCH;
+    *host_flag = 0;
+    for (size_t i = 0; i < count; i++) *host_flag |= words[i];
+    return SPARSEK_OK;
 }
 
 int launch_materialize(const sparsek_cfg& c, const float* u, const float* tau, const int32_t* death,

@@ -346,7 +346,8 @@ __global__ __launch_bounds__(256, 2) void mask_bwd_mfma_kernel(
     const float* __restrict__ u, const float* __restrict__ tau, const int32_t* __restrict__ death,
     const int32_t* __restrict__ lists, const int32_t* __restrict__ counts, const uint16_t* __restrict__ o,
     const float* __restrict__ lse, const uint16_t* __restrict__ dO, float* __restrict__ A, float* __restrict__ C,
-    int H, int Gu, int n, int k, int w, float scale, int nb, int BH, int q_begin, int q_rows)
+    int H, int Gu, int n, int k, int w, float scale, int nb, int BH, int q_begin, int q_rows,
+    const int32_t* __restrict__ first_valid)
 {
     static_assert(RAW <= SEG, "survivors of one segment must fit the staged metadata");
     __shared__ __align__(16) MfmaSmem<D, 16> sm;
@@ -378,7 +379,8 @@ __global__ __launch_bounds__(256, 2) void mask_bwd_mfma_kernel(
     // prefixes of the block's queries that carry gradient: T = i - w with T >= k (prefixes with at
     // most k entries have every gate at 1)
     const int Tmax = min(n - 1, i0 + QB - 1) - w;
-    const int Tmin = max(i0 - w, k);
+    const int kmin = k + (first_valid ? first_valid[row] : 0);
+    const int Tmin = max(i0 - w, kmin);
     if (Tmax < Tmin) return;
     const uint16_t* kh = kk + (size_t)bh * n * D;
     const uint16_t* vh = v + (size_t)bh * n * D;
@@ -395,9 +397,9 @@ __global__ __launch_bounds__(256, 2) void mask_bwd_mfma_kernel(
     const int qb = min(qa + 31, n - 1);
     const int qi = qa + col;
     const int qrow = min(qi, n - 1);
-    const bool qlive = (qi < n) && (qi - w >= k);
+    const bool qlive = (qi < n) && (qi - w >= kmin);
     const int Tp = qlive ? qi - w : -1;
-    const bool wave_live = (qa < n) && (qb - w >= k);
+    const bool wave_live = (qa < n) && (qb - w >= kmin);
     // Order of the prologue's loads: the small, cache-resident ones first (tau, lse, then the
     // candidates with their dependent score / death reads), the cold query rows of Q, dO, O last.
     // Loads complete in issue order, so this lets the candidates be classified and compacted, and
@@ -448,7 +450,7 @@ __global__ __launch_bounds__(256, 2) void mask_bwd_mfma_kernel(
     float rowsum = 0.0f;
     BwdCarry cy;
     if (tid < 3 * KT) colsum[tid / KT][tid % KT] = 0.0f;
-    const bool all_live = (i0 - w >= k) && (i0 + QB <= n);  // every lane of the block owns a query with gradient
+    const bool all_live = (i0 - w >= kmin) && (i0 + QB <= n);  // every lane of the block owns a query with gradient
     __syncthreads();
     const float tau_lo = fminf(fminf(tred[0][0], tred[0][1]), fminf(tred[0][2], tred[0][3]));
     const float tau_hi = fmaxf(fmaxf(tred[1][0], tred[1][1]), fmaxf(tred[1][2], tred[1][3]));
@@ -566,14 +568,15 @@ template <int D>
 static void launch_bwd_mfma(const sparsek_cfg& c, const void* q, const void* k, const void* v, const float* u,
                             const float* tau, const int32_t* death, const int32_t* lists, const int32_t* counts,
                             const void* o, const float* lse, const void* dO, float* A, float* C, int nb,
-                            hipStream_t st, int q_begin, int q_rows)
+                            hipStream_t st, int q_begin, int q_rows, const int32_t* first_valid)
 {
     const int BH = c.B * c.H;
     dim3 grid(nb * BH);
 #define SPK_LAUNCH_B(MODE)                                                                                    \
     hipLaunchKernelGGL((mask_bwd_mfma_kernel<D, MODE>), grid, dim3(256), 0, st, (const uint16_t*)q,           \
                        (const uint16_t*)k, (const uint16_t*)v, u, tau, death, lists, counts, (const uint16_t*)o, \
-                       lse, (const uint16_t*)dO, A, C, c.H, c.Gu, c.n, c.k, c.w, c.softmax_scale, nb, BH, q_begin, q_rows)
+                       lse, (const uint16_t*)dO, A, C, c.H, c.Gu, c.n, c.k, c.w, c.softmax_scale, nb, BH, q_begin, q_rows, \
+                       first_valid)
     if (c.gate_mode == 0) SPK_LAUNCH_B(0);
     else if (c.gate_mode == 3) SPK_LAUNCH_B(3);
     else SPK_LAUNCH_B(1);
@@ -613,11 +616,14 @@ __device__ __forceinline__ int first_true(const float* __restrict__ tr, const fl
 }
 
 __global__ __launch_bounds__(1024) void mask_bwd_ranges_kernel(const float* __restrict__ u,
-                                                                const float* __restrict__ tau, int n, int k,
+                                                                const float* __restrict__ tau, int n, int k_, int t_min,
+                                                                const int32_t* __restrict__ first_valid,
                                                                 int32_t* __restrict__ diff, int2* __restrict__ ab)
 {
     __shared__ float ts[RS_MAX];
     const int row = blockIdx.y;
+    // the first prefix that counts: more than k entries, and its threshold is there
+    const int k = max(k_ + (first_valid ? first_valid[row] : 0), t_min);
     const float* tr = tau + (size_t)row * n;
     const int stride = (n + RS_MAX - 1) / RS_MAX;
     const int ns = (n + stride - 1) / stride;
@@ -756,7 +762,7 @@ __global__ __launch_bounds__(1024) void mask_bwd_scan_final_kernel(const float* 
 
 int launch_mask_bwd(const sparsek_cfg& c, const void* q, const void* k, const void* v, const float* u,
                     const float* tau, const int32_t* death, const void* o, const float* lse, const void* dO,
-                    float* du, void* ws, hipStream_t st, int q_begin, int q_rows, int t_min)
+                    float* du, void* ws, hipStream_t st, int q_begin, int q_rows, int t_min, const int32_t* first_valid)
 {
     const BwdWs W = bwd_ws(c);
     char* base = (char*)ws;
@@ -778,15 +784,17 @@ int launch_mask_bwd(const sparsek_cfg& c, const void* q, const void* k, const vo
     hipLaunchKernelGGL(zero_kernel, dim3(512), dim3(256), 0, st, (uint32_t*)(base + W.A), (W.G - W.A) / 4);
     // t_min: thresholds of earlier prefixes are not available (and no query uses them)
     hipLaunchKernelGGL(mask_bwd_ranges_kernel, dim3((c.n + 1023) / 1024, rows), dim3(1024), 0, st, u, tau, c.n,
-                       std::max(c.k, t_min), diff, ab);
+                       c.k, t_min, first_valid, diff, ab);
     launch_block_lists(c, death, lists, counts, st);
     dim3 grid(nb, c.B * c.H);
     if (c.dtype == SPARSEK_BF16 && (c.d == 64 || c.d == 128) && (uint64_t)c.n * c.d * 2 <= 0xFFFFFFFFull) {
         if (c.d == 64)
-            launch_bwd_mfma<64>(c, q, k, v, u, tau, death, lists, counts, o, lse, dO, A, C, nb, st, q_begin, q_rows);
+            launch_bwd_mfma<64>(c, q, k, v, u, tau, death, lists, counts, o, lse, dO, A, C, nb, st, q_begin, q_rows,
+                                first_valid);
         else
-            launch_bwd_mfma<128>(c, q, k, v, u, tau, death, lists, counts, o, lse, dO, A, C, nb, st, q_begin, q_rows);
-    } else if (q_begin != 0 || q_rows != 0 || t_min != 0)
+            launch_bwd_mfma<128>(c, q, k, v, u, tau, death, lists, counts, o, lse, dO, A, C, nb, st, q_begin, q_rows,
+                                first_valid);
+    } else if (q_begin != 0 || q_rows != 0 || t_min != 0 || first_valid)
         return SPARSEK_ERR_UNSUPPORTED;  // the offset-query form exists on the MFMA path only
     else if (c.dtype == SPARSEK_F32)
         hipLaunchKernelGGL(mask_bwd_generic_kernel<float>, grid, dim3(256), 0, st, (const float*)q, (const float*)k,

@@ -1,6 +1,6 @@
 // sparsek_mask_static: the thresholds and lifetimes of sparsek_mask for callers that cannot bring a workspace
 // (code under HIP graph capture, serving loops and harnesses that forbid allocation).  The kernels are those of
-// sparsek_mask; their scratch -- the per-super-block lower bounds and the status word -- lives in a file-scope device
+// sparsek_mask; their scratch -- the status words -- lives in a file-scope device
 // array that every GPU holds once, until the process ends.  Nothing here allocates or frees.
 #include <mutex>
 
@@ -8,7 +8,7 @@
 
 namespace {
 
-// rows * ceil(n / 2048) lower bounds (fp32) + 256 bytes for the status word must fit
+// mask_ws_bytes of a call must fit
 constexpr size_t SCRATCH_BYTES = SPARSEK_MASK_STATIC_MAX_BYTES;
 static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
 
@@ -51,8 +51,7 @@ int sparsek_mask_static(const sparsek_cfg* cfg, const float* u, float* tau, int3
     void* ws = nullptr;
     int rc = scratch_address(&ws);
     if (rc) return rc;
-    // every word of the scratch that a call reads is written earlier in the same call (the lower bounds and the
-    // cleared status word by the first kernel), so nothing needs clearing here
+    // every word of the scratch that a call reads is written earlier in the same call, so nothing needs clearing here
     return spk::launch_mask(*cfg, u, tau, death, ws, (hipStream_t)stream);
 }
 

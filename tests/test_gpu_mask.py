@@ -87,6 +87,21 @@ def test_mask_config1(oracle):
     check_rows(oracle, inp["u"].reshape(1, -1), inp["k"], sample_t=[63, 64, 100, 500, 1023])
 
 
+@pytest.mark.parametrize("n,k,scale,offset", [
+    (1500, 200, 1.0, 100.0),    # another histogram window over the whole range
+    (1500, 200, 5.0, -40.0),    # a range too wide for one window: the window below the largest score
+    (3000, 700, 0.02, 0.0),     # most scores between the bounds: more than one list or the breakpoint table holds
+    (2200, 500, 0.2, 3.0),      # more breakpoints than the table of the parallel solution
+    (1281, 1152, 1.0, 0.0),     # the k-th prefix ends a chunk
+    (1283, 1153, 1.0, 0.0),     # ... and starts one
+])
+def test_mask_ranges_and_clusters(oracle, n, k, scale, offset):
+    require_gpu()
+    say("mask range", n, k, scale, offset)
+    rng = np.random.default_rng(n + k)
+    check_rows(oracle, (rng.standard_normal((2, n)) * scale + offset).astype(np.float32), k)
+
+
 def test_mask_candidate_overflow_fallback(oracle):
     """More scores above the threshold than the LDS list holds: the kernel must switch to
     its global-memory path and still be exact."""
