@@ -198,7 +198,8 @@ int sparsek_decode_load(const sparsek_decode_cfg *cfg, void *state, size_t state
 int sparsek_decode_step(const sparsek_decode_cfg *cfg, void *state, const void *q_new,
                         const void *k_new, const void *v_new, const float *u_new, void *o,
                         void *stream);
-/* copies the per-row status words [B*Gu] to host memory; synchronises the stream.  bit 0: candidate overflow */
+/* copies the per-row status words [B*Gu] to host memory; synchronises the stream.  bit 0: candidate overflow; bit 1: a
+ * threshold solve stopped at its iteration cap; bit 2: a bounded wait inside a step ran out (neither observed) */
 int sparsek_decode_status(const sparsek_decode_cfg *cfg, const void *state, int32_t *host_flags,
                           void *stream);
 

@@ -7,17 +7,31 @@
 // per-slot gate score (+inf = window key, gate 1; finite = selected key, gate
 // clip(u - tau, 0, 1); -inf = empty), so one step moves no K/V rows except the new token's.
 //
-// One step = two launches: (1) one workgroup per score row updates tau / top-k / candidates
-// for the key that leaves the window and stores the new token's K/V rows; (2) one workgroup
-// per head streams the k+w slots once (HBM-bound) with an online softmax.
+// One step = one launch.  The first workgroups of the grid, one per score row, update tau / top-k / candidates for the
+// key that leaves the window and store the new token's K/V rows; the others stream the k+w slots of a head (HBM-bound),
+// or a share of them when there are few heads.  A head needs the row's update only for the gates, so it takes the dot
+// products of all its K rows first and then picks the few changes of the step up from a record that the row's workgroup
+// publishes; the update (dependent loads, 7 to 20 us) runs in the shadow of the K stream.
 #include "common.hpp"
 
 namespace spk {
 
+// What a step changes for the attention of one score row.  Every word carries the step's number in its upper half, so
+// that a reader needs no ordering between them: it waits until all six have the number of the step it belongs to.
+// `done` counts the heads of the row that have finished, over all steps: divided by the number of heads per row it is
+// the number of the steps before this one for as long as any head of this step still runs.
+enum { REC_TAU = 0, REC_EVICTED = 1, REC_LEFT = 2, REC_LEFT_U = 3, REC_NEW = 4, REC_NEW_U = 5, REC_WORDS = 6 };
+struct StepRecord {
+    unsigned long long word[REC_WORDS];
+    unsigned long long done;
+    unsigned long long pad;
+};
+
 struct DecodeLayout {
     int rows, NS, cap, wlen, klen;
     size_t pos, nsel, ncand, status, nfree, new_slot, tau_d, tau_f;
-    size_t win_u, win_slot, sel_u, sel_pos, sel_slot, cand_u, slot_u, free_stack, kslots, vslots, total;
+    size_t win_u, win_slot, sel_u, sel_pos, sel_slot, cand_u, slot_u, free_stack, kslots, vslots, rec, heads, part, total;
+    int nsplit;
 };
 
 __host__ __device__ inline DecodeLayout decode_layout(const sparsek_decode_cfg& c)
@@ -55,6 +69,14 @@ __host__ __device__ inline DecodeLayout decode_layout(const sparsek_decode_cfg& 
     const size_t kv = (size_t)c.B * c.H * L.NS * c.d * esz;
     L.kslots = take(kv);
     L.vslots = take(kv);
+    // A head's slots are dealt to nsplit workgroups: up to four per compute unit when there are few heads, but at least
+    // 128 KB of K and V each (adding the shares up costs 3 us).
+    const long long heads = (long long)c.B * c.H, bytes = 2ll * L.NS * c.d * (long long)esz;
+    const long long want = (1024 + heads - 1) / heads, most = bytes >> 17 > 1 ? bytes >> 17 : 1;
+    L.nsplit = (int)(want < most ? want : most);
+    L.rec = take(r * sizeof(StepRecord));
+    L.heads = take((size_t)heads * 4);
+    L.part = take(L.nsplit > 1 ? (size_t)heads * L.nsplit * (c.d + 2) * 8 : 0);
     L.total = off;
     return L;
 }
@@ -71,6 +93,7 @@ struct RowState {
     int *sel_pos, *sel_slot;
     float *cand_u, *slot_u;
     int* free_stack;
+    StepRecord* rec;
 };
 
 __device__ inline RowState row_state(char* st, const DecodeLayout& L, int row)
@@ -92,6 +115,7 @@ __device__ inline RowState row_state(char* st, const DecodeLayout& L, int row)
     R.cand_u = (float*)(st + L.cand_u) + (size_t)row * L.cap;
     R.slot_u = (float*)(st + L.slot_u) + (size_t)row * L.NS;
     R.free_stack = (int*)(st + L.free_stack) + (size_t)row * L.NS;
+    R.rec = (StepRecord*)(st + L.rec) + row;
     return R;
 }
 
@@ -104,10 +128,10 @@ struct BlockRed {
     float f32[NT_ROW / 64];
 };
 
-__device__ inline void block_eval(BlockRed& red, const float* a, int na, const float* b, int nb, bool with_z,
-                                  float z, double x, int& F, int& S, double& fsum, float& minF)
+__device__ inline void block_eval(BlockRed& red, const float* a, int na, const float* b, int nb, double x, int& F, int& S,
+                                  double& fsum, float& minF)
 {
-    // right-limit counts of the piece of f that starts at x, over a[0..na) U b[0..nb) U {z}
+    // right-limit counts of the piece of f that starts at x, over a[0..na) U b[0..nb)
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     int f = 0, s = 0;
     double sum = 0.0;
@@ -123,7 +147,6 @@ __device__ inline void block_eval(BlockRed& red, const float* a, int na, const f
     };
     for (int i = tid; i < na; i += NT_ROW) add(a[i]);
     for (int i = tid; i < nb; i += NT_ROW) add(b[i]);
-    if (with_z && tid == 0) add(z);
     unsigned long long packed = wave_sum_u64(((unsigned long long)f << 32) | (unsigned long long)s);
     double ws = wave_sum_f64(sum);
     float wm = wave_min_f32(mf);
@@ -143,8 +166,8 @@ __device__ inline void block_eval(BlockRed& red, const float* a, int na, const f
 // Same iteration as the prefill solver: tau <- (fsum + F - k)/(S - F), the root of the linear piece
 // through the current point (from whichever side of the root it lies on), until (F, S) reproduce;
 // a bracket of the root is kept and a step that leaves it is replaced by its midpoint.
-__device__ double block_solve_tau(BlockRed& red, const float* a, int na, const float* b, int nb, bool with_z,
-                                  float z, int k, double start, int* status)
+template <typename Eval>
+__device__ double solve_tau_iter(Eval&& eval, int k, double start, int* status)
 {
     double lo_b = start, hi_b = INFINITY, x = start;
     int pF = -1, pS = -1;
@@ -152,7 +175,7 @@ __device__ double block_solve_tau(BlockRed& red, const float* a, int na, const f
         int F, S;
         double fsum;
         float minF;
-        block_eval(red, a, na, b, nb, with_z, z, x, F, S, fsum, minF);
+        eval(x, F, S, fsum, minF);
         if (F == pF && S == pS) return x;
         pF = pS = -1;
         const double f = (double)F + fsum - (double)(S - F) * x;
@@ -188,9 +211,8 @@ __device__ double block_solve_tau(BlockRed& red, const float* a, int na, const f
 }
 
 // In-place, order-preserving removal of candidates <= tau.  Returns the new count.
-__device__ int block_prune(int* scan, float* cand, int n, float keep_above_as_double_hi, double tau)
+__device__ int block_prune(int* scan, float* cand, int n, double tau)
 {
-    (void)keep_above_as_double_hi;
     const int tid = threadIdx.x;
     __shared__ int base_s;
     if (tid == 0) base_s = 0;
@@ -214,54 +236,101 @@ __device__ int block_prune(int* scan, float* cand, int n, float keep_above_as_do
     return base_s;
 }
 
-template <typename T>
-__device__ __forceinline__ void copy_row(T* dst, const T* src, int d, int tid, int nt)
+// ---------------------------------------------------------------------------------
+// (1) per score row: the key leaving the window joins the SPARSEK prefix; the new token is appended to the window; its
+// K/V rows go to the freed slot.  A chain of dependent loads on an otherwise idle workgroup, so everything that can be
+// fetched before anything is known is fetched first: the selected keys and the candidates (up to SEL_REG / CAND_REG
+// per thread in registers, the rest is read again where it is needed).
+// ---------------------------------------------------------------------------------
+constexpr int SEL_REG = 4, CAND_REG = 8;
+
+struct RowRegs {
+    float su[SEL_REG], cu[CAND_REG];
+    int sp[SEL_REG];
+};
+
+// Right-limit counts of the piece of f that starts at x, over the selected keys, the candidates and z.
+__device__ inline void row_eval(BlockRed& red, const RowRegs& G, const RowState& R, int nsel, int ncand, float z, double x,
+                                int& F, int& S, double& fsum, float& minF)
 {
-    for (int c = tid; c < d; c += nt) dst[c] = src[c];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    int f = 0, s = 0;
+    double sum = 0.0;
+    float mf = INFINITY;
+    const double x1 = x + 1.0;
+    auto add = [&](float v) {
+        const double dv = (double)v;
+        const bool a = dv > x, b = dv > x1;
+        s += a ? 1 : 0;
+        f += b ? 1 : 0;
+        mf = b ? fminf(mf, v) : mf;
+        sum += a && !b ? dv : 0.0;
+    };
+#pragma unroll
+    for (int r = 0; r < SEL_REG; r++) add(r * NT_ROW + tid < nsel ? G.su[r] : -INFINITY);
+    for (int i = SEL_REG * NT_ROW + tid; i < nsel; i += NT_ROW) add(R.sel_u[i]);
+#pragma unroll
+    for (int r = 0; r < CAND_REG; r++) add(r * NT_ROW + tid < ncand ? G.cu[r] : -INFINITY);
+    for (int i = CAND_REG * NT_ROW + tid; i < ncand; i += NT_ROW) add(R.cand_u[i]);
+    if (tid == 0) add(z);
+    unsigned long long packed = wave_sum_u64(((unsigned long long)f << 32) | (unsigned long long)s);
+    double ws = wave_sum_f64(sum);
+    float wm = wave_min_f32(mf);
+    __syncthreads();
+    if (lane == 0) { red.u64[wv] = packed; red.f64[wv] = ws; red.f32[wv] = wm; }
+    __syncthreads();
+    packed = 0;
+    ws = 0.0;
+    wm = INFINITY;
+    for (int i = 0; i < NT_ROW / 64; i++) { packed += red.u64[i]; ws += red.f64[i]; wm = fminf(wm, red.f32[i]); }
+    F = (int)(packed >> 32);
+    S = (int)(packed & 0xFFFFFFFFull);
+    fsum = ws;
+    minF = wm;
 }
 
-// ---------------------------------------------------------------------------------
-// (1) per score row: the key leaving the window joins the SPARSEK prefix; the new token is
-// appended to the window; its K/V rows go to the freed slot.
-// ---------------------------------------------------------------------------------
+struct UpdateSmem {
+    BlockRed red;
+    int scan[NT_ROW / 64];
+    unsigned long long minkey[NT_ROW / 64];
+    int at[4];
+    float ev_u;
+};
+
 template <typename T>
-__global__ __launch_bounds__(NT_ROW) void decode_update_kernel(sparsek_decode_cfg c, char* st,
-                                                               const T* __restrict__ k_new,
-                                                               const T* __restrict__ v_new,
-                                                               const float* __restrict__ u_new)
+__device__ void decode_update(UpdateSmem& sm, const sparsek_decode_cfg& c, const DecodeLayout& L, char* st, int row,
+                              const T* __restrict__ k_new, const T* __restrict__ v_new, const float* __restrict__ u_new)
 {
-    __shared__ BlockRed red;
-    __shared__ int scan[NT_ROW / 64];
-    __shared__ unsigned long long minkey_s[NT_ROW / 64];
-    __shared__ int sh_i[4];
-    const DecodeLayout L = decode_layout(c);
-    const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    RowState R = row_state(st, L, row);
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const RowState R = row_state(st, L, row);
     const int k = c.k, w = c.w;
+    // ---- everything that depends on nothing ----
     const int t = *R.pos;
     int nsel = *R.nsel, ncand = *R.ncand;
     const int nfree0 = *R.nfree;
     const double tau_old = *R.tau_d;
     const float unew = u_new[row];
-    // The new token's K/V rows of this score row's heads do not depend on the state: fetch the
-    // first batch (16-byte vectors, 4 per thread and tensor) now, store it once the slot is known.
-    const int b_ = row / c.Gu, g_ = row % c.Gu;
-    const int h0 = (c.Gu == 1) ? 0 : g_, nh = (c.Gu == 1) ? c.H : 1;
-    const int vpr = c.d * (int)sizeof(T) / 16;  // vectors per row
-    const int nvec = nh * vpr;
-    const uint4* ksrc = (const uint4*)(k_new + ((size_t)b_ * c.H + h0) * c.d);
-    const uint4* vsrc = (const uint4*)(v_new + ((size_t)b_ * c.H + h0) * c.d);
-    constexpr int VB = 4;
-    uint4 kpre[VB], vpre[VB];
+    const unsigned long long done = R.rec->done;
+    RowRegs G;
+    int ss[SEL_REG];
 #pragma unroll
-    for (int r = 0; r < VB; r++) {
-        const int v = r * NT_ROW + tid;
-        if (v < nvec) { kpre[r] = ksrc[v]; vpre[r] = vsrc[v]; }
+    for (int r = 0; r < SEL_REG; r++) {
+        const int i = min(r * NT_ROW + tid, L.klen - 1);
+        G.su[r] = R.sel_u[i];
+        G.sp[r] = R.sel_pos[i];
+        ss[r] = R.sel_slot[i];
     }
-    __syncthreads();
-
+#pragma unroll
+    for (int r = 0; r < CAND_REG; r++) G.cu[r] = R.cand_u[min(r * NT_ROW + tid, L.cap - 1)];
+    // ---- what depends on the position and the free count alone ----
     const bool leave = (w == 0) || (t >= w);
-    int new_slot = -1;
+    const int p = (w > 0) ? t - w : t;  // position joining the prefix (= prefix index T)
+    float z = unew;
+    int zslot = -1;
+    if (leave && w > 0) {
+        z = R.win_u[p % w];
+        zslot = R.win_slot[p % w];
+    }
     // Free-slot stack: at most one slot is pushed and at most one is popped per step, so the
     // step works on a local copy (count, the slot pushed in this step, the old top fetched
     // ahead) and writes the stack back once.
@@ -272,152 +341,179 @@ __global__ __launch_bounds__(NT_ROW) void decode_update_kernel(sparsek_decode_cf
         nfree--;
         return old_top;
     };
+    const int b_ = row / c.Gu, g_ = row % c.Gu;
+    const int h0 = (c.Gu == 1) ? 0 : g_, nh = (c.Gu == 1) ? c.H : 1;
+
+    bool selected = false, evict = false;
+    int e = -1;  // entry of the selected arrays that receives z
+    int ev_slot = -1;
+    float ev_u = 0.0f;
+    double tau_new = tau_old;
+    const int len = p + 1;
     if (leave) {
-        const int p = (w > 0) ? t - w : t;          // position joining the prefix (= prefix index T)
-        const float z = (w > 0) ? R.win_u[p % w] : unew;
-        const int zslot = (w > 0) ? R.win_slot[p % w] : -1;
-        const int len = p + 1;
-        // ---- (a) top-k decision (nothing is modified yet) ----
-        bool selected = false;
-        int e = -1;  // entry of the selected arrays that receives z
-        bool evict = false;
+        // ---- (a) top-k decision ----
         if (k > 0) {
             if (nsel < k) {
                 selected = true;
                 e = nsel;
             } else {
                 unsigned long long mk = ~0ull;
-                for (int i = tid; i < nsel; i += NT_ROW) {
-                    unsigned long long key = sel_key(R.sel_u[i], R.sel_pos[i]);
+#pragma unroll
+                for (int r = 0; r < SEL_REG; r++) {
+                    const unsigned long long key = sel_key(G.su[r], G.sp[r]);
+                    if (r * NT_ROW + tid < nsel) mk = key < mk ? key : mk;
+                }
+                for (int i = SEL_REG * NT_ROW + tid; i < nsel; i += NT_ROW) {
+                    const unsigned long long key = sel_key(R.sel_u[i], R.sel_pos[i]);
                     mk = key < mk ? key : mk;
                 }
                 mk = wave_min_u64(mk);
-                if (lane == 0) minkey_s[wv] = mk;
+                if (lane == 0) sm.minkey[wv] = mk;
                 __syncthreads();
-                mk = minkey_s[0];
-                for (int i = 1; i < NT_ROW / 64; i++) mk = minkey_s[i] < mk ? minkey_s[i] : mk;
+                mk = sm.minkey[0];
+                for (int i = 1; i < NT_ROW / 64; i++) mk = sm.minkey[i] < mk ? sm.minkey[i] : mk;
                 if (sel_key(z, p) > mk) {
                     selected = true;
                     evict = true;
-                    for (int i = tid; i < nsel; i += NT_ROW)
-                        if (sel_key(R.sel_u[i], R.sel_pos[i]) == mk) sh_i[0] = i;
+#pragma unroll
+                    for (int r = 0; r < SEL_REG; r++)
+                        if (r * NT_ROW + tid < nsel && sel_key(G.su[r], G.sp[r]) == mk) {
+                            sm.at[0] = r * NT_ROW + tid;
+                            sm.at[3] = ss[r];
+                            sm.ev_u = G.su[r];
+                        }
+                    for (int i = SEL_REG * NT_ROW + tid; i < nsel; i += NT_ROW)
+                        if (sel_key(R.sel_u[i], R.sel_pos[i]) == mk) {
+                            sm.at[0] = i;
+                            sm.at[3] = R.sel_slot[i];
+                            sm.ev_u = R.sel_u[i];
+                        }
                     __syncthreads();
-                    e = sh_i[0];
+                    e = sm.at[0];
+                    ev_slot = sm.at[3];
+                    ev_u = sm.ev_u;
                 }
             }
         }
         // ---- (b) threshold of prefix p ----
-        double tau_new;
         if (k == 0) {
             tau_new = (len == 1) ? (double)z : fmax(tau_old, (double)z);
         } else if (len <= k) {
             tau_new = (len == 1) ? (double)z - 1.0 : fmin(tau_old, (double)z - 1.0);
         } else if ((double)z > tau_old) {
-            tau_new = block_solve_tau(red, R.sel_u, nsel, R.cand_u, ncand, true, z, k, tau_old, R.status);
-        } else {
-            tau_new = tau_old;
+            tau_new = solve_tau_iter([&](double x, int& F, int& S, double& fsum, float& minF) {
+                row_eval(sm.red, G, R, nsel, ncand, z, x, F, S, fsum, minF);
+            }, k, tau_old, R.status);
         }
-        // ---- (c) candidates: scores above tau outside the top-k ----
-        const float ev_u = evict ? R.sel_u[e] : 0.0f;
-        const int ev_slot = evict ? R.sel_slot[e] : -1;
+    }
+    // ---- (c) slots, and the record the attention waits for ----
+    int new_slot = -1;
+    int zval_slot = -1;          // the slot of the key that left the window and its gate score
+    float zval = -INFINITY;
+    if (leave) {
+        if (selected) {
+            int slot = zslot;
+            if (evict) pushed = ev_slot;
+            if (w == 0) new_slot = slot = pop_slot();
+            zval_slot = slot;
+            zval = z;
+        } else if (w > 0) {
+            zval_slot = zslot;
+            pushed = zslot;
+        }
+    }
+    if (w > 0) new_slot = pop_slot();
+    const float new_u = w > 0 ? INFINITY : z;
+    if (tid == 0) {
+        const unsigned long long tag = (done / (unsigned)nh + 1ull) << 32;
+        auto put = [&](int i, unsigned x) {
+            __hip_atomic_store(&R.rec->word[i], tag | x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+        put(REC_TAU, __float_as_uint((float)tau_new));
+        put(REC_EVICTED, (unsigned)(evict ? ev_slot : -1));
+        put(REC_LEFT, (unsigned)zval_slot);
+        put(REC_LEFT_U, __float_as_uint(zval));
+        put(REC_NEW, (unsigned)new_slot);
+        put(REC_NEW_U, __float_as_uint(new_u));
+    }
+    // ---- (d) candidates: scores above tau outside the top-k ----
+    if (leave && k > 0 && len > k) {
         __syncthreads();
-        if (k > 0 && len > k) {
-            // Candidates that fell to or below tau do no harm (they count nowhere); they are only
-            // swept out when the set gets three quarters full, not at every rise of tau.
-            if ((tau_new > tau_old && ncand + 2 > (L.cap / 4) * 3) || ncand + 2 > L.cap)
-                ncand = block_prune(scan, R.cand_u, ncand, 0.0f, tau_new);
-            if (tid == 0) {
-                float add[2];
-                int na = 0;
-                if (!selected && (double)z > tau_new) add[na++] = z;
-                if (evict && (double)ev_u > tau_new) add[na++] = ev_u;
-                for (int i = 0; i < na; i++) {
-                    if (ncand < L.cap) R.cand_u[ncand++] = add[i];
-                    else {  // bounded set (Sec. 3.3): drop the smallest, flag the row
-                        atomicOr(R.status, 1);
-                        int mi = 0;
-                        for (int x = 1; x < ncand; x++) if (R.cand_u[x] < R.cand_u[mi]) mi = x;
-                        if (ncand > 0 && R.cand_u[mi] < add[i]) R.cand_u[mi] = add[i];
-                    }
-                }
-                sh_i[1] = ncand;
-            }
-            __syncthreads();
-            ncand = sh_i[1];
-        }
-        // ---- (d) slots ----
+        // Candidates that fell to or below tau do no harm (they count nowhere); they are only
+        // swept out when the set gets three quarters full, not at every rise of tau.
+        if ((tau_new > tau_old && ncand + 2 > (L.cap / 4) * 3) || ncand + 2 > L.cap)
+            ncand = block_prune(sm.scan, R.cand_u, ncand, tau_new);
         if (tid == 0) {
-            if (selected) {
-                int slot = zslot;
-                if (evict) {
-                    R.slot_u[ev_slot] = -INFINITY;
-                    pushed = ev_slot;
+            float add[2];
+            int na = 0;
+            if (!selected && (double)z > tau_new) add[na++] = z;
+            if (evict && (double)ev_u > tau_new) add[na++] = ev_u;
+            for (int i = 0; i < na; i++) {
+                if (ncand < L.cap) R.cand_u[ncand++] = add[i];
+                else {  // bounded set (Sec. 3.3): drop the smallest, flag the row
+                    atomicOr(R.status, 1);
+                    int mi = 0;
+                    for (int x = 1; x < ncand; x++) if (R.cand_u[x] < R.cand_u[mi]) mi = x;
+                    if (ncand > 0 && R.cand_u[mi] < add[i]) R.cand_u[mi] = add[i];
                 }
-                if (w == 0) slot = pop_slot();
+            }
+        }
+    }
+    // ---- (e) the state ----
+    if (tid == 0) {
+        if (leave) {
+            if (evict) R.slot_u[ev_slot] = -INFINITY;
+            if (zval_slot >= 0) R.slot_u[zval_slot] = zval;
+            if (selected) {
                 R.sel_u[e] = z;
                 R.sel_pos[e] = p;
-                R.sel_slot[e] = slot;
-                R.slot_u[slot] = z;
+                R.sel_slot[e] = zval_slot;
                 if (!evict) nsel++;
-                if (w == 0) new_slot = slot;
-            } else if (w > 0) {
-                R.slot_u[zslot] = -INFINITY;
-                pushed = zslot;
             }
             *R.nsel = nsel;
             *R.ncand = ncand;
             *R.tau_d = tau_new;
             *R.tau_f = (float)tau_new;
         }
-    }
-    // ---- (2) append the new token to the window ----
-    if (tid == 0) {
         if (w > 0) {
-            const int slot = pop_slot();
             R.win_u[t % w] = unew;
-            R.win_slot[t % w] = slot;
-            R.slot_u[slot] = INFINITY;
-            new_slot = slot;
+            R.win_slot[t % w] = new_slot;
+            R.slot_u[new_slot] = INFINITY;
         }
         if (pushed >= 0) R.free_stack[nfree++] = pushed;
         *R.nfree = nfree;
         *R.new_slot = new_slot;
         *R.pos = t + 1;
-        sh_i[2] = new_slot;
     }
-    __syncthreads();
-    new_slot = sh_i[2];
     if (new_slot >= 0) {
-        T* ks = (T*)(st + L.kslots);
-        T* vs = (T*)(st + L.vslots);
-        auto dst = [&](T* slots, int v) -> uint4* {  // vector v of the rows -> its place in slot new_slot
-            const size_t bh = (size_t)b_ * c.H + h0 + v / vpr;
-            return (uint4*)(slots + (bh * L.NS + new_slot) * c.d) + v % vpr;
-        };
-#pragma unroll
-        for (int r = 0; r < VB; r++) {
-            const int v = r * NT_ROW + tid;
-            if (v < nvec) { *dst(ks, v) = kpre[r]; *dst(vs, v) = vpre[r]; }
-        }
-        for (int v = VB * NT_ROW + tid; v < nvec; v += NT_ROW) {  // more heads than one batch holds
-            *dst(ks, v) = ksrc[v];
-            *dst(vs, v) = vsrc[v];
+        const int vpr = c.d * (int)sizeof(T) / 16;  // 16-byte vectors per row
+        const uint4* ksrc = (const uint4*)(k_new + ((size_t)b_ * c.H + h0) * c.d);
+        const uint4* vsrc = (const uint4*)(v_new + ((size_t)b_ * c.H + h0) * c.d);
+        for (int v = tid; v < nh * vpr; v += NT_ROW) {
+            const size_t dst = (((size_t)b_ * c.H + h0 + v / vpr) * L.NS + new_slot) * vpr + v % vpr;
+            ((uint4*)(st + L.kslots))[dst] = ksrc[v];
+            ((uint4*)(st + L.vslots))[dst] = vsrc[v];
         }
     }
 }
 
 // ---------------------------------------------------------------------------------
-// (2) attention of the one new query over the k+w slots of its head.
-// LPR lanes share a slot row (8 elements each); 64/LPR rows per wave-load; 16 independent
-// online-softmax streams per workgroup, merged through LDS at the end.
+// (2) attention of the one new query over the k+w slots of its head, or over one of nsplit shares of them.
+// LPR lanes share a slot row (8 elements each), 64/LPR rows per wave-load.  Up to SLAB slots at a time: the dot products
+// of their K rows go to LDS, one thread per slot turns them into weights, and the V rows are summed with those.
+// HBM-bound with many heads (64 x 32 heads, 2048 slots of 256 bytes: 2.15 GB in 355 us = 6.0 TB/s; 376 us when the row
+// updates ran in a launch of their own ahead of it), bound by latency with few (32 heads: 48 us with one workgroup per
+// head, 14 us with eight; 16 and 32 shares take 16 and 25 us: the shares' partial results have to meet).
+// Five workgroups per compute unit (96 registers) keep enough rows in flight; six spill.
 // ---------------------------------------------------------------------------------
 template <typename T>
-struct Ld8;
+struct Row8;
 template <>
-struct Ld8<uint16_t> {
-    static __device__ __forceinline__ void ld(const uint16_t* p, float (&x)[8])
+struct Row8<uint16_t> {
+    uint4 r;
+    __device__ __forceinline__ void load(const uint16_t* p) { r = *(const uint4*)p; }
+    __device__ __forceinline__ void get(float (&x)[8]) const
     {
-        const uint4 r = *(const uint4*)p;
         x[0] = __uint_as_float(r.x << 16); x[1] = __uint_as_float(r.x & 0xFFFF0000u);
         x[2] = __uint_as_float(r.y << 16); x[3] = __uint_as_float(r.y & 0xFFFF0000u);
         x[4] = __uint_as_float(r.z << 16); x[5] = __uint_as_float(r.z & 0xFFFF0000u);
@@ -425,96 +521,282 @@ struct Ld8<uint16_t> {
     }
 };
 template <>
-struct Ld8<float> {
-    static __device__ __forceinline__ void ld(const float* p, float (&x)[8])
+struct Row8<float> {
+    float4 a, b;
+    __device__ __forceinline__ void load(const float* p) { a = *(const float4*)p; b = *(const float4*)(p + 4); }
+    __device__ __forceinline__ void get(float (&x)[8]) const
     {
-        const float4 a = *(const float4*)p, b = *(const float4*)(p + 4);
         x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
     }
 };
 __device__ __forceinline__ void st1(uint16_t* p, float v) { *p = f32_to_bf16(v); }
 __device__ __forceinline__ void st1(float* p, float v) { *p = v; }
 
+constexpr int SLAB = 2048;
+constexpr int SPT = SLAB / NT_ROW;   // slots per thread
+
+template <int LPR>
+struct AttnSmem {
+    float w[SLAB];                            // dot products, then weights
+    float part[4 * (64 / LPR)][LPR * 8];      // sums of the workgroup's streams
+    float red[2][NT_ROW / 64];
+    unsigned rec[REC_WORDS];
+    float newdot;
+    int last;
+};
+
+template <int LPR>
+__device__ __forceinline__ float row_sum(float x)   // over the LPR lanes of a row
+{
+    x += dpp_f32(x, 0);
+    x += dpp_f32(x, 1);
+    if (LPR >= 8) x += dpp_f32(x, 2);
+    if (LPR >= 16) x += dpp_f32(x, 3);
+    return x;
+}
+
 template <typename T, int LPR, int MODE>
-__global__ __launch_bounds__(256) void decode_attn_kernel(sparsek_decode_cfg c, const char* st,
-                                                          const T* __restrict__ q_new, T* __restrict__ o)
+__device__ void decode_attend(AttnSmem<LPR>& sm, const sparsek_decode_cfg& c, const DecodeLayout& L, char* st, int id,
+                              const T* __restrict__ q_new, const T* __restrict__ k_new, const T* __restrict__ v_new,
+                              T* __restrict__ o)
 {
     constexpr int D = LPR * 8;
     constexpr int RPW = 64 / LPR;        // rows per wave-load
     constexpr int NSTREAM = 4 * RPW;     // streams per workgroup
-    __shared__ float part[NSTREAM][D + 2];
-    const DecodeLayout L = decode_layout(c);
-    const int bh = blockIdx.x;
+    constexpr int UNR = sizeof(T) == 2 ? 4 : 2;   // rows in flight per stream
+    const int bh = id / L.nsplit, sp = id % L.nsplit;
     const int b = bh / c.H, h = bh % c.H;
     const int row = b * c.Gu + (c.Gu == 1 ? 0 : h);
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int sub = lane % LPR, grp = lane / LPR;
     const int stream = wv * RPW + grp;
+    StepRecord* rec = (StepRecord*)(st + L.rec) + row;
+    // (read before this head reports its end, so the quotient is the number of the steps before this one)
+    const unsigned long long done = __hip_atomic_load(&rec->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const float* slot_u = (const float*)(st + L.slot_u) + (size_t)row * L.NS;
-    const float tau = *((const float*)(st + L.tau_f) + row);
     const T* ks = (const T*)(st + L.kslots) + (size_t)bh * L.NS * D;
     const T* vs = (const T*)(st + L.vslots) + (size_t)bh * L.NS * D;
+    const int per = (L.NS + L.nsplit - 1) / L.nsplit;
+    const int s_begin = min(L.NS, sp * per), s_end = min(L.NS, s_begin + per);
     float qf[8];
-    Ld8<T>::ld(q_new + (size_t)bh * D + sub * 8, qf);
+    {
+        Row8<T> r;
+        r.load(q_new + (size_t)bh * D + sub * 8);
+        r.get(qf);
+    }
     const float c2 = c.softmax_scale * 1.4426950408889634f;
 #pragma unroll
     for (int e = 0; e < 8; e++) qf[e] *= c2;
-
+    auto dot = [&](const Row8<T>& r) {
+        float x[8], d = 0.0f;
+        r.get(x);
+#pragma unroll
+        for (int e = 0; e < 8; e++) d += qf[e] * x[e];
+        return row_sum<LPR>(d);
+    };
     float m_run = -INFINITY, l_run = 0.0f, acc[8];
 #pragma unroll
     for (int e = 0; e < 8; e++) acc[e] = 0.0f;
 
-    constexpr int UNR = 4;
-    for (int s0 = stream; s0 < L.NS; s0 += NSTREAM * UNR) {
-        float kf[UNR][8], vf[UNR][8], su[UNR];
-#pragma unroll
-        for (int x = 0; x < UNR; x++) {
-            const int s = s0 + x * NSTREAM;
-            const bool in = s < L.NS;
-            const int sc = in ? s : 0;
-            su[x] = in ? slot_u[sc] : -INFINITY;
-            Ld8<T>::ld(ks + (size_t)sc * D + sub * 8, kf[x]);
-            Ld8<T>::ld(vs + (size_t)sc * D + sub * 8, vf[x]);
+    float tau = 0.0f, left_u = 0.0f, new_u = 0.0f;
+    int evicted = -1, left = -1, fresh = -1;
+    for (int s0 = s_begin; s0 < s_end; s0 += SLAB) {
+        const int sn = min(SLAB, s_end - s0);
+        const T* kb = ks + (size_t)s0 * D;   // 32-bit offsets from here: a slab holds at most 1 MB
+        const T* vb = vs + (size_t)s0 * D;
+        auto at = [&](int i) { return (unsigned)(min(i, sn - 1) * D + sub * 8); };
+        // ---- K: dot products (a slot the update is rewriting meanwhile is replaced below) ----
+        if (s0 == s_begin && wv == 0) {
+            Row8<T> r;
+            r.load(k_new + (size_t)bh * D + sub * 8);
+            const float d = dot(r);
+            if (lane == 0) sm.newdot = d;
         }
+#pragma unroll 1
+        for (int x0 = stream; x0 < sn; x0 += NSTREAM * UNR) {
+            Row8<T> r[UNR];
 #pragma unroll
-        for (int x = 0; x < UNR; x++) {
-            float dot = 0.0f;
+            for (int x = 0; x < UNR; x++) r[x].load(kb + at(x0 + x * NSTREAM));
 #pragma unroll
-            for (int e = 0; e < 8; e++) dot += qf[e] * kf[x][e];
-#pragma unroll
-            for (int off = 1; off < LPR; off <<= 1) dot += __shfl_xor(dot, off, 64);
-            const bool valid = su[x] > -INFINITY;
-            const float g = clip01(su[x] - tau);  // +inf -> 1
-            float s2 = (MODE == 0) ? dot * g : dot;
-            s2 = valid ? s2 : -INFINITY;
-            const float m_new = fmaxf(m_run, s2);
-            const float m_safe = (m_new == -INFINITY) ? 0.0f : m_new;
-            const float alpha = exp2f(m_run - m_safe);
-            const float p = exp2f(s2 - m_safe);
-            const float pv = (MODE == 2) ? p : p * g;
-            l_run = l_run * alpha + p;
-#pragma unroll
-            for (int e = 0; e < 8; e++) acc[e] = acc[e] * alpha + pv * vf[x][e];
-            m_run = m_new;
+            for (int x = 0; x < UNR; x++) {
+                const float d = dot(r[x]);
+                if (sub == 0 && x0 + x * NSTREAM < sn) sm.w[x0 + x * NSTREAM] = d;
+            }
         }
+        // the first V rows are on their way while the gates are formed
+        float su[SPT];
+#pragma unroll
+        for (int r = 0; r < SPT; r++) su[r] = r * NT_ROW + tid < sn ? slot_u[s0 + r * NT_ROW + tid] : -INFINITY;
+        Row8<T> vr[UNR];
+#pragma unroll
+        for (int x = 0; x < UNR; x++) vr[x].load(vb + at(stream + x * NSTREAM));
+        // ---- the record of this step ----
+        if (s0 == s_begin) {
+            if (tid < REC_WORDS) {
+                const unsigned tag = (unsigned)(done / (unsigned)(c.Gu == 1 ? c.H : 1)) + 1u;
+                unsigned long long x = 0ull;
+                int spins = 0;
+                // The row's workgroup has a lower index, so it was dispatched before this one and waits for nobody.
+                for (; spins < (1 << 20); spins++) {
+                    x = __hip_atomic_load(&rec->word[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if ((unsigned)(x >> 32) == tag) break;
+                    __builtin_amdgcn_s_sleep(2);
+                }
+                if (spins == (1 << 20)) atomicOr((int*)(st + L.status) + row, 4);
+                sm.rec[tid] = (unsigned)x;
+            }
+        }
+        __syncthreads();
+        if (s0 == s_begin) {
+            tau = __uint_as_float(sm.rec[REC_TAU]);
+            evicted = (int)sm.rec[REC_EVICTED];
+            left = (int)sm.rec[REC_LEFT];
+            left_u = __uint_as_float(sm.rec[REC_LEFT_U]);
+            fresh = (int)sm.rec[REC_NEW];
+            new_u = __uint_as_float(sm.rec[REC_NEW_U]);
+        }
+        // ---- weights ----
+        float s2[SPT], mx = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < SPT; r++) {
+            const int s = s0 + r * NT_ROW + tid;
+            float x = su[r];
+            x = s == evicted ? -INFINITY : x;
+            x = s == left ? left_u : x;
+            x = s == fresh ? new_u : x;
+            su[r] = clip01(x - tau);   // +inf (window) -> 1
+            float d = -INFINITY;
+            if (r * NT_ROW + tid < sn) d = s == fresh ? sm.newdot : sm.w[r * NT_ROW + tid];
+            if (MODE == 0) d *= su[r];
+            s2[r] = x > -INFINITY && r * NT_ROW + tid < sn ? d : -INFINITY;
+            mx = fmaxf(mx, s2[r]);
+        }
+        mx = wave_max_f32(mx);
+        if (lane == 0) sm.red[0][wv] = mx;
+        __syncthreads();
+        const float m_new = fmaxf(m_run, fmaxf(fmaxf(sm.red[0][0], sm.red[0][1]), fmaxf(sm.red[0][2], sm.red[0][3])));
+        const float m_safe = m_new == -INFINITY ? 0.0f : m_new;
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
+        m_run = m_new;
+        l_run *= alpha;
+#pragma unroll
+        for (int r = 0; r < SPT; r++) {
+            const float p = __builtin_amdgcn_exp2f(s2[r] - m_safe);
+            l_run += p;
+            if (r * NT_ROW + tid < sn) sm.w[r * NT_ROW + tid] = MODE == 2 ? p : p * su[r];
+        }
+        __syncthreads();
+        // ---- V ----
+#pragma unroll
+        for (int e = 0; e < 8; e++) acc[e] *= alpha;
+#pragma unroll 1
+        for (int x0 = stream; x0 < sn; x0 += NSTREAM * UNR) {
+            if (x0 >= NSTREAM * UNR) {
+#pragma unroll
+                for (int x = 0; x < UNR; x++) vr[x].load(vb + at(x0 + x * NSTREAM));
+            }
+#pragma unroll
+            for (int x = 0; x < UNR; x++) {
+                const int i = x0 + x * NSTREAM;
+                if (s0 + i == fresh) vr[x].load(v_new + (size_t)bh * D + sub * 8);
+                const float pw = i < sn ? sm.w[i] : 0.0f;
+                float v[8];
+                vr[x].get(v);
+#pragma unroll
+                for (int e = 0; e < 8; e++) acc[e] = fmaf(pw, i < sn ? v[e] : 0.0f, acc[e]);
+            }
+        }
+        __syncthreads();
     }
     // ---- merge the streams ----
-    if (sub == 0) { part[stream][D] = m_run; part[stream][D + 1] = l_run; }
 #pragma unroll
-    for (int e = 0; e < 8; e++) part[stream][sub * 8 + e] = acc[e];
+    for (int e = 0; e < 8; e++) sm.part[stream][sub * 8 + e] = acc[e];
+    const float lw = wave_sum_f32(l_run);
+    if (lane == 0) sm.red[1][wv] = lw;
     __syncthreads();
+    const float l_tot = (sm.red[1][0] + sm.red[1][1]) + (sm.red[1][2] + sm.red[1][3]);
+    float osum = 0.0f;
     if (tid < D) {
-        float M = -INFINITY;
-        for (int s = 0; s < NSTREAM; s++) M = fmaxf(M, part[s][D]);
-        float lsum = 0.0f, osum = 0.0f;
-        for (int s = 0; s < NSTREAM; s++) {
-            const float ms = part[s][D];
-            const float f = (ms == -INFINITY) ? 0.0f : exp2f(ms - M);
-            lsum += f * part[s][D + 1];
-            osum += f * part[s][tid];
-        }
-        st1(o + (size_t)bh * D + tid, osum / lsum);
+#pragma unroll
+        for (int s = 0; s < NSTREAM; s++) osum += sm.part[s][tid];
     }
+    bool finish = true;
+    if (L.nsplit == 1) {
+        if (tid < D) st1(o + (size_t)bh * D + tid, osum / l_tot);
+    } else {
+        // Partial results meet in memory, every value with the step's number beside it: as with the record, a reader
+        // waits for the number, so nothing has to be flushed or fenced.  The workgroup that arrives last adds them up,
+        // in the order of the shares.
+        const unsigned tag = (unsigned)(done / (unsigned)(c.Gu == 1 ? c.H : 1)) + 1u;
+        unsigned long long* part = (unsigned long long*)(st + L.part) + (size_t)bh * L.nsplit * (D + 2);
+        auto put = [&](int i, float x) {
+            __hip_atomic_store(&part[(size_t)sp * (D + 2) + i], (unsigned long long)tag << 32 | __float_as_uint(x),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        };
+        if (tid < D) put(tid, osum);
+        if (tid == 0) { put(D, m_run); put(D + 1, l_tot); }
+        if (tid == 0) {
+            unsigned* arrived = (unsigned*)(st + L.heads) + bh;
+            const unsigned n = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            sm.last = n == (unsigned)L.nsplit - 1u;
+            if (sm.last) __hip_atomic_store(arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        finish = sm.last;
+        if (finish) {
+            // (maximum, sum) of every share, then this column of every share; all words are on their way at once
+            auto get = [&](int s, int i) {
+                unsigned long long x = 0ull;
+                for (int spins = 0; spins < (1 << 20); spins++) {
+                    x = __hip_atomic_load(&part[(size_t)s * (D + 2) + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if ((unsigned)(x >> 32) == tag) break;
+                }
+                return __uint_as_float((unsigned)x);
+            };
+            for (int s = tid; s < 2 * L.nsplit; s += NT_ROW) sm.w[s] = get(s >> 1, D + (s & 1));
+            __syncthreads();
+            float M = -INFINITY, lsum = 0.0f;
+            for (int s = 0; s < L.nsplit; s++) M = fmaxf(M, sm.w[2 * s]);
+            constexpr int CG = NT_ROW / D;   // groups of threads that share the shares of a column
+            float sum = 0.0f;
+            for (int s = tid / D; s < L.nsplit; s += CG) {
+                const float ms = sm.w[2 * s];
+                const float f = ms == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(ms - M);
+                lsum += f * sm.w[2 * s + 1];
+                sum += f * get(s, tid % D);
+            }
+            float* comb = &sm.part[0][0];
+            comb[tid] = sum;
+            comb[NT_ROW + tid] = lsum;
+            __syncthreads();
+            if (tid < D) {
+                for (int x = 1; x < CG; x++) {
+                    sum += comb[x * D + tid];
+                    lsum += comb[NT_ROW + x * D + tid];
+                }
+                st1(o + (size_t)bh * D + tid, sum / lsum);
+            }
+        }
+    }
+    if (finish && tid == 0) __hip_atomic_fetch_add(&rec->done, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int LPR>
+union StepSmem {
+    UpdateSmem u;
+    AttnSmem<LPR> a;
+};
+
+template <typename T, int LPR, int MODE>
+__global__ __launch_bounds__(NT_ROW, 5) void decode_step_kernel(sparsek_decode_cfg c, DecodeLayout L, char* st,
+                                                                const T* __restrict__ q_new, const T* __restrict__ k_new,
+                                                                const T* __restrict__ v_new,
+                                                                const float* __restrict__ u_new, T* __restrict__ o)
+{
+    __shared__ __align__(16) StepSmem<LPR> sm;
+    const int id = blockIdx.x;
+    if (id < L.rows) decode_update<T>(sm.u, c, L, st, id, k_new, v_new, u_new);
+    else decode_attend<T, LPR, MODE>(sm.a, c, L, st, id - L.rows, q_new, k_new, v_new, o);
 }
 
 // ---------------------------------------------------------------------------------
@@ -540,6 +822,14 @@ __global__ __launch_bounds__(256) void decode_zero_slots_kernel(sparsek_decode_c
     }
 }
 
+// The step record of a row and the arrival counters of its heads.
+__device__ __forceinline__ void clear_sync(const sparsek_decode_cfg& c, char* st, const DecodeLayout& L, const RowState& R, int row)
+{
+    if (threadIdx.x < sizeof(StepRecord) / 8) ((unsigned long long*)R.rec)[threadIdx.x] = 0ull;
+    const int nh = c.Gu == 1 ? c.H : 1, first = (row / c.Gu) * c.H + (c.Gu == 1 ? 0 : row % c.Gu);
+    for (int h = threadIdx.x; h < nh; h += NT_ROW) ((unsigned*)(st + L.heads))[first + h] = 0u;
+}
+
 __global__ __launch_bounds__(NT_ROW) void decode_init_kernel(sparsek_decode_cfg c, char* st)
 {
     const DecodeLayout L = decode_layout(c);
@@ -553,6 +843,7 @@ __global__ __launch_bounds__(NT_ROW) void decode_init_kernel(sparsek_decode_cfg 
         *R.pos = 0; *R.nsel = 0; *R.ncand = 0; *R.status = 0; *R.nfree = L.NS; *R.new_slot = -1;
         *R.tau_d = 0.0; *R.tau_f = 0.0f;
     }
+    clear_sync(c, st, L, R, row);
 }
 
 // State after positions 0..n_ctx-1: selected = top-k of prefix T = n_ctx-1-w, window = last w.
@@ -616,9 +907,12 @@ __global__ __launch_bounds__(NT_ROW) void decode_load_kernel(sparsek_decode_cfg 
     if (Tp >= 0) {
         if (k == 0) tau_d = (double)tau_f;
         else if (!long_prefix) tau_d = (double)tau_f;  // min(prefix) - 1: exact in fp32
-        else tau_d = block_solve_tau(red, R.sel_u, nsel, R.cand_u, ncand, false, 0.0f, k, tau_lo, R.status);
+        else
+            tau_d = solve_tau_iter([&](double x, int& F, int& S, double& fsum, float& minF) {
+                block_eval(red, R.sel_u, nsel, R.cand_u, ncand, x, F, S, fsum, minF);
+            }, k, tau_lo, R.status);
     }
-    if (long_prefix) ncand = block_prune(scan, R.cand_u, ncand, 0.0f, tau_d);
+    if (long_prefix) ncand = block_prune(scan, R.cand_u, ncand, tau_d);
     // ---- window: positions max(0, n_ctx-w) .. n_ctx-1 -> slots nsel.. ----
     const int wb = max(0, n_ctx - w);
     const int nwin = n_ctx - wb;
@@ -634,6 +928,7 @@ __global__ __launch_bounds__(NT_ROW) void decode_load_kernel(sparsek_decode_cfg 
         *R.pos = n_ctx; *R.nsel = nsel; *R.ncand = ncand; *R.nfree = L.NS - used; *R.new_slot = -1;
         *R.tau_d = tau_d; *R.tau_f = (float)tau_d;
     }
+    clear_sync(c, st, L, R, row);
 }
 
 // K/V rows of the loaded positions, one workgroup per head, 16-byte copies.
@@ -688,18 +983,18 @@ int launch_decode_load(const sparsek_decode_cfg& c, void* state, int n_ctx, cons
 }
 
 template <typename T, int LPR>
-static void launch_attn_t(const sparsek_decode_cfg& c, const void* state, const void* q, void* o, hipStream_t st)
+static void launch_step_t(const sparsek_decode_cfg& c, void* state, const void* q, const void* k, const void* v,
+                          const float* u_new, void* o, hipStream_t st)
 {
-    dim3 grid(c.B * c.H);
-    if (c.gate_mode == 0)
-        hipLaunchKernelGGL((decode_attn_kernel<T, LPR, 0>), grid, dim3(256), 0, st, c, (const char*)state,
-                           (const T*)q, (T*)o);
-    else if (c.gate_mode == 1)
-        hipLaunchKernelGGL((decode_attn_kernel<T, LPR, 1>), grid, dim3(256), 0, st, c, (const char*)state,
-                           (const T*)q, (T*)o);
-    else
-        hipLaunchKernelGGL((decode_attn_kernel<T, LPR, 2>), grid, dim3(256), 0, st, c, (const char*)state,
-                           (const T*)q, (T*)o);
+    const DecodeLayout L = decode_layout(c);
+    dim3 grid((unsigned)(L.rows + c.B * c.H * L.nsplit));
+#define SPK_STEP(MODE)                                                                                                 \
+    hipLaunchKernelGGL((decode_step_kernel<T, LPR, MODE>), grid, dim3(NT_ROW), 0, st, c, L, (char*)state, (const T*)q, \
+                       (const T*)k, (const T*)v, u_new, (T*)o)
+    if (c.gate_mode == 0) SPK_STEP(0);
+    else if (c.gate_mode == 1) SPK_STEP(1);
+    else SPK_STEP(2);
+#undef SPK_STEP
 }
 
 int launch_decode_step(const sparsek_decode_cfg& c, void* state, const void* q, const void* k, const void* v,
@@ -707,17 +1002,13 @@ int launch_decode_step(const sparsek_decode_cfg& c, void* state, const void* q, 
 {
     if (c.d != 32 && c.d != 64 && c.d != 128) return SPARSEK_ERR_UNSUPPORTED;
     if (c.dtype == SPARSEK_BF16) {
-        hipLaunchKernelGGL(decode_update_kernel<uint16_t>, dim3(c.B * c.Gu), dim3(NT_ROW), 0, st, c, (char*)state,
-                           (const uint16_t*)k, (const uint16_t*)v, u_new);
-        if (c.d == 128) launch_attn_t<uint16_t, 16>(c, state, q, o, st);
-        else if (c.d == 64) launch_attn_t<uint16_t, 8>(c, state, q, o, st);
-        else launch_attn_t<uint16_t, 4>(c, state, q, o, st);
+        if (c.d == 128) launch_step_t<uint16_t, 16>(c, state, q, k, v, u_new, o, st);
+        else if (c.d == 64) launch_step_t<uint16_t, 8>(c, state, q, k, v, u_new, o, st);
+        else launch_step_t<uint16_t, 4>(c, state, q, k, v, u_new, o, st);
     } else {
-        hipLaunchKernelGGL(decode_update_kernel<float>, dim3(c.B * c.Gu), dim3(NT_ROW), 0, st, c, (char*)state,
-                           (const float*)k, (const float*)v, u_new);
-        if (c.d == 128) launch_attn_t<float, 16>(c, state, q, o, st);
-        else if (c.d == 64) launch_attn_t<float, 8>(c, state, q, o, st);
-        else launch_attn_t<float, 4>(c, state, q, o, st);
+        if (c.d == 128) launch_step_t<float, 16>(c, state, q, k, v, u_new, o, st);
+        else if (c.d == 64) launch_step_t<float, 8>(c, state, q, k, v, u_new, o, st);
+        else launch_step_t<float, 4>(c, state, q, k, v, u_new, o, st);
     }
     return launch_status();
 }

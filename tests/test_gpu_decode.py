@@ -96,6 +96,19 @@ def test_decode_load_boundaries(oracle, n_ctx):
     run_decode(oracle, 1, 2, 1, 64, 25, 20, n_ctx, 30, seed=n_ctx)
 
 
+@pytest.mark.parametrize("B,H,Gu,d,k,w,n_ctx,steps,dtype,gate_mode,heads", [
+    (1, 2, 1, 128, 300, 261, 700, 24, "bf16", 0, None),     # a head's slots in two uneven shares
+    (1, 2, 2, 128, 1100, 950, 2100, 16, "bf16", 1, None),   # ... in eight, per-head selection, still filling up
+    (1, 3, 1, 64, 500, 700, 1300, 12, "fp32", 2, None),
+    (16, 64, 1, 32, 1200, 901, 2150, 2, "bf16", 0, [(0, 0), (7, 33), (15, 63)]),  # one workgroup per head, more slots than a slab
+])
+def test_decode_shares_and_slabs(oracle, B, H, Gu, d, k, w, n_ctx, steps, dtype, gate_mode, heads):
+    require_gpu()
+    say("decode shares", B, H, Gu, d, k, w, n_ctx, dtype, gate_mode)
+    _, _, flags, _ = run_decode(oracle, B, H, Gu, d, k, w, n_ctx, steps, dtype, gate_mode, seed=k, check_heads=heads)
+    assert not flags.any()
+
+
 def test_decode_step_equals_prefill_row_on_gpu(oracle):
     """Sec. 3.4: recurrent evaluation gives the same result as the one-shot one."""
     require_gpu()
