@@ -103,53 +103,96 @@ def check(rc):
         raise RuntimeError("libsparsek: %s (%d)" % (lib().sparsek_strerror(rc).decode(), rc))
 
 
-def _torch():
-    import torch
+# Host time per call matters where the kernels take a few microseconds: configurations (with their workspace sizes) are
+# kept, pointers are passed as plain integers, and the stream is asked for without building a Stream object.
+torch = None
+_raw_stream = None
+_CFG_KEPT = 256   # configurations kept per kind
+_cfgs = {}
 
+
+def _torch():
+    global torch, _raw_stream
+    if torch is None:
+        import torch as t
+
+        get, dev = getattr(t._C, "_cuda_getCurrentRawStream", None), getattr(t._C, "_cuda_getDevice", None)
+        _raw_stream = (lambda: get(dev())) if get and dev else (lambda: t.cuda.current_stream().cuda_stream)
+        torch = t
     return torch
 
 
 def _stream():
-    return C.c_void_p(_torch().cuda.current_stream().cuda_stream)
+    return (_raw_stream or (_torch() and _raw_stream))()
 
 
 def _ptr(t):
-    return C.c_void_p(t.data_ptr()) if t is not None else C.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _dtype_code(t):
-    torch = _torch()
-    if t.dtype == torch.float32:
-        return F32
-    if t.dtype == torch.bfloat16:
+    if t.dtype is torch.bfloat16:
         return BF16
+    if t.dtype is torch.float32:
+        return F32
     raise TypeError("q,k,v must be float32 or bfloat16, got %s" % t.dtype)
 
 
 def _need(t, dtype, name):
-    if not t.is_cuda or not t.is_contiguous() or t.dtype != dtype:
+    if t.dtype is not dtype or not t.is_cuda or not t.is_contiguous():
         raise ValueError("%s must be a contiguous %s tensor on the GPU" % (name, dtype))
 
 
 def _ws(nbytes, device):
-    return _torch().empty(max(int(nbytes), 256), dtype=_torch().uint8, device=device)
+    return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
+
+
+def _kept(kind, key, make):
+    """(reference to pass, configuration, {query: bytes}) of a configuration, made once."""
+    d = _cfgs.get(kind)
+    if d is None:
+        d = _cfgs.setdefault(kind, {})
+    got = d.get(key)
+    if got is None:
+        cfg = make(*key)
+        got = (C.byref(cfg), cfg, {})
+        if len(d) >= _CFG_KEPT:
+            d.clear()
+        d[key] = got
+    return got
+
+
+def _bytes(kept, query):
+    n = kept[2].get(query)
+    if n is None:
+        n = kept[2][query] = max(int(getattr(lib(), query)(kept[0])), 256)
+    return n
+
+
+def _make_mask_cfg(B, Gu, n, k):
+    return SparsekCfg(B=B, H=Gu, Gu=Gu, n=n, d=64, k=k, w=1, dtype=F32, gate_mode=0, softmax_scale=1.0)
 
 
 def _mask_cfg(u, k):
     B, Gu, n = u.shape
-    return SparsekCfg(B=B, H=Gu, Gu=Gu, n=n, d=64, k=int(k), w=1, dtype=F32, gate_mode=0, softmax_scale=1.0)
+    return _kept("mask", (B, Gu, n, int(k)), _make_mask_cfg)
 
 
 def sparsek_mask(u, k, ws=None):
     """u [B,Gu,n] fp32 -> (tau [B,Gu,n] fp32, death [B,Gu,n] int32)."""
-    torch = _torch()
+    torch, L = _torch(), lib()
     _need(u, torch.float32, "u")
     cfg = _mask_cfg(u, k)
     tau = torch.empty_like(u)
-    death = torch.empty(u.shape, dtype=torch.int32, device=u.device)
+    death = torch.empty_like(u, dtype=torch.int32)
     if ws is None:
-        ws = _ws(lib().sparsek_mask_workspace_bytes(C.byref(cfg)), u.device)
-    check(lib().sparsek_mask(C.byref(cfg), _ptr(u), _ptr(tau), _ptr(death), _ptr(ws), ws.numel(), _stream()))
+        nbytes = _bytes(cfg, "sparsek_mask_workspace_bytes")
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=u.device)
+    else:
+        nbytes = ws.numel()
+    rc = L.sparsek_mask(cfg[0], u.data_ptr(), tau.data_ptr(), death.data_ptr(), ws.data_ptr(), nbytes, _raw_stream())
+    if rc:
+        check(rc)
     return tau, death
 
 
@@ -164,19 +207,21 @@ def sparsek_mask_static(u, k, tau=None, death=None):
         death = torch.empty(u.shape, dtype=torch.int32, device=u.device)
     _need(tau, torch.float32, "tau")
     _need(death, torch.int32, "death")
-    check(lib().sparsek_mask_static(C.byref(cfg), _ptr(u), _ptr(tau), _ptr(death), _stream()))
+    check(lib().sparsek_mask_static(cfg[0], _ptr(u), _ptr(tau), _ptr(death), _stream()))
     return tau, death
 
 
 def sparsek_mask_workspace(u, k):
     """A workspace for sparsek_mask(u, k, ws=...), to be read back with sparsek_mask_status."""
-    return _ws(lib().sparsek_mask_workspace_bytes(C.byref(_mask_cfg(u, k))), u.device)
+    _torch()
+    return _ws(lib().sparsek_mask_workspace_bytes(_mask_cfg(u, k)[0]), u.device)
 
 
 def sparsek_mask_status(u, k, ws):
     """Status word of the last sparsek_mask(u, k, ws=ws) call (0 = every threshold solve converged).  Synchronises."""
     flag = C.c_int32(-1)
-    check(lib().sparsek_mask_status(C.byref(_mask_cfg(u, k)), _ptr(ws), ws.numel(), C.byref(flag), _stream()))
+    _torch()
+    check(lib().sparsek_mask_status(_mask_cfg(u, k)[0], _ptr(ws), ws.numel(), C.byref(flag), _stream()))
     return int(flag.value)
 
 
@@ -195,81 +240,98 @@ def sparsek_materialize(u, tau, death, k, t_begin, t_end, with_gate=True):
     return idx, gate
 
 
+def _make_attn_cfg(B, H, Gu, n, d, k, w, dtype, gate_mode, scale):
+    return SparsekCfg(B=B, H=H, Gu=Gu, n=n, d=d, k=k, w=w, dtype=dtype, gate_mode=gate_mode, softmax_scale=scale)
+
+
 def _attn_cfg(q, u, k, w, gate_mode, scale):
     B, H, n, d = q.shape
-    Gu = u.shape[1]
-    return SparsekCfg(B=B, H=H, Gu=Gu, n=n, d=d, k=int(k), w=int(w), dtype=_dtype_code(q),
-                      gate_mode=int(gate_mode), softmax_scale=float(scale))
+    return _kept("attn", (B, H, u.shape[1], n, d, int(k), int(w), _dtype_code(q), int(gate_mode), float(scale)),
+                 _make_attn_cfg)
+
+
+def _attn_ws(cfg, query, ws, device):
+    """(workspace, its size): the caller's, or a new one of the size the query says."""
+    if ws is not None:
+        return ws, ws.numel()
+    n = _bytes(cfg, query)
+    return torch.empty(n, dtype=torch.uint8, device=device), n
 
 
 def sparsek_attn_fwd(q, k, v, u, tau, death, k_sel, w, gate_mode=0, scale=1.0, return_lse=True, ws=None):
     """q,k,v [B,H,n,d]; u,tau,death [B,Gu,n] -> o [B,H,n,d] (and lse [B,H,n] fp32)."""
-    torch = _torch()
+    torch, L = _torch(), lib()
     cfg = _attn_cfg(q, u, k_sel, w, gate_mode, scale)
-    for t, name in ((q, "q"), (k, "k"), (v, "v")):
-        _need(t, q.dtype, name)
-    _need(u, torch.float32, "u")
-    _need(tau, torch.float32, "tau")
+    dt, f32 = q.dtype, torch.float32
+    _need(q, dt, "q")
+    _need(k, dt, "k")
+    _need(v, dt, "v")
+    _need(u, f32, "u")
+    _need(tau, f32, "tau")
     _need(death, torch.int32, "death")
     o = torch.empty_like(q)
-    lse = torch.empty(q.shape[:3], dtype=torch.float32, device=q.device) if return_lse else None
-    if ws is None:
-        ws = _ws(lib().sparsek_attn_fwd_workspace_bytes(C.byref(cfg)), q.device)
-    check(lib().sparsek_attn_fwd(C.byref(cfg), _ptr(q), _ptr(k), _ptr(v), _ptr(u), _ptr(tau), _ptr(death),
-                                 _ptr(o), _ptr(lse), _ptr(ws), ws.numel(), _stream()))
+    lse = torch.empty(q.shape[:3], dtype=f32, device=q.device) if return_lse else None
+    ws, nbytes = _attn_ws(cfg, "sparsek_attn_fwd_workspace_bytes", ws, q.device)
+    rc = L.sparsek_attn_fwd(cfg[0], q.data_ptr(), k.data_ptr(), v.data_ptr(), u.data_ptr(), tau.data_ptr(), death.data_ptr(),
+                            o.data_ptr(), lse.data_ptr() if return_lse else None, ws.data_ptr(), nbytes, _raw_stream())
+    if rc:
+        check(rc)
     return (o, lse) if return_lse else o
 
 
 def sparsek_mask_bwd(q, k, v, u, tau, death, o, lse, dO, k_sel, w, gate_mode=0, scale=1.0, ws=None):
     """du [B,Gu,n] fp32: gradient of sum(dO*O) w.r.t. the scores through the soft gates."""
-    torch = _torch()
+    torch, L = _torch(), lib()
     cfg = _attn_cfg(q, u, k_sel, w, gate_mode, scale)
     du = torch.empty_like(u)
-    if ws is None:
-        ws = _ws(lib().sparsek_mask_bwd_workspace_bytes(C.byref(cfg)), q.device)
-    check(lib().sparsek_mask_bwd(C.byref(cfg), _ptr(q), _ptr(k), _ptr(v), _ptr(u), _ptr(tau), _ptr(death),
-                                 _ptr(o), _ptr(lse), _ptr(dO), _ptr(du), _ptr(ws), ws.numel(), _stream()))
+    ws, nbytes = _attn_ws(cfg, "sparsek_mask_bwd_workspace_bytes", ws, q.device)
+    check(L.sparsek_mask_bwd(cfg[0], q.data_ptr(), k.data_ptr(), v.data_ptr(), u.data_ptr(), tau.data_ptr(),
+                             death.data_ptr(), o.data_ptr(), lse.data_ptr(), dO.data_ptr(), du.data_ptr(), ws.data_ptr(),
+                             nbytes, _raw_stream()))
     return du
 
 
 def sparsek_attn_bwd(q, k, v, u, tau, death, o, lse, dO, k_sel, w, gate_mode=0, scale=1.0, ws=None):
     """dq, dk, dv [B,H,n,d]: gradients of sum(dO*O) with respect to q, k, v (gates held fixed)."""
-    torch = _torch()
+    torch, L = _torch(), lib()
     cfg = _attn_cfg(q, u, k_sel, w, gate_mode, scale)
     dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
-    if ws is None:
-        ws = _ws(lib().sparsek_attn_bwd_workspace_bytes(C.byref(cfg)), q.device)
-    check(lib().sparsek_attn_bwd(C.byref(cfg), _ptr(q), _ptr(k), _ptr(v), _ptr(u), _ptr(tau), _ptr(death), _ptr(o),
-                                 _ptr(lse), _ptr(dO), _ptr(dq), _ptr(dk), _ptr(dv), _ptr(ws), ws.numel(), _stream()))
+    ws, nbytes = _attn_ws(cfg, "sparsek_attn_bwd_workspace_bytes", ws, q.device)
+    check(L.sparsek_attn_bwd(cfg[0], q.data_ptr(), k.data_ptr(), v.data_ptr(), u.data_ptr(), tau.data_ptr(),
+                             death.data_ptr(), o.data_ptr(), lse.data_ptr(), dO.data_ptr(), dq.data_ptr(), dk.data_ptr(),
+                             dv.data_ptr(), ws.data_ptr(), nbytes, _raw_stream()))
     return dq, dk, dv
 
 
 def sparsek_bwd(q, k, v, u, tau, death, o, lse, dO, k_sel, w, gate_mode=0, scale=1.0, ws=None):
     """The whole backward in one call: (dq, dk, dv, du)."""
-    torch = _torch()
+    torch, L = _torch(), lib()
     cfg = _attn_cfg(q, u, k_sel, w, gate_mode, scale)
     dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
     du = torch.empty_like(u)
-    if ws is None:
-        ws = _ws(lib().sparsek_bwd_workspace_bytes(C.byref(cfg)), q.device)
-    check(lib().sparsek_bwd(C.byref(cfg), _ptr(q), _ptr(k), _ptr(v), _ptr(u), _ptr(tau), _ptr(death), _ptr(o), _ptr(lse),
-                            _ptr(dO), _ptr(dq), _ptr(dk), _ptr(dv), _ptr(du), _ptr(ws), ws.numel(), _stream()))
+    ws, nbytes = _attn_ws(cfg, "sparsek_bwd_workspace_bytes", ws, q.device)
+    check(L.sparsek_bwd(cfg[0], q.data_ptr(), k.data_ptr(), v.data_ptr(), u.data_ptr(), tau.data_ptr(), death.data_ptr(),
+                        o.data_ptr(), lse.data_ptr(), dO.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(),
+                        du.data_ptr(), ws.data_ptr(), nbytes, _raw_stream()))
     return dq, dk, dv, du
+
+
+def _make_scores_cfg(B, n, D, dtype, norm, slope, norm_eps):
+    return SparsekScoresCfg(B=B, n=n, D=D, dtype=dtype, norm=norm, slope=slope, norm_eps=norm_eps)
 
 
 def sparsek_scores(x, w, slope=0.0, norm=False, norm_eps=1e-5, ws=None):
     """u [B,n] fp32 from hidden states x [B,n,D] (bf16 or fp32) and the scorer w [D] fp32:
     x.w + position slope, optionally timestep-normalised."""
-    torch = _torch()
+    torch, L = _torch(), lib()
     B, n, D = x.shape
     assert x.is_contiguous() and w.is_contiguous() and w.dtype == torch.float32 and w.numel() == D
     dt = BF16 if x.dtype == torch.bfloat16 else F32
     assert dt == BF16 or x.dtype == torch.float32
-    cfg = SparsekScoresCfg(B=B, n=n, D=D, dtype=dt, norm=int(bool(norm)), slope=float(slope), norm_eps=float(norm_eps))
+    cfg = _kept("scores", (B, n, D, dt, int(bool(norm)), float(slope), float(norm_eps)), _make_scores_cfg)
     u = torch.empty(B, n, dtype=torch.float32, device=x.device)
-    if ws is None:
-        ws = _ws(lib().sparsek_scores_workspace_bytes(C.byref(cfg)), x.device)
-    check(lib().sparsek_scores(C.byref(cfg), _ptr(x), _ptr(w), _ptr(u), _ptr(ws), ws.numel(), _stream()))
+    ws, nbytes = _attn_ws(cfg, "sparsek_scores_workspace_bytes", ws, x.device)
+    check(L.sparsek_scores(cfg[0], x.data_ptr(), w.data_ptr(), u.data_ptr(), ws.data_ptr(), nbytes, _raw_stream()))
     return u
 
 
@@ -281,12 +343,13 @@ class ChunkState:
         self.cfg = SparsekChunkCfg(B=B, H=H, Gu=Gu, d=d, k=int(k), w=int(w), cand_cap=int(cand_cap),
                                    chunk_max=int(chunk_max), dtype=dtype, gate_mode=int(gate_mode),
                                    softmax_scale=float(scale))
-        nbytes = lib().sparsek_chunk_state_bytes(C.byref(self.cfg))
+        self.ref = C.byref(self.cfg)
+        nbytes = lib().sparsek_chunk_state_bytes(self.ref)
         if nbytes == 0:
             raise ValueError("invalid chunk configuration")
         self.buf = torch.empty(nbytes, dtype=torch.uint8, device=device)
-        self.ws = torch.empty(lib().sparsek_chunk_workspace_bytes(C.byref(self.cfg)), dtype=torch.uint8, device=device)
-        check(lib().sparsek_chunk_init(C.byref(self.cfg), _ptr(self.buf), self.buf.numel(), _stream()))
+        self.ws = torch.empty(lib().sparsek_chunk_workspace_bytes(self.ref), dtype=torch.uint8, device=device)
+        check(lib().sparsek_chunk_init(self.ref, _ptr(self.buf), self.buf.numel(), _stream()))
 
 
 def sparsek_chunk_prefill(state, q, k, v, u):
@@ -294,7 +357,7 @@ def sparsek_chunk_prefill(state, q, k, v, u):
     torch = _torch()
     c = q.shape[2]
     o = torch.empty_like(q)
-    check(lib().sparsek_chunk_prefill(C.byref(state.cfg), _ptr(state.buf), state.buf.numel(), c, _ptr(q), _ptr(k),
+    check(lib().sparsek_chunk_prefill(state.ref, _ptr(state.buf), state.buf.numel(), c, _ptr(q), _ptr(k),
                                       _ptr(v), _ptr(u), _ptr(o), _ptr(state.ws), state.ws.numel(), _stream()))
     return o
 
@@ -304,14 +367,14 @@ def sparsek_chunk_bwd(state, q, o, dO):
     sparsek_chunk_prefill call on this state processed, the retained keys of earlier chunks held constant."""
     torch = _torch()
     c = q.shape[2]
-    nbytes = lib().sparsek_chunk_bwd_workspace_bytes(C.byref(state.cfg))
+    nbytes = lib().sparsek_chunk_bwd_workspace_bytes(state.ref)
     if nbytes == 0:
         raise ValueError("sparsek_chunk_bwd: unsupported configuration (bf16 with d = 64 or 128 only)")
     if getattr(state, "bwd_ws", None) is None or state.bwd_ws.numel() < nbytes:
         state.bwd_ws = torch.empty(nbytes, dtype=torch.uint8, device=q.device)
     dq, dk, dv = torch.empty_like(q), torch.empty_like(q), torch.empty_like(q)
     du = torch.empty((state.cfg.B, state.cfg.Gu, c), dtype=torch.float32, device=q.device)
-    check(lib().sparsek_chunk_bwd(C.byref(state.cfg), c, _ptr(q), _ptr(o), _ptr(dO), _ptr(state.ws), state.ws.numel(),
+    check(lib().sparsek_chunk_bwd(state.ref, c, _ptr(q), _ptr(o), _ptr(dO), _ptr(state.ws), state.ws.numel(),
                                   _ptr(dq), _ptr(dk), _ptr(dv), _ptr(du), _ptr(state.bwd_ws), state.bwd_ws.numel(),
                                   _stream()))
     return dq, dk, dv, du
@@ -319,8 +382,8 @@ def sparsek_chunk_bwd(state, q, o, dO):
 
 def sparsek_chunk_to_decode(state, n_consumed, decode_state):
     """Fills a DecodeState with the state after the n_consumed tokens the chunks have covered."""
-    check(lib().sparsek_chunk_to_decode(C.byref(state.cfg), _ptr(state.buf), state.buf.numel(), int(n_consumed),
-                                        _ptr(state.ws), state.ws.numel(), C.byref(decode_state.cfg),
+    check(lib().sparsek_chunk_to_decode(state.ref, _ptr(state.buf), state.buf.numel(), int(n_consumed),
+                                        _ptr(state.ws), state.ws.numel(), decode_state.ref,
                                         _ptr(decode_state.buf), decode_state.buf.numel(), _stream()))
 
 
@@ -331,7 +394,7 @@ def sparsek_chunk_status(state):
     rows = state.cfg.B * state.cfg.Gu
     counts = np.zeros(rows, np.int32)
     flags = np.zeros(rows, np.int32)
-    check(lib().sparsek_chunk_status(C.byref(state.cfg), _ptr(state.buf), counts.ctypes.data_as(C.c_void_p),
+    check(lib().sparsek_chunk_status(state.ref, _ptr(state.buf), counts.ctypes.data_as(C.c_void_p),
                                      flags.ctypes.data_as(C.c_void_p), _stream()))
     return counts, flags
 
@@ -345,27 +408,30 @@ class DecodeState:
                                     dtype=BF16 if dtype == torch.bfloat16 else F32,
                                     gate_mode=int(gate_mode), softmax_scale=float(scale))
         self.torch_dtype = dtype
-        nbytes = lib().sparsek_decode_state_bytes(C.byref(self.cfg))
+        self.ref = C.byref(self.cfg)
+        nbytes = lib().sparsek_decode_state_bytes(self.ref)
         if nbytes == 0:
             raise ValueError("unsupported decode configuration")
         self.buf = torch.empty(int(nbytes), dtype=torch.uint8, device=device)
 
 
 def sparsek_decode_init(state):
-    check(lib().sparsek_decode_init(C.byref(state.cfg), _ptr(state.buf), state.buf.numel(), _stream()))
+    check(lib().sparsek_decode_init(state.ref, _ptr(state.buf), state.buf.numel(), _stream()))
 
 
 def sparsek_decode_load(state, k, v, u, tau, death):
     n_ctx = k.shape[2]
-    check(lib().sparsek_decode_load(C.byref(state.cfg), _ptr(state.buf), state.buf.numel(), int(n_ctx),
+    check(lib().sparsek_decode_load(state.ref, _ptr(state.buf), state.buf.numel(), int(n_ctx),
                                     _ptr(k), _ptr(v), _ptr(u), _ptr(tau), _ptr(death), _stream()))
 
 
 def sparsek_decode_step(state, q_new, k_new, v_new, u_new, out=None):
-    torch = _torch()
+    torch, L = _torch(), lib()
     o = out if out is not None else torch.empty_like(q_new)
-    check(lib().sparsek_decode_step(C.byref(state.cfg), _ptr(state.buf), _ptr(q_new), _ptr(k_new),
-                                    _ptr(v_new), _ptr(u_new), _ptr(o), _stream()))
+    rc = L.sparsek_decode_step(state.ref, state.buf.data_ptr(), q_new.data_ptr(), k_new.data_ptr(), v_new.data_ptr(),
+                               u_new.data_ptr(), o.data_ptr(), _raw_stream())
+    if rc:
+        check(rc)
     return o
 
 
@@ -373,6 +439,6 @@ def sparsek_decode_status(state):
     import numpy as np
 
     flags = np.zeros(state.cfg.B * state.cfg.Gu, np.int32)
-    check(lib().sparsek_decode_status(C.byref(state.cfg), _ptr(state.buf),
+    check(lib().sparsek_decode_status(state.ref, _ptr(state.buf),
                                       flags.ctypes.data_as(C.c_void_p), _stream()))
     return flags
