@@ -35,107 +35,173 @@ size_t attn_fwd_ws_bytes(const sparsek_cfg& c) { return block_lists_bytes(c, nul
 // first the keys that stay selected for every query of the block (death >= T0 + QB, ascending),
 // then, filled from the back, the keys that expire inside the block.  Only the tiles of the
 // second partition need a per-pair validity test.  Each of the 16 waves owns a slice of
-// [0, T0]: one counting pass, one barrier, one placement pass.
+// [0, T0]: one counting pass, one barrier, one placement pass; up to BL_REG lifetimes per lane stay in
+// registers in between.  The list is put together in LDS and written from there in order, with the
+// scores fetched at that point: placing entries straight into memory made every group of 64 positions
+// wait for its scores.
+// A workgroup that owns several consecutive blocks scans the prefix for the first one only: the top-k of the next
+// block's prefix are the keys that stayed selected, and the 128 positions in between.
+// Bounded by latency for one row (18.9 -> 12.5 us at n = 32768, k = 1024), by the scans' issue for many
+// (82 us, 62 us with a workgroup per block, 42 us with eight blocks per workgroup, for 32 rows of 16384).
 // With xpos != nullptr the same lists are also written in the extended form described above.
 // ---------------------------------------------------------------------------------
 constexpr int BL_WAVES = 16;   // waves per workgroup of block_lists_kernel
-constexpr int BL_UNROLL = 8;   // loads in flight per lane
+constexpr int BL_LDS = 4096;   // entries put together in LDS; longer lists are placed in memory directly
 
-__global__ __launch_bounds__(64 * BL_WAVES) void block_lists_kernel(const int32_t* __restrict__ death, int n, int k,
-                                                                     int w, int nb, int32_t* __restrict__ lists,
-                                                                     int32_t* __restrict__ counts,
-                                                                     const float* __restrict__ u,
-                                                                     int32_t* __restrict__ xpos,
-                                                                     int32_t* __restrict__ xdeath,
-                                                                     float* __restrict__ xu, int KP)
+struct ListSmem {
+    int wstay[BL_WAVES], wgo[BL_WAVES];
+    int pos[2][BL_LDS], death[2][BL_LDS];   // the list of this block, of the one before
+};
+struct ListOut {
+    int32_t *lo, *xpos, *xdeath;
+    float* xu;
+};
+
+// The lists of `cand(e)` = (position, lifetime), e = 0 .. ncand - 1, that are alive at T0, each wave owning a slice of
+// the candidates, REG per lane at a time: into LDS, or into memory when there are more than BL_LDS of them.
+// Returns the number of entries that stay for the whole block, cnt = entries in all.
+template <int REG, typename Death, typename Pos>
+__device__ __forceinline__ int block_list(ListSmem& sm, int buf, int ncand, int T0, int k, const float* __restrict__ ur,
+                                          const ListOut& out, int& cnt, Death&& death_of, Pos&& pos_of)
 {
-    __shared__ int wstay[BL_WAVES], wgo[BL_WAVES];
-    const int blk = blockIdx.x, row = blockIdx.y;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int T0 = blk * QB - w;
-    int32_t* lo = lists + ((size_t)row * nb + blk) * (size_t)(k > 0 ? k : 1);
-    if (T0 < 0 || k == 0) {
-        if (tid == 0) {
-            counts[(size_t)row * nb + blk] = 0;
-            counts[((size_t)gridDim.y + row) * nb + blk] = 0;
-        }
-        return;
-    }
-    const int32_t* dr = death + (size_t)row * n;
-    const float* ur = u ? u + (size_t)row * n : nullptr;
-    const size_t xo = ((size_t)row * nb + blk) * (size_t)KP;
-    const int len = T0 + 1;
-    constexpr int STEP = 64 * BL_UNROLL;
-    const int per = ((len + BL_WAVES - 1) / BL_WAVES + STEP - 1) / STEP * STEP;
-    const int j_lo = wv * per, j_hi = min(len, j_lo + per);
-    const int stay_from = T0 + QB;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const unsigned long long below = (1ull << lane) - 1ull;
-    int ns = 0, ng = 0;
-    for (int j0 = j_lo; j0 < j_hi; j0 += STEP) {
-        int dj[BL_UNROLL];
+    const int per = ((ncand + BL_WAVES - 1) / BL_WAVES + 63) / 64 * 64;
+    const int e_lo = min(ncand, wv * per), e_hi = min(ncand, e_lo + per);
+    const int stay_from = T0 + QB;
+    int dj[REG];
+    auto load = [&](int e0) {
 #pragma unroll
-        for (int e = 0; e < BL_UNROLL; e++) {
-            const int j = j0 + 64 * e + lane;
-            dj[e] = j < j_hi ? dr[j] : 0;
+        for (int r = 0; r < REG; r++) {
+            if (e0 + 64 * r >= e_hi) break;   // (uniform)
+            const int e = e0 + 64 * r + lane;
+            dj[r] = e < e_hi ? death_of(e) : 0;
         }
+    };
+    int ns = 0, ng = 0;
+    for (int e0 = e_lo; e0 < e_hi; e0 += 64 * REG) {
+        load(e0);
 #pragma unroll
-        for (int e = 0; e < BL_UNROLL; e++) {
-            ns += __popcll(__ballot(dj[e] >= stay_from));
-            ng += __popcll(__ballot(dj[e] > T0 && dj[e] < stay_from));
+        for (int r = 0; r < REG; r++) {
+            if (e0 + 64 * r >= e_hi) break;
+            const unsigned long long alive = __ballot(dj[r] > T0), stay = __ballot(dj[r] >= stay_from);
+            ns += __popcll(stay);
+            ng += __popcll(alive) - __popcll(stay);
         }
     }
-    if (lane == 0) { wstay[wv] = ns; wgo[wv] = ng; }
+    if (lane == 0) { sm.wstay[wv] = ns; sm.wgo[wv] = ng; }
     __syncthreads();
     int os = 0, og = 0, tot_s = 0, tot_g = 0;
     for (int i = 0; i < BL_WAVES; i++) {
-        if (i < wv) { os += wstay[i]; og += wgo[i]; }
-        tot_s += wstay[i];
-        tot_g += wgo[i];
+        if (i < wv) { os += sm.wstay[i]; og += sm.wgo[i]; }
+        tot_s += sm.wstay[i];
+        tot_g += sm.wgo[i];
     }
     // min(k, T0 + 1) for a consistent death array; counted, so that every entry below cnt is written
-    const int cnt = min(k, tot_s + tot_g);
-    for (int j0 = j_lo; j0 < j_hi; j0 += STEP) {
-        int dj[BL_UNROLL];
+    cnt = min(k, tot_s + tot_g);
+    const bool in_lds = cnt <= BL_LDS;
+    for (int e0 = e_lo; e0 < e_hi; e0 += 64 * REG) {
+        if (per > 64 * REG) load(e0);
 #pragma unroll
-        for (int e = 0; e < BL_UNROLL; e++) {
-            const int j = j0 + 64 * e + lane;
-            dj[e] = j < j_hi ? dr[j] : 0;
-        }
-#pragma unroll
-        for (int e = 0; e < BL_UNROLL; e++) {
-            const int j = j0 + 64 * e + lane;
-            const bool stay = dj[e] >= stay_from, go = dj[e] > T0 && dj[e] < stay_from;
-            const unsigned long long bs = __ballot(stay), bg = __ballot(go);
+        for (int r = 0; r < REG; r++) {
+            if (e0 + 64 * r >= e_hi) break;
+            const unsigned long long alive = __ballot(dj[r] > T0), bs = __ballot(dj[r] >= stay_from), bg = alive & ~bs;
+            if (!alive) continue;
             int o = -1;
-            if (stay) {
+            if (dj[r] >= stay_from) {
                 o = os + __popcll(bs & below);
                 if (o >= cnt) o = -1;
+            } else if (dj[r] > T0) {
+                o = cnt - 1 - (og + __popcll(bg & below));
             }
-            if (go) o = cnt - 1 - (og + __popcll(bg & below));
             if (o >= 0) {
-                lo[o] = j;
-                if (xpos) {
-                    xpos[xo + o] = j;
-                    xdeath[xo + o] = dj[e];
-                    xu[xo + o] = ur[j];
+                const int j = pos_of(e0 + 64 * r + lane);
+                if (in_lds) {
+                    sm.pos[buf][o] = j;
+                    sm.death[buf][o] = dj[r];
+                } else {
+                    out.lo[o] = j;
+                    if (out.xpos) {
+                        out.xpos[o] = j;
+                        out.xdeath[o] = dj[r];
+                        out.xu[o] = ur[j];
+                    }
                 }
             }
             os += __popcll(bs);
             og += __popcll(bg);
         }
     }
-    if (tid == 0) {
-        counts[(size_t)row * nb + blk] = cnt;
-        counts[((size_t)gridDim.y + row) * nb + blk] = min(cnt, tot_s);
-    }
-    if (xpos) {
-        // padding up to the tile boundary above min(k, T0 + 1), the length the forward kernel lays its tiles out for
-        const int padded = (min(k, len) + KT - 1) / KT * KT;
-        for (int o = cnt + tid; o < padded; o += 64 * BL_WAVES) {
-            xpos[xo + o] = 0;
-            xdeath[xo + o] = INT32_MIN;
-            xu[xo + o] = 0.0f;
+    __syncthreads();   // the list is complete; wstay and wgo may be written again
+    return tot_s;
+}
+
+// BL_REG: lifetimes per lane of a scan.  32 read a prefix of 32768 once; 8 leave room for a second workgroup on the
+// compute unit.  RUNS: a workgroup owns `run` consecutive blocks, else one.
+template <int BL_REG, bool RUNS>
+__global__ __launch_bounds__(64 * BL_WAVES, RUNS ? 8 : 4) void block_lists_kernel(
+    const int32_t* __restrict__ death, int n, int k, int w, int nb, int run /* consecutive blocks per workgroup */,
+    int32_t* __restrict__ lists, int32_t* __restrict__ counts, const float* __restrict__ u, int32_t* __restrict__ xpos,
+    int32_t* __restrict__ xdeath, float* __restrict__ xu, int KP)
+{
+    constexpr int NT = 64 * BL_WAVES;
+    __shared__ ListSmem sm;
+    const int row = blockIdx.y, nrows = gridDim.y;
+    const int tid = threadIdx.x;
+    const int32_t* dr = death + (size_t)row * n;
+    const float* ur = u ? u + (size_t)row * n : nullptr;
+    int stayed = -1;   // entries of the list before that stayed selected; -1: no such list
+    int buf = 0;
+    const int b_first = RUNS ? blockIdx.x * run : blockIdx.x, b_end = RUNS ? min(nb, b_first + run) : b_first + 1;
+    for (int blk = b_first; blk < b_end; blk++) {
+        const int T0 = blk * QB - w;
+        if (T0 < 0 || k == 0) {
+            if (tid == 0) {
+                counts[(size_t)row * nb + blk] = 0;
+                counts[((size_t)nrows + row) * nb + blk] = 0;
+            }
+            continue;
         }
+        const size_t xo = ((size_t)row * nb + blk) * (size_t)KP;
+        const ListOut out{lists + ((size_t)row * nb + blk) * (size_t)k, xpos ? xpos + xo : nullptr, xdeath + xo, xu + xo};
+        int cnt, tot_s;
+        if (!RUNS || stayed < 0) {
+            tot_s = block_list<BL_REG>(sm, buf, T0 + 1, T0, k, ur, out, cnt, [&](int e) { return dr[e]; },
+                                       [](int e) { return e; });
+        } else {   // what stayed, then the positions T0 - QB + 1 .. T0: ascending again
+            const int* pp = sm.pos[buf ^ 1];
+            const int* pd = sm.death[buf ^ 1];
+            const int first = T0 - QB + 1 - stayed;
+            tot_s = block_list<2>(sm, buf, stayed + QB, T0, k, ur, out, cnt,
+                                  [&](int e) { return e < stayed ? pd[e] : dr[first + e]; },
+                                  [&](int e) { return e < stayed ? pp[e] : first + e; });
+        }
+        if (tid == 0) {
+            counts[(size_t)row * nb + blk] = cnt;
+            counts[((size_t)nrows + row) * nb + blk] = min(cnt, tot_s);
+        }
+        if (cnt <= BL_LDS) {
+            for (int o = tid; o < cnt; o += NT) {
+                const int j = sm.pos[buf][o];
+                out.lo[o] = j;
+                if (xpos) {
+                    out.xpos[o] = j;
+                    out.xdeath[o] = sm.death[buf][o];
+                    out.xu[o] = ur[j];
+                }
+            }
+        }
+        if (xpos) {
+            // padding up to the tile boundary above min(k, T0 + 1), the length the forward kernel lays its tiles out for
+            const int padded = (min(k, T0 + 1) + KT - 1) / KT * KT;
+            for (int o = cnt + tid; o < padded; o += NT) {
+                out.xpos[o] = 0;
+                out.xdeath[o] = INT32_MIN;
+                out.xu[o] = 0.0f;
+            }
+        }
+        stayed = cnt <= BL_LDS && tot_s <= cnt ? tot_s : -1;
+        buf ^= 1;
     }
 }
 
@@ -691,8 +757,16 @@ void launch_block_lists_ext(const sparsek_cfg& c, const int32_t* death, int32_t*
                                    const float* u, const ExtLists& x, hipStream_t st)
 {
     const int nb = nblocks(c.n);
-    hipLaunchKernelGGL(block_lists_kernel, dim3(nb, c.B * c.Gu), dim3(64 * BL_WAVES), 0, st, death, c.n, c.k, c.w, nb,
-                       lists, counts, u, x.pos, x.death, x.u, x.KP);
+    // Up to 256 blocks: a compute unit for each.  More: two workgroups per compute unit, and runs of up to 16 blocks
+    // once there are several rounds of them.
+    const long long blocks = (long long)nb * c.B * c.Gu;
+    const int run = (int)std::max(1ll, std::min(16ll, blocks / 512));
+    if (blocks > 256)
+        hipLaunchKernelGGL((block_lists_kernel<8, true>), dim3((nb + run - 1) / run, c.B * c.Gu), dim3(64 * BL_WAVES), 0, st, death,
+                           c.n, c.k, c.w, nb, run, lists, counts, u, x.pos, x.death, x.u, x.KP);
+    else
+        hipLaunchKernelGGL((block_lists_kernel<32, false>), dim3(nb, c.B * c.Gu), dim3(64 * BL_WAVES), 0, st, death, c.n, c.k, c.w,
+                           nb, 1, lists, counts, u, x.pos, x.death, x.u, x.KP);
 }
 
 void launch_block_lists(const sparsek_cfg& c, const int32_t* death, int32_t* lists, int32_t* counts,
