@@ -206,27 +206,33 @@ __global__ __launch_bounds__(64 * BL_WAVES, RUNS ? 8 : 4) void block_lists_kerne
 }
 
 // ---------------------------------------------------------------------------------
-// Generic vector-ALU kernel (fp32 or bf16 storage, any d <= 128 that is a multiple of 4).
-// One wave per query, lanes over keys for the logits and over columns for the output.
-// Used for fp32 tensors and head dims the MFMA kernel does not cover.  A query block of QB
-// queries (the granularity of the lists) is spread over GEN_SPLIT workgroups of four waves, one
-// query per wave, so that small problems still fill the chip.
+// Kernel for fp32 storage, and for bf16 with a head dimension the kernel below does not cover (any d <= 128 that is a
+// multiple of 4): fp32 matrix instructions (v_mfma_f32_16x16x4_f32, full fp32 products and sums).  A workgroup owns 16
+// queries; its four waves take the 16-key tiles of their key set in turn, each with an online softmax of its own, and
+// merge through LDS.  No LDS staging: operands come from memory in the layout the instruction wants --
+//   S^T = K.Q^T    lane l supplies K[key l % 16] at d = 16 x + 4 (l / 16) + {0..3}: one 16-byte load feeds four steps (the
+//                  order of d inside a contraction is free, Q uses the same);
+//   O^T += V^T.P^T step r contracts the keys 4 g + r, g = 0..3: exactly the P values that lane group g holds.
+// Problems of this kind are small (one head of 1024 queries, k = w = 64: 31 us with a wave per query and scalar
+// products), so it is built for latency: GEN_SPLIT workgroups per query block, positions one tile ahead; 11.6 us now.
 // ---------------------------------------------------------------------------------
-constexpr int GEN_SPLIT = QB / 4;
-template <typename T>
-__device__ __forceinline__ float ld(const T* p);
-template <>
-__device__ __forceinline__ float ld<float>(const float* p) { return *p; }
-template <>
-__device__ __forceinline__ float ld<uint16_t>(const uint16_t* p) { return bf16_to_f32(*p); }
-template <typename T>
-__device__ __forceinline__ void st(T* p, float v);
-template <>
-__device__ __forceinline__ void st<float>(float* p, float v) { *p = v; }
-template <>
-__device__ __forceinline__ void st<uint16_t>(uint16_t* p, float v) { *p = f32_to_bf16(v); }
+constexpr int GQ = 16;                 // queries per workgroup
+constexpr int GEN_SPLIT = QB / GQ;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
-template <typename T>
+__device__ __forceinline__ f32x4 load4(const float* p) { return *(const f32x4*)p; }
+__device__ __forceinline__ f32x4 load4(const uint16_t* p)
+{
+    const uint2 r = *(const uint2*)p;
+    return f32x4{__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xFFFF0000u), __uint_as_float(r.y << 16),
+                 __uint_as_float(r.y & 0xFFFF0000u)};
+}
+__device__ __forceinline__ float load1(const float* p) { return *p; }
+__device__ __forceinline__ float load1(const uint16_t* p) { return bf16_to_f32(*p); }
+__device__ __forceinline__ void store1(float* p, float v) { *p = v; }
+__device__ __forceinline__ void store1(uint16_t* p, float v) { *p = f32_to_bf16(v); }
+
+template <typename T, int DT>   // DT = number of 16-column blocks of the head dimension (rounded up)
 __global__ __launch_bounds__(256) void attn_fwd_generic_kernel(
     const T* __restrict__ q, const T* __restrict__ kk, const T* __restrict__ v,
     const float* __restrict__ u, const float* __restrict__ tau, const int32_t* __restrict__ death,
@@ -234,84 +240,127 @@ __global__ __launch_bounds__(256) void attn_fwd_generic_kernel(
     float* __restrict__ lse, int H, int Gu, int n, int d, int k, int w, int gate_mode, float scale, int nb,
     int q_begin, const int32_t* __restrict__ first_valid, int q_rows)
 {
-    __shared__ float qs[4][128];
+    __shared__ float po[4][DT * 16][GQ + 1], pm[4][GQ], pl[4][GQ];
     const int blk = blockIdx.x / GEN_SPLIT, sub = blockIdx.x % GEN_SPLIT, bh = blockIdx.y;
     const int b = bh / H, h = bh % H;
     const int row = b * Gu + (Gu == 1 ? 0 : h);
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int i0 = blk * QB;
-    if (i0 + QB <= q_begin) return;  // queries before q_begin are not wanted (chunked prefill)
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, grp = lane >> 4;
+    const int i0 = blk * QB, ia = i0 + GQ * sub;   // first query of the block, of this workgroup
+    if (i0 + QB <= q_begin || ia >= n) return;     // queries before q_begin are not wanted (chunked prefill)
     // q and o hold q_rows rows per head starting at query q_begin (0: all n rows)
     const ptrdiff_t qo = q_rows ? (ptrdiff_t)bh * q_rows - q_begin : (ptrdiff_t)bh * n;
-    const T* qh = q + qo * d;
     const T* kh = kk + (size_t)bh * n * d;
     const T* vh = v + (size_t)bh * n * d;
-    T* oh = o + qo * d;
     const float* ur = u + (size_t)row * n;
-    const float* tr = tau + (size_t)row * n;
     const int32_t* dr = death + (size_t)row * n;
     const int32_t* list = lists + ((size_t)row * nb + blk) * (size_t)(k > 0 ? k : 1);
-    const int cnt = counts[(size_t)row * nb + blk];
     // keys before first_valid[row] (padding of a chunked prefill) are attended by nobody
     const int c0 = max(max(0, i0 - w + 1), first_valid ? first_valid[row] : 0);
-
-    {
-        const int i = i0 + 4 * sub + wv;
-        if (i >= n || i < q_begin) return;
-        for (int c = lane; c < d; c += 64) qs[wv][c] = ld(qh + (size_t)i * d + c);
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        const int Tp = i - w;
-        const float tauT = (Tp >= 0) ? tr[Tp] : 0.0f;
-        float m_run = -INFINITY, l_run = 0.0f, acc0 = 0.0f, acc1 = 0.0f;
-        const int n_list = (Tp >= 0) ? cnt : 0;
-        const int n_cont = i - c0 + 1;
-        const int total = n_list + n_cont;
-        for (int e0 = 0; e0 < total; e0 += 64) {
-            const int e = e0 + lane;
-            int j = -1;
-            if (e < total) j = (e < n_list) ? list[e] : c0 + (e - n_list);
-            bool valid = false;
-            float gate = 1.0f;
-            if (j >= 0) {
-                if (i - j < w) valid = true;  // window (j <= i by construction)
-                else if (dr[j] > Tp) { valid = true; gate = clip01(ur[j] - tauT); }
-            }
-            float s = -INFINITY;
-            if (valid) {
-                float dot = 0.0f;
-                const T* kj = kh + (size_t)j * d;
-                for (int c = 0; c < d; c += 4) {
-                    dot += qs[wv][c] * ld(kj + c) + qs[wv][c + 1] * ld(kj + c + 1) +
-                           qs[wv][c + 2] * ld(kj + c + 2) + qs[wv][c + 3] * ld(kj + c + 3);
-                }
-                s = scale * dot * (gate_mode == 0 ? gate : 1.0f);
-            }
-            const float tmax = wave_max_f32(s);
-            if (tmax == -INFINITY) continue;  // no valid key in this tile
-            const float m_new = fmaxf(m_run, tmax);
-            const float corr = __expf(m_run - m_new);
-            const float p = valid ? __expf(s - m_new) : 0.0f;
-            l_run = l_run * corr + wave_sum_f32(p);
-            acc0 *= corr;
-            acc1 *= corr;
-            m_run = m_new;
-            const float pv = p * (gate_mode == 2 ? 1.0f : gate);
-            unsigned long long ball = __ballot(valid);
-            while (ball) {
-                const int src = __builtin_ctzll(ball);
-                ball &= ball - 1;
-                const float ps = __shfl(pv, src, 64);
-                const int js = __shfl(j, src, 64);
-                const T* vj = vh + (size_t)js * d;
-                if (lane < d) acc0 += ps * ld(vj + lane);
-                if (lane + 64 < d) acc1 += ps * ld(vj + lane + 64);
-            }
+    const int i = ia + col;                        // this lane's query
+    const int iq = min(i, n - 1);
+    const int Tp = i - w;
+    const float tauT = (Tp >= 0 && i < n) ? tau[(size_t)row * n + Tp] : 0.0f;
+    const int ib = min(ia + GQ - 1, n - 1);        // last query of the workgroup
+    const int nl = ib - w >= 0 ? counts[(size_t)row * nb + blk] : 0;
+    const int total = nl + max(0, ib - c0 + 1);
+    f32x4 qf[DT], acc[DT];
+#pragma unroll
+    for (int x = 0; x < DT; x++) {
+        const int dd = 16 * x + 4 * grp;
+        qf[x] = f32x4{0, 0, 0, 0};
+        if (dd < d) qf[x] = load4(q + (qo + iq) * d + dd);
+        acc[x] = f32x4{0, 0, 0, 0};
+    }
+    const float c2 = scale * 1.4426950408889634f;
+    auto pos = [&](int e) { return e >= total ? -1 : e < nl ? list[e] : c0 + (e - nl); };
+    float m_run = -INFINITY, l_run = 0.0f;
+    // positions of this lane's K row and of its four P / V rows
+    int jk = pos(16 * wv + col), jp[4];
+#pragma unroll
+    for (int r = 0; r < 4; r++) jp[r] = pos(16 * wv + 4 * grp + r);
+    for (int e0 = 16 * wv; e0 < total; e0 += 64) {
+        const T* kr = kh + (size_t)max(jk, 0) * d;
+        f32x4 kf[DT];
+#pragma unroll
+        for (int x = 0; x < DT; x++) {
+            const int dd = 16 * x + 4 * grp;
+            kf[x] = f32x4{0, 0, 0, 0};
+            if (dd < d) kf[x] = load4(kr + dd);
         }
-        const float inv = 1.0f / l_run;
-        if (lane < d) st(oh + (size_t)i * d + lane, acc0 * inv);
-        if (lane + 64 < d) st(oh + (size_t)i * d + lane + 64, acc1 * inv);
-        if (lse && lane == 0) lse[qo + i] = m_run + __logf(l_run);
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        float vf[4][DT], uj[4];
+        int dj[4];
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int j = max(jp[r], 0);
+            uj[r] = ur[j];
+            dj[r] = dr[j];
+#pragma unroll
+            for (int x = 0; x < DT; x++) vf[r][x] = 16 * x + col < d ? load1(vh + (size_t)j * d + 16 * x + col) : 0.0f;
+        }
+        const int jc[4] = {jp[0], jp[1], jp[2], jp[3]};
+        jk = pos(e0 + 64 + col);
+#pragma unroll
+        for (int r = 0; r < 4; r++) jp[r] = pos(e0 + 64 + 4 * grp + r);
+        f32x4 s = {0, 0, 0, 0};
+#pragma unroll
+        for (int x = 0; x < DT; x++)
+#pragma unroll
+            for (int e = 0; e < 4; e++) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[x][e], qf[x][e], s, 0, 0, 0);
+        float s2[4], g[4], mx = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int j = jc[r];
+            const bool win = i - j < w;
+            // a window key (not in the future), or selected for prefix i - w
+            const bool valid = j >= 0 && j <= i && (win || dj[r] > Tp);
+            g[r] = win ? 1.0f : clip01(uj[r] - tauT);
+            s2[r] = valid ? s[r] * (gate_mode == 0 ? g[r] : 1.0f) * c2 : -INFINITY;
+            mx = fmaxf(mx, s2[r]);
+        }
+        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        const float m_new = fmaxf(m_run, mx);
+        const float m_safe = m_new == -INFINITY ? 0.0f : m_new;
+        const float corr = __builtin_amdgcn_exp2f(m_run - m_safe);
+        m_run = m_new;
+        l_run *= corr;
+        float p[4];
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            p[r] = __builtin_amdgcn_exp2f(s2[r] - m_safe);
+            l_run += p[r];
+            if (gate_mode != 2) p[r] *= g[r];
+        }
+#pragma unroll
+        for (int x = 0; x < DT; x++) {
+            acc[x] *= corr;
+#pragma unroll
+            for (int r = 0; r < 4; r++) acc[x] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][x], p[r], acc[x], 0, 0, 0);
+        }
+    }
+    // ---- merge the waves: O^T rows 16 x + 4 grp + e, column col ----
+    l_run += __shfl_xor(l_run, 16, 64);
+    l_run += __shfl_xor(l_run, 32, 64);
+    if (grp == 0) { pm[wv][col] = m_run; pl[wv][col] = l_run; }
+#pragma unroll
+    for (int x = 0; x < DT; x++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) po[wv][16 * x + 4 * grp + e][col] = acc[x][e];
+    __syncthreads();
+    for (int x = tid; x < GQ * d; x += 256) {
+        const int qi = x / d, dd = x % d;
+        if (ia + qi >= n || ia + qi < q_begin) continue;
+        const float M = fmaxf(fmaxf(pm[0][qi], pm[1][qi]), fmaxf(pm[2][qi], pm[3][qi]));
+        float num = 0.0f, den = 0.0f;
+#pragma unroll
+        for (int y = 0; y < 4; y++) {
+            const float f = pm[y][qi] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(pm[y][qi] - M);
+            num += f * po[y][dd][qi];
+            den += f * pl[y][qi];
+        }
+        store1(o + (qo + ia + qi) * d + dd, num / den);
+        if (lse && dd == 0) lse[qo + ia + qi] = (M + log2f(den)) * 0.6931471805599453f;
     }
 }
 
@@ -734,6 +783,22 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(
     }
 }
 
+template <typename T>
+static void launch_generic(const sparsek_cfg& c, const void* q, const void* k, const void* v, const float* u,
+                           const float* tau, const int32_t* death, const int32_t* lists, const int32_t* counts, void* o,
+                           float* lse, int nb, int q_begin, const int32_t* first_valid, int q_rows, hipStream_t st)
+{
+    dim3 grid(nb * GEN_SPLIT, c.B * c.H);
+#define SPK_LAUNCH_G(DT)                                                                                              \
+    hipLaunchKernelGGL((attn_fwd_generic_kernel<T, DT>), grid, dim3(256), 0, st, (const T*)q, (const T*)k, (const T*)v, \
+                       u, tau, death, lists, counts, (T*)o, lse, c.H, c.Gu, c.n, c.d, c.k, c.w, c.gate_mode,            \
+                       c.softmax_scale, nb, q_begin, first_valid, q_rows)
+    if (c.d <= 32) SPK_LAUNCH_G(2);
+    else if (c.d <= 64) SPK_LAUNCH_G(4);
+    else SPK_LAUNCH_G(8);
+#undef SPK_LAUNCH_G
+}
+
 template <int D>
 static void launch_mfma(const sparsek_cfg& c, const void* q, const void* k, const void* v, const float* u,
                         const float* tau, const int32_t* death, const ExtLists& x, const int32_t* counts,
@@ -797,16 +862,10 @@ int launch_attn_fwd(const sparsek_cfg& c, const void* q, const void* k, const vo
         return launch_status();
     }
     launch_block_lists(c, death, lists, counts, st);
-    dim3 grid(nb * GEN_SPLIT, c.B * c.H);
-    if (c.dtype == SPARSEK_F32) {
-        hipLaunchKernelGGL(attn_fwd_generic_kernel<float>, grid, dim3(256), 0, st, (const float*)q,
-                           (const float*)k, (const float*)v, u, tau, death, lists, counts, (float*)o, lse, c.H,
-                           c.Gu, c.n, c.d, c.k, c.w, c.gate_mode, c.softmax_scale, nb, q_begin, first_valid, q_rows);
-    } else {
-        hipLaunchKernelGGL(attn_fwd_generic_kernel<uint16_t>, grid, dim3(256), 0, st, (const uint16_t*)q,
-                           (const uint16_t*)k, (const uint16_t*)v, u, tau, death, lists, counts, (uint16_t*)o,
-                           lse, c.H, c.Gu, c.n, c.d, c.k, c.w, c.gate_mode, c.softmax_scale, nb, q_begin, first_valid, q_rows);
-    }
+    if (c.dtype == SPARSEK_F32)
+        launch_generic<float>(c, q, k, v, u, tau, death, lists, counts, o, lse, nb, q_begin, first_valid, q_rows, st);
+    else
+        launch_generic<uint16_t>(c, q, k, v, u, tau, death, lists, counts, o, lse, nb, q_begin, first_valid, q_rows, st);
     return launch_status();
 }
 
