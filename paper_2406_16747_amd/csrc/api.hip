@@ -1,5 +1,6 @@
 // C-ABI entry points of libsparsek: argument validation, then the launch wrappers.
 #include "common.hpp"
+#include "mask_ranges.hpp"
 
 using namespace spk;
 
@@ -236,11 +237,7 @@ int sparsek_bwd(const sparsek_cfg* cfg, const void* q, const void* k, const void
     if (!q || !k || !v || !u || !tau || !death || !o || !lse || !dO || !dq || !dk || !dv || !du || !ws)
         return SPARSEK_ERR_INVALID_ARG;
     if (ws_bytes < sparsek_bwd_workspace_bytes(cfg)) return SPARSEK_ERR_WORKSPACE;
-    sparsek_cfg c = *cfg;
-    if (c.gate_mode == 3) c.gate_mode = 2;  // the straight-through forward has no gates on q, k, v
-    rc = spk::launch_attn_bwd(c, q, k, v, u, tau, death, o, lse, dO, dq, dk, dv, ws, (hipStream_t)stream);
-    if (rc) return rc;
-    return launch_mask_bwd(*cfg, q, k, v, u, tau, death, o, lse, dO, du,
+    return spk::launch_bwd(*cfg, q, k, v, u, tau, death, o, lse, dO, dq, dk, dv, du, ws,
                            (char*)ws + align_up(spk::attn_bwd_ws_bytes(*cfg), 256), (hipStream_t)stream);
 }
 

@@ -8,6 +8,7 @@
 // p_ij is recomputed from q, k and the forward's lse; nothing of size n x (k + w) is stored.
 #include "common.hpp"
 #include "attn_tiles.hpp"
+#include "mask_ranges.hpp"
 
 namespace spk {
 
@@ -75,33 +76,6 @@ __global__ __launch_bounds__(256) void abwd_delta_kernel(const T* __restrict__ o
     for (int c = lane; c < d; c += 64) s += ldg(o + r * d + c) * ldg(dO + r * d + c);
     s = wave_sum_f32(s);
     if (lane == 0) delta[r] = s;
-}
-
-// The same for bf16 rows of d = 8 * LPR elements: LPR lanes per row, 16 bytes per lane.  Also writes
-// lse2 = lse * log2(e), the form the exponent of the dK/dV kernel subtracts.
-template <int LPR>
-__global__ __launch_bounds__(256) void abwd_delta_bf16_kernel(const uint16_t* __restrict__ o, const uint16_t* __restrict__ dO,
-                                                              size_t rows, float* __restrict__ delta,
-                                                              const float* __restrict__ lse, float* __restrict__ lse2)
-{
-    constexpr int RPB = 256 / LPR;  // rows per workgroup
-    const size_t r = (size_t)blockIdx.x * RPB + threadIdx.x / LPR;
-    if (r >= rows) return;  // whole groups of LPR lanes leave together
-    const size_t off = (r * LPR + threadIdx.x % LPR) * 8;
-    const uint4 a = *(const uint4*)(o + off), b = *(const uint4*)(dO + off);
-    const unsigned aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
-    float s = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-        s = fmaf(__uint_as_float(aw[i] << 16), __uint_as_float(bw[i] << 16), s);
-        s = fmaf(__uint_as_float(aw[i] & 0xffff0000u), __uint_as_float(bw[i] & 0xffff0000u), s);
-    }
-#pragma unroll
-    for (int m = LPR / 2; m > 0; m >>= 1) s += __shfl_xor(s, m, 64);
-    if (threadIdx.x % LPR == 0) {
-        delta[r] = s;
-        lse2[r] = lse[r] * 1.4426950408889634f;
-    }
 }
 
 // fp32 accumulators -> storage type
@@ -384,20 +358,140 @@ __device__ __forceinline__ void dq_run_tiles(DqSmem<D>& sm, const StageSrc& src,
     }
 }
 
+// elist: the ever-selected keys of a score row (death_j > j), ordered by death_j / bw and then by position,
+// so that the 32 keys of a wave and the 128 of a block stop being attended at about the same query and the
+// span of query tiles they walk is short.  eslot[j]: where key j sits in that list, -1 if it is not in it.
+// A counting sort whose result does not depend on timing: every wave owns a contiguous range of positions
+// and its own cursor per bucket.  One workgroup per row, at the head of the dQ kernel's grid: dK/dV, which needs the
+// list, is the next launch, and a launch of its own (28 us at n = 8192) would only be waited for.
+constexpr int EBK = 512;
+constexpr int EW = 4;   // waves
+struct ElistSmem {
+    int cur[EW][EBK];
+    int start[EBK];
+};
+__device__ void abwd_elist(ElistSmem& sm, int row, const int32_t* __restrict__ death, int n, int j_min,
+                           int32_t* __restrict__ elist, int32_t* __restrict__ ecount, int32_t* __restrict__ eslot)
+{
+    auto& cur = sm.cur;
+    auto& start = sm.start;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int32_t* dr = death + (size_t)row * n;
+    int32_t* el = elist + (size_t)row * n;
+    int32_t* es = eslot + (size_t)row * n;
+    const int bw = max(256, (n + EBK) / EBK);  // death <= n, so death / bw < EBK
+    for (int i = tid; i < EW * EBK; i += 64 * EW) (&cur[0][0])[i] = 0;
+    __syncthreads();
+    const int per = ((n + EW - 1) / EW + 63) / 64 * 64;
+    const int j_begin = min(n, wv * per), j_end = min(n, j_begin + per);
+    for (int j0 = j_begin; j0 < j_end; j0 += 256) {   // four loads in flight
+        int dj[4];
+#pragma unroll
+        for (int x = 0; x < 4; x++) dj[x] = j0 + 64 * x + lane < j_end ? dr[j0 + 64 * x + lane] : 0;
+#pragma unroll
+        for (int x = 0; x < 4; x++) {
+            const int j = j0 + 64 * x + lane;
+            if (j < j_end && dj[x] > j && j >= j_min) atomicAdd(&cur[wv][dj[x] / bw], 1);
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < EBK; i += 64 * EW) {  // per bucket: each wave's offset inside the bucket, and the bucket's size
+        int acc = 0;
+#pragma unroll
+        for (int x = 0; x < EW; x++) {
+            const int c = cur[x][i];
+            cur[x][i] = acc;
+            acc += c;
+        }
+        start[i] = acc;
+    }
+    __syncthreads();
+    if (wv == 0) {  // exclusive scan of the bucket sizes, 8 buckets per lane
+        int v[EBK / 64], sum = 0;
+#pragma unroll
+        for (int i = 0; i < EBK / 64; i++) { v[i] = start[lane * (EBK / 64) + i]; sum += v[i]; }
+        int incl = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += y;
+        }
+        int ex = incl - sum;
+#pragma unroll
+        for (int i = 0; i < EBK / 64; i++) { start[lane * (EBK / 64) + i] = ex; ex += v[i]; }
+        if (lane == 63) ecount[row] = incl;
+    }
+    __syncthreads();
+    const unsigned long long below = (1ull << lane) - 1ull;
+    int next = j_begin + lane < j_end ? dr[j_begin + lane] : 0;
+    for (int j0 = j_begin; j0 < j_end; j0 += 64) {
+        const int j = j0 + lane;
+        const int dj = next;
+        next = j + 64 < j_end ? dr[j + 64] : 0;
+        const bool sel = j < j_end && dj > j && j >= j_min;  // keys before j_min receive no gradient
+        const int bkt = sel ? dj / bw : -1;
+        int slot = -1;
+        unsigned long long rem = __ballot(sel);
+        while (rem) {  // one turn per distinct bucket among this step's lanes
+            const int l = __ffsll((long long)rem) - 1;
+            const int bb = __shfl(bkt, l, 64);
+            const unsigned long long m = __ballot(bkt == bb);
+            const int base = start[bb] + cur[wv][bb];
+            if (bkt == bb) slot = base + __popcll(m & below);
+            if (lane == l) cur[wv][bb] += __popcll(m);
+            rem &= ~m;
+        }
+        if (sel) el[slot] = j;
+        if (j < j_end) es[j] = slot;
+    }
+}
+
+// What the first workgroups of the dQ kernel do: the lists of ever-selected keys, and clearing words for whoever asks.
+struct DqAux {
+    int rows, zero_blocks;
+    int j_min;
+    int32_t *elist, *ecount, *eslot;
+    uint32_t* zero;
+    size_t zero_words;
+};
+constexpr int ZERO_PER_BLOCK = 256 * 32;   // words
+
+__device__ __forceinline__ void dq_aux(ElistSmem& sm, const DqAux& a, int id, const int32_t* __restrict__ death, int n)
+{
+    if (id < a.rows) {
+        abwd_elist(sm, id, death, n, a.j_min, a.elist, a.ecount, a.eslot);
+        return;
+    }
+    const size_t w0 = (size_t)(id - a.rows) * ZERO_PER_BLOCK;
+    for (size_t i = w0 + threadIdx.x; i < min(a.zero_words, w0 + ZERO_PER_BLOCK); i += 256) a.zero[i] = 0u;
+}
+
 template <int D, int MODE>
 __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ kk, const uint16_t* __restrict__ v,
     const float* __restrict__ u, const float* __restrict__ tau, const int32_t* __restrict__ death,
     const int32_t* __restrict__ xpos, const int32_t* __restrict__ xdeath, const float* __restrict__ xu, int KP,
-    const int32_t* __restrict__ counts, const float* __restrict__ lse, const uint16_t* __restrict__ dO,
-    const float* __restrict__ delta, uint16_t* __restrict__ dq, int H, int Gu, int n, int k, int w, float scale,
-    int nb, int BH, int nrows, int q_begin, const int32_t* __restrict__ first_valid, int q_rows)
+    const int32_t* __restrict__ counts, const float* __restrict__ lse, const uint16_t* __restrict__ o,
+    const uint16_t* __restrict__ dO, float* __restrict__ delta, float* __restrict__ lse2s, uint16_t* __restrict__ dq,
+    int H, int Gu, int n, int k, int w, float scale, int nb, int BH, int nrows, int q_begin,
+    const int32_t* __restrict__ first_valid, int q_rows, DqAux aux)
 {
-    __shared__ __align__(16) DqSmem<D> sm;
+    union Smem {
+        __device__ Smem() {}
+        DqSmem<D> t;
+        ElistSmem e;
+    };
+    __shared__ __align__(16) Smem smem;
+    DqSmem<D>& sm = smem.t;
     constexpr int DS = D / 16, DB = D / 32;
+    const int n_aux = aux.rows + aux.zero_blocks;
+    if ((int)blockIdx.x < n_aux) {
+        dq_aux(smem.e, aux, blockIdx.x, death, n);
+        return;
+    }
     int bh, blk;
     {
-        const int id = blockIdx.x;
+        const int id = blockIdx.x - n_aux;
         if (BH % 8 == 0) {
             const int xcd = id & 7, slot = id >> 3;
             bh = (slot / nb) * 8 + xcd;
@@ -448,13 +542,28 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(
     const int qrow = min(ln.qi, n - 1);
     ln.tau_q = (ln.qi < n && ln.qi - w >= 0) ? tr[ln.qi - w] : 0.0f;
     ln.lse2 = lse[qo + qrow] * 1.4426950408889634f;
-    ln.Di = delta[qo + qrow];
     bf16x8 qreg[DS], dreg[DS];
+    {
+        // D_i = dO_i . o_i is formed here, where the dO rows are loaded anyway, and left for the kernels that follow
+        // together with lse * log2(e), the form their exponents subtract
+        bf16x8 oreg[DS];
 #pragma unroll
-    for (int s = 0; s < DS; s++) {
-        const size_t off = (size_t)(qo + qrow) * D + 16 * s + 8 * half;
-        qreg[s] = *(const bf16x8*)(q + off);
-        dreg[s] = *(const bf16x8*)(dO + off);
+        for (int s = 0; s < DS; s++) {
+            const size_t off = (size_t)(qo + qrow) * D + 16 * s + 8 * half;
+            qreg[s] = *(const bf16x8*)(q + off);
+            dreg[s] = *(const bf16x8*)(dO + off);
+            oreg[s] = *(const bf16x8*)(o + off);
+        }
+        float dpart = 0.0f;
+#pragma unroll
+        for (int s = 0; s < DS; s++)
+#pragma unroll
+            for (int e = 0; e < 8; e++) dpart = fmaf((float)dreg[s][e], (float)oreg[s][e], dpart);
+        ln.Di = dpart + __shfl_xor(dpart, 32, 64);
+        if (half == 0 && ln.qi < n) {
+            delta[qo + ln.qi] = ln.Di;
+            lse2s[qo + ln.qi] = ln.lse2;
+        }
     }
     stage_meta(sm, src, 0, wv, lane);
     const WaveRuns wr = wave_runs(wave_live, nkl, nkc, nstay, qa, qb, w, c0);
@@ -503,16 +612,17 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(
 template <int D>
 static void launch_dq_mfma(const sparsek_cfg& c, const void* q, const void* k, const void* v, const float* u,
                            const float* tau, const int32_t* death, const ExtLists& x, const int32_t* counts,
-                           const float* lse, const void* dO, const float* delta, void* dq, int nb, hipStream_t st,
-                           int q_begin, const int32_t* first_valid, int q_rows)
+                           const float* lse, const void* o, const void* dO, float* delta, float* lse2, void* dq, int nb,
+                           hipStream_t st, int q_begin, const int32_t* first_valid, int q_rows, const DqAux& aux)
 {
     const int BH = c.B * c.H;
-    dim3 grid(nb * BH);
+    dim3 grid(nb * BH + aux.rows + aux.zero_blocks);
 #define SPK_LAUNCH_DQ(MODE)                                                                                        \
     hipLaunchKernelGGL((attn_bwd_dq_kernel<D, MODE>), grid, dim3(256), 0, st, (const uint16_t*)q, (const uint16_t*)k, \
                        (const uint16_t*)v, u, tau, death, (const int32_t*)x.pos, (const int32_t*)x.death,          \
-                       (const float*)x.u, x.KP, counts, lse, (const uint16_t*)dO, delta, (uint16_t*)dq, c.H, c.Gu, \
-                       c.n, c.k, c.w, c.softmax_scale, nb, BH, c.B * c.Gu, q_begin, first_valid, q_rows)
+                       (const float*)x.u, x.KP, counts, lse, (const uint16_t*)o, (const uint16_t*)dO, delta, lse2, \
+                       (uint16_t*)dq, c.H, c.Gu, c.n, c.k, c.w, c.softmax_scale, nb, BH, c.B * c.Gu, q_begin,      \
+                       first_valid, q_rows, aux)
     if (c.gate_mode == 0) SPK_LAUNCH_DQ(0);
     else if (c.gate_mode == 1) SPK_LAUNCH_DQ(1);
     else SPK_LAUNCH_DQ(2);
@@ -552,82 +662,6 @@ __device__ __forceinline__ int wave_min_i32(int x)
 
 __device__ __forceinline__ int b_row(int bh, int H, int Gu) { return (bh / H) * Gu + (Gu == 1 ? 0 : bh % H); }
 
-// elist: the ever-selected keys of a score row (death_j > j), ordered by death_j / bw and then by position,
-// so that the 32 keys of a wave and the 128 of a block stop being attended at about the same query and the
-// span of query tiles they walk is short.  eslot[j]: where key j sits in that list, -1 if it is not in it.
-// A counting sort whose result does not depend on timing: every wave owns a contiguous range of positions
-// and its own cursor per bucket.
-constexpr int EBK = 512;
-__global__ __launch_bounds__(1024) void abwd_elist_kernel(const int32_t* __restrict__ death, int n, int j_min,
-                                                          int32_t* __restrict__ elist, int32_t* __restrict__ ecount,
-                                                          int32_t* __restrict__ eslot)
-{
-    __shared__ int cur[16][EBK];
-    __shared__ int start[EBK];
-    const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int32_t* dr = death + (size_t)row * n;
-    int32_t* el = elist + (size_t)row * n;
-    int32_t* es = eslot + (size_t)row * n;
-    const int bw = max(256, (n + EBK) / EBK);  // death <= n, so death / bw < EBK
-    for (int i = tid; i < 16 * EBK; i += 1024) (&cur[0][0])[i] = 0;
-    __syncthreads();
-    const int per = ((n + 15) / 16 + 63) / 64 * 64;
-    const int j_begin = min(n, wv * per), j_end = min(n, j_begin + per);
-    for (int j0 = j_begin; j0 < j_end; j0 += 64) {
-        const int j = j0 + lane;
-        const int dj = j < j_end ? dr[j] : 0;
-        if (j < j_end && dj > j && j >= j_min) atomicAdd(&cur[wv][dj / bw], 1);
-    }
-    __syncthreads();
-    if (tid < EBK) {  // per bucket: each wave's offset inside the bucket, and the bucket's size
-        int acc = 0;
-#pragma unroll
-        for (int x = 0; x < 16; x++) {
-            const int c = cur[x][tid];
-            cur[x][tid] = acc;
-            acc += c;
-        }
-        start[tid] = acc;
-    }
-    __syncthreads();
-    if (wv == 0) {  // exclusive scan of the bucket sizes, 8 buckets per lane
-        int v[EBK / 64], sum = 0;
-#pragma unroll
-        for (int i = 0; i < EBK / 64; i++) { v[i] = start[lane * (EBK / 64) + i]; sum += v[i]; }
-        int incl = sum;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int y = __shfl_up(incl, o, 64);
-            if (lane >= o) incl += y;
-        }
-        int ex = incl - sum;
-#pragma unroll
-        for (int i = 0; i < EBK / 64; i++) { start[lane * (EBK / 64) + i] = ex; ex += v[i]; }
-        if (lane == 63) ecount[row] = incl;
-    }
-    __syncthreads();
-    const unsigned long long below = (1ull << lane) - 1ull;
-    for (int j0 = j_begin; j0 < j_end; j0 += 64) {
-        const int j = j0 + lane;
-        const int dj = j < j_end ? dr[j] : 0;
-        const bool sel = j < j_end && dj > j && j >= j_min;  // keys before j_min receive no gradient
-        const int bkt = sel ? dj / bw : -1;
-        int slot = -1;
-        unsigned long long rem = __ballot(sel);
-        while (rem) {  // one turn per distinct bucket among this step's lanes
-            const int l = __ffsll((long long)rem) - 1;
-            const int bb = __shfl(bkt, l, 64);
-            const unsigned long long m = __ballot(bkt == bb);
-            const int base = start[bb] + cur[wv][bb];
-            if (bkt == bb) slot = base + __popcll(m & below);
-            if (lane == l) cur[wv][bb] += __popcll(m);
-            rem &= ~m;
-        }
-        if (sel) el[slot] = j;
-        if (j < j_end) es[j] = slot;
-    }
-}
-
 constexpr int DKV_NBUF = 2;  // tiles in LDS: one in use, one being filled
 template <int D>
 struct DkvSmem {
@@ -646,10 +680,22 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(
     const uint16_t* __restrict__ dO, const float* __restrict__ delta, float* __restrict__ dk32,
     float* __restrict__ dv32, float* __restrict__ sk32, float* __restrict__ sv32, const int32_t* __restrict__ eslot,
     uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int H, int Gu, int n, int w, float scale, int nb,
-    int q_begin, int q_rows)
+    int q_begin, int q_rows, RangesArgs ranges)
 {
     using S = MfmaTileBufs<D, 64>;  // (tile geometry only)
-    __shared__ __align__(16) DkvSmem<D> sm;
+    union Smem {
+        __device__ Smem() {}
+        DkvSmem<D> t;
+        float ts[RS_MAX];
+    };
+    __shared__ __align__(16) Smem smem;
+    DkvSmem<D>& sm = smem.t;
+    if ((int)blockIdx.y >= 2 * nb) {   // the last rows of the grid: the ranges of the score gradient, 256 keys each
+        const int id = (blockIdx.y - 2 * nb) * gridDim.x + blockIdx.x, per_row = (n + 255) / 256;
+        const int rows = gridDim.x / H * Gu;
+        if (id < rows * per_row) mask_bwd_ranges(ranges, smem.ts, id % per_row, id / per_row);
+        return;
+    }
     // per query of a tile: lse * log2(e), D_i, tau_{i-w} (and a fourth row that only keeps the loads branch-free)
     __shared__ __align__(16) float meta[DKV_NBUF][4][KT];
     constexpr int DS = D / 16, DB = D / 32, NX = S::NL / 4, LPR = S::RB / 16, RB = S::RB, RPL = S::RPL;
@@ -983,14 +1029,17 @@ static void launch_dkv_mfma(const sparsek_cfg& c, const void* q, const void* k, 
                             const float* tau, const int32_t* death, const int32_t* elist, const int32_t* ecount,
                             const float* lse, const void* dO, const float* delta, float* dk32, float* dv32,
                             float* sk32, float* sv32, const int32_t* eslot, void* dk, void* dv, int nb, hipStream_t st,
-                            int q_begin, int q_rows)
+                            int q_begin, int q_rows, const RangesArgs& ranges)
 {
-    dim3 grid(c.B * c.H, 2 * nb);  // per head: (up to) nb blocks of selected keys, then the nb window blocks
+    // per head: (up to) nb blocks of selected keys, then the nb window blocks
+    const int BH = c.B * c.H;
+    const int extra = ranges.diff ? (c.B * c.Gu * ((c.n + 255) / 256) + BH - 1) / BH : 0;
+    dim3 grid(BH, 2 * nb + extra);
 #define SPK_LAUNCH_KV(MODE)                                                                                         \
     hipLaunchKernelGGL((attn_bwd_dkv_kernel<D, MODE>), grid, dim3(256), 0, st, (const uint16_t*)q, (const uint16_t*)k, \
                        (const uint16_t*)v, u, tau, death, elist, ecount, lse, (const uint16_t*)dO, delta, dk32, dv32,  \
                        sk32, sv32, eslot, (uint16_t*)dk, (uint16_t*)dv, c.H, c.Gu, c.n, c.w, c.softmax_scale, nb, q_begin, \
-                       q_rows)
+                       q_rows, ranges)
     if (c.gate_mode == 0) SPK_LAUNCH_KV(0);
     else if (c.gate_mode == 1) SPK_LAUNCH_KV(1);
     else SPK_LAUNCH_KV(2);
@@ -999,7 +1048,8 @@ static void launch_dkv_mfma(const sparsek_cfg& c, const void* q, const void* k, 
 
 int launch_attn_bwd(const sparsek_cfg& c, const void* q, const void* k, const void* v, const float* u,
                     const float* tau, const int32_t* death, const void* o, const float* lse, const void* dO, void* dq,
-                    void* dk, void* dv, void* ws, hipStream_t st, int q_begin, const int32_t* first_valid, int q_rows)
+                    void* dk, void* dv, void* ws, hipStream_t st, int q_begin, const int32_t* first_valid, int q_rows,
+                    const MaskBwdPrep* prep, BwdShared* shared)
 {
     const AbwdWs W = abwd_ws(c);
     char* base = (char*)ws;
@@ -1036,13 +1086,7 @@ int launch_attn_bwd(const sparsek_cfg& c, const void* q, const void* k, const vo
         hipLaunchKernelGGL(abwd_convert_kernel<float>, dim3(2048), dim3(256), 0, st, dk32, dv32, (float*)dk, (float*)dv,
                            nelem);
     } else {
-        if (c.d == 128)
-            hipLaunchKernelGGL(abwd_delta_bf16_kernel<16>, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st,
-                               (const uint16_t*)o, (const uint16_t*)dO, rows, delta, lse, lse2);
-        else if (c.d == 64)
-            hipLaunchKernelGGL(abwd_delta_bf16_kernel<8>, dim3((unsigned)((rows + 31) / 32)), dim3(256), 0, st,
-                               (const uint16_t*)o, (const uint16_t*)dO, rows, delta, lse, lse2);
-        else
+        if (!mfma)
             hipLaunchKernelGGL(abwd_delta_kernel<uint16_t>, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st,
                                (const uint16_t*)o, (const uint16_t*)dO, rows, c.d, delta);
         if (mfma) {
@@ -1051,18 +1095,27 @@ int launch_attn_bwd(const sparsek_cfg& c, const void* q, const void* k, const vo
             int32_t* eslot = (int32_t*)(base + W.eslot);
             float* sk32 = (float*)(base + W.sk32);
             float* sv32 = (float*)(base + W.sv32);
-            hipLaunchKernelGGL(abwd_elist_kernel, dim3(c.B * c.Gu), dim3(1024), 0, st, death, c.n, q_begin, elist, ecount,
-                               eslot);
+            DqAux aux{c.B * c.Gu, 0, q_begin, elist, ecount, eslot, nullptr, 0};
+            RangesArgs ranges{};
+            // (the score gradient's ranges take at most nb + 1 more rows of the dK/dV kernel's grid)
+            const bool share = shared && 3 * nb + 1 <= 65535;
+            if (prep && prep->zero && share) {
+                aux.zero = prep->zero;
+                aux.zero_words = prep->zero_words;
+                aux.zero_blocks = (int)((prep->zero_words + ZERO_PER_BLOCK - 1) / ZERO_PER_BLOCK);
+                ranges = prep->ranges;
+            }
+            if (share) *shared = BwdShared{lists, counts, delta};
             if (c.d == 64) {
-                launch_dq_mfma<64>(c, q, k, v, u, tau, death, x, counts, lse, dO, delta, dq, nb, st, q_begin, first_valid,
-                                   q_rows);
+                launch_dq_mfma<64>(c, q, k, v, u, tau, death, x, counts, lse, o, dO, delta, lse2, dq, nb, st, q_begin,
+                                   first_valid, q_rows, aux);
                 launch_dkv_mfma<64>(c, q, k, v, u, tau, death, elist, ecount, lse2, dO, delta, dk32, dv32, sk32, sv32, eslot,
-                                    dk, dv, nb, st, q_begin, q_rows);
+                                    dk, dv, nb, st, q_begin, q_rows, ranges);
             } else {
-                launch_dq_mfma<128>(c, q, k, v, u, tau, death, x, counts, lse, dO, delta, dq, nb, st, q_begin, first_valid,
-                                    q_rows);
+                launch_dq_mfma<128>(c, q, k, v, u, tau, death, x, counts, lse, o, dO, delta, lse2, dq, nb, st, q_begin,
+                                    first_valid, q_rows, aux);
                 launch_dkv_mfma<128>(c, q, k, v, u, tau, death, elist, ecount, lse2, dO, delta, dk32, dv32, sk32, sv32, eslot,
-                                     dk, dv, nb, st, q_begin, q_rows);
+                                     dk, dv, nb, st, q_begin, q_rows, ranges);
             }
             const int d4 = c.d / 4;
             const int gx = (int)std::min<size_t>(((size_t)c.n * d4 + 255) / 256, 1024);
@@ -1078,6 +1131,21 @@ int launch_attn_bwd(const sparsek_cfg& c, const void* q, const void* k, const vo
         }
     }
     return launch_status();
+}
+
+int launch_bwd(const sparsek_cfg& cfg, const void* q, const void* k, const void* v, const float* u, const float* tau,
+               const int32_t* death, const void* o, const float* lse, const void* dO, void* dq, void* dk, void* dv, float* du,
+               void* attn_ws, void* mask_ws, hipStream_t st, int q_begin, const int32_t* first_valid, int q_rows, int t_min)
+{
+    sparsek_cfg c = cfg;
+    if (c.gate_mode == 3) c.gate_mode = 2;  // the straight-through forward has no gates on q, k, v
+    const MaskBwdPrep prep = mask_bwd_prep(cfg, u, tau, mask_ws, t_min, first_valid);
+    BwdShared shared{nullptr, nullptr, nullptr};
+    const int rc = launch_attn_bwd(c, q, k, v, u, tau, death, o, lse, dO, dq, dk, dv, attn_ws, st, q_begin, first_valid, q_rows,
+                                   &prep, &shared);
+    if (rc) return rc;
+    return launch_mask_bwd(cfg, q, k, v, u, tau, death, o, lse, dO, du, mask_ws, st, q_begin, q_rows, t_min, first_valid,
+                           shared.delta ? &shared : nullptr);
 }
 
 }  // namespace spk

@@ -371,14 +371,11 @@ int launch_chunk_bwd(const sparsek_chunk_cfg& c, int clen, const void* q, const 
     const float* lse = (const float*)(w + W.lse);
     const void* k_v = w + W.k;
     const void* v_v = w + W.v;
-    sparsek_cfg cv = virtual_cfg(c, nv);  // hard gates for gate_mode 3: what the forward computed
-    int rc = launch_attn_bwd(cv, q, k_v, v_v, u_v, tau_v, death_v, o, lse, dO, dq, dk, dv, b + Bw.attn, st, L.rcap,
-                             first_valid, clen);
-    if (rc) return rc;
-    cv.gate_mode = c.gate_mode;  // the straight-through mode has its own score gradient
+    sparsek_cfg cv = virtual_cfg(c, nv);
+    cv.gate_mode = c.gate_mode;  // (the straight-through mode has its own score gradient)
     float* du_v = (float*)(b + Bw.du);
-    rc = launch_mask_bwd(cv, q, k_v, v_v, u_v, tau_v, death_v, o, lse, dO, du_v, b + Bw.mask, st, L.rcap, clen,
-                         std::max(0, L.rcap - c.w - 1), first_valid);
+    const int rc = launch_bwd(cv, q, k_v, v_v, u_v, tau_v, death_v, o, lse, dO, dq, dk, dv, du_v, b + Bw.attn, b + Bw.mask, st,
+                              L.rcap, first_valid, clen, std::max(0, L.rcap - c.w - 1));
     if (rc) return rc;
     hipLaunchKernelGGL(chunk_slice_du_kernel, dim3((clen + 255) / 256, rows), dim3(256), 0, st, du_v, nv, L.rcap, clen, du);
     return launch_status();

@@ -29,20 +29,37 @@ int launch_attn_fwd(const sparsek_cfg& c, const void* q, const void* k, const vo
 // (query blocks that end at or before q_begin are skipped; keys before first_valid[row] are never attended;
 //  q_rows != 0: q, o and lse hold q_rows rows per head, the first being query q_begin, a multiple of 128)
 size_t attn_fwd_ws_bytes(const sparsek_cfg& c);
+// What a backward of both kinds shares.  launch_attn_bwd builds the per-block lists and dO.o of every query (bf16, d = 64
+// or 128); given `prep` it also clears and fills what launch_mask_bwd starts from, in launches it makes anyway.
+struct BwdShared {
+    const int32_t *lists, *counts;
+    const float* delta;
+};
+struct MaskBwdPrep;
 int launch_mask_bwd(const sparsek_cfg& c, const void* q, const void* k, const void* v,
                     const float* u, const float* tau, const int32_t* death, const void* o,
                     const float* lse, const void* dO, float* du, void* ws, hipStream_t st, int q_begin = 0,
-                    int q_rows = 0, int t_min = 0, const int32_t* first_valid = nullptr);
+                    int q_rows = 0, int t_min = 0, const int32_t* first_valid = nullptr,
+                    const BwdShared* shared = nullptr);
 // (q_begin, q_rows as in launch_attn_fwd, for q, o, dO and lse; thresholds of prefixes before t_min are not read, row r
 //  starts at position first_valid[r]; bf16 with d = 64 or 128 only when any of them is set)
 size_t mask_bwd_ws_bytes(const sparsek_cfg& c);
 int launch_attn_bwd(const sparsek_cfg& c, const void* q, const void* k, const void* v, const float* u,
                     const float* tau, const int32_t* death, const void* o, const float* lse, const void* dO,
                     void* dq, void* dk, void* dv, void* ws, hipStream_t st, int q_begin = 0,
-                    const int32_t* first_valid = nullptr, int q_rows = 0);
+                    const int32_t* first_valid = nullptr, int q_rows = 0, const MaskBwdPrep* prep = nullptr,
+                    BwdShared* shared = nullptr);
+// (shared->delta stays null where the caller's launch_mask_bwd has to do its own preparation)
 // (q_rows != 0: q, o, dO, lse, dq and also dk, dv hold q_rows rows per head, the first being position q_begin: only
 //  keys from q_begin on receive a gradient; keys before first_valid[row] are attended by nobody; bf16, d = 64 / 128)
 size_t attn_bwd_ws_bytes(const sparsek_cfg& c);
+
+// Both of them, sharing what they can (workspaces of attn_bwd_ws_bytes and mask_bwd_ws_bytes; gate_mode as the caller's:
+// the attention part of mode 3 is that of mode 2).
+int launch_bwd(const sparsek_cfg& c, const void* q, const void* k, const void* v, const float* u, const float* tau,
+               const int32_t* death, const void* o, const float* lse, const void* dO, void* dq, void* dk, void* dv, float* du,
+               void* attn_ws, void* mask_ws, hipStream_t st, int q_begin = 0, const int32_t* first_valid = nullptr,
+               int q_rows = 0, int t_min = 0);
 
 inline int launch_status()
 {

@@ -16,6 +16,7 @@
 // soft mask.
 #include "common.hpp"
 #include "attn_tiles.hpp"
+#include "mask_ranges.hpp"
 
 namespace spk {
 
@@ -347,7 +348,7 @@ __global__ __launch_bounds__(256, 2) void mask_bwd_mfma_kernel(
     const int32_t* __restrict__ lists, const int32_t* __restrict__ counts, const uint16_t* __restrict__ o,
     const float* __restrict__ lse, const uint16_t* __restrict__ dO, float* __restrict__ A, float* __restrict__ C,
     int H, int Gu, int n, int k, int w, float scale, int nb, int BH, int q_begin, int q_rows,
-    const int32_t* __restrict__ first_valid)
+    const int32_t* __restrict__ first_valid, const float* __restrict__ delta /* dO.o of every query, or null */)
 {
     static_assert(RAW <= SEG, "survivors of one segment must fit the staged metadata");
     __shared__ __align__(16) MfmaSmem<D, 16> sm;
@@ -436,7 +437,7 @@ __global__ __launch_bounds__(256, 2) void mask_bwd_mfma_kernel(
         const size_t off = (qo + qrow) * D + 16 * s + 8 * half;
         qreg[s] = *(const bf16x8*)(q + off);
         dreg[s] = *(const bf16x8*)(dO + off);
-        oreg[s] = *(const bf16x8*)(o + off);
+        if (!delta) oreg[s] = *(const bf16x8*)(o + off);
     }
     __builtin_amdgcn_sched_barrier(0);
     const float tau1_up = __double2float_ru((double)tau_q + 1.0);
@@ -445,8 +446,8 @@ __global__ __launch_bounds__(256, 2) void mask_bwd_mfma_kernel(
         const float hi = wave_max_f32(qlive ? tau_q : -INFINITY);
         if (lane == 0) { tred[0][wv] = lo; tred[1][wv] = hi; }
     }
-    float Di = 0.0f;       // dO_i . o_i, formed when the rows have arrived (first segment with tiles)
-    bool have_di = false;
+    float Di = delta ? delta[qo + qrow] : 0.0f;   // dO_i . o_i, else formed when the rows have arrived (first segment with tiles)
+    bool have_di = delta != nullptr;
     float rowsum = 0.0f;
     BwdCarry cy;
     if (tid < 3 * KT) colsum[tid / KT][tid % KT] = 0.0f;
@@ -568,7 +569,7 @@ template <int D>
 static void launch_bwd_mfma(const sparsek_cfg& c, const void* q, const void* k, const void* v, const float* u,
                             const float* tau, const int32_t* death, const int32_t* lists, const int32_t* counts,
                             const void* o, const float* lse, const void* dO, float* A, float* C, int nb,
-                            hipStream_t st, int q_begin, int q_rows, const int32_t* first_valid)
+                            hipStream_t st, int q_begin, int q_rows, const int32_t* first_valid, const float* delta)
 {
     const int BH = c.B * c.H;
     dim3 grid(nb * BH);
@@ -576,80 +577,17 @@ static void launch_bwd_mfma(const sparsek_cfg& c, const void* q, const void* k, 
     hipLaunchKernelGGL((mask_bwd_mfma_kernel<D, MODE>), grid, dim3(256), 0, st, (const uint16_t*)q,           \
                        (const uint16_t*)k, (const uint16_t*)v, u, tau, death, lists, counts, (const uint16_t*)o, \
                        lse, (const uint16_t*)dO, A, C, c.H, c.Gu, c.n, c.k, c.w, c.softmax_scale, nb, BH, q_begin, q_rows, \
-                       first_valid)
+                       first_valid, delta)
     if (c.gate_mode == 0) SPK_LAUNCH_B(0);
     else if (c.gate_mode == 3) SPK_LAUNCH_B(3);
     else SPK_LAUNCH_B(1);
 #undef SPK_LAUNCH_B
 }
 
-// ---------------------------------------------------------------------------------
-// Epilogue 1: per key j the range [a_j, b_j] of prefixes T with j in S*_T; difference array
-// of |S*_T|.  tau is non-decreasing for T >= k-1, so both ends come from binary searches:
-//   b_j = last  T in [max(j,k), n-1] with tau_T < u_j
-//   a_j = first T in [max(j,k), n-1] with u_j < tau_T + 1      (compared in fp64, exact)
-// A workgroup holds every stride-th threshold of its row in LDS (all of them up to n = 8192);
-// a search runs on those samples first and finishes in global memory inside one stride.
-// ---------------------------------------------------------------------------------
-constexpr int RS_MAX = 8192;  // sampled thresholds per row held in LDS
-
-// first T in [lo, n) with pred(tau_T), n if none; pred is monotone (false ... false true ... true)
-template <typename Pred>
-__device__ __forceinline__ int first_true(const float* __restrict__ tr, const float* ts, int lo, int n, int stride,
-                                          int ns, Pred pred)
-{
-    const int ifirst = (lo + stride - 1) / stride;  // samples sit at T = i * stride
-    int x = ifirst, y = ns;
-    while (x < y) {
-        const int m = (x + y) >> 1;
-        if (pred(ts[m])) y = m;
-        else x = m + 1;
-    }
-    int t0 = (x == ifirst) ? lo : (x - 1) * stride + 1;  // samples before x are false
-    int t1 = (x < ns) ? x * stride : n;                  // sample x is true
-    while (t0 < t1) {
-        const int m = (t0 + t1) >> 1;
-        if (pred(tr[m])) t1 = m;
-        else t0 = m + 1;
-    }
-    return t0;
-}
-
-__global__ __launch_bounds__(1024) void mask_bwd_ranges_kernel(const float* __restrict__ u,
-                                                                const float* __restrict__ tau, int n, int k_, int t_min,
-                                                                const int32_t* __restrict__ first_valid,
-                                                                int32_t* __restrict__ diff, int2* __restrict__ ab)
+__global__ __launch_bounds__(1024) void mask_bwd_ranges_kernel(RangesArgs a)
 {
     __shared__ float ts[RS_MAX];
-    const int row = blockIdx.y;
-    // the first prefix that counts: more than k entries, and its threshold is there
-    const int k = max(k_ + (first_valid ? first_valid[row] : 0), t_min);
-    const float* tr = tau + (size_t)row * n;
-    const int stride = (n + RS_MAX - 1) / RS_MAX;
-    const int ns = (n + stride - 1) / stride;
-    for (int i = threadIdx.x; i < ns; i += blockDim.x) ts[i] = tr[(size_t)i * stride];
-    __syncthreads();
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    int a = 1, b = 0;
-    if (j < n) {
-        const float uj = u[(size_t)row * n + j];
-        const int lo = max(j, k);  // shorter prefixes have every gate at 1: S* empty
-        if (lo <= n - 1) {
-            b = first_true(tr, ts, lo, n, stride, ns, [&](float t) { return !(t < uj); }) - 1;
-            a = first_true(tr, ts, lo, n, stride, ns, [&](float t) { return (double)uj < (double)t + 1.0; });
-        }
-        ab[(size_t)row * n + j] = make_int2(a, b);
-    }
-    // difference array: +1 at a_j, -1 at b_j + 1.  Two addresses collect most of the updates and
-    // would serialise them: every key j <= k that is fractional from the start has a_j = k (one
-    // add per wave instead), and every key still fractional at the end has b_j + 1 = n, an entry
-    // the prefix sum never reads (dropped).
-    const bool any = a <= b;
-    int32_t* dr = diff + (size_t)row * (n + 1);
-    const unsigned long long at_k = __ballot(any && a == k);
-    if (any && a != k) atomicAdd(dr + a, 1);
-    if (at_k != 0 && (threadIdx.x & 63) == 0) atomicAdd(dr + k, (int)__popcll(at_k));
-    if (any && b + 1 < n) atomicAdd(dr + b + 1, -1);
+    mask_bwd_ranges(a, ts, blockIdx.x, blockIdx.y);
 }
 
 // Exclusive prefix sum of one value per thread over the 1024 threads of a workgroup; `total`
@@ -760,9 +698,26 @@ __global__ __launch_bounds__(1024) void mask_bwd_scan_final_kernel(const float* 
     }
 }
 
+// no soft gate anywhere: the gradient is identically zero
+static bool mask_bwd_is_zero(const sparsek_cfg& c) { return c.gate_mode == 2 || c.k <= 0 || c.n <= c.w; }
+
+MaskBwdPrep mask_bwd_prep(const sparsek_cfg& c, const float* u, const float* tau, void* ws, int t_min,
+                          const int32_t* first_valid)
+{
+    const BwdWs W = bwd_ws(c);
+    char* base = (char*)ws;
+    MaskBwdPrep P{};
+    if (mask_bwd_is_zero(c)) return P;
+    P.zero = (uint32_t*)(base + W.A);
+    P.zero_words = (W.G - W.A) / 4;
+    // t_min: thresholds of earlier prefixes are not available (and no query uses them)
+    P.ranges = RangesArgs{u, tau, c.n, c.k, t_min, first_valid, (int32_t*)(base + W.diff), (int2*)(base + W.ab)};
+    return P;
+}
+
 int launch_mask_bwd(const sparsek_cfg& c, const void* q, const void* k, const void* v, const float* u,
                     const float* tau, const int32_t* death, const void* o, const float* lse, const void* dO,
-                    float* du, void* ws, hipStream_t st, int q_begin, int q_rows, int t_min, const int32_t* first_valid)
+                    float* du, void* ws, hipStream_t st, int q_begin, int q_rows, int t_min, const int32_t* first_valid, const BwdShared* sh)
 {
     const BwdWs W = bwd_ws(c);
     char* base = (char*)ws;
@@ -775,25 +730,28 @@ int launch_mask_bwd(const sparsek_cfg& c, const void* q, const void* k, const vo
     int32_t* diff = (int32_t*)(base + W.diff);
     double* G = (double*)(base + W.G);
     int2* ab = (int2*)(base + W.ab);
-    if (c.gate_mode == 2 || c.k <= 0 || c.n <= c.w) {
-        // no soft gate anywhere: the gradient is identically zero
+    if (mask_bwd_is_zero(c)) {
         hipLaunchKernelGGL(zero_kernel, dim3(512), dim3(256), 0, st, (uint32_t*)du, (size_t)rows * c.n);
         return launch_status();
     }
-    // A, C, diff are contiguous: clear them with one fill kernel (safe under graph capture)
-    hipLaunchKernelGGL(zero_kernel, dim3(512), dim3(256), 0, st, (uint32_t*)(base + W.A), (W.G - W.A) / 4);
-    // t_min: thresholds of earlier prefixes are not available (and no query uses them)
-    hipLaunchKernelGGL(mask_bwd_ranges_kernel, dim3((c.n + 1023) / 1024, rows), dim3(1024), 0, st, u, tau, c.n,
-                       c.k, t_min, first_valid, diff, ab);
-    launch_block_lists(c, death, lists, counts, st);
+    if (sh) {   // launch_attn_bwd has built the lists, cleared A, C and diff and written the ranges
+        lists = const_cast<int32_t*>(sh->lists);
+        counts = const_cast<int32_t*>(sh->counts);
+    } else {
+        // A, C, diff are contiguous: clear them with one fill kernel (safe under graph capture)
+        const MaskBwdPrep P = mask_bwd_prep(c, u, tau, ws, t_min, first_valid);
+        hipLaunchKernelGGL(zero_kernel, dim3(512), dim3(256), 0, st, P.zero, P.zero_words);
+        hipLaunchKernelGGL(mask_bwd_ranges_kernel, dim3((c.n + 1023) / 1024, rows), dim3(1024), 0, st, P.ranges);
+        launch_block_lists(c, death, lists, counts, st);
+    }
     dim3 grid(nb, c.B * c.H);
     if (c.dtype == SPARSEK_BF16 && (c.d == 64 || c.d == 128) && (uint64_t)c.n * c.d * 2 <= 0xFFFFFFFFull) {
         if (c.d == 64)
             launch_bwd_mfma<64>(c, q, k, v, u, tau, death, lists, counts, o, lse, dO, A, C, nb, st, q_begin, q_rows,
-                                first_valid);
+                                first_valid, sh ? sh->delta : nullptr);
         else
             launch_bwd_mfma<128>(c, q, k, v, u, tau, death, lists, counts, o, lse, dO, A, C, nb, st, q_begin, q_rows,
-                                first_valid);
+                                first_valid, sh ? sh->delta : nullptr);
     } else if (q_begin != 0 || q_rows != 0 || t_min != 0 || first_valid)
         return SPARSEK_ERR_UNSUPPORTED;  // the offset-query form exists on the MFMA path only
     else if (c.dtype == SPARSEK_F32)
