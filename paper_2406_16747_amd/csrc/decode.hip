@@ -751,6 +751,7 @@ __device__ void decode_attend(AttnSmem<LPR>& sm, const sparsek_decode_cfg& c, co
                     x = __hip_atomic_load(&part[(size_t)s * (D + 2) + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     if ((unsigned)(x >> 32) == tag) break;
                 }
+                if ((unsigned)(x >> 32) != tag) atomicOr((int*)(st + L.status) + row, 4);
                 return __uint_as_float((unsigned)x);
             };
             for (int s = tid; s < 2 * L.nsplit; s += NT_ROW) sm.w[s] = get(s >> 1, D + (s & 1));
@@ -819,6 +820,12 @@ __global__ __launch_bounds__(256) void decode_zero_slots_kernel(sparsek_decode_c
     for (size_t x = threadIdx.x + (size_t)blockIdx.y * 256; x < nchunk; x += (size_t)gridDim.y * 256) {
         kd[x] = make_uint4(0, 0, 0, 0);
         vd[x] = make_uint4(0, 0, 0, 0);
+    }
+    // The step numbers beside the partial results start again at 1: what an earlier generation (or another use of the
+    // memory) left there must not pass for a result of the step of the same number.
+    if (L.nsplit > 1) {
+        unsigned long long* part = (unsigned long long*)(st + L.part) + (size_t)bh * L.nsplit * (c.d + 2);
+        for (int x = threadIdx.x + blockIdx.y * 256; x < L.nsplit * (c.d + 2); x += gridDim.y * 256) part[x] = 0ull;
     }
 }
 

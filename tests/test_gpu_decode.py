@@ -109,6 +109,33 @@ def test_decode_shares_and_slabs(oracle, B, H, Gu, d, k, w, n_ctx, steps, dtype,
     assert not flags.any()
 
 
+def test_decode_state_used_again(oracle):
+    """A state that is set up again counts its steps from the start: partial results left in its memory with the step
+    numbers of an earlier generation must not pass for those of the new one."""
+    require_gpu()
+    say("decode state used again")
+    B, H, d, k, w, n_ctx = 1, 2, 128, 600, 500, 1200   # heads in several shares
+    rng = np.random.default_rng(5)
+    states, outs = [spk.DecodeState(B, H, 1, d, k, w, torch.bfloat16) for _ in range(2)], [[], []]
+    states[0].buf.fill_(255)
+    states[1].buf[: states[1].buf.numel() // 8 * 8].view(torch.int64).fill_(1 << 32)   # zeros of "step 1" everywhere
+    for gen in range(3):
+        hist = history(rng, B, H, 1, n_ctx + 1, d, "bf16")
+        Q, K, V = (dev(hist[x], True) for x in ("Q", "K", "V"))
+        u = dev(hist["u"])
+        u_ctx = u[:, :, :n_ctx].contiguous()
+        tau, death = spk.sparsek_mask(u_ctx, k)
+        for st, out in zip(states, outs):
+            if gen == 1 and st is states[0]:   # as new
+                st.buf.fill_(255)
+            spk.sparsek_decode_load(st, K[:, :, :n_ctx].contiguous(), V[:, :, :n_ctx].contiguous(), u_ctx, tau, death)
+            assert not st.buf[-1024:-256].any().item()   # (the partial results are the last part of a state)
+            out.append(host(spk.sparsek_decode_step(st, *(x[:, :, n_ctx].contiguous() for x in (Q, K, V, u)))))
+            assert not spk.sparsek_decode_status(st).any()
+    for a, b in zip(*outs):
+        np.testing.assert_array_equal(a, b)
+
+
 def test_decode_step_equals_prefill_row_on_gpu(oracle):
     """Sec. 3.4: recurrent evaluation gives the same result as the one-shot one."""
     require_gpu()
