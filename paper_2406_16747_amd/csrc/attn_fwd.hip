@@ -219,13 +219,16 @@ __global__ __launch_bounds__(64 * BL_WAVES, RUNS ? 8 : 4) void block_lists_kerne
 constexpr int GQ = 16;                 // queries per workgroup
 constexpr int GEN_SPLIT = QB / GQ;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+// As wide as the head dimension's multiple of 4 allows, but tensors of this kernel need no more than element alignment.
+typedef float f32x4_any __attribute__((__vector_size__(16), __aligned__(4)));
+typedef uint32_t u32x2_any __attribute__((__vector_size__(8), __aligned__(2)));
 
-__device__ __forceinline__ f32x4 load4(const float* p) { return *(const f32x4*)p; }
+__device__ __forceinline__ f32x4 load4(const float* p) { return *(const f32x4_any*)p; }
 __device__ __forceinline__ f32x4 load4(const uint16_t* p)
 {
-    const uint2 r = *(const uint2*)p;
-    return f32x4{__uint_as_float(r.x << 16), __uint_as_float(r.x & 0xFFFF0000u), __uint_as_float(r.y << 16),
-                 __uint_as_float(r.y & 0xFFFF0000u)};
+    const u32x2_any r = *(const u32x2_any*)p;
+    return f32x4{__uint_as_float(r[0] << 16), __uint_as_float(r[0] & 0xFFFF0000u), __uint_as_float(r[1] << 16),
+                 __uint_as_float(r[1] & 0xFFFF0000u)};
 }
 __device__ __forceinline__ float load1(const float* p) { return *p; }
 __device__ __forceinline__ float load1(const uint16_t* p) { return bf16_to_f32(*p); }
@@ -290,13 +293,17 @@ __global__ __launch_bounds__(256) void attn_fwd_generic_kernel(
         }
         float vf[4][DT], uj[4];
         int dj[4];
+        unsigned vtop = 0;   // largest magnitude among the values, as bits
 #pragma unroll
         for (int r = 0; r < 4; r++) {
             const int j = max(jp[r], 0);
             uj[r] = ur[j];
             dj[r] = dr[j];
 #pragma unroll
-            for (int x = 0; x < DT; x++) vf[r][x] = 16 * x + col < d ? load1(vh + (size_t)j * d + 16 * x + col) : 0.0f;
+            for (int x = 0; x < DT; x++) {
+                vf[r][x] = 16 * x + col < d ? load1(vh + (size_t)j * d + 16 * x + col) : 0.0f;
+                vtop = max(vtop, __float_as_uint(vf[r][x]) & 0x7FFFFFFFu);
+            }
         }
         const int jc[4] = {jp[0], jp[1], jp[2], jp[3]};
         jk = pos(e0 + 64 + col);
@@ -308,12 +315,14 @@ __global__ __launch_bounds__(256) void attn_fwd_generic_kernel(
 #pragma unroll
             for (int e = 0; e < 4; e++) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[x][e], qf[x][e], s, 0, 0, 0);
         float s2[4], g[4], mx = -INFINITY;
+        int ok = 0;
 #pragma unroll
         for (int r = 0; r < 4; r++) {
             const int j = jc[r];
             const bool win = i - j < w;
             // a window key (not in the future), or selected for prefix i - w
             const bool valid = j >= 0 && j <= i && (win || dj[r] > Tp);
+            ok |= valid ? 1 << r : 0;
             g[r] = win ? 1.0f : clip01(uj[r] - tauT);
             s2[r] = valid ? s[r] * (gate_mode == 0 ? g[r] : 1.0f) * c2 : -INFINITY;
             mx = fmaxf(mx, s2[r]);
@@ -333,11 +342,30 @@ __global__ __launch_bounds__(256) void attn_fwd_generic_kernel(
             if (gate_mode != 2) p[r] *= g[r];
         }
 #pragma unroll
-        for (int x = 0; x < DT; x++) {
-            acc[x] *= corr;
+        for (int x = 0; x < DT; x++) acc[x] *= corr;
+        if (__any(vtop >= 0x7F800000u)) {
+            // An infinity or NaN among the values reaches the queries that attend its key and no other: no zero weights.
+#pragma unroll
+            for (int r = 0; r < 4; r++)
+#pragma unroll 1
+                for (int y = 0; y < 4; y++) {
+                    const float py = __shfl(p[r], 16 * y + col, 64);
+                    const bool oy = __shfl(ok, 16 * y + col, 64) >> r & 1;
+                    const T* vr = vh + (size_t)max(__shfl(jc[r], 16 * y, 64), 0) * d;
+#pragma unroll
+                    for (int x = 0; x < DT; x++)
+#pragma unroll
+                        for (int e = 0; e < 4; e++) {
+                            const int dd = 16 * x + 4 * grp + e;
+                            if (oy && dd < d) acc[x][e] += py * load1(vr + dd);
+                        }
+                }
+            continue;
+        }
+#pragma unroll
+        for (int x = 0; x < DT; x++)
 #pragma unroll
             for (int r = 0; r < 4; r++) acc[x] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][x], p[r], acc[x], 0, 0, 0);
-        }
     }
     // ---- merge the waves: O^T rows 16 x + 4 grp + e, column col ----
     l_run += __shfl_xor(l_run, 16, 64);

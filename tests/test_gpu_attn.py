@@ -84,6 +84,44 @@ def test_small_shapes(oracle, n, d, k, w, Gu, dtype, gate_mode):
     run_case(oracle, inp, gate_mode, qk_boost=8.0)
 
 
+@pytest.mark.parametrize("dtype,d", [("fp32", 64), ("fp32", 100), ("bf16", 36)])
+def test_generic_kernel_alignment_and_nonfinite_values(oracle, dtype, d):
+    """Tensors that start at any element, and values that are not finite: those reach the queries that attend their key
+    and nobody else."""
+    require_gpu()
+    say("attn generic", dtype, d)
+    bf16, n, k, w = dtype == "bf16", 300, 20, 33
+    inp = synth.make(1, Gu=1, seed=d, B=1, H=2, n=n, d=d, k=k, w=w, dtype=dtype, qk_div=float(np.sqrt(d)))
+    u = dev(inp["u"])
+    tau, death = spk.sparsek_mask(u, k)
+    q, kk, v = (dev(inp[x], bf16) for x in ("Q", "K", "V"))
+    want = spk.sparsek_attn_fwd(q, kk, v, u, tau, death, k, w, 0, inp["scale"])
+
+    def shifted(t):
+        buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+        out = buf[1:].view(t.shape)
+        out.copy_(t)
+        return out
+
+    got = spk.sparsek_attn_fwd(shifted(q), shifted(kk), shifted(v), u, tau, death, k, w, 0, inp["scale"])
+    for a, b in zip(want, got):
+        np.testing.assert_array_equal(host(a), host(b))
+    bad = v.clone()
+    bad[:, :, 150, 3] = float("nan")
+    bad[:, :, 201, :] = float("inf")
+    o, lse = spk.sparsek_attn_fwd(q, kk, bad, u, tau, death, k, w, 0, inp["scale"])
+    np.testing.assert_array_equal(host(lse), host(want[1]))
+    i = np.arange(n)
+    clean = np.ones(n, bool)
+    for j in (150, 201):
+        clean &= ~((i >= j) & (i <= w - 1 + host(death)[0, 0, j]))
+    assert clean[:150].all() and not clean[150] and not clean[201]
+    # the tiles that hold such a key add up in another order: a few units of the sums' last place
+    np.testing.assert_allclose(host(o)[:, :, clean], host(want[0])[:, :, clean], atol=1e-2 if bf16 else 1e-5)
+    other = np.arange(d) != 3   # (query 201 may still attend key 150)
+    assert np.isnan(host(o)[:, :, 150, 3]).all() and np.isinf(host(o)[:, :, 201][..., other]).all()
+
+
 def test_config2_shape_reduced_batch(oracle):
     """Config 2 recipe (scores from a linear scorer on a hidden state) at B=1, 3 heads."""
     require_gpu()
