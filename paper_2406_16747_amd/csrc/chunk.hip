@@ -110,35 +110,14 @@ __global__ __launch_bounds__(1024) void chunk_assemble_scores_kernel(const int32
                                                                    : u_chunk[(size_t)row * clen + (e - rcap)];
 }
 
-// K and V rows of the virtual sequence of one head (16 bytes per thread and step).  Padding rows
-// are zero.  (Q and O stay in the caller's chunk tensors: the attention kernel addresses them from
-// its first query.)
-__global__ __launch_bounds__(256) void chunk_assemble_rows_kernel(
-    const int32_t* __restrict__ count, const uint4* __restrict__ ret_k, const uint4* __restrict__ ret_v,
-    const uint4* __restrict__ k_c, const uint4* __restrict__ v_c, int H, int Gu, int rcap, int clen,
-    int row16 /* 16-byte units per row */, uint4* __restrict__ k_v, uint4* __restrict__ v_v)
+// K and V rows of the virtual sequence: moved by workgroups of the mask's launch.  (Q and O stay in the caller's chunk
+// tensors: the attention kernel addresses them from its first query.)
+static RowCopy chunk_rows(const sparsek_chunk_cfg& c, const ChunkLayout& L, char* state, const void* k, const void* v,
+                          int clen, char* kd, char* vd)
 {
-    const int bh = blockIdx.y;
-    const int b = bh / H, h = bh % H;
-    const int row = b * Gu + (Gu == 1 ? 0 : h);
-    const int pad = rcap - count[row], nv = rcap + clen;
-    const size_t total = (size_t)nv * row16;
-    for (size_t x = (size_t)blockIdx.x * 256 + threadIdx.x; x < total; x += (size_t)gridDim.x * 256) {
-        const int e = (int)(x / row16), c16 = (int)(x % row16);
-        const size_t dst = ((size_t)bh * nv + e) * row16 + c16;
-        uint4 kk = make_uint4(0, 0, 0, 0), vv = kk;
-        if (e >= rcap) {
-            const size_t src = ((size_t)bh * clen + (e - rcap)) * row16 + c16;
-            kk = k_c[src];
-            vv = v_c[src];
-        } else if (e >= pad) {
-            const size_t src = ((size_t)bh * rcap + (e - pad)) * row16 + c16;
-            kk = ret_k[src];
-            vv = ret_v[src];
-        }
-        k_v[dst] = kk;
-        v_v[dst] = vv;
-    }
+    return RowCopy{(const int32_t*)(state + L.count), (const uint4*)(state + L.ret_k), (const uint4*)(state + L.ret_v),
+                   (const uint4*)k, (const uint4*)v, (uint4*)kd, (uint4*)vd, c.Gu == 1 ? c.H : 1, L.rcap, clen, c.w,
+                   (int)(c.d * esize(c.dtype) / 16), 0};
 }
 
 // Padding entries are never selected: death[e] = e.  The same holds for retained keys that were
@@ -304,11 +283,9 @@ int launch_chunk_prefill(const sparsek_chunk_cfg& c, void* state, int clen, cons
 
     hipLaunchKernelGGL(chunk_assemble_scores_kernel, dim3((nv + 1023) / 1024, rows), dim3(1024), 0, st, count, ret_u, u, L.rcap, clen, u_v,
                        first_valid);
-    const int gx = (int)std::min<size_t>(((size_t)nv * row16 + 255) / 256, 2048);
-    hipLaunchKernelGGL(chunk_assemble_rows_kernel, dim3(gx, BH), dim3(256), 0, st, count, ret_k, ret_v, (const uint4*)k,
-                       (const uint4*)v, c.H, c.Gu, L.rcap, clen, row16, k_v, v_v);
+    const RowCopy copy = chunk_rows(c, L, s, k, v, clen, w + W.k, w + W.v);
     // thresholds are needed from prefix R_cap - w - 1 on (the last one the previous call used)
-    int rc = launch_mask(cv, u_v, tau_v, death_v, w + W.mask, st, std::max(0, L.rcap - c.w - 1), first_valid);
+    int rc = launch_mask(cv, u_v, tau_v, death_v, w + W.mask, st, std::max(0, L.rcap - c.w - 1), first_valid, &copy);
     if (rc) return rc;
     hipLaunchKernelGGL(chunk_clear_padding_kernel, dim3((L.rcap + 255) / 256, rows), dim3(256), 0, st, count,
                        (const int32_t*)(s + L.ret_sel), L.rcap, nv, death_v);
@@ -393,9 +370,8 @@ int launch_chunk_to_decode(const sparsek_chunk_cfg& c, void* state, void* ws, co
 {
     const ChunkLayout L = chunk_layout(c);
     const ChunkWs W = chunk_ws(c, 0);
-    const int rows = c.B * c.Gu, BH = c.B * c.H;
+    const int rows = c.B * c.Gu;
     const int nv = L.rcap;
-    const int row16 = (int)(c.d * esize(c.dtype) / 16);
     char* s = (char*)state;
     char* w = (char*)ws;
     int32_t* count = (int32_t*)(s + L.count);
@@ -407,11 +383,8 @@ int launch_chunk_to_decode(const sparsek_chunk_cfg& c, void* state, void* ws, co
     const sparsek_cfg cv = virtual_cfg(c, nv);
     hipLaunchKernelGGL(chunk_assemble_scores_kernel, dim3((nv + 1023) / 1024, rows), dim3(1024), 0, st, count, (const float*)(s + L.ret_u),
                        (const float*)nullptr, L.rcap, 0, u_v, (int32_t*)(w + W.first));
-    const int gx = (int)std::min<size_t>(((size_t)nv * row16 + 255) / 256, 2048);
-    hipLaunchKernelGGL(chunk_assemble_rows_kernel, dim3(gx, BH), dim3(256), 0, st, count, (const uint4*)(s + L.ret_k),
-                       (const uint4*)(s + L.ret_v), (const uint4*)nullptr, (const uint4*)nullptr, c.H, c.Gu, L.rcap, 0,
-                       row16, k_v, v_v);
-    int rc = launch_mask(cv, u_v, tau_v, death_v, w + W.mask, st, std::max(0, L.rcap - c.w - 1), (const int32_t*)(w + W.first));
+    const RowCopy copy = chunk_rows(c, L, s, nullptr, nullptr, 0, w + W.k, w + W.v);
+    int rc = launch_mask(cv, u_v, tau_v, death_v, w + W.mask, st, std::max(0, L.rcap - c.w - 1), (const int32_t*)(w + W.first), &copy);
     if (rc) return rc;
     hipLaunchKernelGGL(chunk_clear_padding_kernel, dim3((L.rcap + 255) / 256, rows), dim3(256), 0, st, count,
                        (const int32_t*)(s + L.ret_sel), L.rcap, nv, death_v);

@@ -14,9 +14,20 @@ namespace spk {
 // Launch wrappers implemented in the .hip files; all return a SPARSEK_* code.
 // t_begin > 0 (chunked prefill): the 128-prefix blocks that end at or before t_begin are skipped; their thresholds and
 // the lifetimes of the keys that die there are not written.  first_valid: row r starts at position first_valid[r] (what
-// lies before does not exist and nothing is written for it).
+// lies before does not exist and nothing is written for it).  rows: K and V rows to put together in the same launch.
+struct RowCopy;
 int launch_mask(const sparsek_cfg& c, const float* u, float* tau, int32_t* death, void* ws,
-                hipStream_t st, int t_begin = 0, const int32_t* first_valid = nullptr);
+                hipStream_t st, int t_begin = 0, const int32_t* first_valid = nullptr, const RowCopy* rows = nullptr);
+// The K and V rows of a virtual sequence [ padding | retained entries | chunk ], in units of 16 bytes: `unit` per row,
+// `heads` consecutive heads per score row.  Rows of padding that a kernel may load (row 0, and the w + 64 before the
+// chunk) are cleared, the others left as they are.
+struct RowCopy {
+    const int32_t* count;   // retained entries of a score row
+    const uint4 *ret_k, *ret_v, *chunk_k, *chunk_v;
+    uint4 *k, *v;
+    int heads, rcap, clen, w, unit;
+    int wgs;                // workgroups per score row (set by launch_mask)
+};
 size_t mask_ws_bytes(const sparsek_cfg& c);
 // copies the status word that the last launch_mask on `ws` left (bit 0: a threshold solve hit its iteration cap) and waits
 int mask_status(const sparsek_cfg& c, const void* ws, int32_t* host_flag, hipStream_t st);

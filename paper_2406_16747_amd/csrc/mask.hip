@@ -1585,14 +1585,62 @@ __device__ void window_only_chunk(float* red, const ChunkJob& J)
 // (76 KB of LDS, 64 registers): 256 chunks of one row run at once wherever they land.
 __global__ void mask_clear_status_kernel(int* __restrict__ status) { *status = 0; }
 
-__global__ __launch_bounds__(NT_CHUNK, 8) void mask_kernel(ChunkArgs a, int* __restrict__ status, int shared_status)
+// Rows for the attention that follows (chunked prefill).  A thread keeps its column and moves ROW_UNR rows at a time.
+constexpr int ROW_UNR = 4;
+__device__ void copy_rows(const RowCopy& R, int row, int wg)
+{
+    const int tid = threadIdx.x, per = NT_CHUNK / R.unit, col = tid % R.unit, r0 = tid / R.unit;
+    if (r0 >= per) return;
+    const int pad = R.rcap - R.count[row], nv = R.rcap + R.clen;
+    const int first = min(pad, max(0, R.rcap - R.w - 64));
+    const int step = per * ROW_UNR, runs = (nv - first + step - 1) / step;
+    for (int i = wg; i < R.heads * runs; i += R.wgs) {
+        const int h = i / runs, e0 = first + (i - h * runs) * step + r0;
+        const size_t bh = (size_t)row * R.heads + h;
+        const uint4 zero = make_uint4(0, 0, 0, 0);
+        uint4 kk[ROW_UNR], vv[ROW_UNR];
+#pragma unroll
+        for (int x = 0; x < ROW_UNR; x++) {
+            const int e = e0 + x * per;
+            kk[x] = zero;
+            vv[x] = zero;
+            if (e < nv && e >= pad) {
+                const bool own = e >= R.rcap;
+                const size_t src = (own ? bh * R.clen + (e - R.rcap) : bh * R.rcap + (e - pad)) * R.unit + col;
+                kk[x] = (own ? R.chunk_k : R.ret_k)[src];
+                vv[x] = (own ? R.chunk_v : R.ret_v)[src];
+            }
+        }
+#pragma unroll
+        for (int x = 0; x < ROW_UNR; x++) {
+            const int e = e0 + x * per;
+            const size_t dst = (bh * nv + e) * R.unit + col;
+            if (e < nv) {
+                R.k[dst] = kk[x];
+                R.v[dst] = vv[x];
+            }
+        }
+        if (i == h * runs && first > 0 && r0 == 0) {
+            R.k[bh * nv * R.unit + col] = zero;
+            R.v[bh * nv * R.unit + col] = zero;
+        }
+    }
+}
+
+__global__ __launch_bounds__(NT_CHUNK, 8) void mask_kernel(ChunkArgs a, int nchunks, int* __restrict__ status,
+                                                           int shared_status, RowCopy rows)
 {
     __shared__ __align__(16) MaskSmem sm;
+    const int row = blockIdx.y;
+    if ((int)blockIdx.x >= nchunks) {
+        copy_rows(rows, row, blockIdx.x - nchunks);
+        return;
+    }
     // late chunks have the longest prefixes: they go first
-    const int c = gridDim.x - 1 - blockIdx.x, row = blockIdx.y;
+    const int c = nchunks - 1 - blockIdx.x;
     int* st = status;
     if (!shared_status) {
-        st += (size_t)row * gridDim.x + c;
+        st += (size_t)row * nchunks + c;
         if (threadIdx.x == 0) *st = 0;
     }
     ChunkJob J;
@@ -1650,13 +1698,23 @@ __global__ __launch_bounds__(256) void materialize_kernel(const float* __restric
 }
 
 int launch_mask(const sparsek_cfg& c, const float* u, float* tau, int32_t* death, void* ws,
-                hipStream_t st, int t_begin, const int32_t* first_valid)
+                hipStream_t st, int t_begin, const int32_t* first_valid, const RowCopy* rows)
 {
-    const int nchunks = (c.n + CHUNK - 1) / CHUNK;
+    const int nchunks = (c.n + CHUNK - 1) / CHUNK, nrows = c.B * c.Gu;
     const ChunkArgs a{u, tau, death, c.n, c.k, t_begin, first_valid};
     const bool shared = mask_shared_status(c);
+    RowCopy R{};
+    if (rows) {
+        // The chunks are bound by latency and, with one score row, few: the rows are moved by what is left of the chip
+        // (two workgroups per compute unit) meanwhile.  With many score rows a few workgroups follow each of them.
+        R = *rows;
+        const int step = NT_CHUNK / R.unit * ROW_UNR;
+        const long long most = (long long)R.heads * ((R.rcap + R.clen + step - 1) / step);
+        const long long idle = (512 - (long long)nrows * (nchunks - t_begin / CHUNK)) / nrows;
+        R.wgs = (int)std::min(most, std::max(idle, 8ll));
+    }
     if (shared) hipLaunchKernelGGL(mask_clear_status_kernel, dim3(1), dim3(1), 0, st, (int*)ws);
-    hipLaunchKernelGGL(mask_kernel, dim3(nchunks, c.B * c.Gu), dim3(NT_CHUNK), 0, st, a, (int*)ws, shared ? 1 : 0);
+    hipLaunchKernelGGL(mask_kernel, dim3(nchunks + R.wgs, nrows), dim3(NT_CHUNK), 0, st, a, nchunks, (int*)ws, shared ? 1 : 0, R);
     return launch_status();
 }
 
