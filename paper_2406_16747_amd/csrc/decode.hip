@@ -8,8 +8,8 @@
 // clip(u - tau, 0, 1); -inf = empty), so one step moves no K/V rows except the new token's.
 //
 // One step = one launch.  The first workgroups of the grid, one per score row, update tau / top-k / candidates for the
-// key that leaves the window and store the new token's K/V rows; the others stream the k+w slots of a head (HBM-bound),
-// or a share of them when there are few heads.  A head needs the row's update only for the gates, so it takes the dot
+// key that leaves the window; the others stream the k+w slots of a head (HBM-bound), or a share of them when there are few
+// heads, and the one that holds the new token's slot stores its K/V rows.  A head needs the row's update only for the gates, so it takes the dot
 // products of all its K rows first and then picks the few changes of the step up from a record that the row's workgroup
 // publishes; the update (dependent loads, 7 to 20 us) runs in the shadow of the K stream.
 #include "common.hpp"
@@ -237,8 +237,8 @@ __device__ int block_prune(int* scan, float* cand, int n, double tau)
 }
 
 // ---------------------------------------------------------------------------------
-// (1) per score row: the key leaving the window joins the SPARSEK prefix; the new token is appended to the window; its
-// K/V rows go to the freed slot.  A chain of dependent loads on an otherwise idle workgroup, so everything that can be
+// (1) per score row: the key leaving the window joins the SPARSEK prefix; the new token is appended to the window and gets
+// the freed slot.  A chain of dependent loads on an otherwise idle workgroup, so everything that can be
 // fetched before anything is known is fetched first: the selected keys and the candidates (up to SEL_REG / CAND_REG
 // per thread in registers, the rest is read again where it is needed).
 // ---------------------------------------------------------------------------------
@@ -297,9 +297,8 @@ struct UpdateSmem {
     float ev_u;
 };
 
-template <typename T>
 __device__ void decode_update(UpdateSmem& sm, const sparsek_decode_cfg& c, const DecodeLayout& L, char* st, int row,
-                              const T* __restrict__ k_new, const T* __restrict__ v_new, const float* __restrict__ u_new)
+                              const float* __restrict__ u_new)
 {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const RowState R = row_state(st, L, row);
@@ -341,8 +340,7 @@ __device__ void decode_update(UpdateSmem& sm, const sparsek_decode_cfg& c, const
         nfree--;
         return old_top;
     };
-    const int b_ = row / c.Gu, g_ = row % c.Gu;
-    const int h0 = (c.Gu == 1) ? 0 : g_, nh = (c.Gu == 1) ? c.H : 1;
+    const int nh = (c.Gu == 1) ? c.H : 1;   // heads of the row
 
     bool selected = false, evict = false;
     int e = -1;  // entry of the selected arrays that receives z
@@ -485,16 +483,6 @@ __device__ void decode_update(UpdateSmem& sm, const sparsek_decode_cfg& c, const
         *R.new_slot = new_slot;
         *R.pos = t + 1;
     }
-    if (new_slot >= 0) {
-        const int vpr = c.d * (int)sizeof(T) / 16;  // 16-byte vectors per row
-        const uint4* ksrc = (const uint4*)(k_new + ((size_t)b_ * c.H + h0) * c.d);
-        const uint4* vsrc = (const uint4*)(v_new + ((size_t)b_ * c.H + h0) * c.d);
-        for (int v = tid; v < nh * vpr; v += NT_ROW) {
-            const size_t dst = (((size_t)b_ * c.H + h0 + v / vpr) * L.NS + new_slot) * vpr + v % vpr;
-            ((uint4*)(st + L.kslots))[dst] = ksrc[v];
-            ((uint4*)(st + L.vslots))[dst] = vsrc[v];
-        }
-    }
 }
 
 // ---------------------------------------------------------------------------------
@@ -557,13 +545,13 @@ __device__ __forceinline__ float row_sum(float x)   // over the LPR lanes of a r
 
 template <typename T, int LPR, int MODE>
 __device__ void decode_attend(AttnSmem<LPR>& sm, const sparsek_decode_cfg& c, const DecodeLayout& L, char* st, int id,
-                              const T* __restrict__ q_new, const T* __restrict__ k_new, const T* __restrict__ v_new,
-                              T* __restrict__ o)
+                              const T* q_new, const T* k_new, const T* v_new, T* o)
 {
     constexpr int D = LPR * 8;
     constexpr int RPW = 64 / LPR;        // rows per wave-load
     constexpr int NSTREAM = 4 * RPW;     // streams per workgroup
     constexpr int UNR = sizeof(T) == 2 ? 4 : 2;   // rows in flight per stream
+    constexpr int ROW16 = sizeof(T) / 2;          // 16-byte units of a row per lane
     const int bh = id / L.nsplit, sp = id % L.nsplit;
     const int b = bh / c.H, h = bh % c.H;
     const int row = b * c.Gu + (c.Gu == 1 ? 0 : h);
@@ -708,6 +696,14 @@ __device__ void decode_attend(AttnSmem<LPR>& sm, const sparsek_decode_cfg& c, co
         }
         __syncthreads();
     }
+    // The new rows move into their slot here and not in the row's workgroup: nobody outside this head's workgroups
+    // reads them, so o may be the memory of q_new, k_new or v_new.  (The share's slots have been read.)
+    if (fresh >= s_begin && fresh < s_end && tid < 2 * LPR * ROW16) {
+        const int i = tid % (LPR * ROW16);
+        const uint4* src = (const uint4*)((tid < LPR * ROW16 ? k_new : v_new) + (size_t)bh * D);
+        uint4* dst = (uint4*)(st + (tid < LPR * ROW16 ? L.kslots : L.vslots)) + ((size_t)bh * L.NS + fresh) * (LPR * ROW16);
+        dst[i] = src[i];
+    }
     // ---- merge the streams ----
 #pragma unroll
     for (int e = 0; e < 8; e++) sm.part[stream][sub * 8 + e] = acc[e];
@@ -790,13 +786,12 @@ union StepSmem {
 
 template <typename T, int LPR, int MODE>
 __global__ __launch_bounds__(NT_ROW, 5) void decode_step_kernel(sparsek_decode_cfg c, DecodeLayout L, char* st,
-                                                                const T* __restrict__ q_new, const T* __restrict__ k_new,
-                                                                const T* __restrict__ v_new,
-                                                                const float* __restrict__ u_new, T* __restrict__ o)
+                                                                const T* q_new, const T* k_new, const T* v_new,
+                                                                const float* __restrict__ u_new, T* o)
 {
     __shared__ __align__(16) StepSmem<LPR> sm;
     const int id = blockIdx.x;
-    if (id < L.rows) decode_update<T>(sm.u, c, L, st, id, k_new, v_new, u_new);
+    if (id < L.rows) decode_update(sm.u, c, L, st, id, u_new);
     else decode_attend<T, LPR, MODE>(sm.a, c, L, st, id - L.rows, q_new, k_new, v_new, o);
 }
 

@@ -136,6 +136,28 @@ def test_decode_state_used_again(oracle):
         np.testing.assert_array_equal(a, b)
 
 
+@pytest.mark.parametrize("k,w", [(20, 33), (600, 500)])   # one workgroup per head, several shares
+@pytest.mark.parametrize("over", ["q", "k", "v"])
+def test_decode_output_over_an_input(oracle, k, w, over):
+    """The output may take the place of the new token's q, k or v."""
+    require_gpu()
+    say("decode output over", over, k, w)
+    B, H, d, n_ctx, steps = 1, 4, 128, 1200, 6
+    hist = history(np.random.default_rng(k), B, H, 1, n_ctx + steps, d, "bf16")
+    Q, K, V = (dev(hist[x], True) for x in ("Q", "K", "V"))
+    u = dev(hist["u"])
+    u_ctx = u[:, :, :n_ctx].contiguous()
+    tau, death = spk.sparsek_mask(u_ctx, k)
+    states = [spk.DecodeState(B, H, 1, d, k, w, torch.bfloat16) for _ in range(2)]
+    for st in states:
+        spk.sparsek_decode_load(st, K[:, :, :n_ctx].contiguous(), V[:, :, :n_ctx].contiguous(), u_ctx, tau, death)
+    for i in range(n_ctx, n_ctx + steps):
+        new = [[x[:, :, i].contiguous() for x in (Q, K, V, u)] for _ in states]
+        want = spk.sparsek_decode_step(states[0], *new[0])
+        got = spk.sparsek_decode_step(states[1], *new[1], out=new[1]["qkv".index(over)])
+        np.testing.assert_array_equal(host(got), host(want))
+
+
 def test_decode_step_equals_prefill_row_on_gpu(oracle):
     """Sec. 3.4: recurrent evaluation gives the same result as the one-shot one."""
     require_gpu()
