@@ -36,6 +36,31 @@ def test_scores_small(oracle, B, n, D, dtype, norm):
     check(oracle, B, n, D, dtype, 0.0, norm, seed=7 + n)
 
 
+@pytest.mark.parametrize("n,D,dtype", [(32, 512, "bf16"), (65, 8, "fp32"), (300, 264, "fp32"), (513, 1544, "bf16"),
+                                       (8193, 24, "bf16")])
+def test_scores_blocks_and_features(oracle, n, D, dtype):
+    """Edges of the 32- and 256-position blocks, rows that end inside a step of the feature loop."""
+    require_gpu()
+    say("scores blocks", n, D, dtype)
+    check(oracle, 2, n, D, dtype, 2.0 ** -9, True, seed=n + D)
+    check(oracle, 2, n, D, dtype, 0.0, False, seed=n + D)
+
+
+@pytest.mark.parametrize("t", [64, 65])   # the first of a block of 32 positions, and another
+def test_scores_after_an_infinite_one(oracle, t):
+    """An infinite score makes the mean of what follows infinite and leaves what is before it alone."""
+    require_gpu()
+    say("scores infinite", t)
+    xs, _, w = synth.hidden_states(1, 700, 64, 5, "fp32", 0.0)
+    w = np.abs(w) + 0.1
+    clean = host(spk.sparsek_scores(dev(xs), dev(w), 0.0, True))
+    xs = xs.copy()
+    xs[0, t, 3] = np.inf
+    u = host(spk.sparsek_scores(dev(xs), dev(w), 0.0, True))
+    np.testing.assert_array_equal(u[:, :t], clean[:, :t])
+    assert (u[:, t + 1:] == -np.inf).all()
+
+
 def test_scores_with_a_large_common_offset(oracle):
     """Hidden states far from zero: raw scores share a large offset that the normalisation must
     remove without losing the small differences (the kernel sums shifted scores)."""
