@@ -322,7 +322,7 @@ def decode_leg(steps=256, warm=8, with_cpu=True):
         "workload": "config 5: decode, B=64 H=32 d=128 k=w=1024 bf16, context 32768, %d steps, Gu=1" % steps,
         "us_per_step": wall_us, "device_us_per_step": dev_us, "device_us_per_step_stats": per_step,
         "tokens_per_s": B / (wall_us * 1e-6), "candidate_overflow": overflow,
-        "roofline": {"bound": "hbm", "kernel": "decode_update_kernel + decode_attn_kernel (the whole step)",
+        "roofline": {"bound": "hbm", "kernel": "decode_step_kernel (the whole step)",
                      "achieved": gbs, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS, "algorithmic_bytes": bytes_step,
                      "traffic": read_traffic("decode_config5_counters.txt")},
