@@ -131,6 +131,7 @@ def _ptr(t):
 
 
 def _dtype_code(t):
+    _torch()
     if t.dtype is torch.bfloat16:
         return BF16
     if t.dtype is torch.float32:
@@ -173,7 +174,7 @@ def _make_mask_cfg(B, Gu, n, k):
     return SparsekCfg(B=B, H=Gu, Gu=Gu, n=n, d=64, k=k, w=1, dtype=F32, gate_mode=0, softmax_scale=1.0)
 
 
-def _mask_cfg(u, k):
+def _mask_kept(u, k):
     B, Gu, n = u.shape
     return _kept("mask", (B, Gu, n, int(k)), _make_mask_cfg)
 
@@ -182,7 +183,7 @@ def sparsek_mask(u, k, ws=None):
     """u [B,Gu,n] fp32 -> (tau [B,Gu,n] fp32, death [B,Gu,n] int32)."""
     torch, L = _torch(), lib()
     _need(u, torch.float32, "u")
-    cfg = _mask_cfg(u, k)
+    cfg = _mask_kept(u, k)
     tau = torch.empty_like(u)
     death = torch.empty_like(u, dtype=torch.int32)
     if ws is None:
@@ -200,7 +201,7 @@ def sparsek_mask_static(u, k, tau=None, death=None):
     """sparsek_mask without a workspace (the library's built-in scratch array); tau, death may be preallocated."""
     torch = _torch()
     _need(u, torch.float32, "u")
-    cfg = _mask_cfg(u, k)
+    cfg = _mask_kept(u, k)
     if tau is None:
         tau = torch.empty_like(u)
     if death is None:
@@ -214,14 +215,14 @@ def sparsek_mask_static(u, k, tau=None, death=None):
 def sparsek_mask_workspace(u, k):
     """A workspace for sparsek_mask(u, k, ws=...), to be read back with sparsek_mask_status."""
     _torch()
-    return _ws(lib().sparsek_mask_workspace_bytes(_mask_cfg(u, k)[0]), u.device)
+    return _ws(lib().sparsek_mask_workspace_bytes(_mask_kept(u, k)[0]), u.device)
 
 
 def sparsek_mask_status(u, k, ws):
     """Status word of the last sparsek_mask(u, k, ws=ws) call (0 = every threshold solve converged).  Synchronises."""
     flag = C.c_int32(-1)
     _torch()
-    check(lib().sparsek_mask_status(_mask_cfg(u, k)[0], _ptr(ws), ws.numel(), C.byref(flag), _stream()))
+    check(lib().sparsek_mask_status(_mask_kept(u, k)[0], _ptr(ws), ws.numel(), C.byref(flag), _stream()))
     return int(flag.value)
 
 
@@ -244,10 +245,16 @@ def _make_attn_cfg(B, H, Gu, n, d, k, w, dtype, gate_mode, scale):
     return SparsekCfg(B=B, H=H, Gu=Gu, n=n, d=d, k=k, w=w, dtype=dtype, gate_mode=gate_mode, softmax_scale=scale)
 
 
-def _attn_cfg(q, u, k, w, gate_mode, scale):
+def _attn_kept(q, u, k, w, gate_mode, scale):
     B, H, n, d = q.shape
     return _kept("attn", (B, H, u.shape[1], n, d, int(k), int(w), _dtype_code(q), int(gate_mode), float(scale)),
                  _make_attn_cfg)
+
+
+def _attn_cfg(q, u, k, w, gate_mode, scale):
+    """A configuration of the caller's own, for the size queries of the C interface."""
+    B, H, n, d = q.shape
+    return _make_attn_cfg(B, H, u.shape[1], n, d, int(k), int(w), _dtype_code(q), int(gate_mode), float(scale))
 
 
 def _attn_ws(cfg, query, ws, device):
@@ -261,7 +268,7 @@ def _attn_ws(cfg, query, ws, device):
 def sparsek_attn_fwd(q, k, v, u, tau, death, k_sel, w, gate_mode=0, scale=1.0, return_lse=True, ws=None):
     """q,k,v [B,H,n,d]; u,tau,death [B,Gu,n] -> o [B,H,n,d] (and lse [B,H,n] fp32)."""
     torch, L = _torch(), lib()
-    cfg = _attn_cfg(q, u, k_sel, w, gate_mode, scale)
+    cfg = _attn_kept(q, u, k_sel, w, gate_mode, scale)
     dt, f32 = q.dtype, torch.float32
     _need(q, dt, "q")
     _need(k, dt, "k")
@@ -282,7 +289,7 @@ def sparsek_attn_fwd(q, k, v, u, tau, death, k_sel, w, gate_mode=0, scale=1.0, r
 def sparsek_mask_bwd(q, k, v, u, tau, death, o, lse, dO, k_sel, w, gate_mode=0, scale=1.0, ws=None):
     """du [B,Gu,n] fp32: gradient of sum(dO*O) w.r.t. the scores through the soft gates."""
     torch, L = _torch(), lib()
-    cfg = _attn_cfg(q, u, k_sel, w, gate_mode, scale)
+    cfg = _attn_kept(q, u, k_sel, w, gate_mode, scale)
     du = torch.empty_like(u)
     ws, nbytes = _attn_ws(cfg, "sparsek_mask_bwd_workspace_bytes", ws, q.device)
     check(L.sparsek_mask_bwd(cfg[0], q.data_ptr(), k.data_ptr(), v.data_ptr(), u.data_ptr(), tau.data_ptr(),
@@ -294,7 +301,7 @@ def sparsek_mask_bwd(q, k, v, u, tau, death, o, lse, dO, k_sel, w, gate_mode=0, 
 def sparsek_attn_bwd(q, k, v, u, tau, death, o, lse, dO, k_sel, w, gate_mode=0, scale=1.0, ws=None):
     """dq, dk, dv [B,H,n,d]: gradients of sum(dO*O) with respect to q, k, v (gates held fixed)."""
     torch, L = _torch(), lib()
-    cfg = _attn_cfg(q, u, k_sel, w, gate_mode, scale)
+    cfg = _attn_kept(q, u, k_sel, w, gate_mode, scale)
     dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
     ws, nbytes = _attn_ws(cfg, "sparsek_attn_bwd_workspace_bytes", ws, q.device)
     check(L.sparsek_attn_bwd(cfg[0], q.data_ptr(), k.data_ptr(), v.data_ptr(), u.data_ptr(), tau.data_ptr(),
@@ -306,7 +313,7 @@ def sparsek_attn_bwd(q, k, v, u, tau, death, o, lse, dO, k_sel, w, gate_mode=0, 
 def sparsek_bwd(q, k, v, u, tau, death, o, lse, dO, k_sel, w, gate_mode=0, scale=1.0, ws=None):
     """The whole backward in one call: (dq, dk, dv, du)."""
     torch, L = _torch(), lib()
-    cfg = _attn_cfg(q, u, k_sel, w, gate_mode, scale)
+    cfg = _attn_kept(q, u, k_sel, w, gate_mode, scale)
     dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
     du = torch.empty_like(u)
     ws, nbytes = _attn_ws(cfg, "sparsek_bwd_workspace_bytes", ws, q.device)

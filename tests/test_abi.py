@@ -144,3 +144,18 @@ def test_toolchain_record_and_m0_check():
     open(f.name, "w").write(good)
     assert build.check_m0(f.name) == {"k1": 1}
     os.remove(f.name)
+
+
+def test_configuration_before_any_call(monkeypatch):
+    """A program that sizes its workspace first: the configuration is a structure of its own, whatever ran before."""
+    import ctypes
+
+    import torch
+
+    import paper_2406_16747_amd as spk
+
+    monkeypatch.setattr(spk.binding, "torch", None)
+    q, u = torch.empty(1, 2, 640, 64, dtype=torch.bfloat16), torch.empty(1, 1, 640)
+    a, b = (spk.binding._attn_cfg(q, u, 32, 16, 0, 1.0) for _ in range(2))
+    assert a is not b and (a.B, a.H, a.Gu, a.n, a.d, a.k, a.w, a.dtype) == (1, 2, 1, 640, 64, 32, 16, spk.BF16)
+    assert spk.lib().sparsek_attn_fwd_workspace_bytes(ctypes.byref(a)) > 0
