@@ -133,32 +133,16 @@ __global__ void chunk_clear_padding_kernel(const int32_t* __restrict__ count, co
     if (e < pad || !ret_sel[(size_t)row * rcap + (e - pad)]) death[(size_t)row * nv + e] = e;
 }
 
-// Exclusive prefix sums of two counters over the 1024 threads of a workgroup.
-__device__ __forceinline__ void block_scan2_1024(int a, int b, int (*wt)[16], int& ea, int& eb, int& ta, int& tb)
-{
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    int ia = a, ib = b;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int ya = __shfl_up(ia, o, 64), yb = __shfl_up(ib, o, 64);
-        if (lane >= o) { ia += ya; ib += yb; }
-    }
-    __syncthreads();
-    if (lane == 63) { wt[0][wv] = ia; wt[1][wv] = ib; }
-    __syncthreads();
-    ea = ia - a; eb = ib - b; ta = 0; tb = 0;
-#pragma unroll
-    for (int i = 0; i < 16; i++) {
-        if (i < wv) { ea += wt[0][i]; eb += wt[1][i]; }
-        ta += wt[0][i]; tb += wt[1][i];
-    }
-}
-
 // The survivors of one row, in position order: the last w entries, the keys still selected for the
 // last prefix used so far (T = nv - 1 - w) and every other real key whose score is above that
 // prefix's threshold.  The first two classes always fit; if the third does not, its oldest members
 // are dropped and bit 0 of the row's flag word is set (later thresholds are then approximate).
-constexpr int RETAIN_LDS = 48 * 1024;  // classes of up to this many virtual positions are cached in LDS
+//
+// One workgroup per row, so what counts is the number of dependent round trips: a wave owns a contiguous run of positions,
+// fetches 8 x 64 of them at once, whatever their class, and takes counts and ranks from ballots.  Classes are formed again
+// in the second pass, from loads that are in flight together with the scores it needs anyway.
+// Rows of 14336 virtual positions: 17 -> 11 us; four chunks of 8192 tokens with their attention 1626 -> 1588 us.
+constexpr int RETAIN_UNR = 8;
 
 __global__ __launch_bounds__(1024) void chunk_retain_kernel(int32_t* __restrict__ count, int32_t* __restrict__ flags,
                                                             const float* __restrict__ u_v,
@@ -168,59 +152,78 @@ __global__ __launch_bounds__(1024) void chunk_retain_kernel(int32_t* __restrict_
                                                             int32_t* __restrict__ ret_sel)
 {
     __shared__ int wt[2][16];
-    __shared__ unsigned char cls[RETAIN_LDS];
-    const int row = blockIdx.x, tid = threadIdx.x;
+    const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nv = rcap + clen;
     const int pad = rcap - count[row];
     const int T = nv - 1 - w;  // last prefix any query has used
-    const bool cached = nv <= RETAIN_LDS;
     const float* ur = u_v + (size_t)row * nv;
     const int32_t* dr = death_v + (size_t)row * nv;
     const float thr = T >= pad ? tau_v[(size_t)row * nv + T] : -INFINITY;
+    const int groups = (nv + 63) / 64, per = (groups + 15) / 16;
+    const int g0 = min(wv * per, groups), g1 = min(g0 + per, groups);
     // class 1: mandatory (window, or selected for prefix T); class 2: other keys above the threshold
-    auto classify = [&](int e) -> int {
-        if (e < pad || e >= nv) return 0;
-        if (e > T) return 1;
-        if (dr[e] > T) return 1;
-        return ur[e] > thr ? 2 : 0;
+    float uu[RETAIN_UNR];
+    unsigned long long m1[RETAIN_UNR], m2[RETAIN_UNR];
+    auto classify = [&](int g) {
+        int dd[RETAIN_UNR];
+#pragma unroll
+        for (int x = 0; x < RETAIN_UNR; x++) {
+            const int e = min((g + x) * 64 + lane, nv - 1);
+            dd[x] = dr[e];
+            uu[x] = ur[e];
+        }
+#pragma unroll
+        for (int x = 0; x < RETAIN_UNR; x++) {
+            const int e = (g + x) * 64 + lane;
+            const bool in = g + x < g1 && e >= pad && e < nv, must = e > T || dd[x] > T;
+            m1[x] = __ballot(in && must);
+            m2[x] = __ballot(in && !must && uu[x] > thr);
+        }
     };
     int n1 = 0, n2 = 0;
-    for (int e = tid; e < nv; e += 1024) {
-        const int c = classify(e);
-        if (cached) cls[e] = (unsigned char)c;
-        n1 += c == 1;
-        n2 += c == 2;
+    for (int g = g0; g < g1; g += RETAIN_UNR) {
+        classify(g);
+#pragma unroll
+        for (int x = 0; x < RETAIN_UNR; x++) {
+            n1 += __popcll(m1[x]);
+            n2 += __popcll(m2[x]);
+        }
     }
-    int e1, e2, t1, t2;
-    block_scan2_1024(n1, n2, wt, e1, e2, t1, t2);  // (its barriers also publish cls[])
+    if (lane == 0) {
+        wt[0][wv] = n1;
+        wt[1][wv] = n2;
+    }
+    __syncthreads();
+    int p1 = 0, p2 = 0, t1 = 0, t2 = 0;
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        if (i < wv) {
+            p1 += wt[0][i];
+            p2 += wt[1][i];
+        }
+        t1 += wt[0][i];
+        t2 += wt[1][i];
+    }
     const int allowed = rcap - t1;        // >= 0: the mandatory classes hold at most k + w entries
     const int drop = t2 > allowed ? t2 - allowed : 0;  // the oldest `drop` members of class 2 go
-    // second pass in position order: contiguous slices per thread keep the order
-    const int per = (nv + 1023) / 1024;
-    const int b0 = min(tid * per, nv), b1 = min(b0 + per, nv);
-    int c1 = 0, c2 = 0;
-    for (int e = b0; e < b1; e++) {
-        const int c = cached ? cls[e] : classify(e);
-        c1 += c == 1;
-        c2 += c == 2;
-    }
-    int p1, p2, u1, u2;
-    block_scan2_1024(c1, c2, wt, p1, p2, u1, u2);
-    for (int e = b0; e < b1; e++) {
-        const int c = cached ? cls[e] : classify(e);
-        if (c == 0) continue;
-        const bool keep = c == 1 || p2 >= drop;
-        if (keep) {
-            const int kept2 = p2 > drop ? p2 - drop : 0;  // class-2 survivors before e
-            const int j = p1 + kept2;
-            map[(size_t)row * rcap + j] = e;
-            ret_u[(size_t)row * rcap + j] = ur[e];
-            ret_sel[(size_t)row * rcap + j] = c == 1;
+    const unsigned long long below = (1ull << lane) - 1;
+    for (int g = g0; g < g1; g += RETAIN_UNR) {
+        classify(g);
+#pragma unroll
+        for (int x = 0; x < RETAIN_UNR; x++) {
+            const bool must = m1[x] >> lane & 1, above = m2[x] >> lane & 1;
+            const int before = p2 + __popcll(m2[x] & below);   // members of class 2 ahead of this entry
+            if (must || (above && before >= drop)) {
+                const size_t j = (size_t)row * rcap + p1 + __popcll(m1[x] & below) + max(before - drop, 0);
+                map[j] = (g + x) * 64 + lane;
+                ret_u[j] = uu[x];
+                ret_sel[j] = must;
+            }
+            p1 += __popcll(m1[x]);
+            p2 += __popcll(m2[x]);
         }
-        p1 += c == 1;
-        p2 += c == 2;
     }
-    if (tid == 0) {  // every thread has read the old count (before the first scan's barriers)
+    if (tid == 0) {  // every thread has read the old count (before the barrier)
         count[row] = t1 + t2 - drop;
         if (drop > 0) flags[row] |= 1;
     }

@@ -95,6 +95,19 @@ def test_chunked_longer_sequence_constant_state(oracle):
     assert counts.max() < 1024
 
 
+@pytest.mark.parametrize("chunks", [[575, 130], [576, 130], [577, 130], [7743, 130], [7744, 130], [7745, 130]])
+def test_survivors_at_the_edges_of_a_waves_run(oracle, chunks):
+    """Virtual sequences of 1024 and 8192 positions (448 retained at most), one less and one more: the choice of survivors
+    gives every wave a run of 64 and of 8 x 64 positions there, and an unfinished one beside it."""
+    require_gpu()
+    say("chunked prefill survivors", chunks)
+    inp = synth.make(3, seed=sum(chunks), B=1, H=1, n=sum(chunks), d=64, k=64, w=64, qk_div=2.0)
+    o_g, counts, flags = run_chunked(inp, chunks)
+    compare(oracle, inp, o_g)
+    assert not flags.any()
+    assert (counts >= 128).all() and (counts <= 448).all()
+
+
 def test_overflow_sets_the_flag(oracle):
     """Nearly equal scores keep every key above the threshold: with a small candidate capacity the
     oldest unselected ones are dropped, the flag is raised, outputs stay finite."""
