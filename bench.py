@@ -423,7 +423,7 @@ def scores_leg(iters=20, warm=3):
         nbytes = B * n * D * 2 + D * 4 + B * n * 4
         gbs = nbytes / (ms * 1e-3) / 1e9
         res.append({"workload": name + ", slope 2^-14, timestep norm", "ms": ms,
-                    "roofline": {"bound": "hbm", "kernel": "scores_dot_kernel + partial + norm", "achieved": gbs,
+                    "roofline": {"bound": "hbm", "kernel": "scores_dot_kernel + scores_norm_kernel", "achieved": gbs,
                                  "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS,
                                  "algorithmic_bytes": nbytes, "traffic": None}})
         del x
