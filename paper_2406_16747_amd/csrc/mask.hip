@@ -683,16 +683,18 @@ __device__ void bitonic_sort_desc(unsigned long long* key, int N)
 }
 
 // pref[i] = sum of the scores of key[0, PSTRIDE * i), i = 0..N / PSTRIDE, in fp64 (N a multiple of NT_CHUNK * 2).
+// Infinite scores count as 0: they are never fractional, and a difference of two sums has to stay a number.
 __device__ void sorted_prefix_sums(const unsigned long long* key, double* pref, int N, int m_old, double* wtot)
 {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     double carry = 0.0;
+    auto score = [&](int i) {
+        const float z = i < m_old ? key_score(key[i]) : 0.0f;
+        return fabsf(z) < INFINITY ? (double)z : 0.0;
+    };
     for (int base = 0; base < N; base += NT_CHUNK * PSTRIDE) {
         double run = 0.0;
-        for (int r = 0; r < PSTRIDE; r++) {
-            const int i = base + tid * PSTRIDE + r;
-            run += (i < m_old) ? (double)key_score(key[i]) : 0.0;
-        }
+        for (int r = 0; r < PSTRIDE; r++) run += score(base + tid * PSTRIDE + r);
         // inclusive scan of the thread totals across the wave, then across the waves
         double inc = run;
 #pragma unroll
@@ -737,7 +739,9 @@ __device__ __noinline__ void mask_chunk_sorted(SortedSmem& sm, const float* __re
     // ---- compaction of {j < t0 : u_j > lo} as selection keys, in one pass: each wave owns a contiguous slice, read
     // in segments of 64*SLICE_REG scores held in registers (independent loads, one latency); a segment reserves
     // its room in the list with one LDS atomic.  The order in which the segments land does not matter: the list
-    // is sorted next, and the keys are distinct. ----
+    // is sorted next, and the keys are distinct.  A prefix of fewer than k keys selects all of them, scores of -inf
+    // included: then every position is taken. ----
+    const bool all = t0 < k;
     const int per = ((t0 + NW_CHUNK - 1) / NW_CHUNK + 63) / 64 * 64;
     const int sb = min(t0, wv * per), se = min(t0, sb + per);
     constexpr int SEGN = 64 * SLICE_REG;
@@ -753,7 +757,7 @@ __device__ __noinline__ void mask_chunk_sorted(SortedSmem& sm, const float* __re
         int seg_cnt = 0;
 #pragma unroll
         for (int r = 0; r < SLICE_REG; r++) {
-            const bool p = z[r] > lo;
+            const bool p = g0 + r * 64 + lane < se && (all || z[r] > lo);
             seg_cnt += __popcll(__ballot(p));
         }
         int off = 0;
@@ -761,7 +765,7 @@ __device__ __noinline__ void mask_chunk_sorted(SortedSmem& sm, const float* __re
         off = __builtin_amdgcn_readfirstlane(off);
 #pragma unroll
         for (int r = 0; r < SLICE_REG; r++) {
-            const bool p = z[r] > lo;
+            const bool p = g0 + r * 64 + lane < se && (all || z[r] > lo);
             const unsigned long long ball = __ballot(p);
             const int pos = off + __popcll(ball & ((1ull << lane) - 1ull));
             if (p && pos < CAP) sm.skey[pos] = sel_key(z[r], g0 + r * 64 + lane);   // beyond CAP: the slow path below

@@ -108,6 +108,21 @@ def test_survivors_at_the_edges_of_a_waves_run(oracle, chunks):
     assert (counts >= 128).all() and (counts <= 448).all()
 
 
+@pytest.mark.parametrize("chunks", [[130, 200, 170], [100, 37, 363]])
+def test_chunked_scores_of_minus_infinity(oracle, chunks):
+    """Keys scored -inf among the first k and later ones, in rows that start at any offset of the virtual sequence.
+    Without gates the output depends on the selection alone, so the oracle may have a finite lowest score instead."""
+    require_gpu()
+    say("chunked prefill -inf", chunks)
+    inp = synth.make(3, seed=chunks[0], B=1, H=2, n=sum(chunks), d=64, k=200, w=33, qk_div=2.0)
+    low = [0, 3, 99, 100, 128, 150, 199, 260]
+    stand_in = inp["u"].copy()
+    inp["u"][:, :, low], stand_in[:, :, low] = -np.inf, np.float32(-1e30)
+    o_g, _, flags = run_chunked(inp, chunks, gate_mode=2)
+    compare(oracle, dict(inp, u=stand_in), o_g, gate_mode=2)
+    assert not flags.any()
+
+
 def test_overflow_sets_the_flag(oracle):
     """Nearly equal scores keep every key above the threshold: with a small candidate capacity the
     oldest unselected ones are dropped, the flag is raised, outputs stay finite."""

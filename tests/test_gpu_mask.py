@@ -102,6 +102,34 @@ def test_mask_ranges_and_clusters(oracle, n, k, scale, offset):
     check_rows(oracle, (rng.standard_normal((2, n)) * scale + offset).astype(np.float32), k)
 
 
+@pytest.mark.parametrize("n,k,low", [
+    (700, 200, [5]),                                # ahead of the chunk that holds prefix k
+    (700, 200, [0, 1, 60, 127, 130, 199, 200, 500]),
+    (900, 300, [3, 255, 256, 299, 300, 301]),
+    (900, 300, list(range(0, 280, 2))),             # fewer than k finite scores until position 440
+    (1500, 1153, [7, 1100, 1151, 1152]),
+])
+def test_mask_scores_of_minus_infinity(oracle, n, k, low):
+    """Padding scored -inf is selected while there are fewer than k other keys, and every lifetime is written.  The
+    oracle gets a finite score below all others in its place: the order is the same, and so is every threshold that
+    the finite scores determine (the others are -inf)."""
+    require_gpu()
+    say("mask -inf", n, k, len(low))
+    u = np.random.default_rng(n + len(low)).standard_normal((2, n)).astype(np.float32)
+    stand_in = u.copy()
+    u[:, low], stand_in[:, low] = -np.inf, np.float32(-1e30)
+    ud = dev(u.reshape(2, 1, n))
+    tau = torch.full_like(ud, float("nan"))
+    death = torch.full(ud.shape, -(2 ** 31), dtype=torch.int32, device="cuda")
+    spk.sparsek_mask_static(ud, k, tau, death)
+    for r in range(2):
+        np.testing.assert_array_equal(host(death)[r, 0], oracle.death(stand_in[r], k))
+        tau_r, tau_g = oracle.tau_prefixes(stand_in[r], k)[0], host(tau)[r, 0].astype(np.float64)
+        np.testing.assert_array_equal(tau_g == -np.inf, tau_r < -1e29)
+        real = tau_r > -1e29
+        np.testing.assert_allclose(tau_g[real], tau_r[real], rtol=1e-5, atol=1e-5)
+
+
 def test_mask_candidate_overflow_fallback(oracle):
     """More scores above the threshold than the LDS list holds: the kernel must switch to
     its global-memory path and still be exact."""
