@@ -194,12 +194,15 @@ int sparsek_decode_init(const sparsek_decode_cfg *cfg, void *state, size_t state
 int sparsek_decode_load(const sparsek_decode_cfg *cfg, void *state, size_t state_bytes, int32_t n_ctx,
                         const void *k, const void *v, const float *u, const float *tau,
                         const int32_t *death, void *stream);
-/* q_new,k_new,v_new [B,H,d]; u_new [B,Gu]; o out [B,H,d].  state is updated in place. */
+/* q_new,k_new,v_new [B,H,d]; u_new [B,Gu]; o out [B,H,d].  state is updated in place.  With w > 0 a step also makes the
+ * update of thresholds and selection that the step after it needs.  Steps of one state must be ordered; steps of different
+ * states may run at the same time. */
 int sparsek_decode_step(const sparsek_decode_cfg *cfg, void *state, const void *q_new,
                         const void *k_new, const void *v_new, const float *u_new, void *o,
                         void *stream);
 /* copies the per-row status words [B*Gu] to host memory; synchronises the stream.  bit 0: candidate overflow; bit 1: a
- * threshold solve stopped at its iteration cap; bit 2: a bounded wait inside a step ran out (neither observed) */
+ * threshold solve stopped at its iteration cap; bit 2: a bounded wait for a head's partial results ran out, and the head's
+ * output is NaN (neither observed).  With w > 0 they cover the update for the next step too. */
 int sparsek_decode_status(const sparsek_decode_cfg *cfg, const void *state, int32_t *host_flags,
                           void *stream);
 

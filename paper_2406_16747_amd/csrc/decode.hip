@@ -7,30 +7,40 @@
 // per-slot gate score (+inf = window key, gate 1; finite = selected key, gate
 // clip(u - tau, 0, 1); -inf = empty), so one step moves no K/V rows except the new token's.
 //
-// One step = one launch.  The first workgroups of the grid, one per score row, update tau / top-k / candidates for the
-// key that leaves the window; the others stream the k+w slots of a head (HBM-bound), or a share of them when there are few
-// heads, and the one that holds the new token's slot stores its K/V rows.  A head needs the row's update only for the gates, so it takes the dot
-// products of all its K rows first and then picks the few changes of the step up from a record that the row's workgroup
-// publishes; the update (dependent loads, 7 to 20 us) runs in the shadow of the K stream.
+// One step = one launch.  What a step changes in a score row -- tau, the slot that becomes empty, the gate of the key that
+// leaves the window, the new token's slot -- depends on earlier tokens only (w > 0), so every step finds it ready in a
+// record and leaves that of the next one: the first workgroups of the grid, one per score row, update tau / top-k /
+// candidates for the key that leaves the window in the step after this one (dependent loads, 7 to 20 us), while the others
+// stream the k+w slots of a head (HBM-bound), or a share of them when there are few heads, and the one that holds the new
+// token's slot stores its K/V rows.  No workgroup waits for one that may not have been dispatched yet: an order of dispatch
+// holds within one XCD only.  Without a window (w == 0) the new token's own score decides, and the update runs ahead of
+// the heads in a launch of its own.
 #include "common.hpp"
 
 namespace spk {
 
-// What a step changes for the attention of one score row.  Every word carries the step's number in its upper half, so
-// that a reader needs no ordering between them: it waits until all six have the number of the step it belongs to.
-// `done` counts the heads of the row that have finished, over all steps: divided by the number of heads per row it is
-// the number of the steps before this one for as long as any head of this step still runs.
-enum { REC_TAU = 0, REC_EVICTED = 1, REC_LEFT = 2, REC_LEFT_U = 3, REC_NEW = 4, REC_NEW_U = 5, REC_WORDS = 6 };
+// What a step changes for the attention of one score row.
 struct StepRecord {
-    unsigned long long word[REC_WORDS];
-    unsigned long long done;
-    unsigned long long pad;
+    float tau;
+    int evicted;      // the slot that becomes empty, -1: none
+    int left;         // the slot of the key that leaves the window, -1: none,
+    float left_u;     // and its gate score from now on
+    int fresh;        // the new token's slot, -1: it has none,
+    float fresh_u;    // and its gate score
+    int pad[2];
 };
+struct RowSync {
+    StepRecord rec[2];          // step s finds its record in rec[s & 1]
+    unsigned long long step;    // steps that are over: counted by the last workgroup of the row to finish
+    unsigned finished, pad;     // heads of the row, and its own workgroup, that are through with this step
+    unsigned long long pad2[6];
+};
+static_assert(sizeof(RowSync) == 128, "one cache line per row");
 
 struct DecodeLayout {
     int rows, NS, cap, wlen, klen;
-    size_t pos, nsel, ncand, status, nfree, new_slot, tau_d, tau_f;
-    size_t win_u, win_slot, sel_u, sel_pos, sel_slot, cand_u, slot_u, free_stack, kslots, vslots, rec, heads, part, total;
+    size_t pos, nsel, ncand, status, nfree, tau_d;
+    size_t win_u, win_slot, sel_u, sel_pos, sel_slot, cand_u, slot_u, free_stack, kslots, vslots, sync, heads, part, total;
     int nsplit;
 };
 
@@ -54,9 +64,7 @@ __host__ __device__ inline DecodeLayout decode_layout(const sparsek_decode_cfg& 
     L.ncand = take(r * 4);
     L.status = take(r * 4);
     L.nfree = take(r * 4);
-    L.new_slot = take(r * 4);
     L.tau_d = take(r * 8);
-    L.tau_f = take(r * 4);
     L.win_u = take(r * L.wlen * 4);
     L.win_slot = take(r * L.wlen * 4);
     L.sel_u = take(r * L.klen * 4);
@@ -74,7 +82,7 @@ __host__ __device__ inline DecodeLayout decode_layout(const sparsek_decode_cfg& 
     const long long heads = (long long)c.B * c.H, bytes = 2ll * L.NS * c.d * (long long)esz;
     const long long want = (1024 + heads - 1) / heads, most = bytes >> 17 > 1 ? bytes >> 17 : 1;
     L.nsplit = (int)(want < most ? want : most);
-    L.rec = take(r * sizeof(StepRecord));
+    L.sync = take(r * sizeof(RowSync));
     L.heads = take((size_t)heads * 4);
     L.part = take(L.nsplit > 1 ? (size_t)heads * L.nsplit * (c.d + 2) * 8 : 0);
     L.total = off;
@@ -84,16 +92,15 @@ __host__ __device__ inline DecodeLayout decode_layout(const sparsek_decode_cfg& 
 size_t decode_state_bytes(const sparsek_decode_cfg& c) { return decode_layout(c).total; }
 
 struct RowState {
-    int *pos, *nsel, *ncand, *status, *nfree, *new_slot;
+    int *pos, *nsel, *ncand, *status, *nfree;
     double* tau_d;
-    float* tau_f;
     float* win_u;
     int* win_slot;
     float* sel_u;
     int *sel_pos, *sel_slot;
     float *cand_u, *slot_u;
     int* free_stack;
-    StepRecord* rec;
+    RowSync* sync;
 };
 
 __device__ inline RowState row_state(char* st, const DecodeLayout& L, int row)
@@ -104,9 +111,7 @@ __device__ inline RowState row_state(char* st, const DecodeLayout& L, int row)
     R.ncand = (int*)(st + L.ncand) + row;
     R.status = (int*)(st + L.status) + row;
     R.nfree = (int*)(st + L.nfree) + row;
-    R.new_slot = (int*)(st + L.new_slot) + row;
     R.tau_d = (double*)(st + L.tau_d) + row;
-    R.tau_f = (float*)(st + L.tau_f) + row;
     R.win_u = (float*)(st + L.win_u) + (size_t)row * L.wlen;
     R.win_slot = (int*)(st + L.win_slot) + (size_t)row * L.wlen;
     R.sel_u = (float*)(st + L.sel_u) + (size_t)row * L.klen;
@@ -115,7 +120,7 @@ __device__ inline RowState row_state(char* st, const DecodeLayout& L, int row)
     R.cand_u = (float*)(st + L.cand_u) + (size_t)row * L.cap;
     R.slot_u = (float*)(st + L.slot_u) + (size_t)row * L.NS;
     R.free_stack = (int*)(st + L.free_stack) + (size_t)row * L.NS;
-    R.rec = (StepRecord*)(st + L.rec) + row;
+    R.sync = (RowSync*)(st + L.sync) + row;
     return R;
 }
 
@@ -237,8 +242,8 @@ __device__ int block_prune(int* scan, float* cand, int n, double tau)
 }
 
 // ---------------------------------------------------------------------------------
-// (1) per score row: the key leaving the window joins the SPARSEK prefix; the new token is appended to the window and gets
-// the freed slot.  A chain of dependent loads on an otherwise idle workgroup, so everything that can be
+// (1) per score row: the step under way appends its token to the window; the key that the next step takes out of it joins
+// the SPARSEK prefix, and the next token gets the freed slot.  A chain of dependent loads on an otherwise idle workgroup, so everything that can be
 // fetched before anything is known is fetched first: the selected keys and the candidates (up to SEL_REG / CAND_REG
 // per thread in registers, the rest is read again where it is needed).
 // ---------------------------------------------------------------------------------
@@ -297,6 +302,9 @@ struct UpdateSmem {
     float ev_u;
 };
 
+// UNDER_WAY: inside step number `sync->step`, whose token has the score u_new; prepares the one after it.  Else: prepares
+// step number `sync->step` itself, ahead of it (u_new is read without a window only).
+template <bool UNDER_WAY>
 __device__ void decode_update(UpdateSmem& sm, const sparsek_decode_cfg& c, const DecodeLayout& L, char* st, int row,
                               const float* __restrict__ u_new)
 {
@@ -304,12 +312,15 @@ __device__ void decode_update(UpdateSmem& sm, const sparsek_decode_cfg& c, const
     const RowState R = row_state(st, L, row);
     const int k = c.k, w = c.w;
     // ---- everything that depends on nothing ----
-    const int t = *R.pos;
+    const int t_now = *R.pos, t = t_now + (UNDER_WAY ? 1 : 0);   // t: position of the step that is prepared
     int nsel = *R.nsel, ncand = *R.ncand;
     const int nfree0 = *R.nfree;
     const double tau_old = *R.tau_d;
-    const float unew = u_new[row];
-    const unsigned long long done = R.rec->done;
+    const float unew = UNDER_WAY || w == 0 ? u_new[row] : 0.0f;
+    const int step = (int)(R.sync->step & 1);
+    StepRecord now = R.sync->rec[0];
+    const StepRecord odd = R.sync->rec[1];
+    if (step) now = odd;
     RowRegs G;
     int ss[SEL_REG];
 #pragma unroll
@@ -327,8 +338,11 @@ __device__ void decode_update(UpdateSmem& sm, const sparsek_decode_cfg& c, const
     float z = unew;
     int zslot = -1;
     if (leave && w > 0) {
-        z = R.win_u[p % w];
-        zslot = R.win_slot[p % w];
+        if (UNDER_WAY && p == t_now) zslot = now.fresh;   // (w == 1: the token of this step)
+        else {
+            z = R.win_u[p % w];
+            zslot = R.win_slot[p % w];
+        }
     }
     // Free-slot stack: at most one slot is pushed and at most one is popped per step, so the
     // step works on a local copy (count, the slot pushed in this step, the old top fetched
@@ -340,7 +354,6 @@ __device__ void decode_update(UpdateSmem& sm, const sparsek_decode_cfg& c, const
         nfree--;
         return old_top;
     };
-    const int nh = (c.Gu == 1) ? c.H : 1;   // heads of the row
 
     bool selected = false, evict = false;
     int e = -1;  // entry of the selected arrays that receives z
@@ -404,7 +417,7 @@ __device__ void decode_update(UpdateSmem& sm, const sparsek_decode_cfg& c, const
             }, k, tau_old, R.status);
         }
     }
-    // ---- (c) slots, and the record the attention waits for ----
+    // ---- (c) slots, and the record of the step ----
     int new_slot = -1;
     int zval_slot = -1;          // the slot of the key that left the window and its gate score
     float zval = -INFINITY;
@@ -422,18 +435,9 @@ __device__ void decode_update(UpdateSmem& sm, const sparsek_decode_cfg& c, const
     }
     if (w > 0) new_slot = pop_slot();
     const float new_u = w > 0 ? INFINITY : z;
-    if (tid == 0) {
-        const unsigned long long tag = (done / (unsigned)nh + 1ull) << 32;
-        auto put = [&](int i, unsigned x) {
-            __hip_atomic_store(&R.rec->word[i], tag | x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        };
-        put(REC_TAU, __float_as_uint((float)tau_new));
-        put(REC_EVICTED, (unsigned)(evict ? ev_slot : -1));
-        put(REC_LEFT, (unsigned)zval_slot);
-        put(REC_LEFT_U, __float_as_uint(zval));
-        put(REC_NEW, (unsigned)new_slot);
-        put(REC_NEW_U, __float_as_uint(new_u));
-    }
+    if (tid == 0)
+        R.sync->rec[step ^ (UNDER_WAY ? 1 : 0)] =
+            StepRecord{(float)tau_new, evict ? ev_slot : -1, zval_slot, zval, new_slot, new_u, {0, 0}};
     // ---- (d) candidates: scores above tau outside the top-k ----
     if (leave && k > 0 && len > k) {
         __syncthreads();
@@ -460,8 +464,6 @@ __device__ void decode_update(UpdateSmem& sm, const sparsek_decode_cfg& c, const
     // ---- (e) the state ----
     if (tid == 0) {
         if (leave) {
-            if (evict) R.slot_u[ev_slot] = -INFINITY;
-            if (zval_slot >= 0) R.slot_u[zval_slot] = zval;
             if (selected) {
                 R.sel_u[e] = z;
                 R.sel_pos[e] = p;
@@ -471,17 +473,32 @@ __device__ void decode_update(UpdateSmem& sm, const sparsek_decode_cfg& c, const
             *R.nsel = nsel;
             *R.ncand = ncand;
             *R.tau_d = tau_new;
-            *R.tau_f = (float)tau_new;
-        }
-        if (w > 0) {
-            R.win_u[t % w] = unew;
-            R.win_slot[t % w] = new_slot;
-            R.slot_u[new_slot] = INFINITY;
         }
         if (pushed >= 0) R.free_stack[nfree++] = pushed;
         *R.nfree = nfree;
-        *R.new_slot = new_slot;
-        *R.pos = t + 1;
+        // gate scores and window of the step under way; without a window those of the step prepared, whose heads come later
+        // (heads of this step read the gate scores meanwhile, and replace these three by their record)
+        if (UNDER_WAY || w == 0) {
+            const int gone = UNDER_WAY ? now.evicted : evict ? ev_slot : -1, left = UNDER_WAY ? now.left : zval_slot;
+            if (gone >= 0) R.slot_u[gone] = -INFINITY;
+            if (left >= 0) R.slot_u[left] = UNDER_WAY ? now.left_u : zval;
+            *R.pos = t_now + 1;
+        }
+        if (UNDER_WAY) {
+            R.slot_u[now.fresh] = INFINITY;
+            R.win_u[t_now % w] = unew;
+            R.win_slot[t_now % w] = now.fresh;
+        }
+    }
+}
+
+// One of the row's heads, or its own workgroup (there is one with a window), is through with this step.
+__device__ __forceinline__ void report_finished(const sparsek_decode_cfg& c, RowSync* sync)
+{
+    const unsigned all = (c.Gu == 1 ? c.H : 1) + (c.w > 0 ? 1 : 0);
+    if (__hip_atomic_fetch_add(&sync->finished, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == all) {
+        __hip_atomic_store(&sync->finished, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(&sync->step, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -528,7 +545,6 @@ struct AttnSmem {
     float w[SLAB];                            // dot products, then weights
     float part[4 * (64 / LPR)][LPR * 8];      // sums of the workgroup's streams
     float red[2][NT_ROW / 64];
-    unsigned rec[REC_WORDS];
     float newdot;
     int last;
 };
@@ -558,9 +574,8 @@ __device__ void decode_attend(AttnSmem<LPR>& sm, const sparsek_decode_cfg& c, co
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int sub = lane % LPR, grp = lane / LPR;
     const int stream = wv * RPW + grp;
-    StepRecord* rec = (StepRecord*)(st + L.rec) + row;
-    // (read before this head reports its end, so the quotient is the number of the steps before this one)
-    const unsigned long long done = __hip_atomic_load(&rec->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    RowSync* sync = (RowSync*)(st + L.sync) + row;
+    const unsigned step = (unsigned)sync->step;   // (not counted before this head has reported its end)
     const float* slot_u = (const float*)(st + L.slot_u) + (size_t)row * L.NS;
     const T* ks = (const T*)(st + L.kslots) + (size_t)bh * L.NS * D;
     const T* vs = (const T*)(st + L.vslots) + (size_t)bh * L.NS * D;
@@ -586,8 +601,9 @@ __device__ void decode_attend(AttnSmem<LPR>& sm, const sparsek_decode_cfg& c, co
 #pragma unroll
     for (int e = 0; e < 8; e++) acc[e] = 0.0f;
 
-    float tau = 0.0f, left_u = 0.0f, new_u = 0.0f;
-    int evicted = -1, left = -1, fresh = -1;
+    const StepRecord rec = sync->rec[step & 1];   // (the row's workgroup writes the other one meanwhile)
+    const float tau = rec.tau, left_u = rec.left_u, new_u = rec.fresh_u;
+    const int evicted = rec.evicted, left = rec.left, fresh = rec.fresh;
     for (int s0 = s_begin; s0 < s_end; s0 += SLAB) {
         const int sn = min(SLAB, s_end - s0);
         const T* kb = ks + (size_t)s0 * D;   // 32-bit offsets from here: a slab holds at most 1 MB
@@ -618,31 +634,7 @@ __device__ void decode_attend(AttnSmem<LPR>& sm, const sparsek_decode_cfg& c, co
         Row8<T> vr[UNR];
 #pragma unroll
         for (int x = 0; x < UNR; x++) vr[x].load(vb + at(stream + x * NSTREAM));
-        // ---- the record of this step ----
-        if (s0 == s_begin) {
-            if (tid < REC_WORDS) {
-                const unsigned tag = (unsigned)(done / (unsigned)(c.Gu == 1 ? c.H : 1)) + 1u;
-                unsigned long long x = 0ull;
-                int spins = 0;
-                // The row's workgroup has a lower index, so it was dispatched before this one and waits for nobody.
-                for (; spins < (1 << 20); spins++) {
-                    x = __hip_atomic_load(&rec->word[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if ((unsigned)(x >> 32) == tag) break;
-                    __builtin_amdgcn_s_sleep(2);
-                }
-                if (spins == (1 << 20)) atomicOr((int*)(st + L.status) + row, 4);
-                sm.rec[tid] = (unsigned)x;
-            }
-        }
         __syncthreads();
-        if (s0 == s_begin) {
-            tau = __uint_as_float(sm.rec[REC_TAU]);
-            evicted = (int)sm.rec[REC_EVICTED];
-            left = (int)sm.rec[REC_LEFT];
-            left_u = __uint_as_float(sm.rec[REC_LEFT_U]);
-            fresh = (int)sm.rec[REC_NEW];
-            new_u = __uint_as_float(sm.rec[REC_NEW_U]);
-        }
         // ---- weights ----
         float s2[SPT], mx = -INFINITY;
 #pragma unroll
@@ -720,10 +712,10 @@ __device__ void decode_attend(AttnSmem<LPR>& sm, const sparsek_decode_cfg& c, co
     if (L.nsplit == 1) {
         if (tid < D) st1(o + (size_t)bh * D + tid, osum / l_tot);
     } else {
-        // Partial results meet in memory, every value with the step's number beside it: as with the record, a reader
-        // waits for the number, so nothing has to be flushed or fenced.  The workgroup that arrives last adds them up,
-        // in the order of the shares.
-        const unsigned tag = (unsigned)(done / (unsigned)(c.Gu == 1 ? c.H : 1)) + 1u;
+        // Partial results meet in memory, every value with the step's number beside it: a reader waits for the number, so
+        // nothing has to be flushed or fenced.  The workgroup that arrives last adds them up, in the order of the shares;
+        // what it waits for has been sent off by workgroups that arrived before it.
+        const unsigned tag = step + 1u;
         unsigned long long* part = (unsigned long long*)(st + L.part) + (size_t)bh * L.nsplit * (D + 2);
         auto put = [&](int i, float x) {
             __hip_atomic_store(&part[(size_t)sp * (D + 2) + i], (unsigned long long)tag << 32 | __float_as_uint(x),
@@ -745,10 +737,10 @@ __device__ void decode_attend(AttnSmem<LPR>& sm, const sparsek_decode_cfg& c, co
                 unsigned long long x = 0ull;
                 for (int spins = 0; spins < (1 << 20); spins++) {
                     x = __hip_atomic_load(&part[(size_t)s * (D + 2) + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if ((unsigned)(x >> 32) == tag) break;
+                    if ((unsigned)(x >> 32) == tag) return __uint_as_float((unsigned)x);
                 }
-                if ((unsigned)(x >> 32) != tag) atomicOr((int*)(st + L.status) + row, 4);
-                return __uint_as_float((unsigned)x);
+                atomicOr((int*)(st + L.status) + row, 4);   // and no result that could pass for one
+                return __uint_as_float(0x7FC00000u);
             };
             for (int s = tid; s < 2 * L.nsplit; s += NT_ROW) sm.w[s] = get(s >> 1, D + (s & 1));
             __syncthreads();
@@ -775,7 +767,7 @@ __device__ void decode_attend(AttnSmem<LPR>& sm, const sparsek_decode_cfg& c, co
             }
         }
     }
-    if (finish && tid == 0) __hip_atomic_fetch_add(&rec->done, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (finish && tid == 0) report_finished(c, sync);
 }
 
 template <int LPR>
@@ -790,9 +782,20 @@ __global__ __launch_bounds__(NT_ROW, 5) void decode_step_kernel(sparsek_decode_c
                                                                 const float* __restrict__ u_new, T* o)
 {
     __shared__ __align__(16) StepSmem<LPR> sm;
-    const int id = blockIdx.x;
-    if (id < L.rows) decode_update(sm.u, c, L, st, id, u_new);
-    else decode_attend<T, LPR, MODE>(sm.a, c, L, st, id - L.rows, q_new, k_new, v_new, o);
+    const int own = c.w > 0 ? L.rows : 0, id = blockIdx.x;
+    if (id < own) {
+        decode_update<true>(sm.u, c, L, st, id, u_new);
+        if (threadIdx.x == 0) report_finished(c, (RowSync*)(st + L.sync) + id);
+    } else {
+        decode_attend<T, LPR, MODE>(sm.a, c, L, st, id - own, q_new, k_new, v_new, o);
+    }
+}
+
+// The record of the step that comes next: of the first one after a state has been set up, without a window of every one.
+__global__ __launch_bounds__(NT_ROW) void decode_update_kernel(sparsek_decode_cfg c, char* st, const float* __restrict__ u_new)
+{
+    __shared__ UpdateSmem sm;
+    decode_update<false>(sm, c, decode_layout(c), st, blockIdx.x, u_new);
 }
 
 // ---------------------------------------------------------------------------------
@@ -824,10 +827,10 @@ __global__ __launch_bounds__(256) void decode_zero_slots_kernel(sparsek_decode_c
     }
 }
 
-// The step record of a row and the arrival counters of its heads.
+// The records and counters of a row and the arrival counters of its heads.
 __device__ __forceinline__ void clear_sync(const sparsek_decode_cfg& c, char* st, const DecodeLayout& L, const RowState& R, int row)
 {
-    if (threadIdx.x < sizeof(StepRecord) / 8) ((unsigned long long*)R.rec)[threadIdx.x] = 0ull;
+    if (threadIdx.x < sizeof(RowSync) / 8) ((unsigned long long*)R.sync)[threadIdx.x] = 0ull;
     const int nh = c.Gu == 1 ? c.H : 1, first = (row / c.Gu) * c.H + (c.Gu == 1 ? 0 : row % c.Gu);
     for (int h = threadIdx.x; h < nh; h += NT_ROW) ((unsigned*)(st + L.heads))[first + h] = 0u;
 }
@@ -842,8 +845,8 @@ __global__ __launch_bounds__(NT_ROW) void decode_init_kernel(sparsek_decode_cfg 
         R.free_stack[s] = L.NS - 1 - s;  // slot 0 is popped first
     }
     if (tid == 0) {
-        *R.pos = 0; *R.nsel = 0; *R.ncand = 0; *R.status = 0; *R.nfree = L.NS; *R.new_slot = -1;
-        *R.tau_d = 0.0; *R.tau_f = 0.0f;
+        *R.pos = 0; *R.nsel = 0; *R.ncand = 0; *R.status = 0; *R.nfree = L.NS;
+        *R.tau_d = 0.0;
     }
     clear_sync(c, st, L, R, row);
 }
@@ -927,8 +930,8 @@ __global__ __launch_bounds__(NT_ROW) void decode_load_kernel(sparsek_decode_cfg 
     const int used = nsel + nwin;
     for (int s = tid; s < L.NS - used; s += NT_ROW) R.free_stack[s] = L.NS - 1 - s;  // pops `used` first
     if (tid == 0) {
-        *R.pos = n_ctx; *R.nsel = nsel; *R.ncand = ncand; *R.nfree = L.NS - used; *R.new_slot = -1;
-        *R.tau_d = tau_d; *R.tau_f = (float)tau_d;
+        *R.pos = n_ctx; *R.nsel = nsel; *R.ncand = ncand; *R.nfree = L.NS - used;
+        *R.tau_d = tau_d;
     }
     clear_sync(c, st, L, R, row);
 }
@@ -960,11 +963,19 @@ __global__ __launch_bounds__(256) void decode_load_kv_kernel(sparsek_decode_cfg 
 }
 
 // ---------------------------------------------------------------------------------
+// (the last launch of a set-up: those before it count the free slots)
+static void prepare_first_step(const sparsek_decode_cfg& c, void* state, hipStream_t st)
+{
+    if (c.w > 0)
+        hipLaunchKernelGGL(decode_update_kernel, dim3(c.B * c.Gu), dim3(NT_ROW), 0, st, c, (char*)state, (const float*)nullptr);
+}
+
 int launch_decode_init(const sparsek_decode_cfg& c, void* state, hipStream_t st)
 {
     if (c.d != 32 && c.d != 64 && c.d != 128) return SPARSEK_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(decode_init_kernel, dim3(c.B * c.Gu), dim3(NT_ROW), 0, st, c, (char*)state);
     hipLaunchKernelGGL(decode_zero_slots_kernel, dim3(c.B * c.H, 4), dim3(256), 0, st, c, (char*)state, 0);
+    prepare_first_step(c, state, st);
     return launch_status();
 }
 
@@ -981,6 +992,7 @@ int launch_decode_load(const sparsek_decode_cfg& c, void* state, int n_ctx, cons
         hipLaunchKernelGGL(decode_load_kv_kernel<float>, dim3(c.B * c.H), dim3(256), 0, st, c, (char*)state,
                            n_ctx, (const float*)k, (const float*)v);
     hipLaunchKernelGGL(decode_zero_slots_kernel, dim3(c.B * c.H, 4), dim3(256), 0, st, c, (char*)state, 1);
+    prepare_first_step(c, state, st);
     return launch_status();
 }
 
@@ -989,7 +1001,8 @@ static void launch_step_t(const sparsek_decode_cfg& c, void* state, const void* 
                           const float* u_new, void* o, hipStream_t st)
 {
     const DecodeLayout L = decode_layout(c);
-    dim3 grid((unsigned)(L.rows + c.B * c.H * L.nsplit));
+    if (c.w == 0) hipLaunchKernelGGL(decode_update_kernel, dim3(L.rows), dim3(NT_ROW), 0, st, c, (char*)state, u_new);
+    dim3 grid((unsigned)((c.w > 0 ? L.rows : 0) + c.B * c.H * L.nsplit));
 #define SPK_STEP(MODE)                                                                                                 \
     hipLaunchKernelGGL((decode_step_kernel<T, LPR, MODE>), grid, dim3(NT_ROW), 0, st, c, L, (char*)state, (const T*)q, \
                        (const T*)k, (const T*)v, u_new, (T*)o)

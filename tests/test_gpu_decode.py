@@ -208,3 +208,47 @@ def test_decode_candidate_overflow_sets_status(oracle):
     torch.cuda.synchronize()
     assert torch.isfinite(o.float()).all()
     assert spk.sparsek_decode_status(state)[0] & 1
+
+
+@pytest.mark.parametrize("k,w", [(200, 312), (100, 0)])
+def test_decode_steps_of_several_states_at_once(k, w):
+    """Steps of different states overlap on different streams as they like: no head waits for a workgroup that the other
+    states' heads could keep from running."""
+    require_gpu()
+    say("decode states at once", k, w)
+    B, H, d, n_ctx, steps, count = 8, 32, 128, 700, 8, 3
+    g = torch.Generator(device="cuda").manual_seed(k)
+    states = [spk.DecodeState(B, H, 1, d, k, w, torch.bfloat16) for _ in range(count)]
+    new = []
+    for st in states:
+        u = torch.randn(B, 1, n_ctx, device="cuda", generator=g)
+        kk, vv = (torch.randn(B, H, n_ctx, d, device="cuda", generator=g).bfloat16() for _ in range(2))
+        spk.sparsek_decode_load(st, kk, vv, u, *spk.sparsek_mask(u, k))
+        new.append([tuple(torch.randn(B, H, d, device="cuda", generator=g).bfloat16() for _ in range(3))
+                    + (torch.randn(B, 1, device="cuda", generator=g),) for _ in range(steps)])
+    before = [st.buf.clone() for st in states]
+    want = [[spk.sparsek_decode_step(st, *x) for x in xs] for st, xs in zip(states, new)]
+    for st, buf in zip(states, before):
+        st.buf.copy_(buf)
+    got = [[torch.empty_like(o) for o in os] for os in want]
+    streams = [torch.cuda.Stream() for _ in states]
+    torch.cuda.synchronize()
+    for i in range(steps):
+        for st, xs, os, stream in zip(states, new, got, streams):
+            with torch.cuda.stream(stream):
+                spk.sparsek_decode_step(st, *xs[i], out=os[i])
+    torch.cuda.synchronize()
+    for a, b, st in zip(want, got, states):
+        assert all(torch.equal(x, y) for x, y in zip(a, b))
+        assert not spk.sparsek_decode_status(st).any()
+
+
+def test_decode_without_a_window_between_steps_with_one(oracle):
+    """The update of a step is prepared by the one before it, except without a window: both, step by step, from a
+    context that fills neither the selection nor the window."""
+    require_gpu()
+    say("decode prepared updates")
+    for w in (0, 1, 2):
+        for Gu in (1, 2):
+            _, _, flags, _ = run_decode(oracle, 2, 2, Gu, 64, 6, w, 3, 40, ties=True, seed=w)
+            assert not flags.any()
