@@ -350,13 +350,12 @@ class ChunkState:
         self.cfg = SparsekChunkCfg(B=B, H=H, Gu=Gu, d=d, k=int(k), w=int(w), cand_cap=int(cand_cap),
                                    chunk_max=int(chunk_max), dtype=dtype, gate_mode=int(gate_mode),
                                    softmax_scale=float(scale))
-        self.ref = C.byref(self.cfg)
-        nbytes = lib().sparsek_chunk_state_bytes(self.ref)
+        nbytes = lib().sparsek_chunk_state_bytes(self.cfg)
         if nbytes == 0:
             raise ValueError("invalid chunk configuration")
         self.buf = torch.empty(nbytes, dtype=torch.uint8, device=device)
-        self.ws = torch.empty(lib().sparsek_chunk_workspace_bytes(self.ref), dtype=torch.uint8, device=device)
-        check(lib().sparsek_chunk_init(self.ref, _ptr(self.buf), self.buf.numel(), _stream()))
+        self.ws = torch.empty(lib().sparsek_chunk_workspace_bytes(self.cfg), dtype=torch.uint8, device=device)
+        check(lib().sparsek_chunk_init(self.cfg, _ptr(self.buf), self.buf.numel(), _stream()))
 
 
 def sparsek_chunk_prefill(state, q, k, v, u):
@@ -364,7 +363,7 @@ def sparsek_chunk_prefill(state, q, k, v, u):
     torch = _torch()
     c = q.shape[2]
     o = torch.empty_like(q)
-    check(lib().sparsek_chunk_prefill(state.ref, _ptr(state.buf), state.buf.numel(), c, _ptr(q), _ptr(k),
+    check(lib().sparsek_chunk_prefill(state.cfg, _ptr(state.buf), state.buf.numel(), c, _ptr(q), _ptr(k),
                                       _ptr(v), _ptr(u), _ptr(o), _ptr(state.ws), state.ws.numel(), _stream()))
     return o
 
@@ -374,14 +373,14 @@ def sparsek_chunk_bwd(state, q, o, dO):
     sparsek_chunk_prefill call on this state processed, the retained keys of earlier chunks held constant."""
     torch = _torch()
     c = q.shape[2]
-    nbytes = lib().sparsek_chunk_bwd_workspace_bytes(state.ref)
+    nbytes = lib().sparsek_chunk_bwd_workspace_bytes(state.cfg)
     if nbytes == 0:
         raise ValueError("sparsek_chunk_bwd: unsupported configuration (bf16 with d = 64 or 128 only)")
     if getattr(state, "bwd_ws", None) is None or state.bwd_ws.numel() < nbytes:
         state.bwd_ws = torch.empty(nbytes, dtype=torch.uint8, device=q.device)
     dq, dk, dv = torch.empty_like(q), torch.empty_like(q), torch.empty_like(q)
     du = torch.empty((state.cfg.B, state.cfg.Gu, c), dtype=torch.float32, device=q.device)
-    check(lib().sparsek_chunk_bwd(state.ref, c, _ptr(q), _ptr(o), _ptr(dO), _ptr(state.ws), state.ws.numel(),
+    check(lib().sparsek_chunk_bwd(state.cfg, c, _ptr(q), _ptr(o), _ptr(dO), _ptr(state.ws), state.ws.numel(),
                                   _ptr(dq), _ptr(dk), _ptr(dv), _ptr(du), _ptr(state.bwd_ws), state.bwd_ws.numel(),
                                   _stream()))
     return dq, dk, dv, du
@@ -389,8 +388,8 @@ def sparsek_chunk_bwd(state, q, o, dO):
 
 def sparsek_chunk_to_decode(state, n_consumed, decode_state):
     """Fills a DecodeState with the state after the n_consumed tokens the chunks have covered."""
-    check(lib().sparsek_chunk_to_decode(state.ref, _ptr(state.buf), state.buf.numel(), int(n_consumed),
-                                        _ptr(state.ws), state.ws.numel(), decode_state.ref,
+    check(lib().sparsek_chunk_to_decode(state.cfg, _ptr(state.buf), state.buf.numel(), int(n_consumed),
+                                        _ptr(state.ws), state.ws.numel(), decode_state.cfg,
                                         _ptr(decode_state.buf), decode_state.buf.numel(), _stream()))
 
 
@@ -401,7 +400,7 @@ def sparsek_chunk_status(state):
     rows = state.cfg.B * state.cfg.Gu
     counts = np.zeros(rows, np.int32)
     flags = np.zeros(rows, np.int32)
-    check(lib().sparsek_chunk_status(state.ref, _ptr(state.buf), counts.ctypes.data_as(C.c_void_p),
+    check(lib().sparsek_chunk_status(state.cfg, _ptr(state.buf), counts.ctypes.data_as(C.c_void_p),
                                      flags.ctypes.data_as(C.c_void_p), _stream()))
     return counts, flags
 
@@ -415,27 +414,26 @@ class DecodeState:
                                     dtype=BF16 if dtype == torch.bfloat16 else F32,
                                     gate_mode=int(gate_mode), softmax_scale=float(scale))
         self.torch_dtype = dtype
-        self.ref = C.byref(self.cfg)
-        nbytes = lib().sparsek_decode_state_bytes(self.ref)
+        nbytes = lib().sparsek_decode_state_bytes(self.cfg)
         if nbytes == 0:
             raise ValueError("unsupported decode configuration")
         self.buf = torch.empty(int(nbytes), dtype=torch.uint8, device=device)
 
 
 def sparsek_decode_init(state):
-    check(lib().sparsek_decode_init(state.ref, _ptr(state.buf), state.buf.numel(), _stream()))
+    check(lib().sparsek_decode_init(state.cfg, _ptr(state.buf), state.buf.numel(), _stream()))
 
 
 def sparsek_decode_load(state, k, v, u, tau, death):
     n_ctx = k.shape[2]
-    check(lib().sparsek_decode_load(state.ref, _ptr(state.buf), state.buf.numel(), int(n_ctx),
+    check(lib().sparsek_decode_load(state.cfg, _ptr(state.buf), state.buf.numel(), int(n_ctx),
                                     _ptr(k), _ptr(v), _ptr(u), _ptr(tau), _ptr(death), _stream()))
 
 
 def sparsek_decode_step(state, q_new, k_new, v_new, u_new, out=None):
     torch, L = _torch(), lib()
     o = out if out is not None else torch.empty_like(q_new)
-    rc = L.sparsek_decode_step(state.ref, state.buf.data_ptr(), q_new.data_ptr(), k_new.data_ptr(), v_new.data_ptr(),
+    rc = L.sparsek_decode_step(state.cfg, state.buf.data_ptr(), q_new.data_ptr(), k_new.data_ptr(), v_new.data_ptr(),
                                u_new.data_ptr(), o.data_ptr(), _raw_stream())
     if rc:
         check(rc)
@@ -446,6 +444,6 @@ def sparsek_decode_status(state):
     import numpy as np
 
     flags = np.zeros(state.cfg.B * state.cfg.Gu, np.int32)
-    check(lib().sparsek_decode_status(state.ref, _ptr(state.buf),
+    check(lib().sparsek_decode_status(state.cfg, _ptr(state.buf),
                                       flags.ctypes.data_as(C.c_void_p), _stream()))
     return flags

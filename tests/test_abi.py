@@ -111,6 +111,28 @@ def test_argument_validation_needs_no_gpu():
     assert L.sparsek_bwd(ctypes.byref(cfg), *([one] * 9), one, one, one, one, one, 8, null) == -3
 
 
+def test_states_can_be_copied_and_pickled():
+    """A caller forks a generation by copying its state; the copy has buffers and a configuration of its own."""
+    import copy
+    import pickle
+
+    import torch
+
+    state = spk.DecodeState(1, 2, 1, 64, 8, 8, torch.bfloat16, device="cpu")
+    state.buf.fill_(7)
+    for fork in (copy.deepcopy(state), copy.copy(state), pickle.loads(pickle.dumps(state))):
+        assert bytes(fork.cfg) == bytes(state.cfg) and torch.equal(fork.buf, state.buf)
+    fork = copy.deepcopy(state)
+    fork.buf.fill_(1)
+    fork.cfg.k = 3
+    assert state.cfg.k == 8 and (state.buf == 7).all()
+    chunk = object.__new__(spk.ChunkState)   # (setting one up launches a kernel)
+    chunk.cfg = spk.binding.SparsekChunkCfg(B=1, H=2, Gu=1, d=64, k=8, w=8, chunk_max=256, dtype=spk.BF16, softmax_scale=1.0)
+    chunk.buf = chunk.ws = torch.zeros(16, dtype=torch.uint8)
+    for fork in (copy.deepcopy(chunk), pickle.loads(pickle.dumps(chunk))):
+        assert bytes(fork.cfg) == bytes(chunk.cfg)
+
+
 def test_toolchain_record_and_m0_check():
     """Three kernels set the M0 register from inline assembly (direct-to-LDS loads the compiler does not track), which
     is sound only while the compiler keeps nothing of its own in M0 inside those kernels.  The build checks the

@@ -252,3 +252,31 @@ def test_decode_without_a_window_between_steps_with_one(oracle):
         for Gu in (1, 2):
             _, _, flags, _ = run_decode(oracle, 2, 2, Gu, 64, 6, w, 3, 40, ties=True, seed=w)
             assert not flags.any()
+
+
+def test_decode_fork_of_a_copied_state(oracle):
+    """Two generations continue from one state after copy.deepcopy, each as if it were alone; a chunked state as well."""
+    import copy
+
+    require_gpu()
+    say("decode fork")
+    B, H, d, k, w = 1, 2, 64, 10, 8
+    hist = history(np.random.default_rng(4), B, H, 1, 60, d, "bf16")
+    Q, K, V = (dev(hist[x], True) for x in ("Q", "K", "V"))
+    u = dev(hist["u"])
+
+    def go(state, a, b):
+        return [spk.sparsek_decode_step(state, *(x[:, :, t].contiguous() for x in (Q, K, V, u))) for t in range(a, b)]
+
+    state = spk.DecodeState(B, H, 1, d, k, w, torch.bfloat16)
+    spk.sparsek_decode_init(state)
+    go(state, 0, 30)
+    fork = copy.deepcopy(state)
+    for a, b in zip(go(state, 30, 60), go(fork, 30, 60)):
+        assert torch.equal(a, b)
+    chunked = spk.ChunkState(B, H, 1, d, k, w, spk.BF16, 64)
+    first = [x[:, :, :30].contiguous() for x in (Q, K, V, u)]
+    rest = [x[:, :, 30:60].contiguous() for x in (Q, K, V, u)]
+    spk.sparsek_chunk_prefill(chunked, *first)
+    fork = copy.deepcopy(chunked)
+    assert torch.equal(spk.sparsek_chunk_prefill(chunked, *rest), spk.sparsek_chunk_prefill(fork, *rest))
