@@ -526,6 +526,7 @@ __device__ void wave_theta(const ListSorted& L, const float* __restrict__ ur, in
                 }
             }
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (lane 0 wrote some of them)
         // th[i] = max(th_start, th[0..i]): inclusive prefix maximum over the 128 entries
         unsigned long long a = th[lane], b = th[lane + 64];
         a = a > th_start ? a : th_start;
@@ -655,6 +656,8 @@ __device__ void chunk_body_sorted(const ListSorted& L, const float* __restrict__
     if (tid < t1 - t0) write_death(sel_key(ur[t0 + tid], t0 + tid), t0 + tid, t0, t1, k, th, th_start, dr, j0, survivor);
 }
 
+constexpr int WAIT_LDS = 0xC07F;   // s_waitcnt lgkmcnt(0) alone
+
 // Bitonic sort of key[0, N) in descending order, N a power of two >= 2048 (one or more pairs per
 // thread).  Each wave owns a contiguous run of N/32 compare-exchange pairs, so passes whose
 // stride fits into the wave's N/16 elements need no workgroup barrier: a wave's LDS accesses are
@@ -665,7 +668,14 @@ __device__ void bitonic_sort_desc(unsigned long long* key, int N)
     const int P = N / (2 * NW_CHUNK);  // pairs per wave
     for (int k2 = 2; k2 <= N; k2 <<= 1) {
         for (int j = k2 >> 1; j > 0; j >>= 1) {
-            if (j > P) __syncthreads();
+            if (j > P) {
+                // The compiler leaves the wait out here although the stage before, without a barrier of its own, has
+                // writes under way: other waves could read what was there before them.
+                __builtin_amdgcn_s_waitcnt(WAIT_LDS);
+                __syncthreads();
+            } else {
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (what other lanes wrote has to be read)
+            }
             for (int m = lane; m < P; m += 64) {
                 const int i = wv * P + m;
                 const int a = 2 * i - (i & (j - 1)), b = a + j;
