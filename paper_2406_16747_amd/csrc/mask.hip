@@ -16,9 +16,10 @@
 //     guards it;
 //   * key j dies at the first prefix that holds k larger keys: with c older keys above it, at the
 //     (k - c)-th newcomer of the chunk that is larger -- a rank and two ballots per key.
-// Chunks whose scores do not suit this (clusters of equal scores, k-th largest score outside the
-// histogram's range of 16) take the sorted path below it: the candidates above theta - 1 are
-// compacted into LDS, sorted once, and the same iteration runs on searches in the sorted list.
+// The histogram's window follows the scores, in position and in the width of its bins (next_window).  Chunks that no
+// window suits (many equal scores around the threshold, thresholds of -inf, first thresholds spread over more than 2000)
+// take the sorted path: the candidates above a lower bound are compacted into LDS, sorted once, and the same iteration
+// runs on searches in the sorted list.
 #include "common.hpp"
 
 namespace spk {
@@ -586,6 +587,7 @@ __device__ __forceinline__ void write_death(unsigned long long key, int j, int t
                                             int32_t* __restrict__ dr, int j0, int survivor)
 {
     int first;
+    if ((unsigned)j >= (unsigned)t1) return;   // (a key is a position of the chunk's prefix)
     if (j < t0) {
         if (t0 >= k && key < th_start) return;  // already out before this chunk
         first = t0;
@@ -656,6 +658,19 @@ __device__ void chunk_body_sorted(const ListSorted& L, const float* __restrict__
     if (tid < t1 - t0) write_death(sel_key(ur[t0 + tid], t0 + tid), t0 + tid, t0, t1, k, th, th_start, dr, j0, survivor);
 }
 
+// Sorts key[0, m), m <= NT_CHUNK, distinct keys, in descending order by counting (a few entries: no cascade of barriers).
+__device__ void rank_sort_desc(unsigned long long* key, int m)
+{
+    const int tid = threadIdx.x;
+    const unsigned long long mine = key[min(tid, m - 1)];
+    int rank = 0;
+    if (tid < m)
+        for (int j = 0; j < m; j++) rank += key[j] > mine ? 1 : 0;
+    __syncthreads();
+    if (tid < m) key[rank] = mine;
+    __syncthreads();
+}
+
 constexpr int WAIT_LDS = 0xC07F;   // s_waitcnt lgkmcnt(0) alone
 
 // Bitonic sort of key[0, N) in descending order, N a power of two >= 2048 (one or more pairs per
@@ -670,7 +685,7 @@ __device__ void bitonic_sort_desc(unsigned long long* key, int N)
         for (int j = k2 >> 1; j > 0; j >>= 1) {
             if (j > P) {
                 // The compiler leaves the wait out here although the stage before, without a barrier of its own, has
-                // writes under way: other waves could read what was there before them.
+                // writes under way: other waves then read what was there before them.
                 __builtin_amdgcn_s_waitcnt(WAIT_LDS);
                 __syncthreads();
             } else {
@@ -735,16 +750,55 @@ struct SortedSmem {
     unsigned long long bc;
 };
 
-// One chunk by sorting its candidates (whole workgroup).  Positions count from the row's first valid key.
-__device__ __noinline__ void mask_chunk_sorted(SortedSmem& sm, const float* __restrict__ ur, float* __restrict__ tr,
-                                  int32_t* __restrict__ dr, int t0, int t1, int k, int* status, int j0, int survivor)
+// What a function that is not inlined is called with: the address spaces go along, or every access would be a flat one,
+// and what is the same in every lane is moved to scalar registers, or it would not be known to be.
+#define SPK_LDS __attribute__((address_space(3)))
+#define SPK_GLOBAL __attribute__((address_space(1)))
+template <typename T>
+__device__ __forceinline__ T* uniform_global(T* p)
 {
+    const unsigned long long x = (unsigned long long)p;
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)x), hi = __builtin_amdgcn_readfirstlane((unsigned)(x >> 32));
+    return (T*)(SPK_GLOBAL T*)((unsigned long long)hi << 32 | lo);
+}
+__device__ __forceinline__ int uniform_int(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
+// A lower bound of every threshold of a chunk that starts at t0 >= k; tight: a few bins below the first one.
+struct ChunkBound {
+    float lo;
+    bool tight;
+};
+
+// tau lies in [z_(k) - 1, z_(k)) and both ends only rise: theta_{t0-1} - 1 is such a bound.  Ends with a barrier.
+__device__ float theta_bound(SortedSmem& sm, const float* __restrict__ ur, int t0, int k)
+{
+    __syncthreads();
+    const unsigned long long th_start = block_kth_largest(ListGlobal{ur, t0}, t0, k, sm.hist, &sm.bc);
+    __syncthreads();
+    return __double2float_rd((double)key_score(th_start) - 1.0);
+}
+
+// One chunk by sorting its candidates (whole workgroup).  Positions count from the row's first valid key.
+__device__ __noinline__ void mask_chunk_sorted(SPK_LDS SortedSmem* smem, const float* __restrict__ ur, float* __restrict__ tr,
+                                  int32_t* __restrict__ dr, int t0, int t1, int k, int* status, int j0, int survivor,
+                                  ChunkBound known)
+{
+    SortedSmem& sm = *(SortedSmem*)smem;
+    ur = uniform_global(ur);
+    tr = uniform_global(tr);
+    dr = uniform_global(dr);
+    status = uniform_global(status);
+    t0 = uniform_int(t0);
+    t1 = uniform_int(t1);
+    k = uniform_int(k);
+    j0 = uniform_int(j0);
+    survivor = uniform_int(survivor);
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    // tau lies in [z_(k) - 1, z_(k)) and both ends only rise: theta_{t0-1} - 1 bounds every threshold of the chunk
-    float lo = -INFINITY;
-    if (t0 >= k) {
-        const unsigned long long th_start = block_kth_largest(ListGlobal{ur, t0}, t0, k, sm.hist, &sm.bc);
-        lo = __double2float_rd((double)key_score(th_start) - 1.0);
+    float lo = t0 >= k ? readlane_f32(known.lo, 0) : -INFINITY;
+    bool exact = t0 < k || uniform_int(known.tight) != 0;   // no better bound is to be had
+    if (!exact && !(lo > -INFINITY)) {
+        lo = theta_bound(sm, ur, t0, k);
+        exact = true;
     }
     // ---- compaction of {j < t0 : u_j > lo} as selection keys, in one pass: each wave owns a contiguous slice, read
     // in segments of 64*SLICE_REG scores held in registers (independent loads, one latency); a segment reserves
@@ -755,35 +809,40 @@ __device__ __noinline__ void mask_chunk_sorted(SortedSmem& sm, const float* __re
     const int per = ((t0 + NW_CHUNK - 1) / NW_CHUNK + 63) / 64 * 64;
     const int sb = min(t0, wv * per), se = min(t0, sb + per);
     constexpr int SEGN = 64 * SLICE_REG;
-    if (tid == 0) sm.count = 0;
-    __syncthreads();
-    for (int g0 = sb; g0 < se; g0 += SEGN) {
-        float z[SLICE_REG];
-#pragma unroll
-        for (int r = 0; r < SLICE_REG; r++) {
-            const int i = g0 + r * 64 + lane;
-            z[r] = (i < se) ? ur[i] : -INFINITY;
+    for (;;) {
+        if (tid == 0) sm.count = 0;
+        __syncthreads();
+        for (int g0 = sb; g0 < se; g0 += SEGN) {
+            float z[SLICE_REG];
+    #pragma unroll
+            for (int r = 0; r < SLICE_REG; r++) {
+                const int i = g0 + r * 64 + lane;
+                z[r] = (i < se) ? ur[i] : -INFINITY;
+            }
+            int seg_cnt = 0;
+    #pragma unroll
+            for (int r = 0; r < SLICE_REG; r++) {
+                const bool p = g0 + r * 64 + lane < se && (all || z[r] > lo);
+                seg_cnt += __popcll(__ballot(p));
+            }
+            int off = 0;
+            if (lane == 0 && seg_cnt > 0) off = atomicAdd(&sm.count, seg_cnt);
+            off = __builtin_amdgcn_readfirstlane(off);
+    #pragma unroll
+            for (int r = 0; r < SLICE_REG; r++) {
+                const bool p = g0 + r * 64 + lane < se && (all || z[r] > lo);
+                const unsigned long long ball = __ballot(p);
+                const int pos = off + __popcll(ball & ((1ull << lane) - 1ull));
+                if (p && pos < CAP) sm.skey[pos] = sel_key(z[r], g0 + r * 64 + lane);   // beyond CAP: the slow path below
+                off += __popcll(ball);
+            }
         }
-        int seg_cnt = 0;
-#pragma unroll
-        for (int r = 0; r < SLICE_REG; r++) {
-            const bool p = g0 + r * 64 + lane < se && (all || z[r] > lo);
-            seg_cnt += __popcll(__ballot(p));
-        }
-        int off = 0;
-        if (lane == 0 && seg_cnt > 0) off = atomicAdd(&sm.count, seg_cnt);
-        off = __builtin_amdgcn_readfirstlane(off);
-#pragma unroll
-        for (int r = 0; r < SLICE_REG; r++) {
-            const bool p = g0 + r * 64 + lane < se && (all || z[r] > lo);
-            const unsigned long long ball = __ballot(p);
-            const int pos = off + __popcll(ball & ((1ull << lane) - 1ull));
-            if (p && pos < CAP) sm.skey[pos] = sel_key(z[r], g0 + r * 64 + lane);   // beyond CAP: the slow path below
-            off += __popcll(ball);
-        }
+        __syncthreads();
+        if (exact || uniform_int(sm.count) <= CAP) break;
+        lo = theta_bound(sm, ur, t0, k);   // a coarse bound leaves too many
+        exact = true;
     }
-    __syncthreads();
-    const int m_old = sm.count;
+    const int m_old = uniform_int(sm.count);
     // the list must hold the whole top-k of every prefix of the chunk (it does when lo is a lower
     // bound of tau; checked, not assumed)
     const bool fits = (m_old <= CAP) && (t0 < k || m_old >= k);
@@ -793,7 +852,8 @@ __device__ __noinline__ void mask_chunk_sorted(SortedSmem& sm, const float* __re
         for (int i = m_old + tid; i < npad; i += NT_CHUNK) sm.skey[i] = 0ull;  // below every real key
         __syncthreads();
         if (m_old > 0) {
-            bitonic_sort_desc(sm.skey, npad);
+            if (m_old <= 512) rank_sort_desc(sm.skey, m_old);
+            else bitonic_sort_desc(sm.skey, npad);
             sorted_prefix_sums(sm.skey, sm.pref, npad, m_old, sm.wtot);
         }
         const int cn = t1 - t0;
@@ -810,17 +870,28 @@ __device__ __noinline__ void mask_chunk_sorted(SortedSmem& sm, const float* __re
 // The histogram path.  Bounded by latency -- two passes over the prefix, a dozen workgroup barriers, the searches and
 // the newcomers of a wave -- not by bandwidth or arithmetic.  One row of 32768 scores at k = 1024 takes 35 us (late
 // chunks 22 us: histogram 3.9, bounds 2.2, second pass 7.2, sorting the two short lists 3.5, thresholds 4.3, lifetimes
-// 0.9), 32 rows of 16384 take 262 us.  Before, with a lower bound from a 45-point bracket search in a kernel of its own
+// 0.9), 32 rows of 16384 take 260 us.  Before, with a lower bound from a 45-point bracket search in a kernel of its own
 // and a sort of all candidates per chunk: 85 us and 390 us.
+// Other scores, 32 rows of 16384, k = 1024: standard deviation 7 in 292 us, 27 in 291, 0.05 in 760, mean 20 in 308.  With
+// two fixed widths of window and the sorted path for the rest: 716, 834, 3418 and 383; with every chunk sorted: 360, 369,
+// 9185 and 390.  One row of 131072 at k = 16384: 327 us, 13.3 ms with the fixed width.
 // ---------------------------------------------------------------------------------
-constexpr int HBINS = 2048;      // bins of width 1 / HRES: a window of 16 around the scores
-constexpr int HRES = 128;
+constexpr int HBINS = 2048;      // bins of a window; scores below and above it count in the first and the last one
+constexpr int WINDOWS = 4;       // windows tried at most
 constexpr int TL_WAVE = 64;      // per wave: scores with a breakpoint between the bounds
 constexpr int TL_CAP = NW_CHUNK * TL_WAVE;
-constexpr int QL_CAP = 1024;     // keys between the bounds of theta
+constexpr int QL_CAP = 256;      // keys between the bounds of theta (each is compared with all of them)
 constexpr int CP_CAP = 64 + 128 + 64;   // what is left of the last 64, two groups of a wave, slack for reads past the end
 constexpr int BP_REG = 5;
 constexpr int BP_CAP = 64 * BP_REG;     // breakpoints between the bounds, for the parallel solution
+
+// A window: HBINS bins of width 1 / res from origin on.  covers: no score lies above it.  bounded: the thresholds of the
+// chunk lie in [lo, hi).
+struct HistWindow {
+    float origin, res;
+    bool covers, bounded;
+    double lo, hi;
+};
 
 struct HistSmem {
     union {
@@ -852,7 +923,9 @@ struct HistSmem {
     float wmm[2][NW_CHUNK];
     double wsum[NW_CHUNK];
     int wF[NW_CHUNK], wC[NW_CHUNK], wM[NW_CHUNK];
-    int jlo, jhi, jl, jh, above, jmin, nq, nbp, full;
+    int jlo, jhi, jl, jh, upto, above, jmin, nq, nbp, full;
+    HistWindow win;                     // the last window tried
+    ChunkBound known;                   // for the sorted path
 };
 
 // Inclusive sum over the lanes of a wave (DPP row shifts, then the row totals are broadcast).
@@ -1222,10 +1295,54 @@ __device__ __forceinline__ void solve_parallel(HistSmem& sm, const ListBounded& 
     if ((lane & 7) == 0 && t < tb && t >= k) tr[t] = (float)x;
 }
 
-// One chunk (t0 < t1, k >= 1) by its histogram; false, with nothing written but the thresholds of prefixes of at most k
-// entries (and lifetimes that are written again), when the chunk does not suit it.
-__device__ bool mask_chunk_hist(HistSmem& sm, const float* __restrict__ ur, float* __restrict__ tr,
-                                int32_t* __restrict__ dr, int t0, int t1, int k, int* status, int j0, int survivor)
+// The window to try after sm.win, from what that one says of the thresholds and of the k-th largest score, if no more than
+// "above" or "too many in a bin", and from the smallest and the largest score; false: there is none (whole workgroup).
+__device__ bool next_window(HistSmem& sm, const float* __restrict__ ur, int t0, int cn, int k, int tried)
+{
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const HistWindow W = sm.win;
+    const int jl = sm.jl, jh = sm.jh;
+    if (tried == 1) {
+        float a = INFINITY, b = -INFINITY;
+        each_older(ur, t0, [&](float v, int, bool in) { a = fminf(a, in ? v : INFINITY); b = fmaxf(b, v); }, [] {});
+        const float nv0 = sm.own[lane], nv1 = sm.own[lane + 64];
+        a = wave_min_f32(fminf(a, fminf(lane < cn ? nv0 : INFINITY, lane + 64 < cn ? nv1 : INFINITY)));
+        b = wave_max_f32(fmaxf(b, fmaxf(nv0, nv1)));
+        if (lane == 0) { sm.wmm[0][wv] = a; sm.wmm[1][wv] = b; }
+    }
+    __syncthreads();   // (everybody has read what the next window clears)
+    const float smallest = wave_min_f32(lane < NW_CHUNK ? sm.wmm[0][lane] : INFINITY);
+    const float largest = wave_max_f32(lane < NW_CHUNK ? sm.wmm[1][lane] : -INFINITY);
+    // From below the first threshold to the k-th largest score, and to a unit above the last threshold unless no score
+    // lies there.
+    const float edge = 1.0f / W.res;
+    float from, to = jh >= 0 && jh < HBINS - 1 ? fminf(W.origin + (float)(jh + 1) * edge, largest) : largest;
+    if (W.bounded) {
+        from = __double2float_rd(W.lo);
+        to = fmaxf(to, fminf(largest, __double2float_ru(W.hi + 1.0)));
+    } else {
+        from = (t0 < k || jl <= 0 ? smallest : fmaxf(W.origin + (float)jl * edge, smallest)) - 1.0f;
+        to = fminf(largest, to + 1.0f);
+    }
+    const float span = to - from;
+    if (smallest == largest || !(span > 0.0f && span < 1e30f)) return false;   // (one score for all, infinities)
+    int e;
+    frexpf((float)(HBINS - 8) / span, &e);   // 2^(e-1) <= bins per unit < 2^e
+    float res = ldexpf(1.0f, min(e - 1, 15));
+    while (fabsf(from) * res > 4194304.0f) res *= 0.5f;   // the origin as a number of bins has to be exact
+    if ((W.bounded || tried > 1) && res < 2.0f * W.res) return false;   // as fine as it gets
+    const float origin = floorf(from * res - 2.0f) / res;
+    sm.win.res = res;   // (every wave writes the same)
+    sm.win.origin = origin;
+    sm.win.covers = fmaf(largest, res, -origin * res) < (float)HBINS;
+    return true;
+}
+
+// What comes ahead of the windows: the chunk's own scores to LDS, thresholds of prefixes of at most k entries.  NEXT: its
+// own scores say that [-8, 8) is not the window to start with, and sm.win is one that suits them.
+enum { HIST_DONE, HIST_FIRST, HIST_NEXT, HIST_NONE };
+__device__ __forceinline__ int mask_chunk_begin(HistSmem& sm, const float* __restrict__ ur, float* __restrict__ tr, int t0,
+                                                int t1, int k)
 {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int cn = t1 - t0;
@@ -1236,27 +1353,62 @@ __device__ bool mask_chunk_hist(HistSmem& sm, const float* __restrict__ ur, floa
         sm.own[lane] = nv0;
         sm.own[lane + 64] = nv1;
     }
+    if (tid == 0) sm.known = ChunkBound{-INFINITY, false};
     if (t0 < k) {
         float mn = INFINITY;
         each_older(ur, t0, [&](float v, int, bool in) { mn = fminf(mn, in ? v : INFINITY); }, [] {});
         mn = wave_min_f32(mn);
         if (lane == 0) sm.wmm[0][wv] = mn;
         __syncthreads();
-        if (wv == 0)
-            short_prefix_tau(wave_min_f32(lane < NW_CHUNK ? sm.wmm[0][lane] : INFINITY), nv0, nv1, t0, t1, k, lane, tr);
-        if (t1 <= k) return true;
+        const float before = wave_min_f32(lane < NW_CHUNK ? sm.wmm[0][lane] : INFINITY);
+        if (wv == 0) short_prefix_tau(before, nv0, nv1, t0, t1, k, lane, tr);
+        if (t1 <= k) return HIST_DONE;
+        if (!(before > -INFINITY)) return HIST_NONE;   // (thresholds of -inf)
         __syncthreads();
     }
-    float origin = -8.0f;
-    bool ok = false;
-    int jlo = 0, jhi = 0;
+    auto outside = [](float v) { return v >= 8.0f || (v < -8.0f && v > -INFINITY); };
+    if (!uniform(outside(nv0) || outside(nv1))) return HIST_FIRST;
+    const float s0 = nv0 > -INFINITY ? nv0 : INFINITY, s1 = nv1 > -INFINITY ? nv1 : INFINITY;
+    const float mn = wave_min_f32(fminf(s0, s1)), mx = wave_max_f32(fmaxf(nv0, nv1));
+    if (!uniform(mx - mn < 1e30f)) return HIST_FIRST;
+    float res = 128.0f;
+    while (res > 1e-30f && (1.375f * (mx - mn) * res > (float)HBINS || fmaxf(fabsf(mn), fabsf(mx)) * res > 4194304.0f)) res *= 0.5f;
+    sm.win.res = res;   // (every wave writes the same)
+    sm.win.origin = floorf(0.5f * (mn + mx) * res - 0.5f * (float)HBINS) / res;
+    sm.win.covers = false;
+    return HIST_NEXT;
+}
+
+// One chunk (t0 < t1, k >= 1) by its histogram.  FIRST: in the window [-8, 8) with 128 bins per unit, which suits scores of
+// about unit variance around 0; else in up to WINDOWS others, the first of them after [-8, 8) (tried = 1) or instead of it
+// (tried = 0).  If not DONE, nothing has been written but lifetimes that are written again.
+template <bool FIRST>
+__device__ __forceinline__ int mask_chunk_hist(HistSmem& sm, const float* __restrict__ ur, float* __restrict__ tr,
+                                               int32_t* __restrict__ dr, int t0, int t1, int k, int* status, int j0,
+                                               int survivor, int tried)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int cn = t1 - t0;
+    const float nv0 = lane < cn ? ur[t0 + lane] : -INFINITY, nv1 = lane + 64 < cn ? ur[t0 + lane + 64] : -INFINITY;
+    float origin = -8.0f, res = 128.0f, shift = 0.0f;
+    bool covers = false;
     double lo = 0.0, hi = 0.0;
-    for (int attempt = 0; attempt < 2; attempt++) {
-        const float shift = -origin * (float)HRES;  // exact: the origin is a whole number
-        auto bin = [&](float v) { return (int)__builtin_amdgcn_fmed3f(fmaf(v, (float)HRES, shift), 0.0f, (float)(HBINS - 1)); };
+    float lof = 0.0f, hif = 0.0f, lo1f = 0.0f, hi1f = 0.0f, ql = 0.0f, qh = 0.0f;
+    double csum = 0.0;
+    int above = 0, nM = 0, nF = 0, nC = 0, MQ = 0;
+    for (;; tried++) {
+        if (!FIRST) {
+            if (tried > 0 && (tried == WINDOWS || !next_window(sm, ur, t0, cn, k, tried))) return HIST_NONE;
+            origin = readlane_f32(sm.win.origin, 0);
+            res = readlane_f32(sm.win.res, 0);
+            covers = uniform(sm.win.covers);
+        }
+        shift = -origin * res;      // exact: the origin is a multiple of 1 / res, and so many of them fit into 24 bits
+        auto bin = [&](float v) { return (int)__builtin_amdgcn_fmed3f(fmaf(v, res, shift), 0.0f, (float)(HBINS - 1)); };
+        const int R = res >= 1.0f ? (int)res : 0;   // bins of unit width together; none: the bins only find the k-th largest score
         *(uint2*)&sm.x.h.hist[2 * tid] = make_uint2(0, 0);
         *(uint2*)&sm.x.h.own[2 * tid] = make_uint2(0, 0);
-        if (tid == 0) { sm.jlo = -1; sm.jhi = -1; sm.jl = t0 >= k ? -1 : 0; sm.jh = -1; sm.above = 0; sm.jmin = 0; sm.nq = 0; sm.nbp = 0; sm.full = 0; }
+        if (tid == 0) { sm.jlo = -1; sm.jhi = -1; sm.jl = t0 >= k ? -1 : 0; sm.jh = -1; sm.upto = t0; sm.above = 0; sm.jmin = 0; sm.nq = 0; sm.nbp = 0; sm.full = 0; }
         __syncthreads();
         each_older(ur, t0, [&](float v, int, bool in) { if (in) atomicAdd(&sm.x.h.hist[bin(v)], 1u); }, [] {});
         if (tid < cn) atomicAdd(&sm.x.h.own[bin(tid < 64 ? nv0 : nv1)], 1u);  // (waves 0 and 1)
@@ -1268,16 +1420,16 @@ __device__ bool mask_chunk_hist(HistSmem& sm, const float* __restrict__ ur, floa
         unsigned eo, ea;
         block_scan2(o0 + o1, a0 + a1, sm.wscan[0], sm.wscan[1], eo, ea);
         const unsigned No0 = eo + o0, No1 = No0 + o1, Na0 = ea + a0, Na1 = Na0 + a1;
-        if (No0 >= (unsigned)k && eo < (unsigned)k) sm.jl = b0;
-        if (No1 >= (unsigned)k && No0 < (unsigned)k) sm.jl = b0 - 1;
+        if (No0 >= (unsigned)k && eo < (unsigned)k) { sm.jl = b0; sm.upto = (int)No0; }
+        if (No1 >= (unsigned)k && No0 < (unsigned)k) { sm.jl = b0 - 1; sm.upto = (int)No1; }
         if (Na0 >= (unsigned)k && ea < (unsigned)k) { sm.jh = b0; sm.above = (int)eo; }
         if (Na1 >= (unsigned)k && Na0 < (unsigned)k) { sm.jh = b0 - 1; sm.above = (int)No0; }
         if (Na0 == (unsigned)t1 && ea < (unsigned)t1) sm.jmin = b0;
         if (Na1 == (unsigned)t1 && Na0 < (unsigned)t1) sm.jmin = b0 - 1;
-        // Cumulate once more, so that windowed sums of N are differences.  Sums over a window stay below 2^32 up to
-        // 2^24 scores; beyond, the counts are scaled down (older: rounded down, all: rounded up).
+        // Cumulate once more, so that windowed sums of N are differences.  Those of min(R, HBINS) counts have to stay below
+        // 2^32 (2^24 scores at R = 128); beyond, the counts are scaled down (older: rounded down, all: rounded up).
         int s = 0;
-        while ((t1 >> s) > (1 << 24)) s++;
+        while (((unsigned long long)(t1 >> s) * (unsigned)min(R, HBINS)) > 1ull << 31) s++;
         const unsigned up = (1u << s) - 1u;
         unsigned co, ca;
         const unsigned so0 = No0 >> s, so1 = No1 >> s, sa0 = (Na0 + up) >> s, sa1 = (Na1 + up) >> s;
@@ -1285,15 +1437,16 @@ __device__ bool mask_chunk_hist(HistSmem& sm, const float* __restrict__ ur, floa
         *(uint2*)&sm.x.h.cum[0][2 * tid] = make_uint2(co + so0, co + so0 + so1);
         *(uint2*)&sm.x.h.cum[1][2 * tid] = make_uint2(ca + sa0, ca + sa0 + sa1);
         __syncthreads();
-        // f(edge_j) >= (sum of N_{j+1} .. N_{j+HRES} of the older scores) / HRES: the last j with a sum of at least
-        // k * HRES is a lower bound of every threshold from prefix t0 - 1 on.  f(edge_j) <= (N_j + .. + N_{j+HRES-1}
-        // of all scores) / HRES: the first j with a sum below k * HRES bounds every threshold of the chunk from above.
+        // f(edge_j) >= (sum of N_{j+1} .. N_{j+R} of the older scores) / R: the last j with a sum of at least
+        // k * R is a lower bound of every threshold from prefix t0 - 1 on.  f(edge_j) <= (N_j + .. + N_{j+R-1}
+        // of all scores) / R: the first j with a sum below k * R bounds every threshold of the chunk from above.
+        // (Beyond the window N is 0 if it covers the scores; else the sums have to end inside it.)
         auto wsum = [&](int which, int d_hi, int d_lo) { return sm.x.h.cum[which][d_hi] - (d_lo >= 0 ? sm.x.h.cum[which][d_lo] : 0u); };
-        const unsigned want = (unsigned)(((unsigned long long)k * HRES + up) >> s);
-        auto low = [&](int j) { return wsum(0, HBINS - 2 - j, HBINS - 2 - HRES - j) >= want; };  // j <= HBINS - 1 - HRES
-        auto high = [&](int j) { return wsum(1, HBINS - 1 - j, HBINS - 1 - HRES - j) < want; };
-        constexpr int JTOP = HBINS - 1 - HRES;
-        if (b0 - 1 >= 1 && b0 < JTOP) {
+        const unsigned want = (unsigned)min(((unsigned long long)k * (unsigned)R + up) >> s, 0xFFFFFFFFull);
+        auto low = [&](int j) { return wsum(0, HBINS - 2 - j, HBINS - 2 - R - j) >= want; };  // j <= jtop
+        auto high = [&](int j) { return wsum(1, HBINS - 1 - j, HBINS - 1 - R - j) < want; };
+        const int jtop = covers ? HBINS - 2 : HBINS - 1 - R;
+        if (R > 0 && b0 - 1 >= 1 && b0 < jtop) {
             const bool l0 = low(b0 - 1), l1 = low(b0), l2 = low(b0 + 1);
             if (l0 && !l1) sm.jlo = b0 - 1;
             if (l1 && !l2) sm.jlo = b0;
@@ -1302,110 +1455,108 @@ __device__ bool mask_chunk_hist(HistSmem& sm, const float* __restrict__ ur, floa
             if (!h1 && h2) sm.jhi = b0 + 1;
         }
         __syncthreads();
-        jlo = sm.jlo;
-        jhi = sm.jhi;
-        if (t0 < k) jlo = sm.jmin - HRES;  // the first threshold is that of prefix k: at least min - 1
-        // bin() rounds: a score may lie 2^-21 beyond its bin's edges
-        constexpr double EPS = 1.0 / (1 << 20);
-        ok = jhi > 0 && (t0 < k ? sm.jmin > 0 : jlo > 0);
-        lo = (double)origin + (double)jlo / HRES - EPS;
-        hi = (double)origin + (double)jhi / HRES + EPS;
-        if (ok || attempt == 1) break;
-        // another window: over the whole range if it fits, else below the largest score
-        float a = INFINITY, b = -INFINITY;
-        each_older(ur, t0, [&](float v, int, bool in) { a = fminf(a, in ? v : INFINITY); b = fmaxf(b, v); }, [] {});
-        a = wave_min_f32(fminf(a, fminf(lane < cn ? nv0 : INFINITY, lane + 64 < cn ? nv1 : INFINITY)));
-        b = wave_max_f32(fmaxf(b, fmaxf(nv0, nv1)));
-        if (lane == 0) { sm.wmm[0][wv] = a; sm.wmm[1][wv] = b; }
-        __syncthreads();
-        a = wave_min_f32(lane < NW_CHUNK ? sm.wmm[0][lane] : INFINITY);
-        b = wave_max_f32(lane < NW_CHUNK ? sm.wmm[1][lane] : -INFINITY);
-        origin = (b - a <= 12.0f) ? floorf(0.5f * (a + b)) - 8.0f : floorf(b) - 13.0f;
-        if (!(fabsf(origin) < 65536.0f)) break;  // (uniform) the edges would not be exact
-    }
-    if (!ok) return false;
-
-    // ---- second pass: count and sum what is certain between the bounds, collect what is not ----
-    // (for an fp32 score v: v > x <=> v > rd(x))
-    const float lof = __double2float_rd(lo), hif = __double2float_rd(hi);
-    const float lo1f = __double2float_rd(lo + 1.0), hi1f = __double2float_rd(hi + 1.0);
-    const float shift = -origin * (float)HRES;
-    // bins jl .. jh as limits of the value that bin() truncates
-    const int jl = sm.jl, jh = sm.jh, above = sm.above;
-    const float ql = jl == 0 ? -INFINITY : (float)jl, qh = jh == HBINS - 1 ? INFINITY : (float)(jh + 1);
-    // nothing below this matters (a score in bin jl may lie 2^-21 below its edge)
-    const float least = jl == 0 ? -INFINITY : __double2float_rd(fmin(lo, (double)origin + (double)jl / HRES - 1.0 / (1 << 20)));
-    double csum = 0.0;
-    int nF = 0, nC = 0, nM = 0;
-    auto classify = [&](float v, int i, bool in) {
-        const float tb = fmaf(v, (float)HRES, shift);
-        const bool sat = in && v > hi1f;
-        const bool frac = in && v > hif && v <= lo1f;
-        const bool open = in && v > lof && !sat && !frac;
-        const bool sel = in && tb >= ql;
-        const bool q = sel && tb < qh;
-        nF += (int)__popcll(__ballot(sat && !frac));
-        nC += (int)__popcll(__ballot(frac));
-        csum += (double)(frac ? v : 0.0f);
-        if (survivor && sel && !q) dr[i] = survivor;
-        const unsigned long long bo = __ballot(open), bq = __ballot(q);
-        const unsigned long long below = (1ull << lane) - 1ull;
-        if (bo) {
-            const int at = nM + (int)__popcll(bo & below);
-            if (open && at < TL_WAVE) sm.raw[wv][at] = v;
-            nM += (int)__popcll(bo);
-        }
-        if (bq) {
-            int off = 0;
-            if (lane == 0) off = atomicAdd(&sm.nq, (int)__popcll(bq));
-            off = __builtin_amdgcn_readfirstlane(off) + (int)__popcll(bq & below);
-            if (q && off < QL_CAP) sm.qk[off] = sel_key(v, i);
-        }
-    };
-    __syncthreads();  // the histograms are no longer needed
-    // Only a few per cent of the scores lie above the lower bound.  Every wave collects its own and looks at them 64 at
-    // a time, in an order that does not depend on timing (the sum is taken in that order).
-    {
-        float* const cv = sm.x.c.v[wv];
-        int* const cp = sm.x.c.pos[wv];
-        int have = 0;
-        auto flush = [&](int least) {
-            int at = 0;
-            __builtin_amdgcn_wave_barrier();   // (a wave's LDS accesses are performed in program order)
-            while (have - at >= least && have > at) {
-                const bool in = at + lane < have;
-                classify(in ? cv[at + lane] : 0.0f, in ? cp[at + lane] : 0, in);
-                at = min(at + 64, have);
+        // the first threshold of a chunk that holds prefix k: at least the smallest score - 1
+        const int jlo = t0 < k ? sm.jmin - R : sm.jlo, jhi = sm.jhi, jl = sm.jl, jh = sm.jh;
+        above = sm.above;
+        const double eps = 1.0 / 8192.0 / (double)res;   // bin() rounds: a score may lie half as much beyond its bin's edges
+        const bool bounded = R > 0 && jhi > 0 && (t0 < k ? sm.jmin > 0 : jlo > 0);
+        lo = (double)origin + (double)jlo / (double)res - eps;
+        hi = (double)origin + (double)jhi / (double)res + eps;
+        // What the second pass would have to list: where the bins are too wide for that, it is not worth its time.  (In the
+        // first window the scores between the bounds hardly ever are too many, and counting them takes time.)
+        auto N = [&](int j) -> unsigned { return j > HBINS - 1 ? 0u : wsum(0, HBINS - 1 - max(j, 0), HBINS - 2 - max(j, 0)) << s; };
+        const bool worth = sm.upto - above <= QL_CAP && (FIRST || N(jlo) - N(jhi) + N(jlo + R) - N(jhi + R) <= TL_CAP);
+        if (uniform(bounded && worth)) {
+            // ---- second pass: count and sum what is certain between the bounds, collect what is not ----
+            // (for an fp32 score v: v > x <=> v > rd(x))
+            lof = __double2float_rd(lo);
+            hif = __double2float_rd(hi);
+            lo1f = __double2float_rd(lo + 1.0);
+            hi1f = __double2float_rd(hi + 1.0);
+            // bins jl .. jh as limits of the value that bin() truncates
+            ql = jl == 0 ? -INFINITY : (float)jl;
+            qh = jh == HBINS - 1 ? INFINITY : (float)(jh + 1);
+            // nothing below this matters
+            const float least = jl == 0 ? -INFINITY : __double2float_rd(fmin(lo, (double)origin + (double)jl / (double)res - eps));
+            csum = 0.0;
+            nM = nF = nC = 0;
+            auto classify = [&](float v, int i, bool in) {
+                const float tb = fmaf(v, res, shift);
+                const bool sat = in && v > hi1f;
+                const bool frac = in && v > hif && v <= lo1f;
+                const bool open = in && v > lof && !sat && !frac;
+                const bool sel = in && tb >= ql;
+                const bool q = sel && tb < qh;
+                nF += (int)__popcll(__ballot(sat && !frac));
+                nC += (int)__popcll(__ballot(frac));
+                csum += (double)(frac ? v : 0.0f);
+                if (survivor && sel && !q) dr[i] = survivor;
+                const unsigned long long bo = __ballot(open), bq = __ballot(q);
+                const unsigned long long below = (1ull << lane) - 1ull;
+                if (bo) {
+                    const int at = nM + (int)__popcll(bo & below);
+                    if (open && at < TL_WAVE) sm.raw[wv][at] = v;
+                    nM += (int)__popcll(bo);
+                }
+                if (bq) {
+                    int off = 0;
+                    if (lane == 0) off = atomicAdd(&sm.nq, (int)__popcll(bq));
+                    off = __builtin_amdgcn_readfirstlane(off) + (int)__popcll(bq & below);
+                    if (q && off < QL_CAP) sm.qk[off] = sel_key(v, i);
+                }
+            };
+            __syncthreads();  // the histograms are no longer needed
+            // Only a few per cent of the scores lie above the lower bound.  Every wave collects its own and looks at them 64 at
+            // a time, in an order that does not depend on timing (the sum is taken in that order).
+            {
+                float* const cv = sm.x.c.v[wv];
+                int* const cp = sm.x.c.pos[wv];
+                int have = 0;
+                auto flush = [&](int least) {
+                    int at = 0;
+                    __builtin_amdgcn_wave_barrier();   // (a wave's LDS accesses are performed in program order)
+                    while (have - at >= least && have > at) {
+                        const bool in = at + lane < have;
+                        classify(in ? cv[at + lane] : 0.0f, in ? cp[at + lane] : 0, in);
+                        at = min(at + 64, have);
+                    }
+                    if (at > 0 && at < have) {   // fewer than 64 are left: to the front
+                        const float v = cv[at + lane];
+                        const int i = cp[at + lane];
+                        __builtin_amdgcn_wave_barrier();
+                        if (lane < have - at) { cv[lane] = v; cp[lane] = i; }
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    have -= at;
+                };
+                each_older(ur, t0, [&](float v, int i, bool in) {
+                    const bool p = in && v > least;
+                    const unsigned long long m = __ballot(p);
+                    const int at = have + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
+                    if (p) { cv[at] = v; cp[at] = i; }
+                    have += (int)__popcll(m);
+                }, [&] { if (have >= 64) flush(64); });
+                flush(1);
             }
-            if (at > 0 && at < have) {   // fewer than 64 are left: to the front
-                const float v = cv[at + lane];
-                const int i = cp[at + lane];
-                __builtin_amdgcn_wave_barrier();
-                if (lane < have - at) { cv[lane] = v; cp[lane] = i; }
+            csum = wave_sum_f64(csum);
+            if (lane == 0) {
+                sm.wsum[wv] = csum;
+                sm.wF[wv] = nF;
+                sm.wC[wv] = nC;
+                sm.wM[wv] = nM;
+                if (nM > TL_WAVE) sm.full = 1;
             }
-            __builtin_amdgcn_wave_barrier();
-            have -= at;
-        };
-        each_older(ur, t0, [&](float v, int i, bool in) {
-            const bool p = in && v > least;
-            const unsigned long long m = __ballot(p);
-            const int at = have + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-            if (p) { cv[at] = v; cp[at] = i; }
-            have += (int)__popcll(m);
-        }, [&] { if (have >= 64) flush(64); });
-        flush(1);
+            __syncthreads();
+            MQ = sm.nq;
+            if (!sm.full && MQ <= QL_CAP) break;
+        }
+        // (every wave writes the same)
+        sm.win = HistWindow{origin, res, covers, bounded, lo, hi};
+        if (bounded) sm.known = ChunkBound{__double2float_rd(lo), true};
+        else if (jl > 0 && !sm.known.tight)
+            sm.known.lo = fmaxf(sm.known.lo, __double2float_rd((double)origin + (double)jl / (double)res - eps - 1.0));
+        if (FIRST) return HIST_NEXT;
     }
-    csum = wave_sum_f64(csum);
-    if (lane == 0) {
-        sm.wsum[wv] = csum;
-        sm.wF[wv] = nF;
-        sm.wC[wv] = nC;
-        sm.wM[wv] = nM;
-        if (nM > TL_WAVE) sm.full = 1;
-    }
-    __syncthreads();
-    const int MQ = sm.nq;
-    if (sm.full || MQ > QL_CAP) return false;
     // totals over the waves, and this wave's place in the list
     const int tM = (int)wave_scan_u32(lane < NW_CHUNK ? (unsigned)sm.wM[lane] : 0u);
     const int M = __builtin_amdgcn_readlane(tM, NW_CHUNK - 1);
@@ -1486,7 +1637,7 @@ __device__ bool mask_chunk_hist(HistSmem& sm, const float* __restrict__ ur, floa
     // Own keys outside the bins of theta need no counting: below them they are dead on arrival, above they outlive the chunk.
     const unsigned long long k0 = sm.ownkey[lane], k1 = sm.ownkey[lane + 64];
     const bool r0 = lane < cn, r1 = lane + 64 < cn;
-    const float tb0 = fmaf(nv0, (float)HRES, shift), tb1 = fmaf(nv1, (float)HRES, shift);
+    const float tb0 = fmaf(nv0, res, shift), tb1 = fmaf(nv1, res, shift);
     if (wv == NW_CHUNK - 1) {
         if (r0 && tb0 < ql) dr[t0 + lane] = j0 + t0 + lane;
         if (r1 && tb1 < ql) dr[t0 + lane + 64] = j0 + t0 + lane + 64;
@@ -1526,7 +1677,17 @@ __device__ bool mask_chunk_hist(HistSmem& sm, const float* __restrict__ ur, floa
             else if (survivor) dr[j] = survivor;
         }
     }
-    return true;
+    return HIST_DONE;
+}
+
+// (not inlined: the registers of the first window stay as they are)
+__device__ __noinline__ int mask_chunk_windows(SPK_LDS HistSmem* sm, const float* __restrict__ ur, float* __restrict__ tr,
+                                               int32_t* __restrict__ dr, int t0, int t1, int k, int* status, int j0,
+                                               int survivor, int tried)
+{
+    return mask_chunk_hist<false>(*(HistSmem*)sm, uniform_global(ur), uniform_global(tr), uniform_global(dr), uniform_int(t0),
+                                  uniform_int(t1), uniform_int(k), uniform_global(status), uniform_int(j0),
+                                  uniform_int(survivor), uniform_int(tried));
 }
 
 union MaskSmem {
@@ -1661,9 +1822,17 @@ __global__ __launch_bounds__(NT_CHUNK, 8) void mask_kernel(ChunkArgs a, int nchu
     if (!chunk_job(a, c, row, J)) return;
     if (a.k == 0 || a.n - J.j0 <= a.k) trivial_deaths(a, J);
     if (a.k == 0) { window_only_chunk((float*)&sm, J); return; }
-    if (mask_chunk_hist(sm.h, J.ur, J.tr, J.dr, J.t0, J.t1, a.k, st, J.j0, J.survivor)) return;
+    int how = mask_chunk_begin(sm.h, J.ur, J.tr, J.t0, J.t1, a.k), tried = 0;
+    if (how == HIST_FIRST) {
+        how = mask_chunk_hist<true>(sm.h, J.ur, J.tr, J.dr, J.t0, J.t1, a.k, st, J.j0, J.survivor, 0);
+        tried = 1;
+    }
+    if (how == HIST_NEXT)
+        how = mask_chunk_windows((SPK_LDS HistSmem*)&sm.h, J.ur, J.tr, J.dr, J.t0, J.t1, a.k, st, J.j0, J.survivor, tried);
+    if (how == HIST_DONE) return;
+    const ChunkBound known = sm.h.known;
     __syncthreads();
-    mask_chunk_sorted(sm.s, J.ur, J.tr, J.dr, J.t0, J.t1, a.k, st, J.j0, J.survivor);
+    mask_chunk_sorted((SPK_LDS SortedSmem*)&sm.s, J.ur, J.tr, J.dr, J.t0, J.t1, a.k, st, J.j0, J.survivor, known);
 }
 
 // ---------------------------------------------------------------------------------

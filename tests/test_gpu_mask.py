@@ -102,6 +102,30 @@ def test_mask_ranges_and_clusters(oracle, n, k, scale, offset):
     check_rows(oracle, (rng.standard_normal((2, n)) * scale + offset).astype(np.float32), k)
 
 
+@pytest.mark.parametrize("n,k,kind,x", [
+    (1500, 200, "scale", 0.001), (1500, 200, "scale", 0.05), (2600, 300, "scale", 0.05), (1500, 200, "scale", 7.0),
+    (2600, 300, "scale", 30.0), (1500, 200, "scale", 1e3), (1500, 200, "scale", 1e5), (2600, 130, "scale", 1e5),
+    (1500, 200, "offset", 20.0), (1500, 200, "offset", -300.0), (1500, 200, "offset", 1e5),
+    (1500, 200, "outlier", 1e3), (1500, 200, "outlier", -1e3),   # a few scores far from an offset of 20
+    (1500, 200, "rising", 50.0), (2600, 300, "falling", 50.0),   # windows that move from chunk to chunk
+    (1500, 200, "halves", 30.0), (1500, 900, "halves", 300.0),   # two clusters, the k-th largest score in either
+    (1400, 600, "levels", 1.0), (2600, 300, "levels", 9.0),      # few values: no window is fine enough; more than 512 sorted
+])
+def test_mask_windows(oracle, n, k, kind, x):
+    """Histogram windows other than the first one, and what none of them suits."""
+    require_gpu()
+    say("mask window", n, k, kind, x)
+    rng = np.random.default_rng(n + k)
+    z = rng.standard_normal((2, n))
+    pos = np.arange(n) / n
+    u = {"scale": z * x, "offset": z + x, "outlier": z + 20.0, "rising": 0.1 * z + x * pos, "falling": 0.1 * z - x * pos,
+         "halves": 0.05 * z + x * (rng.random((2, n)) < 0.5), "levels": np.round(z * 2) / 2 + x}[kind]
+    if kind == "outlier":
+        u[:, rng.integers(0, n, 3)] = x
+    # (a threshold of 256 or more is rounded by up to 2^-16 in fp32, which is more than the lists' gates may be off)
+    check_rows(oracle, u.astype(np.float32), k, sample_t=None if np.abs(u).max() < 256 else [])
+
+
 @pytest.mark.parametrize("n,k,low", [
     (700, 200, [5]),                                # ahead of the chunk that holds prefix k
     (700, 200, [0, 1, 60, 127, 130, 199, 200, 500]),
