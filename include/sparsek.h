@@ -87,7 +87,7 @@ int sparsek_mask_status(const sparsek_cfg *cfg, const void *ws, size_t ws_bytes,
  * be the one that owns u, tau and death.
  * Limit: sparsek_mask_workspace_bytes(cfg) -- B*Gu*ceil(n/2048)*4 bytes and one bit per 128 positions of every score
  * row, each rounded up to 256 bytes, plus 256 (at least 4 bytes per 128 positions up to 8 KiB) -- must not exceed
- * SPARSEK_MASK_STATIC_MAX_BYTES, e.g. 32 rows of 512 K scores;
+ * SPARSEK_MASK_STATIC_MAX_BYTES, e.g. 32 rows of 512 K scores (the kernels use less; the limit is part of the interface);
  * beyond it nothing is enqueued and SPARSEK_ERR_TOO_LARGE is returned.  All calls on one GPU share the array: calls
  * that may overlap (different streams, or threads) race and must be ordered by the caller.  The status word of this
  * variant is not readable. */

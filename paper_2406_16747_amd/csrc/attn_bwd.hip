@@ -638,7 +638,7 @@ static void launch_dq_mfma(const sparsek_cfg& c, const void* q, const void* k, c
 // Because a key is attended on one contiguous range of queries, two kinds of key blocks cover all
 // pairs with one interval test per pair:
 //   window blocks    128 consecutive positions, queries j <= i <= j + w - 1, gate 1;
-//   selected blocks  128 ever-selected keys (death_j > j, listed by death, see abwd_elist_kernel), queries
+//   selected blocks  128 ever-selected keys (death_j > j, listed by death, see abwd_elist), queries
 //                    j + w <= i <= death_j + w - 1, gate clip(u_j - tau_{i-w}).
 // Every key belongs to exactly one window block and at most one selected block, so nothing needs an
 // atomic: a window block stores the final dk, dv rows of the keys that are never selected, and its

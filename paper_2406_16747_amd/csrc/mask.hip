@@ -34,7 +34,9 @@ constexpr size_t STATUS_WORDS = 2048;   // up to this many chunks, each has a st
 static size_t mask_chunks(const sparsek_cfg& c) { return (size_t)c.B * c.Gu * (((size_t)c.n + CHUNK - 1) / CHUNK); }
 static bool mask_shared_status(const sparsek_cfg& c) { return mask_chunks(c) > STATUS_WORDS; }
 
-// Status words (see mask_kernel), never less than one bit per chunk and 4 bytes per 2048 positions of every row.
+// The kernels need the status words alone (see mask_kernel): one for all chunks, or one each up to STATUS_WORDS chunks.
+// The size asked for is never less than one bit per chunk and 4 bytes per 2048 positions of every row: earlier versions of
+// the library used those, and what fits sparsek_mask_static, and what does not, stays the same.
 size_t mask_ws_bytes(const sparsek_cfg& c)
 {
     const size_t rows = (size_t)c.B * c.Gu, chunks = mask_chunks(c);

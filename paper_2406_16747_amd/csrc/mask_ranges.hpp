@@ -1,5 +1,5 @@
-// The fractional ranges of the score gradient: a device function, because it runs in a launch of its own or beside the
-// merge of the attention backward.
+// The fractional ranges of the score gradient: a device function, because it runs in a launch of its own or in the last
+// workgroups of the attention backward's dK/dV kernel.
 #pragma once
 #include "common.hpp"
 

@@ -84,6 +84,19 @@ def test_small_shapes(oracle, n, d, k, w, Gu, dtype, gate_mode):
     run_case(oracle, inp, gate_mode, qk_boost=8.0)
 
 
+@pytest.mark.parametrize("k", [4095, 4096, 4100])
+@pytest.mark.parametrize("Gu", [1, 24])   # a workgroup per block; runs of two blocks, whose lists grow past the limit
+def test_lists_longer_than_lds_holds(oracle, k, Gu):
+    """Up to 4096 entries of a block's list are put together in LDS, longer ones are written in place; blocks of a run then
+    start anew instead of from the list before.  Queries around the first prefixes of k keys, and the last ones."""
+    require_gpu()
+    say("attn long lists", k, Gu)
+    n, w = 5600, 70
+    inp = synth.make(1, Gu=Gu, seed=k, B=1, H=Gu, n=n, d=64, k=k, w=w, dtype="bf16", qk_div=2.0)
+    heads = [(0, 0)] if Gu == 1 else [(0, 5)]
+    run_case(oracle, inp, 0, heads=heads, rows=[(4000, 4008), (4160, 4170), (4220, 4230), (4420, 4424), (n - 8, n)])
+
+
 @pytest.mark.parametrize("dtype,d", [("fp32", 64), ("fp32", 100), ("bf16", 36)])
 def test_generic_kernel_alignment_and_nonfinite_values(oracle, dtype, d):
     """Tensors that start at any element, and values that are not finite: those reach the queries that attend their key

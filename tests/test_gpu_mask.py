@@ -174,14 +174,13 @@ def test_mask_is_deterministic(oracle):
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
 
 
-def test_many_rows_take_the_two_stage_path_and_hand_on_what_does_not_fit(oracle):
-    """With many score rows the chunks first go to the half-capacity kernel, which hands the chunks whose candidates
-    do not fit its lists on to the full-capacity kernel: rows of unit-variance scores stay in the first stage, rows of
-    narrow scores (nearly every score in the support of the threshold) are handed on.  Both kinds must match the
-    oracle, and the call must clear the hand-on bits itself (the workspace starts as garbage)."""
+def test_many_rows_share_a_status_word(oracle):
+    """With more than 2048 chunks all of them share one status word, which the call must clear itself (the workspace
+    starts as garbage).  Rows of unit variance stay in the first histogram window, narrow scores (nearly every score in
+    the support of the threshold) need others, and many equal scores are sorted: all must match the oracle."""
     require_gpu()
     rng = np.random.default_rng(11)
-    rows, n, k = 20, 16384, 300   # 20 x 128 chunks >= 2048
+    rows, n, k = 20, 16384, 300   # 20 x 128 chunks > 2048
     u = rng.standard_normal((rows, n)).astype(np.float32)
     u[3] *= 0.02
     u[17] = (np.round(u[17] * 2) / 2).astype(np.float32) * 0.1   # narrow and full of ties
@@ -193,7 +192,7 @@ def test_many_rows_take_the_two_stage_path_and_hand_on_what_does_not_fit(oracle)
         assert spk.sparsek_mask_status(ud, k, ws) == 0
         tau_g, death_g = host(tau_g).reshape(rows, n), host(death_g).reshape(rows, n)
         for r in (0, 3, 17):
-            say("  two-stage mask, row", r)
+            say("  mask of many rows, row", r)
             tau_r = oracle.tau_incremental(u[r], k)   # pinned against the sort-based routine in the CPU tests
             np.testing.assert_array_equal(death_g[r], oracle.death(u[r], k))
             err = np.abs(tau_g[r].astype(np.float64) - tau_r) / np.maximum(1.0, np.abs(tau_r))
