@@ -4,7 +4,8 @@ Besides the library the build writes libsparsek.toolchain.json: the compiler it 
 the generated code.  Three kernels (attention forward, mask backward, dK/dV) issue direct-to-LDS loads from inline
 assembly that sets the M0 register itself; that is only sound while the compiler keeps no value of its own in M0
 inside those kernels.  The check reads the device assembly of every translation unit and accepts a mention of M0
-only in the three-instruction pattern of those loads.
+only in the three-instruction pattern of those loads.  A second check looks for barriers that an LDS write can reach
+without a wait: the compiler has left such waits out at the head of loops.
 """
 import json
 import os
@@ -65,6 +66,50 @@ def check_m0(asm_path):
     return found
 
 
+def check_waits(asm_path):
+    """Raises if an LDS write or atomic of some kernel can reach a barrier without a wait (s_waitcnt lgkmcnt(0)) on the
+    way: another wave may then read what was there before.  Returns the number of barriers looked at."""
+    count, name, code = 0, None, []
+    for raw in open(asm_path, errors="replace"):
+        ln = raw.split(";")[0].strip()
+        if re.match(r"^[A-Za-z_][\w$.]*:$", ln) and not ln.startswith(".L"):
+            name, code = ln[:-1], []
+        elif raw.startswith(".Lfunc_end"):
+            bad = _barriers_with_writes(code)
+            if bad:
+                raise RuntimeError("%s: an LDS write of kernel %s reaches a barrier without a wait (instruction %d)"
+                                   % (os.path.basename(asm_path), name, bad[0]))
+            count += code.count("s_barrier")
+            code = []
+        elif ln:
+            code.append(ln)
+    return count
+
+
+def _barriers_with_writes(code):
+    """Indexes of the barriers that an LDS write reaches without a wait, over all paths of a function's instructions."""
+    label = {t[:-1]: i for i, t in enumerate(code) if t.endswith(":")}
+    seen = [None] * len(code)   # whether a write may be under way ahead of the instruction
+    work, bad = [(0, False)], set()
+    while work:
+        i, pending = work.pop()
+        while i < len(code) and (seen[i] is None or (pending and not seen[i])):
+            seen[i] = pending
+            op, _, args = code[i].partition(" ")
+            if op.startswith("ds_") and not re.match(r"ds_(read|bpermute|permute|swizzle)", op):
+                pending = True
+            elif op == "s_waitcnt" and "lgkmcnt(0)" in args or op == "s_swappc_b64":   # (a function starts with a wait)
+                pending = False
+            elif op == "s_barrier" and pending:
+                bad.add(i)
+            if re.match(r"s_c?branch", op) and args.strip() in label:
+                work.append((label[args.strip()], pending))
+            if op in ("s_branch", "s_endpgm", "s_setpc_b64"):
+                break
+            i += 1
+    return sorted(bad)
+
+
 def build(verbose=False):
     """Compiles every .hip file and links the shared library.  Always recompiles."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -92,12 +137,13 @@ def build(verbose=False):
     loads = {}
     for src in sources():
         asm = os.path.join(OBJ, src[:-4] + "-hip-amdgcn-amd-amdhsa-gfx950.s")
+        check_waits(asm)
         n = check_m0(asm)
         if n:
             loads[src] = sum(n.values())
     with open(SIDECAR, "w") as f:
         json.dump({"hipcc_version": version.splitlines(), "flags": FLAGS,
-                   "m0_check": "ok", "untracked_direct_to_lds_loads": loads}, f, indent=1)
+                   "m0_check": "ok", "waits_check": "ok", "untracked_direct_to_lds_loads": loads}, f, indent=1)
     keep = {src[:-4] + ".o" for src in sources()}
     for name in os.listdir(OBJ):   # the intermediate files of -save-temps
         if name not in keep:

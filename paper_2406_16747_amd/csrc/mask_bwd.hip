@@ -529,7 +529,8 @@ __global__ __launch_bounds__(256, 2) void mask_bwd_mfma_kernel(
             colsum[tt % 3][c] = 0.0f;
         };
         for (int t = 0; t < ntiles; t++) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            // (lgkmcnt: the compiler leaves out the wait for the column sums still under way, which other waves are about to read)
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
             __syncthreads();  // tile t landed; everybody is done with the MFMAs of tile t-1 and the sums of tile t-2
             if (t + 1 < ntiles) issue_tile_loads<D, 16>(sm, (t + 1) & 1, sm.jpos + (t + 1) * KT, kh, vh, wv, lane);
             if (t >= 2 && tid < KT) flush(t - 2, tid);

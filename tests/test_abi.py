@@ -111,6 +111,24 @@ def test_argument_validation_needs_no_gpu():
     assert L.sparsek_bwd(ctypes.byref(cfg), *([one] * 9), one, one, one, one, one, 8, null) == -3
 
 
+def test_waits_ahead_of_barriers():
+    """No LDS write may reach a barrier without a wait: the compiler has left waits out where the write comes in over a
+    loop's back edge.  The build refuses such code; the library's own has been looked at."""
+    import json
+
+    from paper_2406_16747_amd import build
+
+    if not os.path.exists(build.SIDECAR) or os.path.getmtime(build.SIDECAR) < os.path.getmtime(spk.lib_path()) - 60:
+        build.build()
+    assert json.load(open(build.SIDECAR))["waits_check"] == "ok"
+    loop = [".LBB0_1:", "s_waitcnt vmcnt(0)", "s_barrier", "ds_read_b32 v0, v1", "s_waitcnt lgkmcnt(0)", "ds_add_f32 v1, v0",
+            "s_cbranch_scc1 .LBB0_1", "s_endpgm"]
+    assert build._barriers_with_writes(loop) == [2]
+    assert build._barriers_with_writes(loop[:1] + ["s_waitcnt vmcnt(0) lgkmcnt(0)"] + loop[2:]) == []
+    assert build._barriers_with_writes(["ds_write_b32 v0, v1", "s_cbranch_vccz .LBB0_2", "s_waitcnt lgkmcnt(0)", ".LBB0_2:",
+                                        "s_barrier", "s_endpgm"]) == [4]
+
+
 def test_states_can_be_copied_and_pickled():
     """A caller forks a generation by copying its state; the copy has buffers and a configuration of its own."""
     import copy
