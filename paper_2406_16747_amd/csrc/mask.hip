@@ -1,7 +1,7 @@
 // Stages 1+2: SPARSEK thresholds tau_t for every causal prefix and per-key lifetimes.
 //
 // The paper evaluates the prefixes one after another with two heaps on the CPU (Sec. 3.3, incremental
-// algorithm; App. B.3).  Here the sequence is cut into chunks of CHUNK prefixes that are solved
+// algorithm; App. B.3).  Here the sequence is cut into chunks of up to CHUNK prefixes that are solved
 // independently, one workgroup each, in one launch (mask_kernel):
 //   * tau_t and the k-th largest selection key never decrease once the prefix holds k entries (Sec. 3.2,
 //     irreversibility), so inside a chunk only the scores between two bounds can change anything.
@@ -10,12 +10,12 @@
 //     in integers, without a search.  A second pass adds up the scores that are saturated or fractional
 //     whatever the threshold does inside the bounds and collects the few others (about 120 of 32768
 //     scores of unit variance at k = 1024);
-//   * every wave then solves a few consecutive prefixes: tau_t is the root of f_t(x) = k, found by
-//     repeating the closed form of the solution equation (tau from u*, w* and the fractional sum) until
-//     no breakpoint lies between two iterates -- exact, not an iteration to a tolerance; a bracket
-//     guards it;
+//   * every wave then solves a few consecutive prefixes: tau_t is the root of f_t(x) = k, on the linear piece between
+//     the last breakpoint with f_t >= k and the next (solve_parallel); with too many breakpoints for that, by repeating
+//     the closed form of the solution equation (tau from u*, w* and the fractional sum) until no breakpoint lies between
+//     two iterates -- exact, not an iteration to a tolerance; a bracket guards it;
 //   * key j dies at the first prefix that holds k larger keys: with c older keys above it, at the
-//     (k - c)-th newcomer of the chunk that is larger -- a rank and two ballots per key.
+//     (k - c)-th newcomer of the chunk that is larger -- a rank and a sum over 16 lanes per key.
 // The histogram's window follows the scores, in position and in the width of its bins (next_window).  Chunks that no
 // window suits (many equal scores around the threshold, thresholds of -inf, first thresholds spread over more than 2000)
 // take the sorted path: the candidates above a lower bound are compacted into LDS, sorted once, and the same iteration
@@ -24,12 +24,18 @@
 
 namespace spk {
 
-constexpr int CHUNK = 128;        // prefixes per workgroup of the chunk kernel
-constexpr int NT_CHUNK = 1024;    // threads per workgroup (16 waves, 8 prefixes each)
+constexpr int CHUNK = 128;        // prefixes per workgroup of the chunk kernel, at most
+constexpr int NT_CHUNK = 1024;    // threads per workgroup (16 waves, up to 8 prefixes each)
 constexpr int NW_CHUNK = NT_CHUNK / 64;
 constexpr int CAP = 8192;         // sorted path: candidate capacity in LDS (64 KB of 64-bit keys, 8 KB of prefix sums)
 constexpr int MAX_ITERS = 4096;
 constexpr size_t STATUS_WORDS = 2048;   // up to this many chunks, each has a status word of its own
+
+// Where a chunk reports that a threshold solve hit its iteration cap: a bit of a word.
+struct Status {
+    int* word;
+    int bit;
+};
 
 static size_t mask_chunks(const sparsek_cfg& c) { return (size_t)c.B * c.Gu * (((size_t)c.n + CHUNK - 1) / CHUNK); }
 static bool mask_shared_status(const sparsek_cfg& c) { return mask_chunks(c) > STATUS_WORDS; }
@@ -193,7 +199,7 @@ __device__ __forceinline__ bool own_piece_clear(const ListSorted& L, int t, doub
 // concave, so a one-sided iteration would creep); a bracket [lo_b, hi_b) of the root is kept and
 // a step that leaves it is replaced by its midpoint.
 template <class List>
-__device__ double solve_tau(const List& L, int t, int k, double start, int lane, int* status)
+__device__ double solve_tau(const List& L, int t, int k, double start, int lane, Status status)
 {
     double lo_b = start, hi_b = INFINITY, x = start;
     int pF = -1, pS = -1;
@@ -232,7 +238,7 @@ __device__ double solve_tau(const List& L, int t, int k, double start, int lane,
             x = mid;
         }
     }
-    if (lane == 0) atomicOr(status, 1);
+    if (lane == 0) atomicOr(status.word, status.bit);
     return x;
 }
 
@@ -357,7 +363,7 @@ __device__ __forceinline__ float prefix_min(const ListSorted& L, int t, int lane
 // One wave, thresholds of prefixes [ta, tb) (those longer than k).
 template <class List>
 __device__ void wave_tau(const List& L, const float* __restrict__ ur, float* __restrict__ tr, int ta, int tb,
-                         int k, float start0, int lane, int* status)
+                         int k, float start0, int lane, Status status)
 {
     const float my_u = (ta + lane < tb) ? ur[ta + lane] : 0.0f;  // tb - ta <= 64
     bool have_prev = false;
@@ -389,7 +395,7 @@ __device__ void wave_tau(const List& L, const float* __restrict__ ur, float* __r
 // (the sorted neighbours and one ballot over the chunk's own scores tell).  Only otherwise the
 // piece is evaluated again (eval_sorted), with the two-sided iteration of solve_tau.
 __device__ void wave_tau(const ListSorted& L, const float* __restrict__ ur, float* __restrict__ tr, int ta,
-                         int tb, int k, float start0, int lane, int* status)
+                         int tb, int k, float start0, int lane, Status status)
 {
     const float my_u = (ta + lane < tb) ? ur[ta + lane] : 0.0f;  // tb - ta <= 64
     bool started = false;  // x = tau of the previous prefix
@@ -457,7 +463,7 @@ __device__ void wave_tau(const ListSorted& L, const float* __restrict__ ur, floa
             x = xn;
             P = eval_sorted(L, t, x, lane);
         }
-        if (it == MAX_ITERS && lane == 0) atomicOr(status, 1);
+        if (it == MAX_ITERS && lane == 0) atomicOr(status.word, status.bit);
         if (lane == 0) tr[t] = (float)x;
     }
 }
@@ -614,7 +620,7 @@ constexpr int SLICE_REG = 8;                             // compaction: scores c
 template <class List>
 __device__ void chunk_body(const List& L, const float* __restrict__ ur, float* __restrict__ tr,
                            int32_t* __restrict__ dr, int t0, int t1, int k, float lo, unsigned* hist,
-                           unsigned long long* bc, unsigned long long* th, int* status, int j0, int survivor)
+                           unsigned long long* bc, unsigned long long* th, Status status, int j0, int survivor)
 {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     // theta at the chunk start, by the whole workgroup
@@ -639,7 +645,7 @@ __device__ void chunk_body(const List& L, const float* __restrict__ ur, float* _
 // The same for the sorted list: theta at the chunk start is the k-th sorted key.
 __device__ void chunk_body_sorted(const ListSorted& L, const float* __restrict__ ur, float* __restrict__ tr,
                                   int32_t* __restrict__ dr, int t0, int t1, int k, float lo,
-                                  unsigned long long* th, int* status, int j0, int survivor)
+                                  unsigned long long* th, Status status, int j0, int survivor)
 {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const unsigned long long th_start = (t0 >= k) ? L.key[k - 1] : 0ull;
@@ -764,6 +770,7 @@ __device__ __forceinline__ T* uniform_global(T* p)
     return (T*)(SPK_GLOBAL T*)((unsigned long long)hi << 32 | lo);
 }
 __device__ __forceinline__ int uniform_int(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ Status uniform_status(Status s) { return Status{uniform_global(s.word), uniform_int(s.bit)}; }
 
 // A lower bound of every threshold of a chunk that starts at t0 >= k; tight: a few bins below the first one.
 struct ChunkBound {
@@ -782,14 +789,14 @@ __device__ float theta_bound(SortedSmem& sm, const float* __restrict__ ur, int t
 
 // One chunk by sorting its candidates (whole workgroup).  Positions count from the row's first valid key.
 __device__ __noinline__ void mask_chunk_sorted(SPK_LDS SortedSmem* smem, const float* __restrict__ ur, float* __restrict__ tr,
-                                  int32_t* __restrict__ dr, int t0, int t1, int k, int* status, int j0, int survivor,
+                                  int32_t* __restrict__ dr, int t0, int t1, int k, Status status, int j0, int survivor,
                                   ChunkBound known)
 {
     SortedSmem& sm = *(SortedSmem*)smem;
     ur = uniform_global(ur);
     tr = uniform_global(tr);
     dr = uniform_global(dr);
-    status = uniform_global(status);
+    status = uniform_status(status);
     t0 = uniform_int(t0);
     t1 = uniform_int(t1);
     k = uniform_int(k);
@@ -869,12 +876,14 @@ __device__ __noinline__ void mask_chunk_sorted(SPK_LDS SortedSmem* smem, const f
 }
 
 // ---------------------------------------------------------------------------------
-// The histogram path.  Bounded by latency -- two passes over the prefix, a dozen workgroup barriers, the searches and
-// the newcomers of a wave -- not by bandwidth or arithmetic.  One row of 32768 scores at k = 1024 takes 35 us (late
-// chunks 22 us: histogram 3.9, bounds 2.2, second pass 7.2, sorting the two short lists 3.5, thresholds 4.3, lifetimes
-// 0.9), 32 rows of 16384 take 260 us.  Before, with a lower bound from a 45-point bracket search in a kernel of its own
-// and a sort of all candidates per chunk: 85 us and 390 us.
-// Other scores, 32 rows of 16384, k = 1024: standard deviation 7 in 292 us, 27 in 291, 0.05 in 760, mean 20 in 308.  With
+// The histogram path.  With few chunks it is bounded by latency -- two passes over the prefix, a dozen workgroup barriers --
+// and by the slowest chunk: 30000 cycles for 128 prefixes far into a row (histogram 2000, bounds 4300, second pass 5000,
+// sorting the two short lists 6000, thresholds 8500, lifetimes 3000), 55000 around prefix k, where four times as many scores
+// lie between the bounds.  With many chunks it is bounded by instruction issue (1600 vector instructions per wave and chunk,
+// four fifths of the cycles of a SIMD).  One row of 32768 scores at k = 1024: 32 -> 25 us, 4096 at k = 256: 29 -> 15 us with
+// chunks dealt as launch_mask says, lifetimes by 16 lanes per key and thresholds by interpolation; 32 rows of 16384: 248 ->
+// 227 us.  Before the histogram, with a bracket search and a sort of all candidates per chunk: 85 us and 390 us.
+// Windows that follow the scores, 32 rows of 16384, k = 1024: standard deviation 7 in 292 us, 27 in 291, 0.05 in 760, mean 20 in 308.  With
 // two fixed widths of window and the sorted path for the rest: 716, 834, 3418 and 383; with every chunk sorted: 360, 369,
 // 9185 and 390.  One row of 131072 at k = 16384: 327 us, 13.3 ms with the fixed width.
 // ---------------------------------------------------------------------------------
@@ -915,12 +924,12 @@ struct HistSmem {
     float raw[NW_CHUNK][TL_WAVE];       // per wave: scores between the bounds
     float tl[TL_CAP];                   // the same in descending order
     double pref[BP_CAP + 1];            // sums of the first i of them
-    double bps[BP_CAP];                 // breakpoints, ascending
-    double bsum[BP_CAP];                // at a breakpoint (ascending): sum of the fractional older scores,
-    int bF[BP_CAP], bS[BP_CAP];         // older scores above it + 1, above it
+    double bps[BP_CAP];                 // lower bound, breakpoints, upper bound: ascending
+    double bf[BP_CAP];                  // f of the prefix before the chunk there
     unsigned long long qk[QL_CAP];      // selection keys between the bounds of theta
     float own[CHUNK];
     unsigned long long ownkey[CHUNK];
+    int oc[CHUNK], no;              // own keys between the bounds of theta, their number
     unsigned wscan[4][NW_CHUNK];
     float wmm[2][NW_CHUNK];
     double wsum[NW_CHUNK];
@@ -1031,7 +1040,7 @@ __device__ __forceinline__ double min_saturated(const ListBounded& L, int t, dou
 // is that of wave_tau(ListSorted): the piece is carried from prefix to prefix and only evaluated again when a breakpoint
 // was crossed; prefixes whose newcomer is not above the threshold are passed over.
 __device__ __forceinline__ void wave_tau(const ListBounded& L, float* __restrict__ tr, int ta, int tb, int k, double lo,
-                                         double hi, int* status)
+                                         double hi, Status status)
 {
     const int first = max(ta, k);   // prefixes of at most k entries: written by short_prefix_tau
     if (first >= tb) return;
@@ -1088,7 +1097,7 @@ __device__ __forceinline__ void wave_tau(const ListBounded& L, float* __restrict
             x = xn;
             P = eval_bounded(L, t, x);
         }
-        if (it == MAX_ITERS && L.lane == 0) atomicOr(status, 1);
+        if (it == MAX_ITERS && L.lane == 0) atomicOr(status.word, status.bit);
         // the next prefix whose newcomer is above the threshold
         const int nc = t + 1 - L.t0;
         unsigned long long m0 = __ballot(L.own[0] > x), m1 = __ballot(L.own[1] > x);
@@ -1169,22 +1178,26 @@ __device__ __forceinline__ double wave_scan_f64(double x)
     return x;
 }
 
-// Thresholds of all prefixes of the chunk at once (whole workgroup; wave w owns the prefixes [ta, tb)).  f_t is linear
-// between neighbouring breakpoints and does not increase, so the root lies right of the last breakpoint at which f_t
-// is still at least k:
+// Thresholds of all prefixes of the chunk at once (whole workgroup; wave w owns the prefixes [ta, tb), at most 64).  f_t is
+// linear between neighbouring breakpoints and does not increase, so the root lies right of the last breakpoint at which
+// f_t is still at least k, and f_t there and at the next one say where.  sm.bps: lo, the breakpoints, hi.
 //   1. f_{t0-1} at every breakpoint: two searches in the sorted list and a difference of its prefix sums;
 //   2. every wave adds up what its own newcomers contribute at every breakpoint;
-//   3. every wave takes the sum over the waves before it, adds its newcomers one by one and counts the breakpoints
-//      with f >= k after each;
-//   4. eight lanes per prefix form the piece right of that breakpoint and its root.
-// A misjudged f (rounding, about 1e-13) only matters where the root is that close to the breakpoint, or where f equals
-// k on a flat stretch: a piece without fractional scores has its root at its right end (sup rule).
+//   3. every wave takes the sum over the waves before it, adds its newcomers one by one, counts the breakpoints with
+//      f >= k after each and keeps f at both ends of the piece;
+//   4. a lane per prefix interpolates.
+// The slope of a piece is a number of scores: below one half it is none, and the root of a flat piece at k is its right
+// end (sup rule).  On a flat piece f is a sum of whole numbers, hence exact.  Elsewhere f is off by about 1e-13, and the
+// root by that over the slope.  (The piece's own counts -- searches and a pass over the newcomers per prefix -- took a
+// quarter of the instructions of this function.)
 __device__ __forceinline__ void solve_parallel(HistSmem& sm, const ListBounded& L, float* __restrict__ tr, int ta, int tb,
-                                               int k, double lo, double hi)
+                                               int k, double lo)
 {
     const int tid = threadIdx.x, lane = L.lane, wv = tid >> 6;
-    const int M = L.M, B = sm.nbp;
-    // prefix sums of the sorted list
+    const int M = L.M, B = sm.nbp + 2;
+    // prefix sums of the sorted list (wave 0) beside the searches of the others
+    int S = 0, F = 0;
+    const int bp = tid - 64;
     if (wv == 0) {
         double carry = 0.0;
         if (lane == 0) sm.pref[0] = 0.0;
@@ -1194,23 +1207,24 @@ __device__ __forceinline__ void solve_parallel(HistSmem& sm, const ListBounded& 
             if (m + lane < M) sm.pref[m + lane + 1] = carry + inc;
             carry += __longlong_as_double((long long)readlane_u64((unsigned long long)__double_as_longlong(inc), 63));
         }
+    } else if (bp < B) {
+        const double x = sm.bps[bp];
+        auto above = [&](double y) {   // listed scores above y
+            int a = 0, b = M;
+            while (a < b) {
+                const int m = (a + b) >> 1;
+                if ((double)sm.tl[m] > y) a = m + 1;
+                else b = m;
+            }
+            return a;
+        };
+        S = above(x);
+        F = above(x + 1.0);
     }
     __syncthreads();
-    auto above = [&](double x) {   // listed scores above x
-        int a = 0, b = M;
-        while (a < b) {
-            const int m = (a + b) >> 1;
-            if ((double)sm.tl[m] > x) a = m + 1;
-            else b = m;
-        }
-        return a;
-    };
-    if (tid < B) {
-        const double b = sm.bps[tid];
-        const int S = above(b), F = above(b + 1.0);
-        sm.bS[tid] = S;
-        sm.bF[tid] = F;
-        sm.bsum[tid] = sm.pref[S] - sm.pref[F];
+    if (wv > 0 && bp < B) {
+        const int Fa = L.Fb + F, Sa = L.Fb + L.Cb + S;
+        sm.bf[bp] = (double)Fa + (L.sumb + (sm.pref[S] - sm.pref[F])) - (double)(Sa - Fa) * sm.bps[bp];
     }
     // 2. (registers: breakpoint 64 r + lane)
     double b[BP_REG];
@@ -1233,68 +1247,49 @@ __device__ __forceinline__ void solve_parallel(HistSmem& sm, const ListBounded& 
         if (64 * r < B) sm.x.gain[wv][64 * r + lane] = g[r];
     __syncthreads();
     // 3.
-    double f[BP_REG];
 #pragma unroll
     for (int r = 0; r < BP_REG; r++) {
-        f[r] = -INFINITY;
+        g[r] = -INFINITY;      // f from here on
         if (64 * r >= B) continue;
-        if (64 * r + lane < B) {
-            const int F = L.Fb + sm.bF[64 * r + lane], S = L.Fb + L.Cb + sm.bS[64 * r + lane];
-            f[r] = (double)F + (L.sumb + sm.bsum[64 * r + lane]) - (double)(S - F) * b[r];
-        }
-        for (int w = 0; w < wv; w++) f[r] += sm.x.gain[w][64 * r + lane];
+        if (64 * r + lane < B) g[r] = sm.bf[64 * r + lane];
+        for (int w = 0; w < wv; w++) g[r] += sm.x.gain[w][64 * r + lane];
     }
-    int seg = 0;      // lanes 8 p .. 8 p + 7: breakpoints with f >= k after the wave's newcomer p
-    int count = -1;
+    int seg = 1;                       // lane p: prefix ta + p
+    double f0 = 0.0, f1 = 0.0;
+    int count = 0;
+    double e0 = 0.0, e1 = 0.0;
     for (int s = 0; s < cn; s++) {
         const double us = (double)sm.own[c0 + s];
-        if (uniform(us > lo)) {
+        const bool on = uniform(us > lo);
+        if (on) {
 #pragma unroll
             for (int r = 0; r < BP_REG; r++)
-                if (64 * r < B) f[r] += clip(us - b[r]);
-            count = -1;
+                if (64 * r < B) g[r] += clip(us - b[r]);
         }
-        if (count < 0) {
+        if (on || s == 0) {
             count = 0;
 #pragma unroll
             for (int r = 0; r < BP_REG; r++)
-                if (64 * r < B) count += (int)__popcll(__ballot(f[r] >= (double)k));
+                if (64 * r < B) count += (int)__popcll(__ballot(g[r] >= (double)k));
+            count = min(max(count, 1), B - 1);
+#pragma unroll
+            for (int r = 0; r < BP_REG; r++) {
+                const unsigned long long fr = (unsigned long long)__double_as_longlong(g[r]);
+                if ((count - 1) >> 6 == r) e0 = __longlong_as_double((long long)readlane_u64(fr, (count - 1) & 63));
+                if (count >> 6 == r) e1 = __longlong_as_double((long long)readlane_u64(fr, count & 63));
+            }
         }
-        seg = (lane >> 3) == s ? count : seg;
+        if (lane == s) {
+            seg = count;
+            f0 = e0;
+            f1 = e1;
+        }
     }
     // 4.
-    const int t = ta + (lane >> 3);
-    const double x0 = seg > 0 ? sm.bps[seg - 1] : lo, x1 = seg < B ? sm.bps[seg] : hi;
-    int F, S;
-    double sum;
-    if (seg > 0) {
-        F = sm.bF[seg - 1];
-        S = sm.bS[seg - 1];
-        sum = sm.bsum[seg - 1];
-    } else {
-        S = above(x0);
-        F = above(x0 + 1.0);
-        sum = sm.pref[S] - sm.pref[F];
-    }
-    int fs = 0;       // own scores of prefix t: saturated, above x0 (two counters)
-    double part = 0.0;
-    for (int s = lane & 7; s <= t - L.t0 && s < CHUNK; s += 8) {
-        const double v = (double)sm.own[s];
-        const bool a = v > x0, c = v > x0 + 1.0;
-        fs += (c ? 1 : 0) + (a ? 1 << 16 : 0);
-        part += a && !c ? v : 0.0;
-    }
-#pragma unroll
-    for (int st = 0; st < 3; st++) {   // within groups of 8 lanes: swap neighbours, swap pairs, mirror
-        fs += dpp_i32(fs, st);
-        part += dpp_f64(part, st);
-    }
-    F += L.Fb + (fs & 0xFFFF);
-    S += L.Fb + L.Cb + (fs >> 16);
-    const double fsum = L.sumb + sum + part;
-    double x = S > F ? (fsum + (double)F - (double)k) / (double)(S - F) : x1;
+    const double x0 = sm.bps[seg - 1], x1 = sm.bps[seg], fall = f0 - f1;
+    double x = fall < 0.5 * (x1 - x0) ? x1 : x0 + (f0 - (double)k) / fall * (x1 - x0);
     x = fmin(fmax(x, x0), x1);
-    if ((lane & 7) == 0 && t < tb && t >= k) tr[t] = (float)x;
+    if (ta + lane < tb && ta + lane >= k) tr[ta + lane] = (float)x;
 }
 
 // The window to try after sm.win, from what that one says of the thresholds and of the k-th largest score, if no more than
@@ -1386,12 +1381,11 @@ __device__ __forceinline__ int mask_chunk_begin(HistSmem& sm, const float* __res
 // (tried = 0).  If not DONE, nothing has been written but lifetimes that are written again.
 template <bool FIRST>
 __device__ __forceinline__ int mask_chunk_hist(HistSmem& sm, const float* __restrict__ ur, float* __restrict__ tr,
-                                               int32_t* __restrict__ dr, int t0, int t1, int k, int* status, int j0,
+                                               int32_t* __restrict__ dr, int t0, int t1, int k, Status status, int j0,
                                                int survivor, int tried)
 {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int cn = t1 - t0;
-    const float nv0 = lane < cn ? ur[t0 + lane] : -INFINITY, nv1 = lane + 64 < cn ? ur[t0 + lane + 64] : -INFINITY;
     float origin = -8.0f, res = 128.0f, shift = 0.0f;
     bool covers = false;
     double lo = 0.0, hi = 0.0;
@@ -1413,7 +1407,7 @@ __device__ __forceinline__ int mask_chunk_hist(HistSmem& sm, const float* __rest
         if (tid == 0) { sm.jlo = -1; sm.jhi = -1; sm.jl = t0 >= k ? -1 : 0; sm.jh = -1; sm.upto = t0; sm.above = 0; sm.jmin = 0; sm.nq = 0; sm.nbp = 0; sm.full = 0; }
         __syncthreads();
         each_older(ur, t0, [&](float v, int, bool in) { if (in) atomicAdd(&sm.x.h.hist[bin(v)], 1u); }, [] {});
-        if (tid < cn) atomicAdd(&sm.x.h.own[bin(tid < 64 ? nv0 : nv1)], 1u);  // (waves 0 and 1)
+        if (tid < cn) atomicAdd(&sm.x.h.own[bin(sm.own[tid])], 1u);
         __syncthreads();
         // Suffix counts N_i = #{bin >= i} of the older and of all scores: thread t owns the bins 2047 - 2t, 2046 - 2t.
         const int b0 = HBINS - 1 - 2 * tid;
@@ -1540,6 +1534,17 @@ __device__ __forceinline__ int mask_chunk_hist(HistSmem& sm, const float* __rest
                 }, [&] { if (have >= 64) flush(64); });
                 flush(1);
             }
+            if (wv == NW_CHUNK - 1) {   // own keys between the bounds of theta
+                int at = 0;
+                for (int c = lane; c < CHUNK; c += 64) {
+                    const float tb = fmaf(sm.own[c], res, shift);
+                    const bool on = c < cn && tb >= ql && tb < qh;
+                    const unsigned long long m = __ballot(on);
+                    if (on) sm.oc[at + (int)__popcll(m & ((1ull << lane) - 1ull))] = c;
+                    at += (int)__popcll(m);
+                }
+                if (lane == 0) sm.no = at;
+            }
             csum = wave_sum_f64(csum);
             if (lane == 0) {
                 sm.wsum[wv] = csum;
@@ -1571,8 +1576,6 @@ __device__ __forceinline__ int mask_chunk_hist(HistSmem& sm, const float* __rest
     for (int i = 0; i < NW_CHUNK; i++) L.sumb += sm.wsum[i];
     L.t0 = t0;
     L.lane = lane;
-    L.own[0] = (double)nv0;
-    L.own[1] = (double)nv1;
     {
         // The list in descending order, by rank (equal scores are interchangeable): sums over it then do not depend on
         // the order in which the scores arrived.  Its breakpoints (z and z - 1, where they lie between the bounds) are
@@ -1593,8 +1596,9 @@ __device__ __forceinline__ int mask_chunk_hist(HistSmem& sm, const float* __rest
             add(real && v > lo1f && v <= hi1f, (double)v - 1.0);
         };
         if (nM > 0) add_both(lane < nM, sm.raw[wv][lane]);
-        if (wv < 2) add_both(64 * wv + lane < cn, wv ? nv1 : nv0);
+        if (wv < CHUNK / 64) add_both(tid < cn, sm.own[tid]);
         if (tid < BP_CAP) sm.x.s.btie[tid] = 0;
+        if (tid == 0) sm.bps[0] = lo;
         __syncthreads();
         // G lanes share the counting for one element: each takes a run of q others
         if (M > 0) {
@@ -1603,6 +1607,7 @@ __device__ __forceinline__ int mask_chunk_hist(HistSmem& sm, const float* __rest
             const int g = tid & (G - 1), e = tid / G, q = (M + 4 * G - 1) / (4 * G) * 4;
             const float v = sm.x.s.v[min(e, M - 1)];
             int rank = 0;
+#pragma unroll 4
             for (int j = g * q; j < min(g * q + q, M); j += 4) {
                 const float4 y = *(const float4*)&sm.x.s.v[j];
                 rank += (y.x > v ? 1 : 0) + (y.y > v ? 1 : 0) + (y.z > v ? 1 : 0) + (y.w > v ? 1 : 0);
@@ -1612,83 +1617,86 @@ __device__ __forceinline__ int mask_chunk_hist(HistSmem& sm, const float* __rest
         }
     }
     const int B = sm.nbp;
-    if (B > 0 && B <= BP_CAP) {
+    if (tid == 0 && B <= BP_CAP - 2) sm.bps[B + 1] = hi;
+    if (B > 0 && B <= BP_CAP - 2) {
         int G = 1;
         while (G < 16 && 2 * G * B <= NT_CHUNK) G *= 2;
         const int g = tid & (G - 1), e = tid / G, q = (B + 2 * G - 1) / (2 * G) * 2;
         const double v = sm.x.s.bp[min(e, B - 1)];
         int rank = 0;
+#pragma unroll 4
         for (int j = g * q; j < min(g * q + q, B); j += 2) {
             const double2 y = *(const double2*)&sm.x.s.bp[j];
             rank += (y.x < v ? 1 : 0) + (y.y < v && j + 1 < B ? 1 : 0);
         }
         for (int o = 1; o < G; o <<= 1) rank += __shfl_xor(rank, o, 64);
-        if (e < B && g == 0) sm.bps[rank + atomicAdd(&sm.x.s.btie[rank], 1)] = v;
+        if (e < B && g == 0) sm.bps[1 + rank + atomicAdd(&sm.x.s.btie[rank], 1)] = v;
     }
     __syncthreads();
-    const int TPW = CHUNK / NW_CHUNK;
+    const int TPW = (cn + NW_CHUNK - 1) / NW_CHUNK;
     const int ta = min(t1, t0 + wv * TPW), tb_ = min(t1, ta + TPW);
-    if (B <= BP_CAP && M <= BP_CAP) {
-        solve_parallel(sm, L, tr, ta, tb_, k, lo, hi);
+    if (B <= BP_CAP - 2 && M <= BP_CAP) {
+        solve_parallel(sm, L, tr, ta, tb_, k, lo);
     } else {
+        L.own[0] = (double)sm.own[lane];
+        L.own[1] = (double)sm.own[lane + 64];
 #pragma unroll
         for (int r = 0; r < TL_REG; r++) L.reg[r] = 64 * r + lane < M ? (double)sm.tl[64 * r + lane] : -INFINITY;
         wave_tau(L, tr, ta, tb_, k, lo, hi, status);
     }
     // ---- lifetimes: key j dies at the first prefix that holds k larger keys ----
     // Own keys outside the bins of theta need no counting: below them they are dead on arrival, above they outlive the chunk.
-    const unsigned long long k0 = sm.ownkey[lane], k1 = sm.ownkey[lane + 64];
-    const bool r0 = lane < cn, r1 = lane + 64 < cn;
-    const float tb0 = fmaf(nv0, res, shift), tb1 = fmaf(nv1, res, shift);
-    if (wv == NW_CHUNK - 1) {
-        if (r0 && tb0 < ql) dr[t0 + lane] = j0 + t0 + lane;
-        if (r1 && tb1 < ql) dr[t0 + lane + 64] = j0 + t0 + lane + 64;
-        if (survivor) {
-            if (r0 && tb0 >= qh) dr[t0 + lane] = survivor;
-            if (r1 && tb1 >= qh) dr[t0 + lane + 64] = survivor;
+    if (wv == NW_CHUNK - 1)
+        for (int c = lane; c < cn; c += 64) {
+            const float tb = fmaf(sm.own[c], res, shift);
+            if (tb < ql) dr[t0 + c] = j0 + t0 + c;
+            else if (survivor && tb >= qh) dr[t0 + c] = survivor;
         }
-    }
-    unsigned long long o0 = __ballot(r0 && tb0 >= ql && tb0 < qh), o1 = __ballot(r1 && tb1 >= ql && tb1 < qh);
-    const int no0 = (int)__popcll(o0), no = no0 + (int)__popcll(o1);
-    auto nth_bit = [&](unsigned long long m, int want) {   // position of the want-th set bit, counted from 1
-        const int bef = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-        return (int)__builtin_ctzll(__ballot(((m >> lane) & 1ull) && bef == want - 1));
-    };
-    for (int i = wv; i < MQ + no; i += NW_CHUNK) {
-        const bool own = i >= MQ;
-        int c = -1;
-        if (own) c = i - MQ < no0 ? nth_bit(o0, i - MQ + 1) : 64 + nth_bit(o1, i - MQ - no0 + 1);
-        const unsigned long long key = readlane_u64(own ? sm.ownkey[c] : sm.qk[i], 0);
-        const int j = key_pos(key);
-        int older = above;           // older keys above this one
-        for (int m = 0; m < MQ; m += 64) older += (int)__popcll(__ballot(m + lane < MQ && sm.qk[min(m + lane, MQ - 1)] > key));
-        const int need = k - older;  // the newcomer that pushes it out: the need-th larger one
-        int d = -1;                  // chunk entry at which it dies
+    // The others, 16 lanes each: the lanes share the counting of older keys, and each looks at 8 of the chunk's own.
+    // (A wave per key took 24000 cycles in the chunk of prefix k.)
+    const int no = sm.no, g = tid & 15;
+    for (int e = tid >> 4; e < MQ + no; e += NT_CHUNK / 16) {
+        const int c = e < MQ ? -1 : sm.oc[e - MQ];
+        const unsigned long long key = c < 0 ? sm.qk[e] : sm.ownkey[c];
+        int older = 0;               // listed keys above this one
+        for (int m = g; m < MQ; m += 16) older += sm.qk[m] > key ? 1 : 0;
+        unsigned larger = 0;         // which of its own keys are above it (entries beyond the chunk are above nothing)
+#pragma unroll
+        for (int m = 0; m < 8; m += 2) {
+            const ulonglong2 y = *(const ulonglong2*)&sm.ownkey[8 * g + m];
+            larger |= (y.x > key ? 1u : 0u) << m | (y.y > key ? 2u : 0u) << m;
+        }
+#pragma unroll
+        for (int st = 0; st < 4; st++) older += dpp_i32(older, st);
+        int upto = __popc(larger);   // inclusive sum over the 16 lanes
+        const int mine = upto;
+        upto += SPK_DPP(upto, 0x111);
+        upto += SPK_DPP(upto, 0x112);
+        upto += SPK_DPP(upto, 0x114);
+        upto += SPK_DPP(upto, 0x118);
+        const int total = __shfl(upto, lane | 15, 64);
+        const int need = k - above - older;   // the newcomer that pushes it out: the need-th larger one
+        int d = -1;                           // chunk entry at which it dies
         if (need <= 0) {
-            if (!own) continue;      // out before this chunk
-            d = c;
-        } else {
-            const unsigned long long m0 = __ballot(r0 && k0 > key), m1 = __ballot(r1 && k1 > key);
-            const int n0 = (int)__popcll(m0);
-            if (need <= n0) d = nth_bit(m0, need);
-            else if (need <= n0 + (int)__popcll(m1)) d = 64 + nth_bit(m1, need - n0);
-            if (d >= 0 && own) d = max(d, c);
+            d = g == 0 ? c : -1;              // own: dead on arrival; older: out before this chunk
+        } else if (need <= upto && need > upto - mine) {
+            for (int x = need - (upto - mine); x > 1; x--) larger &= larger - 1u;
+            d = max(8 * g + __builtin_ctz(larger), c);
         }
-        if (lane == 0) {
-            if (d >= 0) dr[j] = j0 + t0 + d;
-            else if (survivor) dr[j] = survivor;
-        }
+        const int j = key_pos(key);
+        if (d >= 0) dr[j] = j0 + t0 + d;
+        else if (survivor && need > total && g == 0) dr[j] = survivor;
     }
     return HIST_DONE;
 }
 
 // (not inlined: the registers of the first window stay as they are)
 __device__ __noinline__ int mask_chunk_windows(SPK_LDS HistSmem* sm, const float* __restrict__ ur, float* __restrict__ tr,
-                                               int32_t* __restrict__ dr, int t0, int t1, int k, int* status, int j0,
+                                               int32_t* __restrict__ dr, int t0, int t1, int k, Status status, int j0,
                                                int survivor, int tried)
 {
     return mask_chunk_hist<false>(*(HistSmem*)sm, uniform_global(ur), uniform_global(tr), uniform_global(dr), uniform_int(t0),
-                                  uniform_int(t1), uniform_int(k), uniform_global(status), uniform_int(j0),
+                                  uniform_int(t1), uniform_int(k), uniform_status(status), uniform_int(j0),
                                   uniform_int(survivor), uniform_int(tried));
 }
 
@@ -1697,8 +1705,8 @@ union MaskSmem {
     SortedSmem s;
 };
 
-// What a workgroup of both kernels does first: its chunk [t0, t1) of row `row`, in positions that count from the row's
-// first valid key (the pointers are moved there; lifetimes count from the row's start, j0 being the difference).
+// What a workgroup does first: its chunk [t0, t1) of row `row`, in positions that count from the row's first valid key
+// (the pointers are moved there; lifetimes count from the row's start, j0 being the difference).
 struct ChunkArgs {
     const float* u;
     float* tau;
@@ -1712,13 +1720,12 @@ struct ChunkJob {
     int32_t* dr;
     int t0, t1, j0, survivor;
 };
-__device__ __forceinline__ bool chunk_job(const ChunkArgs& a, int c, int row, ChunkJob& J)
+__device__ __forceinline__ bool chunk_job(const ChunkArgs& a, int start, int len, int j0, int row, ChunkJob& J)
 {
-    const int j0 = a.first_valid ? a.first_valid[row] : 0;
-    const int t1 = min(a.n, (c + 1) * CHUNK);
+    const int t1 = min(a.n, start + len);
     if (t1 <= a.t_begin) return false;  // nobody asks for these thresholds and lifetimes
-    if (j0 > c * CHUNK) {               // entries before the row's start: never selected, and a finite threshold
-        const int e = c * CHUNK + threadIdx.x;
+    if (j0 > start) {                   // entries before the row's start: never selected, and a finite threshold
+        const int e = start + threadIdx.x;
         if (e < min(t1, j0)) {
             a.tau[(size_t)row * a.n + e] = 0.0f;
             a.death[(size_t)row * a.n + e] = e;
@@ -1728,7 +1735,7 @@ __device__ __forceinline__ bool chunk_job(const ChunkArgs& a, int c, int row, Ch
     J.ur = a.u + (size_t)row * a.n + j0;
     J.tr = a.tau + (size_t)row * a.n + j0;
     J.dr = a.death + (size_t)row * a.n + j0;
-    J.t0 = max(c * CHUNK - j0, 0);
+    J.t0 = max(start - j0, 0);
     J.t1 = t1 - j0;
     J.j0 = j0;
     // every key's lifetime is written once: by the chunk in which it dies or, if it outlives the row, by the last chunk
@@ -1757,9 +1764,6 @@ __device__ void window_only_chunk(float* red, const ChunkJob& J)
                          lane + 64 < cn ? J.ur[J.t0 + lane + 64] : -INFINITY, J.t0, J.t1, 0, lane, J.tr);
 }
 
-// Few chunks: status has one word per chunk, which the chunk's workgroup sets.  Many (shared_status): one word, cleared
-// ahead of this kernel, because a word per chunk would make the workspace grow.  Two workgroups share a compute unit
-// (76 KB of LDS, 64 registers): 256 chunks of one row run at once wherever they land.
 __global__ void mask_clear_status_kernel(int* __restrict__ status) { *status = 0; }
 
 // Rows for the attention that follows (chunked prefill).  A thread keeps its column and moves ROW_UNR rows at a time.
@@ -1804,24 +1808,56 @@ __device__ void copy_rows(const RowCopy& R, int row, int wg)
     }
 }
 
-__global__ __launch_bounds__(NT_CHUNK, 8) void mask_kernel(ChunkArgs a, int nchunks, int* __restrict__ status,
-                                                           int shared_status, RowCopy rows)
+// The chunks of a row: `nchunks` of `len` prefixes each, of which `nsplit` from that of the first prefix of more than k
+// entries on are dealt out in parts of `part`: thresholds move fastest there, and with them the number of scores and
+// breakpoints a chunk has to look at (55000 cycles for 128 prefixes against 30000 further on).
+struct ChunkDeal {
+    int nchunks, len, nsplit, part;
+    int shared_status;   // one status word for all chunks, cleared ahead of the kernel; else 8 bits per PART prefixes
+    __host__ __device__ int most() const { return nchunks + nsplit * (len / part - 1); }   // workgroups per row
+};
+constexpr int PART = 32;   // lengths of chunks and parts are multiples of it
+constexpr int CUS = 256;   // compute units
+
+// OCC: waves per SIMD.  4: a compute unit's registers for one workgroup (nothing spilled); 8: two workgroups share it (76 KB
+// of LDS, 64 registers).
+template <int OCC>
+__global__ __launch_bounds__(NT_CHUNK, OCC) void mask_kernel(ChunkArgs a, ChunkDeal deal, int* __restrict__ status, RowCopy rows)
 {
     __shared__ __align__(16) MaskSmem sm;
-    const int row = blockIdx.y;
-    if ((int)blockIdx.x >= nchunks) {
-        copy_rows(rows, row, blockIdx.x - nchunks);
+    const int row = blockIdx.y, most = deal.most();
+    if ((int)blockIdx.x >= most) {
+        copy_rows(rows, row, blockIdx.x - most);
         return;
     }
-    // late chunks have the longest prefixes: they go first
-    const int c = nchunks - 1 - blockIdx.x;
-    int* st = status;
-    if (!shared_status) {
-        st += (size_t)row * nchunks + c;
-        if (threadIdx.x == 0) *st = 0;
+    const int j0 = a.first_valid ? a.first_valid[row] : 0;
+    int len = deal.len;
+    const int parts = len / deal.part, first = min((a.k + j0) / len, deal.nchunks);
+    const int nsplit = min(deal.nsplit, deal.nchunks - first);
+    // Late chunks have the longest prefixes: they go first.  In a single round those of prefixes of at most k entries, which
+    // end at once, make room ahead of them; in several they fill the last one.
+    const int id = blockIdx.x, total = deal.nchunks + nsplit * (parts - 1), ahead = OCC == 4 ? first : 0;
+    if (id >= total) return;
+    const int c = id < ahead ? id : total - 1 - (id - ahead);
+    int start = c * len;
+    if (c >= first + nsplit * parts) {
+        start = (c - nsplit * (parts - 1)) * len;
+    } else if (c >= first) {
+        start = first * len + (c - first) * deal.part;
+        len = deal.part;
+    }
+    if (start >= a.n) return;   // (parts of the last chunk)
+    Status st{status, 1};
+    if (!deal.shared_status) {
+        const int words = (a.n + CHUNK - 1) / CHUNK;
+        unsigned char* const bytes = (unsigned char*)(status + (size_t)row * words);
+        const int p = start / PART + threadIdx.x, end = start + len >= a.n ? words * (CHUNK / PART) : (start + len) / PART;
+        if (p < end) bytes[p] = 0;
+        st.word = (int*)bytes + start / CHUNK;
+        st.bit = 1 << start % CHUNK / PART * 8;
     }
     ChunkJob J;
-    if (!chunk_job(a, c, row, J)) return;
+    if (!chunk_job(a, start, len, j0, row, J)) return;
     if (a.k == 0 || a.n - J.j0 <= a.k) trivial_deaths(a, J);
     if (a.k == 0) { window_only_chunk((float*)&sm, J); return; }
     int how = mask_chunk_begin(sm.h, J.ur, J.tr, J.t0, J.t1, a.k), tried = 0;
@@ -1885,21 +1921,36 @@ __global__ __launch_bounds__(256) void materialize_kernel(const float* __restric
 int launch_mask(const sparsek_cfg& c, const float* u, float* tau, int32_t* death, void* ws,
                 hipStream_t st, int t_begin, const int32_t* first_valid, const RowCopy* rows)
 {
-    const int nchunks = (c.n + CHUNK - 1) / CHUNK, nrows = c.B * c.Gu;
+    const int nrows = c.B * c.Gu;
     const ChunkArgs a{u, tau, death, c.n, c.k, t_begin, first_valid};
     const bool shared = mask_shared_status(c);
+    // With no more workgroups than compute units nothing shares a compute unit, and the time is that of the slowest chunk:
+    // as short as fits (4 rows of 2000 at k = 128: chunks of 128 in 25 us, 64 in 16.4, 32 in 15.0; 2 rows of 5003: 22.8,
+    // 17.5 and, beyond one round, 27).  Longer ones keep 128 prefixes, split where thresholds move fastest (8 rows of 4096:
+    // 27.3 -> 21.6 us; 32 rows of 2048: 42 -> 35).  Workgroups of 64 registers, two per compute unit, take over
+    // where one round does not do (32 rows of 16384: 227 us against 310 with one per compute unit).  Row copies need the
+    // rest of the chip: chunks stay long beside them.
+    ChunkDeal deal{0, CHUNK, 2, 64, shared ? 1 : 0};
+    if (!rows && (long long)nrows * ((c.n + 31) / 32) <= CUS) deal = ChunkDeal{0, 32, 0, 32, 0};
+    else if (!rows && (long long)nrows * ((c.n + 63) / 64 + 2) <= CUS) deal = ChunkDeal{0, 64, 2, 32, 0};
+    deal.nchunks = (c.n + deal.len - 1) / deal.len;
+    const int idle = t_begin > 0 ? t_begin / deal.len : std::min(c.k, c.n) / deal.len;   // chunks that end at once
+    const bool one_round = (long long)nrows * (deal.most() - idle) <= CUS;
     RowCopy R{};
     if (rows) {
         // The chunks are bound by latency and, with one score row, few: the rows are moved by what is left of the chip
-        // (two workgroups per compute unit) meanwhile.  With many score rows a few workgroups follow each of them.
+        // meanwhile, in pieces small enough that no compute unit is left with a long one (1024 workgroups: 32 K tokens in
+        // chunks of 8192 in 1609 us, 512: 1633, 256: 1660).  With many score rows a few workgroups follow each of them.
         R = *rows;
         const int step = NT_CHUNK / R.unit * ROW_UNR;
         const long long most = (long long)R.heads * ((R.rcap + R.clen + step - 1) / step);
-        const long long idle = (512 - (long long)nrows * (nchunks - t_begin / CHUNK)) / nrows;
-        R.wgs = (int)std::min(most, std::max(idle, 8ll));
+        const long long free = (1024 - (long long)nrows * (deal.most() - idle)) / nrows;
+        R.wgs = (int)std::min(most, std::max(free, 8ll));
     }
     if (shared) hipLaunchKernelGGL(mask_clear_status_kernel, dim3(1), dim3(1), 0, st, (int*)ws);
-    hipLaunchKernelGGL(mask_kernel, dim3(nchunks + R.wgs, nrows), dim3(NT_CHUNK), 0, st, a, nchunks, (int*)ws, shared ? 1 : 0, R);
+    const dim3 grid(deal.most() + R.wgs, nrows);
+    if (one_round) hipLaunchKernelGGL(mask_kernel<4>, grid, dim3(NT_CHUNK), 0, st, a, deal, (int*)ws, R);
+    else hipLaunchKernelGGL(mask_kernel<8>, grid, dim3(NT_CHUNK), 0, st, a, deal, (int*)ws, R);
     return launch_status();
 }
 
@@ -1911,7 +1962,8 @@ int mask_status(const sparsek_cfg& c, const void* ws, int32_t* host_flag, hipStr
         return SPARSEK_ERR_LAUNCH;
     if (hipStreamSynchronize(st) != hipSuccess) return SPARSEK_ERR_LAUNCH;
     *host_flag = 0;
-    for (size_t i = 0; i < count; i++) *host_flag |= words[i];
+    for (size_t i = 0; i < count; i++) *host_flag |= words[i] | words[i] >> 8 | words[i] >> 16 | words[i] >> 24;
+    *host_flag &= 0xFF;   // (a byte per part of a chunk)
     return SPARSEK_OK;
 }
 

@@ -154,6 +154,20 @@ def test_mask_scores_of_minus_infinity(oracle, n, k, low):
         np.testing.assert_allclose(tau_g[real], tau_r[real], rtol=1e-5, atol=1e-5)
 
 
+@pytest.mark.parametrize("rows,n,k", [
+    (2, 4096, 300), (2, 4097, 300),      # the last size of chunks of 32 prefixes, the first of 64
+    (4, 3968, 200), (4, 3969, 200),      # the last size of chunks of 64, the first of 128
+    (8, 4096, 256), (8, 4096, 255),      # one round of workgroups, and more
+    (8, 1050, 1030), (16, 1080, 1030),   # prefix k in the last chunk: parts of it start beyond the end
+    (16, 1100, 1030), (16, 1200, 1020),  # ... or end there; split chunks ahead of the last one
+    (1, 33, 32), (3, 97, 64),
+])
+def test_mask_deal_of_chunks(oracle, rows, n, k):
+    require_gpu()
+    say("mask deal", rows, n, k)
+    check_rows(oracle, scores("drift", np.random.default_rng(rows + n + k), rows, n), k, sample_t=[k - 1, k, n - 1])
+
+
 def test_mask_candidate_overflow_fallback(oracle):
     """More scores above the threshold than the LDS list holds: the kernel must switch to
     its global-memory path and still be exact."""
