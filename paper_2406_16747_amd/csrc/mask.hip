@@ -1874,6 +1874,226 @@ __global__ __launch_bounds__(NT_CHUNK, OCC) void mask_kernel(ChunkArgs a, ChunkD
 }
 
 // ---------------------------------------------------------------------------------
+// Short sequences.  The kernel above is a chain of a dozen dependent phases of a 1024-thread workgroup, 14 us however short
+// the row.  Here a wave solves one prefix on its own, with the row's scores in LDS: a regula falsi in fp32 (a subtraction
+// with clamp and an addition per score and step) ends within half a score of the root, the exact iteration finishes, and
+// a key above its own threshold counts the larger ones.  One barrier.  Two prefixes or four per wave share the first part,
+// but the wave is then the longer chain: one row of 1024 in 10.5, 12.7 and 16.2 us.  The work grows with the square of the
+// length: see launch_mask for the line.
+// ---------------------------------------------------------------------------------
+constexpr int SMALL_WAVES = 4;
+constexpr long long SMALL_WORK = 1ll << 22;   // rows times the square of their length
+constexpr int SMALL_MAX = 2048;    // scores of a row, hence
+constexpr int FALSI_ITERS = 20;
+constexpr int NEWTON_ITERS = 64;   // beyond, only the middle of the bracket, which closes after some 2000 steps at most
+
+// The scores of a prefix: positions before t0 in LDS, from t0 on one per lane.
+struct ListRow {
+    const float* v;
+    int t0, lane;
+    float own;
+};
+
+// f(four scores) for the positions before end (a multiple of 4), 256 at a time; `none` fills up.
+template <typename F>
+__device__ __forceinline__ void each_row4(const float* v, int end, int lane, float none, F&& f)
+{
+    const float4* v4 = (const float4*)v;
+    int i = 0;
+#pragma unroll 2
+    for (; i + 256 <= end; i += 256) f(v4[(i >> 2) + lane]);
+    if (i < end) f(i + 4 * lane < end ? v4[(i >> 2) + lane] : make_float4(none, none, none, none));
+}
+
+__device__ __forceinline__ PieceB eval_bounded(const ListRow& L, int t, double x)
+{
+    // (for an fp32 score v: v > x <=> v > rd(x))
+    const float xf = __double2float_rd(x), x1f = __double2float_rd(x + 1.0);
+    int F = 0, S = 0;
+    double part = 0.0;
+    auto one = [&](float v) {
+        const unsigned long long a = __ballot(v > xf), b = __ballot(v > x1f);
+        S += (int)__popcll(a);
+        F += (int)__popcll(b);
+        part += v > xf && !(v > x1f) ? (double)v : 0.0;
+    };
+    each_row4(L.v, L.t0, L.lane, -INFINITY, [&](float4 z) { one(z.x); one(z.y); one(z.z); one(z.w); });
+    one(L.lane <= t - L.t0 ? L.own : -INFINITY);
+    return PieceB{F, S, wave_sum_f64(part)};
+}
+
+__device__ __forceinline__ double min_saturated(const ListRow& L, int t, double x)
+{
+    const float x1f = __double2float_rd(x + 1.0);
+    float mf = INFINITY;
+    auto one = [&](float v) { mf = fminf(mf, v > x1f ? v : INFINITY); };
+    each_row4(L.v, L.t0, L.lane, -INFINITY, [&](float4 z) { one(z.x); one(z.y); one(z.z); one(z.w); });
+    one(L.lane <= t - L.t0 ? L.own : -INFINITY);
+    return (double)wave_min_f32(mf);
+}
+
+// A point near the threshold of prefix t, between lo (f_t(lo) >= k) and hi (f_t(hi) < k); `count` scores are above lo.
+__device__ __forceinline__ float near_threshold(const ListRow& L, int t, int k, int count, float lo, float hi)
+{
+    const float want = (float)k + 0.5f;
+    float a = lo, b = hi, fa = (float)count - want, fb = -want, x = lo;
+    int side = 0;
+    for (int it = 0; it < FALSI_ITERS; it++) {
+        x = fmaf((b - a) * fa, __builtin_amdgcn_rcpf(fa - fb), a);
+        if (!uniform(x > a && x < b)) x = 0.5f * a + 0.5f * b;
+        float s0 = L.lane <= t - L.t0 ? clip01(L.own - x) : 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
+        each_row4(L.v, L.t0, L.lane, -INFINITY, [&](float4 z) {
+            s0 += clip01(z.x - x);
+            s1 += clip01(z.y - x);
+            s2 += clip01(z.z - x);
+            s3 += clip01(z.w - x);
+        });
+        const float f = wave_sum_f32((s0 + s1) + (s2 + s3)) - want;
+        if (uniform(fabsf(f) <= 0.5f)) break;
+        if (uniform(f > 0.0f)) {      // (the end that stays counts half from the second time on: Illinois)
+            a = x;
+            fa = f;
+            if (side > 0) fb *= 0.5f;
+            side = 1;
+        } else {
+            b = x;
+            fb = f;
+            if (side < 0) fa *= 0.5f;
+            side = -1;
+        }
+    }
+    return x;
+}
+
+// The threshold of prefix t, in [lo, hi); x: a point to start from.  The iteration of solve_tau, with an upper end.
+__device__ __forceinline__ double solve_row(const ListRow& L, int t, int k, double x, double lo, double hi)
+{
+    PieceB P = eval_bounded(L, t, x);
+    for (int it = 0;; it++) {
+        const double f = (double)P.F + P.fsum - (double)(P.S - P.F) * x;
+        const bool left = uniform(!(f < (double)k));
+        double xn = x;
+        bool step = false, piece = false;   // take xn; xn is the root of the piece
+        if (left) lo = x;
+        else hi = x;
+        if (P.S > P.F) {
+            xn = (P.fsum + (double)P.F - (double)k) / (double)(P.S - P.F);
+            if (left && !uniform(xn > x)) return x;   // f(x) == k up to rounding
+            step = piece = uniform(xn >= lo && xn < hi);
+        } else if (left) {                  // flat to the right of x, f == F there
+            xn = min_saturated(L, t, x) - 1.0;        // the next breakpoint
+            if (P.F == k && uniform(xn < hi)) return xn;   // sup of the level set f == k
+            step = uniform(xn < hi);
+        }
+        if (!step || it >= NEWTON_ITERS) {
+            xn = 0.5 * (lo + hi);
+            piece = false;
+            if (!uniform(xn > lo && xn < hi)) return lo;
+        }
+        const PieceB Q = eval_bounded(L, t, xn);
+        if (piece && Q.F == P.F && Q.S == P.S) return xn;
+        P = Q;
+        x = xn;
+    }
+}
+
+__global__ __launch_bounds__(64 * SMALL_WAVES) void mask_small_kernel(const float* __restrict__ u, float* __restrict__ tau,
+                                                                      int32_t* __restrict__ death, int n, int k,
+                                                                      int* __restrict__ status)
+{
+    __shared__ __align__(16) float row_scores[SMALL_MAX];
+    const int row = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int t = ((int)(gridDim.x - 1 - blockIdx.x)) * SMALL_WAVES + wv;   // late prefixes are the longest: first
+    const float* ur = u + (size_t)row * n;
+    // (the status words are never set: solve_row ends by itself)
+    if (t % CHUNK == 0 && lane == 0 && t < n) status[(size_t)row * ((n + CHUNK - 1) / CHUNK) + t / CHUNK] = 0;
+    for (int i = tid; i < (n + 255) / 256 * 256; i += 64 * SMALL_WAVES) row_scores[i] = i < n ? ur[i] : -INFINITY;
+    __syncthreads();
+    if (t >= n) return;
+    ListRow L;
+    L.v = row_scores;
+    L.t0 = t & ~3;
+    L.lane = lane;
+    L.own = L.t0 + lane <= t ? row_scores[L.t0 + lane] : -INFINITY;
+    const bool older = L.t0 + lane < t;             // positions before t among the wave's own
+    const float v = readlane_f32(L.own, t - L.t0);  // the score of position t
+    // ---- threshold ----
+    // of the finite scores: the smallest and the largest
+    float mn = L.t0 + lane <= t ? L.own : INFINITY, mx = L.own;
+    each_row4(row_scores, L.t0, lane, NAN, [&](float4 z) {
+        mn = fminf(mn, fminf(fminf(z.x, z.y), fminf(z.z, z.w)));
+        mx = fmaxf(mx, fmaxf(fmaxf(z.x, z.y), fmaxf(z.z, z.w)));
+    });
+    mn = wave_min_f32(mn);
+    mx = wave_max_f32(mx);
+    float res = mn - 1.0f;                          // of at most k entries
+    if (t >= k) {
+        int count = t + 1, infs = 0;
+        if (uniform(!(mn > -INFINITY && mx < INFINITY))) {
+            count = 0;
+            mn = INFINITY;
+            mx = -INFINITY;
+            auto one = [&](float z) {
+                count += (int)__popcll(__ballot(z > -INFINITY));
+                infs += (int)__popcll(__ballot(z == INFINITY));
+                if (fabsf(z) < INFINITY) { mx = fmaxf(mx, z); mn = fminf(mn, z); }
+            };
+            each_row4(row_scores, L.t0, lane, -INFINITY, [&](float4 z) { one(z.x); one(z.y); one(z.z); one(z.w); });
+            one(L.own);
+            mn = wave_min_f32(mn);
+            mx = wave_max_f32(mx);
+        }
+        if (count < k) {          // f < k everywhere
+            res = -INFINITY;
+        } else if (infs >= k) {   // f >= k everywhere: gate 1 for the infinite scores alone
+            res = mx;
+        } else {
+            const float x = near_threshold(L, t, k, count, mn - 1.0f, mx);
+            res = (float)solve_row(L, t, k, (double)x, (double)mn - 1.0, (double)mx);
+        }
+    }
+    // ---- lifetime of key t ----
+    // Below its own threshold it is not among the k largest on arrival: tau < z_(k).  (res is rounded to fp32: no fp32
+    // number lies between it and the threshold.)
+    int d = t;
+    if (t < k || uniform(v >= res)) {
+        int need = k - (int)__popcll(__ballot(older && L.own >= v));
+        each_row4(row_scores, L.t0, lane, NAN, [&](float4 z) {
+            need -= (int)(__popcll(__ballot(z.x >= v)) + __popcll(__ballot(z.y >= v)) + __popcll(__ballot(z.z >= v)) +
+                          __popcll(__ballot(z.w >= v)));
+        });
+        if (need > 0) {           // the need-th larger newcomer pushes it out
+            d = n;
+            for (int i = t / 256 * 256; i < n; i += 256) {
+                const int j = i + 4 * lane;
+                const float4 z = *(const float4*)&row_scores[j];
+                const int more = (int)(__popcll(__ballot(j > t && z.x > v)) + __popcll(__ballot(j + 1 > t && z.y > v)) +
+                                       __popcll(__ballot(j + 2 > t && z.z > v)) + __popcll(__ballot(j + 3 > t && z.w > v)));
+                if (need > more) {
+                    need -= more;
+                    continue;
+                }
+                for (int j0 = i; j0 < i + 256; j0 += 64) {
+                    const unsigned long long b = __ballot(j0 + lane > t && row_scores[j0 + lane] > v);
+                    const int got = (int)__popcll(b);
+                    if (need <= got) {
+                        const int before = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(b >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b, 0));
+                        d = j0 + (int)__builtin_ctzll(__ballot((b >> lane & 1ull) && before == need - 1));
+                        break;
+                    }
+                    need -= got;
+                }
+                break;
+            }
+        }
+    }
+    if (lane == 0) {
+        tau[(size_t)row * n + t] = res;
+        death[(size_t)row * n + t] = d;
+    }
+}
+
+// ---------------------------------------------------------------------------------
 // Explicit top-k lists (verification aid): one workgroup per (prefix, row).
 // ---------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void materialize_kernel(const float* __restrict__ u,
@@ -1922,6 +2142,13 @@ int launch_mask(const sparsek_cfg& c, const float* u, float* tau, int32_t* death
                 hipStream_t st, int t_begin, const int32_t* first_valid, const RowCopy* rows)
 {
     const int nrows = c.B * c.Gu;
+    // us, this kernel against the chunks: one row of 500 8.5 / 14.3, of 1024 10.5 / 14.6, of 2000 13.0 / 14.6, of 3000 17.4 /
+    // 14.4; four rows of 1024 12.6 / 14.6; 16 of 512 15.0 / 14.8; two of 2000 15.5 / 14.6.
+    if (!rows && !first_valid && t_begin == 0 && c.k >= 1 && c.n > c.k && c.n <= SMALL_MAX && (long long)nrows * c.n * c.n <= SMALL_WORK) {
+        hipLaunchKernelGGL(mask_small_kernel, dim3((c.n + SMALL_WAVES - 1) / SMALL_WAVES, nrows), dim3(64 * SMALL_WAVES), 0, st, u,
+                           tau, death, c.n, c.k, (int*)ws);
+        return launch_status();
+    }
     const ChunkArgs a{u, tau, death, c.n, c.k, t_begin, first_valid};
     const bool shared = mask_shared_status(c);
     // With no more workgroups than compute units nothing shares a compute unit, and the time is that of the slowest chunk:

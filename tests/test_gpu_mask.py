@@ -168,6 +168,36 @@ def test_mask_deal_of_chunks(oracle, rows, n, k):
     check_rows(oracle, scores("drift", np.random.default_rng(rows + n + k), rows, n), k, sample_t=[k - 1, k, n - 1])
 
 
+@pytest.mark.parametrize("kind", ["normal", "ties", "equal", "wide", "huge", "minus_inf", "plus_inf"])
+@pytest.mark.parametrize("rows,n,k", [
+    (1, 2, 1), (3, 5, 4), (1, 64, 63), (2, 257, 1), (1, 2048, 100), (4, 1024, 1023), (4, 1024, 300), (1, 2047, 1500),
+])
+def test_mask_of_short_rows(oracle, kind, rows, n, k):
+    """A wave per prefix: edges of its groups of 4 and 256 positions, the longest row, and scores that are not finite
+    (the oracle gets +-100 in their place: the order is the same, and so is every threshold that the others, all within
+    +-6, determine)."""
+    require_gpu()
+    say("mask short rows", kind, rows, n, k)
+    rng = np.random.default_rng(n + k)
+    u = (rng.standard_normal((rows, n)) * 1e30).astype(np.float32) if kind == "huge" else scores(
+        kind if kind in ("normal", "ties", "equal", "wide") else "normal", rng, rows, n)
+    at = rng.random((rows, n)) < (0.3 if kind == "minus_inf" else 0.01)
+    odd = {"minus_inf": -np.inf, "plus_inf": np.inf}.get(kind)
+    stand_in = u.copy()
+    if odd is not None:
+        u[at], stand_in[at] = odd, np.float32(np.copysign(100.0, odd))
+    ud = dev(u.reshape(1, rows, n))
+    ws = spk.sparsek_mask_workspace(ud, k)
+    ws.fill_(0xFF)
+    tau, death = spk.sparsek_mask(ud, k, ws=ws)
+    assert spk.sparsek_mask_status(ud, k, ws) == 0
+    for r in range(rows):
+        np.testing.assert_array_equal(host(death)[0, r], oracle.death(stand_in[r], k))
+        tau_r, tau_g = oracle.tau_prefixes(stand_in[r], k)[0], host(tau)[0, r].astype(np.float64)
+        real = np.abs(tau_r) < (np.inf if odd is None else 50.0)   # (else the stand-ins determine it)
+        np.testing.assert_allclose(tau_g[real], tau_r[real], rtol=1e-5, atol=1e-5)
+
+
 def test_mask_candidate_overflow_fallback(oracle):
     """More scores above the threshold than the LDS list holds: the kernel must switch to
     its global-memory path and still be exact."""
