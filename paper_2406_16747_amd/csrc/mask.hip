@@ -1827,7 +1827,7 @@ __global__ __launch_bounds__(NT_CHUNK, OCC) void mask_kernel(ChunkArgs a, ChunkD
     __shared__ __align__(16) MaskSmem sm;
     const int row = blockIdx.y, most = deal.most();
     if ((int)blockIdx.x >= most) {
-        copy_rows(rows, row, blockIdx.x - most);
+        if ((int)blockIdx.x - most < rows.wgs) copy_rows(rows, row, blockIdx.x - most);
         return;
     }
     const int j0 = a.first_valid ? a.first_valid[row] : 0;
@@ -2154,15 +2154,22 @@ int launch_mask(const sparsek_cfg& c, const float* u, float* tau, int32_t* death
     // With no more workgroups than compute units nothing shares a compute unit, and the time is that of the slowest chunk:
     // as short as fits (4 rows of 2000 at k = 128: chunks of 128 in 25 us, 64 in 16.4, 32 in 15.0; 2 rows of 5003: 22.8,
     // 17.5 and, beyond one round, 27).  Longer ones keep 128 prefixes, split where thresholds move fastest (8 rows of 4096:
-    // 27.3 -> 21.6 us; 32 rows of 2048: 42 -> 35).  Workgroups of 64 registers, two per compute unit, take over
-    // where one round does not do (32 rows of 16384: 227 us against 310 with one per compute unit).  Row copies need the
-    // rest of the chip: chunks stay long beside them.
+    // 27.3 -> 22 us) while that still is one round.  Workgroups of 64 registers, two per compute unit, take over where one
+    // round does not do (32 rows of 16384: 227 us against 310 with one per compute unit); chunks are split there too (100
+    // rows of 4000 at k = 1000: 186 -> 169 us) unless that takes the second or third round of workgroups (256 rows of 512:
+    // 56 us, 66 in three).  Row copies need the rest of the chip: chunks stay long beside them.
     ChunkDeal deal{0, CHUNK, 2, 64, shared ? 1 : 0};
     if (!rows && (long long)nrows * ((c.n + 31) / 32) <= CUS) deal = ChunkDeal{0, 32, 0, 32, 0};
     else if (!rows && (long long)nrows * ((c.n + 63) / 64 + 2) <= CUS) deal = ChunkDeal{0, 64, 2, 32, 0};
     deal.nchunks = (c.n + deal.len - 1) / deal.len;
     const int idle = t_begin > 0 ? t_begin / deal.len : std::min(c.k, c.n) / deal.len;   // chunks that end at once
-    const bool one_round = (long long)nrows * (deal.most() - idle) <= CUS;
+    const long long whole = (long long)nrows * (deal.nchunks - idle), split = (long long)nrows * (deal.most() - idle);
+    bool one_round = split <= CUS && (long long)nrows * deal.most() <= CUS + CUS / 8;
+    if (!one_round && (long long)nrows * deal.nchunks <= CUS) {
+        deal.nsplit = 0;
+        one_round = true;
+    }
+    if (!one_round && ((whole <= 2 * CUS && split > 2 * CUS) || (whole <= 4 * CUS && split > 4 * CUS))) deal.nsplit = 0;
     RowCopy R{};
     if (rows) {
         // The chunks are bound by latency and, with one score row, few: the rows are moved by what is left of the chip
@@ -2175,7 +2182,10 @@ int launch_mask(const sparsek_cfg& c, const float* u, float* tau, int32_t* death
         R.wgs = (int)std::min(most, std::max(free, 8ll));
     }
     if (shared) hipLaunchKernelGGL(mask_clear_status_kernel, dim3(1), dim3(1), 0, st, (int*)ws);
-    const dim3 grid(deal.most() + R.wgs, nrows);
+    // Workgroups go to the chip's 8 partitions in turn: with a multiple of 4 per row every partition would get the same chunks
+    // of all rows, and the dispatch waits for the one with the long ones (256 rows of 4096: 595 us against 344).
+    const int per_row = deal.most() + R.wgs;
+    const dim3 grid(per_row + (per_row >= 8 && per_row % 4 == 0 ? 1 : 0), nrows);
     if (one_round) hipLaunchKernelGGL(mask_kernel<4>, grid, dim3(NT_CHUNK), 0, st, a, deal, (int*)ws, R);
     else hipLaunchKernelGGL(mask_kernel<8>, grid, dim3(NT_CHUNK), 0, st, a, deal, (int*)ws, R);
     return launch_status();
