@@ -650,17 +650,29 @@ static void launch_dq_mfma(const sparsek_cfg& c, const void* q, const void* k, c
 __device__ __forceinline__ int wave_max_i32(int x)
 {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x = max(x, __shfl_xor(x, o, 64));
-    return x;
+    for (int s = 0; s < 4; s++) x = max(x, dpp_i32(x, s));
+    return max(max(__builtin_amdgcn_readlane(x, 15), __builtin_amdgcn_readlane(x, 31)),
+               max(__builtin_amdgcn_readlane(x, 47), __builtin_amdgcn_readlane(x, 63)));
 }
-__device__ __forceinline__ int wave_min_i32(int x)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x = min(x, __shfl_xor(x, o, 64));
-    return x;
-}
+__device__ __forceinline__ int wave_min_i32(int x) { return ~wave_max_i32(~x); }
 
 __device__ __forceinline__ int b_row(int bh, int H, int Gu) { return (bh / H) * Gu + (Gu == 1 ? 0 : bh % H); }
+
+// S and dO.V go straight to vector registers: the compiler, given accumulation registers, puts every product there, and the
+// elementwise work then reads each value with an instruction of its own (64 of the 224 vector instructions of a tile without
+// gates).  It does not know the latency of these products: mfma_done waits for 24 states, what a product of 16 passes takes
+// to arrive being at most 19, before anything else looks at them.  Their operands come from LDS and from registers that
+// are loaded once, never from a vector instruction just ahead.  64 heads of 8192 at k = w = 512: the backward -18 us of 930.
+template <bool FIRST>
+__device__ __forceinline__ void mfma_v(f32x16& d, const bf16x8& a, const bf16x8& b)
+{
+    if constexpr (FIRST) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "v"(b));
+    else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void mfma_done(f32x16& a, f32x16& b)
+{
+    asm volatile("s_nop 15\n\ts_nop 7" : "+v"(a), "+v"(b));
+}
 
 constexpr int DKV_NBUF = 2;  // tiles in LDS: one in use, one being filled
 template <int D>
@@ -734,11 +746,14 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(
         else { lo = j; hi = min(n - 1, j + w - 1); }
     }
     const bool kvalid = lo <= hi;
-    const int wlo = wave_min_i32(kvalid ? lo : 0x7fffffff);
-    const int whi = wave_max_i32(kvalid ? hi : -1);
+    int wlo = wave_min_i32(kvalid ? lo : 0x7fffffff);
+    int whi = wave_max_i32(kvalid ? hi : -1);
     // a tile inside [wfull_lo, wfull_hi] is attended in full by every key of the wave: no interval tests there
-    const int wfull_lo = wave_max_i32(kvalid ? lo : 0x7fffffff);
-    const int wfull_hi = wave_min_i32(kvalid ? hi : -1);
+    int wfull_lo = wave_max_i32(kvalid ? lo : 0x7fffffff);
+    int wfull_hi = wave_min_i32(kvalid ? hi : -1);
+    // (branches on these are kept vector branches: with scalar ones the compiler copies the 128 accumulators between the
+    // alternatives of every tile)
+    asm volatile("" : "+v"(wlo), "+v"(whi), "+v"(wfull_lo), "+v"(wfull_hi));
     // query i attends this lane's key iff (unsigned)(i - lo_eff) <= span (never for an empty lane)
     const int lo_eff = kvalid ? lo : 0x7fffffff;
     const unsigned span = kvalid ? (unsigned)(hi - lo) : 0u;
@@ -840,8 +855,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(
         constexpr bool GATED = decltype(gated_c)::value, CHECK = decltype(check_c)::value;
         constexpr int buf = decltype(buf_c)::value;
         constexpr bool GK = GATED && MODE == 0, GV = GATED && MODE != 2;
-        const f32x16 zero = {0};
-        f32x16 s0 = zero, d0 = zero, s1 = zero, d1 = zero;
+        f32x16 s0, d0, s1, d1;
         u32x4 pb0[2], dsb0[2], pb1[2], dsb1[2];
         const int rel0 = i_first + 4 * half - lo_eff;
         // operand idx of the tile's 4 * NS MFMAs, in issue order
@@ -897,22 +911,24 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(
         static_for<0, NS>([&](auto mc) {  // run 1
             constexpr int m = decltype(mc)::value;
             const bf16x8 cur = ring[m % DEPTH];
-            if constexpr (m & 1) d0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, vreg[m / 2], m < 2 ? zero : d0, 0, 0, 0);
-            else s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, kreg[m / 2], m < 2 ? zero : s0, 0, 0, 0);
+            if constexpr (m & 1) mfma_v<(m < 2)>(d0, cur, vreg[m / 2]);
+            else mfma_v<(m < 2)>(s0, cur, kreg[m / 2]);
+            if constexpr (m == NS - 1) mfma_done(s0, d0);
             refill(mc);
             __builtin_amdgcn_sched_barrier(0);
         });
         static_for<0, NS>([&](auto mc) {  // run 2
             constexpr int m = decltype(mc)::value;
             const bf16x8 cur = ring[(NS + m) % DEPTH];
-            if constexpr (m & 1) d1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, vreg[m / 2], m < 2 ? zero : d1, 0, 0, 0);
-            else s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, kreg[m / 2], m < 2 ? zero : s1, 0, 0, 0);
+            if constexpr (m & 1) mfma_v<(m < 2)>(d1, cur, vreg[m / 2]);
+            else mfma_v<(m < 2)>(s1, cur, kreg[m / 2]);
             refill(std::integral_constant<int, NS + m>{});
             static_for<0, EPM>([&](auto ec) {
                 element(std::integral_constant<int, 0>{}, std::integral_constant<int, m * EPM + decltype(ec)::value>{}, s0, d0, pb0, dsb0);
             });
             __builtin_amdgcn_sched_barrier(0);
         });
+        mfma_done(s1, d1);
         static_for<0, NS>([&](auto mc) {  // run 3
             constexpr int m = decltype(mc)::value, i2 = m / 2, x = i2 % DB;
             const bf16x8 cur = ring[(2 * NS + m) % DEPTH];
