@@ -694,17 +694,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(
     // ---- block -> (head, query block): heads are dealt to the 8 XCDs so that one head's
     // blocks share an L2; late (long) blocks go first
     int bh, blk;
-    {
-        const int id = blockIdx.x;
-        if (BH % 8 == 0) {
-            const int xcd = id & 7, slot = id >> 3;
-            bh = (slot / nb) * 8 + xcd;
-            blk = nb - 1 - (slot % nb);
-        } else {
-            bh = id / nb;
-            blk = nb - 1 - (id % nb);
-        }
-    }
+    deal_block(blockIdx.x, nb, BH, bh, blk);
     const int b = bh / H, h = bh % H;
     const int row = b * Gu + (Gu == 1 ? 0 : h);
     const int i0 = blk * QB;

@@ -176,6 +176,24 @@ struct TileTraits {
     static constexpr bool MASKC = KIND == TILE_CONT || KIND == TILE_DIAG;
 };
 
+// Workgroup -> (head, query block).  Workgroups go to the chip's 8 partitions in turn: of every 8 heads each partition gets
+// one, so that a head's blocks share an L2; late (long) blocks go first.  The blocks of up to 7 heads that are left over are
+// dealt to all partitions (dealing all blocks so where the number of heads is no multiple of 8: 25 heads of 20000 at
+// k = w = 1024, d = 128 648 us against 605, 36 heads of 5003 133 against 123).
+__device__ __forceinline__ void deal_block(int id, int nb, int BH, int& bh, int& blk)
+{
+    const int whole = BH & ~7;
+    if (id < whole * nb) {
+        const int slot = id >> 3;
+        bh = slot / nb * 8 + (id & 7);
+        blk = nb - 1 - slot % nb;
+    } else {
+        const int rest = id - whole * nb;
+        bh = whole + rest / nb;
+        blk = nb - 1 - rest % nb;
+    }
+}
+
 // What a wave needs to stage a segment of metadata (see TileMeta).
 struct StageSrc {
     const int32_t* xpos;    // extended list of this (row, block): positions, lifetimes, scores

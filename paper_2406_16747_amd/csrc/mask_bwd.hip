@@ -357,17 +357,7 @@ __global__ __launch_bounds__(256, 2) void mask_bwd_mfma_kernel(
     __shared__ float tred[2][4];
     constexpr int DS = D / 16;
     int bh, blk;
-    {
-        const int id = blockIdx.x;
-        if (BH % 8 == 0) {
-            const int xcd = id & 7, slot = id >> 3;
-            bh = (slot / nb) * 8 + xcd;
-            blk = nb - 1 - (slot % nb);
-        } else {
-            bh = id / nb;
-            blk = nb - 1 - (id % nb);
-        }
-    }
+    deal_block(blockIdx.x, nb, BH, bh, blk);
     const int b = bh / H, h = bh % H;
     const int row = b * Gu + (Gu == 1 ? 0 : h);
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);

@@ -142,3 +142,28 @@ def test_config2_shape_reduced_batch(oracle):
     inp = synth.make(2, B=1, H=3)
     run_case(oracle, inp, 0)
     run_case(oracle, inp, 1, qk_boost=8.0, heads=[(0, 1)])
+
+
+@pytest.mark.parametrize("H", [8, 9, 11, 15, 17])
+def test_heads_left_over_by_the_deal_to_partitions(oracle, H):
+    """Of every 8 heads each partition of the chip gets one; the heads left over are dealt block by block.  Forward and all
+    gradients of the last heads of the whole groups and of every head left over."""
+    require_gpu()
+    say("attn heads", H)
+    inp = synth.make(3, with_dO=True, B=1, H=H, n=300, d=64, k=20, w=40, seed=H)
+    heads = [(0, h) for h in range(H // 8 * 8 - 1, H)]
+    run_case(oracle, inp, heads=heads)
+    u = dev(inp["u"])
+    tau, death = spk.sparsek_mask(u, 20)
+    x = [dev(inp[name], True) for name in ("Q", "K", "V", "dO")]
+    o, lse = spk.sparsek_attn_fwd(*x[:3], u, tau, death, 20, 40, 0, inp["scale"])
+    got = spk.sparsek_bwd(*x[:3], u, tau, death, o, lse, x[3], 20, 40, 0, inp["scale"])
+    tau_r, death_r = oracle.mask_all(inp["u"], 20)
+    tau_r = tau_r.astype(np.float32).astype(np.float64)
+    pick = [h for _, h in heads]
+    ref = oracle.attn_bwd(inp["Q32"][:, pick], inp["K32"][:, pick], inp["V32"][:, pick], inp["u"], tau_r, death_r,
+                          inp["dO32"][:, pick], 20, 40, 0, inp["scale"])
+    for name, g, r in zip(("dq", "dk", "dv"), got, ref):
+        assert np.abs(host(g)[:, pick] - r).max() <= 1e-2 * np.abs(r).max(), name
+    du_r, _ = oracle.mask_bwd(inp["Q32"], inp["K32"], inp["V32"], inp["u"], tau_r, death_r, inp["dO32"], 20, 40, 0, inp["scale"])
+    assert np.abs(host(got[3]) - du_r).max() <= 1e-2 * np.abs(du_r).max()
