@@ -882,7 +882,7 @@ __device__ __noinline__ void mask_chunk_sorted(SPK_LDS SortedSmem* smem, const f
 // lie between the bounds.  With many chunks it is bounded by instruction issue (1600 vector instructions per wave and chunk,
 // four fifths of the cycles of a SIMD).  One row of 32768 scores at k = 1024: 32 -> 25 us, 4096 at k = 256: 29 -> 15 us with
 // chunks dealt as launch_mask says, lifetimes by 16 lanes per key and thresholds by interpolation; 32 rows of 16384: 248 ->
-// 227 us.  Before the histogram, with a bracket search and a sort of all candidates per chunk: 85 us and 390 us.
+// 211 us.  Before the histogram, with a bracket search and a sort of all candidates per chunk: 85 us and 390 us.
 // Windows that follow the scores, 32 rows of 16384, k = 1024: standard deviation 7 in 292 us, 27 in 291, 0.05 in 760, mean 20 in 308.  With
 // two fixed widths of window and the sorted path for the rest: 716, 834, 3418 and 383; with every chunk sorted: 360, 369,
 // 9185 and 390.  One row of 131072 at k = 16384: 327 us, 13.3 ms with the fixed width.
@@ -1379,7 +1379,9 @@ __device__ __forceinline__ int mask_chunk_begin(HistSmem& sm, const float* __res
 // One chunk (t0 < t1, k >= 1) by its histogram.  FIRST: in the window [-8, 8) with 128 bins per unit, which suits scores of
 // about unit variance around 0; else in up to WINDOWS others, the first of them after [-8, 8) (tried = 1) or instead of it
 // (tried = 0).  If not DONE, nothing has been written but lifetimes that are written again.
-template <bool FIRST>
+// UNROLL: of the loops that rank the lists; 4 where there are registers for it (with 64 of them 21 values are spilled around
+// those loops, 130 MB of scratch for 32 rows of 16384).
+template <bool FIRST, int UNROLL>
 __device__ __forceinline__ int mask_chunk_hist(HistSmem& sm, const float* __restrict__ ur, float* __restrict__ tr,
                                                int32_t* __restrict__ dr, int t0, int t1, int k, Status status, int j0,
                                                int survivor, int tried)
@@ -1607,7 +1609,7 @@ __device__ __forceinline__ int mask_chunk_hist(HistSmem& sm, const float* __rest
             const int g = tid & (G - 1), e = tid / G, q = (M + 4 * G - 1) / (4 * G) * 4;
             const float v = sm.x.s.v[min(e, M - 1)];
             int rank = 0;
-#pragma unroll 4
+#pragma unroll UNROLL
             for (int j = g * q; j < min(g * q + q, M); j += 4) {
                 const float4 y = *(const float4*)&sm.x.s.v[j];
                 rank += (y.x > v ? 1 : 0) + (y.y > v ? 1 : 0) + (y.z > v ? 1 : 0) + (y.w > v ? 1 : 0);
@@ -1624,7 +1626,7 @@ __device__ __forceinline__ int mask_chunk_hist(HistSmem& sm, const float* __rest
         const int g = tid & (G - 1), e = tid / G, q = (B + 2 * G - 1) / (2 * G) * 2;
         const double v = sm.x.s.bp[min(e, B - 1)];
         int rank = 0;
-#pragma unroll 4
+#pragma unroll UNROLL
         for (int j = g * q; j < min(g * q + q, B); j += 2) {
             const double2 y = *(const double2*)&sm.x.s.bp[j];
             rank += (y.x < v ? 1 : 0) + (y.y < v && j + 1 < B ? 1 : 0);
@@ -1695,7 +1697,7 @@ __device__ __noinline__ int mask_chunk_windows(SPK_LDS HistSmem* sm, const float
                                                int32_t* __restrict__ dr, int t0, int t1, int k, Status status, int j0,
                                                int survivor, int tried)
 {
-    return mask_chunk_hist<false>(*(HistSmem*)sm, uniform_global(ur), uniform_global(tr), uniform_global(dr), uniform_int(t0),
+    return mask_chunk_hist<false, 1>(*(HistSmem*)sm, uniform_global(ur), uniform_global(tr), uniform_global(dr), uniform_int(t0),
                                   uniform_int(t1), uniform_int(k), uniform_status(status), uniform_int(j0),
                                   uniform_int(survivor), uniform_int(tried));
 }
@@ -1862,7 +1864,7 @@ __global__ __launch_bounds__(NT_CHUNK, OCC) void mask_kernel(ChunkArgs a, ChunkD
     if (a.k == 0) { window_only_chunk((float*)&sm, J); return; }
     int how = mask_chunk_begin(sm.h, J.ur, J.tr, J.t0, J.t1, a.k), tried = 0;
     if (how == HIST_FIRST) {
-        how = mask_chunk_hist<true>(sm.h, J.ur, J.tr, J.dr, J.t0, J.t1, a.k, st, J.j0, J.survivor, 0);
+        how = mask_chunk_hist<true, OCC == 4 ? 4 : 1>(sm.h, J.ur, J.tr, J.dr, J.t0, J.t1, a.k, st, J.j0, J.survivor, 0);
         tried = 1;
     }
     if (how == HIST_NEXT)
@@ -2155,8 +2157,8 @@ int launch_mask(const sparsek_cfg& c, const float* u, float* tau, int32_t* death
     // as short as fits (4 rows of 2000 at k = 128: chunks of 128 in 25 us, 64 in 16.4, 32 in 15.0; 2 rows of 5003: 22.8,
     // 17.5 and, beyond one round, 27).  Longer ones keep 128 prefixes, split where thresholds move fastest (8 rows of 4096:
     // 27.3 -> 22 us) while that still is one round.  Workgroups of 64 registers, two per compute unit, take over where one
-    // round does not do (32 rows of 16384: 227 us against 310 with one per compute unit); chunks are split there too (100
-    // rows of 4000 at k = 1000: 186 -> 169 us) unless that takes the second or third round of workgroups (256 rows of 512:
+    // round does not do (32 rows of 16384: 211 us against 310 with one per compute unit); chunks are split there too (100
+    // rows of 4000 at k = 1000: 186 -> 169 us, now 154) unless that takes the second or third round of workgroups (256 rows of 512:
     // 56 us, 66 in three).  Row copies need the rest of the chip: chunks stay long beside them.
     ChunkDeal deal{0, CHUNK, 2, 64, shared ? 1 : 0};
     if (!rows && (long long)nrows * ((c.n + 31) / 32) <= CUS) deal = ChunkDeal{0, 32, 0, 32, 0};
@@ -2183,7 +2185,7 @@ int launch_mask(const sparsek_cfg& c, const float* u, float* tau, int32_t* death
     }
     if (shared) hipLaunchKernelGGL(mask_clear_status_kernel, dim3(1), dim3(1), 0, st, (int*)ws);
     // Workgroups go to the chip's 8 partitions in turn: with a multiple of 4 per row every partition would get the same chunks
-    // of all rows, and the dispatch waits for the one with the long ones (256 rows of 4096: 595 us against 344).
+    // of all rows, and the dispatch waits for the one with the long ones (256 rows of 4096: 595 us against 341).
     const int per_row = deal.most() + R.wgs;
     const dim3 grid(per_row + (per_row >= 8 && per_row % 4 == 0 ? 1 : 0), nrows);
     if (one_round) hipLaunchKernelGGL(mask_kernel<4>, grid, dim3(NT_CHUNK), 0, st, a, deal, (int*)ws, R);
