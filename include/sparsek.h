@@ -66,7 +66,8 @@ const char *sparsek_strerror(int code);
  * u     in  [B,Gu,n] fp32 scores.
  * tau   out [B,Gu,n] fp32: tau[t] = sup{ x : sum_{j<=t} clip(u_j - x, 0, 1) >= min(k, t+1) };
  *           for t+1 <= k this is min(u[0..t]) - 1 (all gates 1); on a flat segment
- *           (w* == u*) it is z_(k) - 1; for k == 0 it is max(u[0..t]) (all gates 0).
+ *           (w* == u*) it is z_(k) - 1; for k == 0 it is max(u[0..t]) (all gates 0); where
+ *           min(k, t+1) >= 1 or more of the scores are +inf it is +inf.
  * death out [B,Gu,n] int32: key j belongs to the top-k of prefix t exactly for
  *           j <= t < death[j]  (death[j] == j: never selected; == n: still selected at the end).
  *           Order of the top-k: larger score first, among equal scores the older key.

@@ -154,6 +154,32 @@ def test_mask_scores_of_minus_infinity(oracle, n, k, low):
         np.testing.assert_allclose(tau_g[real], tau_r[real], rtol=1e-5, atol=1e-5)
 
 
+@pytest.mark.parametrize("rows,n,k,share", [
+    (1, 1024, 8, 0.02), (1, 500, 64, 0.3), (1, 300, 20, 1.0),      # a wave per prefix
+    (8, 1024, 8, 0.02), (40, 500, 64, 0.3), (60, 300, 20, 1.0),    # the same rows in chunks
+    (2, 5000, 300, 0.4),
+])
+def test_mask_scores_of_plus_infinity(oracle, rows, n, k, share):
+    """A threshold is +inf (the sup of all points) exactly from min(k, length) scores of +inf on, however many rows and
+    however long they are; the others are those of finite scores above all others."""
+    require_gpu()
+    say("mask +inf", rows, n, k, share)
+    rng = np.random.default_rng(n + k)
+    u = rng.standard_normal(n).astype(np.float32)
+    at = rng.random(n) < share
+    stand_in = u.copy()
+    u[at], stand_in[at] = np.inf, 100.0
+    tau, death = spk.sparsek_mask(dev(np.repeat(u[None, None], rows, 1)), k)
+    tau_r, death_r = oracle.tau_prefixes(stand_in, k)[0], oracle.death(stand_in, k)
+    sup = np.cumsum(at) >= np.minimum(k, np.arange(n) + 1)
+    assert sup.any()
+    for r in {0, rows - 1}:
+        tau_g = host(tau)[0, r].astype(np.float64)
+        np.testing.assert_array_equal(host(death)[0, r], death_r)
+        np.testing.assert_array_equal(tau_g == np.inf, sup)
+        np.testing.assert_allclose(tau_g[~sup], tau_r[~sup], rtol=1e-5, atol=1e-5)
+
+
 @pytest.mark.parametrize("rows,n,k", [
     (2, 4096, 300), (2, 4097, 300),      # the last size of chunks of 32 prefixes, the first of 64
     (4, 3968, 200), (4, 3969, 200),      # the last size of chunks of 64, the first of 128
