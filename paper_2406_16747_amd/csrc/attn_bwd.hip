@@ -650,9 +650,10 @@ __device__ __forceinline__ int b_row(int bh, int H, int Gu) { return (bh / H) * 
 
 // S and dO.V go straight to vector registers: the compiler, given accumulation registers, puts every product there, and the
 // elementwise work then reads each value with an instruction of its own (64 of the 224 vector instructions of a tile without
-// gates).  It does not know the latency of these products: mfma_done waits for 24 states, what a product of 16 passes takes
-// to arrive being at most 19, before anything else looks at them.  Their operands come from LDS and from registers that
-// are loaded once, never from a vector instruction just ahead.  64 heads of 8192 at k = w = 512: the backward -18 us of 930.
+// gates).  It does not know the latency of these products (8 passes: behind the builtin form it leaves 12 states):
+// mfma_done waits for 24 before anything else looks at them.  Their operands come from LDS and from registers that are
+// loaded once, never from a vector instruction just ahead.  The build reads the generated code and refuses any in which a
+// result or an operand is touched too early (check_products).  64 heads of 8192 at k = w = 512: the backward -18 us of 930.
 template <bool FIRST>
 __device__ __forceinline__ void mfma_v(f32x16& d, const bf16x8& a, const bf16x8& b)
 {

@@ -129,6 +129,45 @@ def test_waits_ahead_of_barriers():
                                         "s_barrier", "s_endpgm"]) == [4]
 
 
+def test_distances_around_hand_written_products():
+    """The compiler does not know that a product written as inline assembly is one: nothing may name its result for 12
+    states, and no vector instruction may write an operand in the 2 states ahead of it.  The build refuses such code."""
+    import json
+
+    from paper_2406_16747_amd import build
+
+    if not os.path.exists(build.SIDECAR) or os.path.getmtime(build.SIDECAR) < os.path.getmtime(spk.lib_path()) - 60:
+        build.build()
+    assert json.load(open(build.SIDECAR))["hand_written_products"] > 0
+    first = (True, "v_mfma_f32_32x32x16_bf16 v[0:15], v[32:35], v[36:39], 0")
+    more = (True, "v_mfma_f32_32x32x16_bf16 v[0:15], v[40:43], v[36:39], v[0:15]")
+    other = (True, "v_mfma_f32_32x32x16_bf16 v[16:31], v[40:43], v[36:39], 0")
+    wait, end = (True, "s_nop 11"), (False, "s_endpgm")
+    use = (False, "v_add_f32_e32 v50, v51, v15")
+
+    def faults(*code):
+        return len(build._products_at_fault([c if isinstance(c, tuple) else (False, c) for c in code] + [end]))
+
+    assert faults("v_mov_b32_e32 v0, v1", first, other, more, wait, use) == 0
+    assert faults(first, (True, "s_nop 10"), use) == 1                                     # read too early
+    assert faults(first, "v_mov_b32_e32 v60, v3", more, wait) == 1                         # copied between two products
+    assert faults(first, "scratch_store_dwordx4 off, v[12:15], off", more, wait) == 1      # ... or spilled
+    assert faults(first, "ds_read_b128 v[14:17], v60", wait) == 1                          # overwritten
+    assert faults(first, (True, more[1].replace("v[40:43]", "v[4:7]")), wait) == 1         # an operand of the next one
+    assert faults(first, (True, more[1].replace("v[0:15]", "v[8:23]")), wait) == 1         # a sum that overlaps
+    assert faults("v_accvgpr_read_b32 v40, a3", "s_nop 0", more, wait) == 1                # an operand written just ahead
+    assert faults("v_accvgpr_read_b32 v40, a3", "s_nop 1", more, wait) == 0
+    assert faults("v_permlane32_swap_b32_e32 v60, v43", more, wait) == 1
+    assert faults("v_cmpx_lt_i32_e32 v60, v61", "s_nop 2", first, wait) == 1
+    assert faults((False, first[1]), (True, other[1].replace("v[40:43]", "v[4:7]")), wait) == 1   # one of the compiler's own
+    assert faults((False, first[1]), use) == 0                                             # ... which it looks after itself
+    loop = [".LBB0_1:", more, "s_cbranch_vccnz .LBB0_1", "s_cbranch_scc0 .LBB0_2", wait, ".LBB0_2:", use]
+    assert faults(*loop) == 1                                                              # on one of two paths
+    assert faults(*loop[:3], wait, ".LBB0_2:", use) == 0
+    assert faults(".LBB0_1:", use, more, "s_cbranch_vccnz .LBB0_1") == 1                   # over a loop's back edge
+    assert faults(".LBB0_1:", use, more, wait, "s_cbranch_vccnz .LBB0_1") == 0
+
+
 def test_states_can_be_copied_and_pickled():
     """A caller forks a generation by copying its state; the copy has buffers and a configuration of its own."""
     import copy
