@@ -219,7 +219,7 @@ __device__ double solve_tau(const List& L, int t, int k, double start, int lane,
         } else {
             lo_b = x;
             if (S == F) {  // flat to the right of x, f == F there
-                if (F == k || minF == INFINITY) return (double)minF - 1.0;  // sup of the level set; k or more scores of +inf
+                if (F == k || (F > k && minF == INFINITY)) return (double)minF - 1.0;  // sup of the level set; k or more of +inf
                 xn = (double)minF - 1.0;                 // F > k: the next breakpoint, still left of the root
                 if (xn < hi_b) { x = xn; continue; }
             } else {
@@ -441,7 +441,7 @@ __device__ void wave_tau(const ListSorted& L, const float* __restrict__ ur, floa
                 lo_b = x;
                 if (P.S == P.F) {  // flat to the right of x, f == F there
                     const double nb = (double)min_saturated(L, t, x, P.a, lane) - 1.0;  // next breakpoint
-                    if (P.F == k || nb == INFINITY) {  // sup of the level set, where the piece changes; k or more of +inf
+                    if (P.F == k || (P.F > k && nb == INFINITY)) {  // sup of the level set, where the piece changes; k or more of +inf
                         x = nb;
                         have = false;
                         break;

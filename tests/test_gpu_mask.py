@@ -132,6 +132,7 @@ def test_mask_windows(oracle, n, k, kind, x):
     (900, 300, [3, 255, 256, 299, 300, 301]),
     (900, 300, list(range(0, 280, 2))),             # fewer than k finite scores until position 440
     (1500, 1153, [7, 1100, 1151, 1152]),
+    (1500, 100, list(range(0, 700))),               # no finite score until position 700
 ])
 def test_mask_scores_of_minus_infinity(oracle, n, k, low):
     """Padding scored -inf is selected while there are fewer than k other keys, and every lifetime is written.  The
