@@ -225,6 +225,24 @@ def test_mask_of_short_rows(oracle, kind, rows, n, k):
         np.testing.assert_allclose(tau_g[real], tau_r[real], rtol=1e-5, atol=1e-5)
 
 
+@pytest.mark.parametrize("rows,n,k,offset", [
+    (1, 2048, 1500, 1e5), (4, 1024, 300, 1e5), (16, 512, 64, 1e5), (16, 512, 64, -2e6), (64, 250, 16, 20.0),
+])
+def test_mask_of_short_rows_far_from_zero(oracle, rows, n, k, offset):
+    """Scores whose fp32 spacing is coarse: the search for a starting point runs out of numbers between its ends, and
+    f_t at a root is k up to rounding from either side.  The threshold is the root rounded to fp32 (half its spacing,
+    beside which the fp64 error, n * 2^-53 * |offset|, is nothing)."""
+    require_gpu()
+    say("mask short rows far from zero", rows, n, k, offset)
+    u = (np.random.default_rng(n + k).standard_normal((rows, n)) + offset).astype(np.float32)
+    tau, death = spk.sparsek_mask(dev(u[None]), k)
+    for r in range(rows):
+        np.testing.assert_array_equal(host(death)[0, r], oracle.death(u[r], k))
+        tau_r = oracle.tau_prefixes(u[r], k)[0]
+        half = 0.5 * np.spacing(np.abs(u).max())
+        assert np.abs(host(tau)[0, r].astype(np.float64) - tau_r).max() <= 1.01 * half, r
+
+
 def test_mask_candidate_overflow_fallback(oracle):
     """More scores above the threshold than the LDS list holds: the kernel must switch to
     its global-memory path and still be exact."""
