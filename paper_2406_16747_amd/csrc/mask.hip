@@ -1692,12 +1692,15 @@ __device__ __forceinline__ int mask_chunk_hist(HistSmem& sm, const float* __rest
     return HIST_DONE;
 }
 
-// (not inlined: the registers of the first window stay as they are)
+// (not inlined: the registers of the first window stay as they are.  An instance per register budget: one for both kernels
+// keeps to 64 registers in either and spills around all its loops.  us, before and with it: 32 rows of 16384 around 20 319 /
+// 287, one of 32768 39.8 / 27.7, 8 of 4096 31 / 24.)
+template <int OCC>
 __device__ __noinline__ int mask_chunk_windows(SPK_LDS HistSmem* sm, const float* __restrict__ ur, float* __restrict__ tr,
                                                int32_t* __restrict__ dr, int t0, int t1, int k, Status status, int j0,
                                                int survivor, int tried)
 {
-    return mask_chunk_hist<false, 1>(*(HistSmem*)sm, uniform_global(ur), uniform_global(tr), uniform_global(dr), uniform_int(t0),
+    return mask_chunk_hist<false, OCC == 4 ? 4 : 1>(*(HistSmem*)sm, uniform_global(ur), uniform_global(tr), uniform_global(dr), uniform_int(t0),
                                   uniform_int(t1), uniform_int(k), uniform_status(status), uniform_int(j0),
                                   uniform_int(survivor), uniform_int(tried));
 }
@@ -1868,7 +1871,7 @@ __global__ __launch_bounds__(NT_CHUNK, OCC) void mask_kernel(ChunkArgs a, ChunkD
         tried = 1;
     }
     if (how == HIST_NEXT)
-        how = mask_chunk_windows((SPK_LDS HistSmem*)&sm.h, J.ur, J.tr, J.dr, J.t0, J.t1, a.k, st, J.j0, J.survivor, tried);
+        how = mask_chunk_windows<OCC>((SPK_LDS HistSmem*)&sm.h, J.ur, J.tr, J.dr, J.t0, J.t1, a.k, st, J.j0, J.survivor, tried);
     if (how == HIST_DONE) return;
     const ChunkBound known = sm.h.known;
     __syncthreads();
