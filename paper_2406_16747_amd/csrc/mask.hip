@@ -2013,7 +2013,9 @@ __global__ __launch_bounds__(64 * SMALL_WAVES) void mask_small_kernel(const floa
 {
     __shared__ __align__(16) float row_scores[SMALL_MAX];
     const int row = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int t = ((int)(gridDim.x - 1 - blockIdx.x)) * SMALL_WAVES + wv;   // late prefixes are the longest: first
+    const int last = (n + SMALL_WAVES - 1) / SMALL_WAVES - 1;
+    if ((int)blockIdx.x > last) return;
+    const int t = (last - (int)blockIdx.x) * SMALL_WAVES + wv;   // late prefixes are the longest: first
     const float* ur = u + (size_t)row * n;
     // (the status words are never set: solve_row ends by itself)
     if (t % CHUNK == 0 && lane == 0 && t < n) status[(size_t)row * ((n + CHUNK - 1) / CHUNK) + t / CHUNK] = 0;
@@ -2155,8 +2157,11 @@ int launch_mask(const sparsek_cfg& c, const float* u, float* tau, int32_t* death
     // us, this kernel against the chunks: one row of 500 8.5 / 14.3, of 1024 10.5 / 14.6, of 2000 13.0 / 14.6, of 3000 17.4 /
     // 14.4; four rows of 1024 12.6 / 14.6; 16 of 512 15.0 / 14.8; two of 2000 15.5 / 14.6.
     if (!rows && !first_valid && t_begin == 0 && c.k >= 1 && c.n > c.k && c.n <= SMALL_MAX && (long long)nrows * c.n * c.n <= SMALL_WORK) {
-        hipLaunchKernelGGL(mask_small_kernel, dim3((c.n + SMALL_WAVES - 1) / SMALL_WAVES, nrows), dim3(64 * SMALL_WAVES), 0, st, u,
-                           tau, death, c.n, c.k, (int*)ws);
+        // (an odd number of workgroups per row where not all have room at once, as below: 256 rows of 64 at k = 32 19.0 -> 14.5
+        // us, 128 of 128 at k = 64 20.5 -> 14.9)
+        const int quads = (c.n + SMALL_WAVES - 1) / SMALL_WAVES, odd = (long long)nrows * quads > 8 * CUS ? 1 : 0;
+        hipLaunchKernelGGL(mask_small_kernel, dim3(quads | odd, nrows), dim3(64 * SMALL_WAVES), 0, st, u, tau, death, c.n, c.k,
+                           (int*)ws);
         return launch_status();
     }
     const ChunkArgs a{u, tau, death, c.n, c.k, t_begin, first_valid};
@@ -2192,10 +2197,17 @@ int launch_mask(const sparsek_cfg& c, const float* u, float* tau, int32_t* death
         R.wgs = (int)std::min(most, std::max(free, 8ll));
     }
     if (shared) hipLaunchKernelGGL(mask_clear_status_kernel, dim3(1), dim3(1), 0, st, (int*)ws);
-    // Workgroups go to the chip's 8 partitions in turn: with a multiple of 4 per row every partition would get the same chunks
-    // of all rows, and the dispatch waits for the one with the long ones (256 rows of 4096: 595 us against 341).
-    const int per_row = deal.most() + R.wgs;
-    const dim3 grid(per_row + (per_row >= 8 && per_row % 4 == 0 ? 1 : 0), nrows);
+    // Workgroups go to the chip's 8 partitions in turn, and there to 4 groups of 8 compute units: with a multiple of 4 per row
+    // every partition would get the same chunks of all rows, and the dispatch, once it has to wait for room, waits for the one
+    // with the long ones.  An odd number is the best of the small ones (2048 rows of 400 at k = 200 take 454 us with 4 per row,
+    // 322 with 5, 350 with 6, 890 with 8), and next to a multiple of 32 the rows move on too little (150 rows of 3830 at
+    // k = 821 with 30 to 34: 212, 221, 316, 244, 213).  Where all have room at once, or fill it exactly twice, empty ones would
+    // only take it away (21 rows of 3000 at k = 50 with 24: 26 us, 25: 34; 256 of 512 with 4: 55, 5: 59).
+    int per_row = deal.most() + R.wgs;
+    const long long total = (long long)nrows * per_row, room = (one_round ? 1 : 2) * CUS;
+    auto poor = [](int p) { return p < 30 ? p > 1 && p % 2 == 0 : p % 4 == 0 || (p + 1) % 32 <= 2; };
+    while (total > room && (total != 2 * room || per_row >= 8) && poor(per_row)) per_row++;
+    const dim3 grid(per_row, nrows);
     if (one_round) hipLaunchKernelGGL(mask_kernel<4>, grid, dim3(NT_CHUNK), 0, st, a, deal, (int*)ws, R);
     else hipLaunchKernelGGL(mask_kernel<8>, grid, dim3(NT_CHUNK), 0, st, a, deal, (int*)ws, R);
     return launch_status();

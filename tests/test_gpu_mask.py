@@ -33,7 +33,8 @@ def scores(kind, rng, rows, n):
     raise ValueError(kind)
 
 
-def check_rows(oracle, u, k, sample_t=None):
+def check_rows(oracle, u, k, sample_t=None, every=1):
+    """`every`: of many rows, look at the first, the last and each so many in between."""
     rows, n = u.shape
     ud = dev(u.reshape(rows, 1, n))
     ws = spk.sparsek_mask_workspace(ud, k)
@@ -41,7 +42,8 @@ def check_rows(oracle, u, k, sample_t=None):
     tau_g, death_g = spk.sparsek_mask(ud, k, ws=ws)
     assert spk.sparsek_mask_status(ud, k, ws) == 0  # every threshold solve converged
     tau_g, death_g = host(tau_g).reshape(rows, n), host(death_g).reshape(rows, n)
-    for r in range(rows):
+    looked_at = sorted({*range(0, rows, every), rows - 1})
+    for r in looked_at:
         tau_r, us, ws = oracle.tau_prefixes(u[r], k)
         death_r = oracle.death(u[r], k)
         np.testing.assert_array_equal(death_g[r], death_r)
@@ -53,7 +55,7 @@ def check_rows(oracle, u, k, sample_t=None):
         idx, gate = spk.sparsek_materialize(ud, dev(tau_g.reshape(rows, 1, n)), dev(death_g.reshape(rows, 1, n)),
                                             k, t, t + 1)
         idx, gate = host(idx).reshape(rows, -1), host(gate).reshape(rows, -1)
-        for r in range(rows):
+        for r in looked_at:
             want = oracle.select_prefix(u[r], t, k)
             got = idx[r][idx[r] >= 0]
             np.testing.assert_array_equal(got, want)
@@ -188,16 +190,19 @@ def test_mask_scores_of_plus_infinity(oracle, rows, n, k, share):
     (8, 1050, 1030), (16, 1080, 1030),   # prefix k in the last chunk: parts of it start beyond the end
     (16, 1100, 1030), (16, 1200, 1020),  # ... or end there; split chunks ahead of the last one
     (1, 33, 32), (3, 97, 64),
+    (40, 3830, 300), (50, 3000, 100),    # several rounds: numbers of workgroups per row that are passed over
 ])
 def test_mask_deal_of_chunks(oracle, rows, n, k):
     require_gpu()
     say("mask deal", rows, n, k)
-    check_rows(oracle, scores("drift", np.random.default_rng(rows + n + k), rows, n), k, sample_t=[k - 1, k, n - 1])
+    check_rows(oracle, scores("drift", np.random.default_rng(rows + n + k), rows, n), k, sample_t=[k - 1, k, n - 1],
+               every=rows // 16 + 1)
 
 
 @pytest.mark.parametrize("kind", ["normal", "ties", "equal", "wide", "huge", "minus_inf", "plus_inf"])
 @pytest.mark.parametrize("rows,n,k", [
     (1, 2, 1), (3, 5, 4), (1, 64, 63), (2, 257, 1), (1, 2048, 100), (4, 1024, 1023), (4, 1024, 300), (1, 2047, 1500),
+    (140, 64, 40), (600, 30, 9),         # more workgroups than have room at once: an odd number per row
 ])
 def test_mask_of_short_rows(oracle, kind, rows, n, k):
     """A wave per prefix: edges of its groups of 4 and 256 positions, the longest row, and scores that are not finite
@@ -218,9 +223,10 @@ def test_mask_of_short_rows(oracle, kind, rows, n, k):
     ws.fill_(0xFF)
     tau, death = spk.sparsek_mask(ud, k, ws=ws)
     assert spk.sparsek_mask_status(ud, k, ws) == 0
+    tau, death = host(tau)[0], host(death)[0]
     for r in range(rows):
-        np.testing.assert_array_equal(host(death)[0, r], oracle.death(stand_in[r], k))
-        tau_r, tau_g = oracle.tau_prefixes(stand_in[r], k)[0], host(tau)[0, r].astype(np.float64)
+        np.testing.assert_array_equal(death[r], oracle.death(stand_in[r], k))
+        tau_r, tau_g = oracle.tau_prefixes(stand_in[r], k)[0], tau[r].astype(np.float64)
         real = np.abs(tau_r) < (np.inf if odd is None else 50.0)   # (else the stand-ins determine it)
         np.testing.assert_allclose(tau_g[real], tau_r[real], rtol=1e-5, atol=1e-5)
 
