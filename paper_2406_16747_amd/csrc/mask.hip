@@ -2150,6 +2150,24 @@ __global__ __launch_bounds__(256) void materialize_kernel(const float* __restric
     }
 }
 
+// A workgroup per compute unit at a time: do they get one each, all but the first `idle` of every row, which end at once?
+// Workgroups go to GROUPS groups of compute units in turn, and one too many in a group waits for a whole chunk: 9 rows of 3500
+// at k = 256 take 34 us with the chunks around prefix k split and 27 without, 16 of 2048 33 with two of them split, 24 with
+// one.  One that waits for an idle one starts late, which shows where rows are many or a group has nothing to spare (30 rows
+// of 1024 at k = 128, 8.4 per group: 33 us, 27 with 7.5) and does not pay without a split (6 rows of 5425 at k = 256: 29 us, 26 in
+// two rounds of split chunks).
+constexpr int GROUPS = 32;
+static bool fits_one_round(const ChunkDeal& deal, int nrows, int idle)
+{
+    const int per_row = deal.most();
+    const long long total = (long long)nrows * per_row;
+    if (total > CUS + (deal.nsplit > 0 ? CUS / 8 : 0)) return false;
+    int load[GROUPS] = {}, most = 0;
+    for (int r = 0; r < nrows; r++)
+        for (int i = idle; i < per_row; i++) most = std::max(most, ++load[(r * per_row + i) % GROUPS]);
+    return most <= CUS / GROUPS - (total > CUS + (nrows <= 16 ? CUS / 16 : 0) ? 1 : 0);
+}
+
 int launch_mask(const sparsek_cfg& c, const float* u, float* tau, int32_t* death, void* ws,
                 hipStream_t st, int t_begin, const int32_t* first_valid, const RowCopy* rows)
 {
@@ -2169,7 +2187,7 @@ int launch_mask(const sparsek_cfg& c, const float* u, float* tau, int32_t* death
     // With no more workgroups than compute units nothing shares a compute unit, and the time is that of the slowest chunk:
     // as short as fits (4 rows of 2000 at k = 128: chunks of 128 in 25 us, 64 in 16.4, 32 in 15.0; 2 rows of 5003: 22.8,
     // 17.5 and, beyond one round, 27).  Longer ones keep 128 prefixes, split where thresholds move fastest (8 rows of 4096:
-    // 27.3 -> 22 us) while that still is one round.  Workgroups of 64 registers, two per compute unit, take over where one
+    // 27.3 -> 22 us) while that still is one round (fits_one_round).  Workgroups of 64 registers, two per compute unit, take over where one
     // round does not do (32 rows of 16384: 211 us against 310 with one per compute unit); chunks are split there too (100
     // rows of 4000 at k = 1000: 186 -> 169 us, now 154) unless that takes the second or third round of workgroups (256 rows of 512:
     // 56 us, 66 in three).  Row copies need the rest of the chip: chunks stay long beside them.
@@ -2179,11 +2197,10 @@ int launch_mask(const sparsek_cfg& c, const float* u, float* tau, int32_t* death
     deal.nchunks = (c.n + deal.len - 1) / deal.len;
     const int idle = t_begin > 0 ? t_begin / deal.len : std::min(c.k, c.n) / deal.len;   // chunks that end at once
     const long long whole = (long long)nrows * (deal.nchunks - idle), split = (long long)nrows * (deal.most() - idle);
-    bool one_round = split <= CUS && (long long)nrows * deal.most() <= CUS + CUS / 8;
-    if (!one_round && (long long)nrows * deal.nchunks <= CUS) {
-        deal.nsplit = 0;
-        one_round = true;
-    }
+    const int asked = deal.nsplit;
+    while (deal.nsplit > 0 && !fits_one_round(deal, nrows, idle)) deal.nsplit--;
+    const bool one_round = fits_one_round(deal, nrows, idle);
+    if (!one_round) deal.nsplit = asked;
     if (!one_round && ((whole <= 2 * CUS && split > 2 * CUS) || (whole <= 4 * CUS && split > 4 * CUS))) deal.nsplit = 0;
     RowCopy R{};
     if (rows) {

@@ -190,6 +190,7 @@ def test_mask_scores_of_plus_infinity(oracle, rows, n, k, share):
     (8, 1050, 1030), (16, 1080, 1030),   # prefix k in the last chunk: parts of it start beyond the end
     (16, 1100, 1030), (16, 1200, 1020),  # ... or end there; split chunks ahead of the last one
     (1, 33, 32), (3, 97, 64),
+    (16, 2048, 256), (9, 3500, 256),     # one round with one split chunk instead of two, with none
     (40, 3830, 300), (50, 3000, 100),    # several rounds: numbers of workgroups per row that are passed over
 ])
 def test_mask_deal_of_chunks(oracle, rows, n, k):
