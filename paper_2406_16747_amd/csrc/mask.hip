@@ -2190,18 +2190,27 @@ int launch_mask(const sparsek_cfg& c, const float* u, float* tau, int32_t* death
     // 27.3 -> 22 us) while that still is one round (fits_one_round).  Workgroups of 64 registers, two per compute unit, take over where one
     // round does not do (32 rows of 16384: 211 us against 310 with one per compute unit); chunks are split there too (100
     // rows of 4000 at k = 1000: 186 -> 169 us, now 154) unless that takes the second or third round of workgroups (256 rows of 512:
-    // 56 us, 66 in three).  Row copies need the rest of the chip: chunks stay long beside them.
+    // 56 us, 66 in three) or, in more rounds, adds more than an eighth to them: there it is their number that counts (1100
+    // rows of 100 at k = 12: 84 us with two parts, 64 without, 2048 of 511 at k = 64: 408 and 359).  Row copies need the rest of
+    // the chip: chunks stay long beside them.
     ChunkDeal deal{0, CHUNK, 2, 64, shared ? 1 : 0};
     if (!rows && (long long)nrows * ((c.n + 31) / 32) <= CUS) deal = ChunkDeal{0, 32, 0, 32, 0};
     else if (!rows && (long long)nrows * ((c.n + 63) / 64 + 2) <= CUS) deal = ChunkDeal{0, 64, 2, 32, 0};
     deal.nchunks = (c.n + deal.len - 1) / deal.len;
+    if (!first_valid) {   // no parts that hold nothing (1500 rows of 64: 73 us, 60 without)
+        const int first = std::min(c.k / deal.len, deal.nchunks);
+        deal.nsplit = std::min(deal.nsplit, deal.nchunks - first);
+        if (deal.nsplit > 0 && first + deal.nsplit == deal.nchunks && c.n - (deal.nchunks - 1) * deal.len <= deal.part) deal.nsplit--;
+    }
     const int idle = t_begin > 0 ? t_begin / deal.len : std::min(c.k, c.n) / deal.len;   // chunks that end at once
     const long long whole = (long long)nrows * (deal.nchunks - idle), split = (long long)nrows * (deal.most() - idle);
     const int asked = deal.nsplit;
     while (deal.nsplit > 0 && !fits_one_round(deal, nrows, idle)) deal.nsplit--;
     const bool one_round = fits_one_round(deal, nrows, idle);
     if (!one_round) deal.nsplit = asked;
-    if (!one_round && ((whole <= 2 * CUS && split > 2 * CUS) || (whole <= 4 * CUS && split > 4 * CUS))) deal.nsplit = 0;
+    if (!one_round && ((whole <= 2 * CUS && split > 2 * CUS) || (whole <= 4 * CUS && split > 4 * CUS) ||
+                       (whole > 4 * CUS && 8 * deal.nsplit > deal.nchunks - idle)))
+        deal.nsplit = 0;
     RowCopy R{};
     if (rows) {
         // The chunks are bound by latency and, with one score row, few: the rows are moved by what is left of the chip
