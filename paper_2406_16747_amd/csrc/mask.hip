@@ -1890,6 +1890,8 @@ __global__ __launch_bounds__(NT_CHUNK, OCC) void mask_kernel(ChunkArgs a, ChunkD
 // ---------------------------------------------------------------------------------
 constexpr int SMALL_WAVES = 4;
 constexpr long long SMALL_WORK = 1ll << 22;   // rows times the square of their length
+constexpr long long SMALL_LOAD = 20 << 10;     // rows times their length; any number of rows of up to SMALL_ROW
+constexpr int SMALL_ROW = 48;
 constexpr int SMALL_MAX = 2048;    // scores of a row, hence
 constexpr int FALSI_ITERS = 20;
 constexpr int NEWTON_ITERS = 64;   // beyond, only the middle of the bracket, which closes after some 2000 steps at most
@@ -2173,8 +2175,12 @@ int launch_mask(const sparsek_cfg& c, const float* u, float* tau, int32_t* death
 {
     const int nrows = c.B * c.Gu;
     // us, this kernel against the chunks: one row of 500 8.5 / 14.3, of 1024 10.5 / 14.6, of 2000 13.0 / 14.6, of 3000 17.4 /
-    // 14.4; four rows of 1024 12.6 / 14.6; 16 of 512 15.0 / 14.8; two of 2000 15.5 / 14.6.
-    if (!rows && !first_valid && t_begin == 0 && c.k >= 1 && c.n > c.k && c.n <= SMALL_MAX && (long long)nrows * c.n * c.n <= SMALL_WORK) {
+    // 14.4; four rows of 1024 12.6 / 14.6; 16 of 512 15.0 / 14.8; two of 2000 15.5 / 14.6.  Many shorter rows fill the chip (8192
+    // waves) more than twice at a smaller square: 160 of 100 17.2 / 18.5, 240 22.6 / 18.4; 125 of 128 17.2 / 15.3 (k = 64: 14.7 /
+    // 18.3), 187 22.6 / 20.7; 266 of 60 16.7 / 21.8, 666 32.8 / 32.3.  Up to some 48 prefixes a workgroup of 16 waves has too
+    // little to do: 1333 of 30 33.3 / 47.0, 869 of 46 32.6 / 37.2.
+    if (!rows && !first_valid && t_begin == 0 && c.k >= 1 && c.n > c.k && c.n <= SMALL_MAX &&
+        (long long)nrows * c.n * c.n <= SMALL_WORK && (c.n <= SMALL_ROW || (long long)nrows * c.n <= SMALL_LOAD)) {
         // (an odd number of workgroups per row where not all have room at once, as below: 256 rows of 64 at k = 32 19.0 -> 14.5
         // us, 128 of 128 at k = 64 20.5 -> 14.9)
         const int quads = (c.n + SMALL_WAVES - 1) / SMALL_WAVES, odd = (long long)nrows * quads > 8 * CUS ? 1 : 0;

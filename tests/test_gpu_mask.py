@@ -193,6 +193,7 @@ def test_mask_scores_of_plus_infinity(oracle, rows, n, k, share):
     (16, 2048, 256), (9, 3500, 256),     # one round with one split chunk instead of two, with none
     (40, 3830, 300), (50, 3000, 100),    # several rounds: numbers of workgroups per row that are passed over
     (1100, 100, 12), (70, 2000, 200),    # ... without a split
+    (160, 129, 60), (1100, 60, 40),      # many short rows that go to the chunks
 ])
 def test_mask_deal_of_chunks(oracle, rows, n, k):
     require_gpu()
