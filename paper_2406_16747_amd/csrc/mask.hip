@@ -1187,8 +1187,9 @@ __device__ __forceinline__ double wave_scan_f64(double x)
 //      f >= k after each and keeps f at both ends of the piece;
 //   4. a lane per prefix interpolates.
 // The slope of a piece is a number of scores: below one half it is none, and the root of a flat piece at k is its right
-// end (sup rule).  On a flat piece f is a sum of whole numbers, hence exact.  Elsewhere f is off by about 1e-13, and the
-// root by that over the slope.  (The piece's own counts -- searches and a pass over the newcomers per prefix -- took a
+// end (sup rule).  On a flat piece f is a sum of whole numbers, hence exact.  Elsewhere f is off by about 2^-53 times the
+// fractional scores' number and distance from 0 (1e-13 for a thousand around 0, 1e-8 around 1e5), as any sum of them is,
+// and the root by that over the slope, but never out of its piece.  (The piece's own counts -- searches and a pass over the newcomers per prefix -- took a
 // quarter of the instructions of this function.)
 __device__ __forceinline__ void solve_parallel(HistSmem& sm, const ListBounded& L, float* __restrict__ tr, int ta, int tb,
                                                int k, double lo)
@@ -1903,13 +1904,14 @@ struct ListRow {
     float own;
 };
 
-// f(four scores) for the positions before end (a multiple of 4), 256 at a time; `none` fills up.
-template <typename F>
+// f(four scores) for the positions before end (a multiple of 4), 256 at a time; `none` fills up.  (UNROLL 1 where f counts with
+// ballots: the compiler unrolls no such loop of unknown length.)
+template <int UNROLL, typename F>
 __device__ __forceinline__ void each_row4(const float* v, int end, int lane, float none, F&& f)
 {
     const float4* v4 = (const float4*)v;
     int i = 0;
-#pragma unroll 2
+#pragma unroll UNROLL
     for (; i + 256 <= end; i += 256) f(v4[(i >> 2) + lane]);
     if (i < end) f(i + 4 * lane < end ? v4[(i >> 2) + lane] : make_float4(none, none, none, none));
 }
@@ -1926,7 +1928,7 @@ __device__ __forceinline__ PieceB eval_bounded(const ListRow& L, int t, double x
         F += (int)__popcll(b);
         part += v > xf && !(v > x1f) ? (double)v : 0.0;
     };
-    each_row4(L.v, L.t0, L.lane, -INFINITY, [&](float4 z) { one(z.x); one(z.y); one(z.z); one(z.w); });
+    each_row4<1>(L.v, L.t0, L.lane, -INFINITY, [&](float4 z) { one(z.x); one(z.y); one(z.z); one(z.w); });
     one(L.lane <= t - L.t0 ? L.own : -INFINITY);
     return PieceB{F, S, wave_sum_f64(part)};
 }
@@ -1936,7 +1938,7 @@ __device__ __forceinline__ double min_saturated(const ListRow& L, int t, double 
     const float x1f = __double2float_rd(x + 1.0);
     float mf = INFINITY;
     auto one = [&](float v) { mf = fminf(mf, v > x1f ? v : INFINITY); };
-    each_row4(L.v, L.t0, L.lane, -INFINITY, [&](float4 z) { one(z.x); one(z.y); one(z.z); one(z.w); });
+    each_row4<2>(L.v, L.t0, L.lane, -INFINITY, [&](float4 z) { one(z.x); one(z.y); one(z.z); one(z.w); });
     one(L.lane <= t - L.t0 ? L.own : -INFINITY);
     return (double)wave_min_f32(mf);
 }
@@ -1954,7 +1956,7 @@ __device__ __forceinline__ float near_threshold(const ListRow& L, int t, int k, 
             if (!uniform(x > a && x < b)) break;   // no fp32 number lies between them
         }
         float s0 = L.lane <= t - L.t0 ? clip01(L.own - x) : 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
-        each_row4(L.v, L.t0, L.lane, -INFINITY, [&](float4 z) {
+        each_row4<2>(L.v, L.t0, L.lane, -INFINITY, [&](float4 z) {
             s0 += clip01(z.x - x);
             s1 += clip01(z.y - x);
             s2 += clip01(z.z - x);
@@ -2034,7 +2036,7 @@ __global__ __launch_bounds__(64 * SMALL_WAVES) void mask_small_kernel(const floa
     // ---- threshold ----
     // of the finite scores: the smallest and the largest
     float mn = L.t0 + lane <= t ? L.own : INFINITY, mx = L.own;
-    each_row4(row_scores, L.t0, lane, NAN, [&](float4 z) {
+    each_row4<2>(row_scores, L.t0, lane, NAN, [&](float4 z) {
         mn = fminf(mn, fminf(fminf(z.x, z.y), fminf(z.z, z.w)));
         mx = fmaxf(mx, fmaxf(fmaxf(z.x, z.y), fmaxf(z.z, z.w)));
     });
@@ -2052,7 +2054,7 @@ __global__ __launch_bounds__(64 * SMALL_WAVES) void mask_small_kernel(const floa
                 infs += (int)__popcll(__ballot(z == INFINITY));
                 if (fabsf(z) < INFINITY) { mx = fmaxf(mx, z); mn = fminf(mn, z); }
             };
-            each_row4(row_scores, L.t0, lane, -INFINITY, [&](float4 z) { one(z.x); one(z.y); one(z.z); one(z.w); });
+            each_row4<1>(row_scores, L.t0, lane, -INFINITY, [&](float4 z) { one(z.x); one(z.y); one(z.z); one(z.w); });
             one(L.own);
             mn = wave_min_f32(mn);
             mx = wave_max_f32(mx);
@@ -2072,7 +2074,7 @@ __global__ __launch_bounds__(64 * SMALL_WAVES) void mask_small_kernel(const floa
     int d = t;
     if (t < k || uniform(v >= res)) {
         int need = k - (int)__popcll(__ballot(older && L.own >= v));
-        each_row4(row_scores, L.t0, lane, NAN, [&](float4 z) {
+        each_row4<1>(row_scores, L.t0, lane, NAN, [&](float4 z) {
             need -= (int)(__popcll(__ballot(z.x >= v)) + __popcll(__ballot(z.y >= v)) + __popcll(__ballot(z.z >= v)) +
                           __popcll(__ballot(z.w >= v)));
         });
