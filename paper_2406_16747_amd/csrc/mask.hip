@@ -883,9 +883,9 @@ __device__ __noinline__ void mask_chunk_sorted(SPK_LDS SortedSmem* smem, const f
 // four fifths of the cycles of a SIMD).  One row of 32768 scores at k = 1024: 32 -> 25 us, 4096 at k = 256: 29 -> 15 us with
 // chunks dealt as launch_mask says, lifetimes by 16 lanes per key and thresholds by interpolation; 32 rows of 16384: 248 ->
 // 211 us.  Before the histogram, with a bracket search and a sort of all candidates per chunk: 85 us and 390 us.
-// Windows that follow the scores, 32 rows of 16384, k = 1024: standard deviation 7 in 292 us, 27 in 291, 0.05 in 760, mean 20 in 308.  With
+// Windows that follow the scores, 32 rows of 16384, k = 1024: standard deviation 7 in 279 us, 27 in 276, 0.05 in 405, mean 20 in 297.  With
 // two fixed widths of window and the sorted path for the rest: 716, 834, 3418 and 383; with every chunk sorted: 360, 369,
-// 9185 and 390.  One row of 131072 at k = 16384: 327 us, 13.3 ms with the fixed width.
+// 9185 and 390.  One row of 131072 at k = 16384: 314 us, 13.3 ms with the fixed width.
 // ---------------------------------------------------------------------------------
 constexpr int HBINS = 2048;      // bins of a window; scores below and above it count in the first and the last one
 constexpr int WINDOWS = 4;       // windows tried at most
