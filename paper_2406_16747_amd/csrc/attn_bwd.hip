@@ -195,6 +195,7 @@ __global__ __launch_bounds__(256) void attn_bwd_generic_kernel(
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2v __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
+typedef float f32x4v __attribute__((ext_vector_type(4)));
 // two floats rounded to bf16 (nearest even), the first in the low half
 __device__ __forceinline__ unsigned pack_bf16x2(float a, float b)
 {
@@ -202,33 +203,63 @@ __device__ __forceinline__ unsigned pack_bf16x2(float a, float b)
     return __builtin_bit_cast(unsigned, __builtin_convertvector(f, bf16x2v));
 }
 
-// A 64-row tile in LDS (K rows in the dQ kernel, Q and dO rows in the dK/dV kernel) serves two kinds of reads: 16-byte
-// row reads (A operand of the contractions over the head dimension) and transposing 8-byte reads (A operand of the
-// contractions over the tile's rows).  Each row lands once, unpadded, with its 16-byte chunks
-// permuted: chunk c of tile row R sits at chunk position c ^ swz(R).  swz is chosen so that both read patterns
-// touch every bank once per pass:
-//   row reads take one chunk column of 16 consecutive rows per 16 lanes  -> swz must differ on those rows
-//   transposing reads take 4 neighbouring chunks of 4 consecutive rows per 32 lanes -> swz / 4 must differ on those rows
-// (head dim 64: a row is half of the 64 banks, two rows share a pass, and the row's parity takes the place of one bit).
+// A tile of 64 rows (Q or dO) in LDS serves 16-byte row reads (A operand of the contractions over the head dimension) and
+// transposing 8-byte reads (A operand of the contractions over the queries).  Every row lands once, in groups of 1 KB (a
+// wave-load) padded by 16 bytes; which rows share a group is chosen so that both kinds of reads touch every bank once per
+// pass: 16 consecutive rows differ in (group, slot) modulo the 16 chunks of 256 bytes, and 4 consecutive ones by multiples
+// of 4 chunks.  Unlike a permutation of the chunks inside a row this leaves every operand of a tile at a constant distance
+// from one address per lane (two in all, one for each kind of read), so tiles can sit in a ring without code of their own.
 template <int D>
-__device__ __forceinline__ int tile_swz(int R)
-{
-    if constexpr (D == 128) return 4 * (R & 3) + ((R >> 2) & 3);
-    else return 4 * ((R >> 1) & 1) + ((R >> 2) & 3);
-}
+struct RowTile {
+    static constexpr int RB = D * 2, RPL = 1024 / RB, NL = KT / RPL;   // bytes per row, rows per group, groups
+    static constexpr int GS = 1024 + 16, BYTES = NL * GS;
+    // tile row r sits in group g(r), slot s(r)
+    __device__ static constexpr int group(int r) { return D == 128 ? 4 * (r & 3) + ((r >> 2) & 3) : 4 * (r & 1) + ((r >> 2) & 3); }
+    __device__ static constexpr int slot(int r) { return D == 128 ? r >> 4 : ((r >> 1) & 1) + 2 * (r >> 4); }
+    __device__ static constexpr int row(int g, int s)   // the inverse
+    {
+        return D == 128 ? (g >> 2) + 4 * (g & 3) + 16 * s : (g >> 2) + 2 * (s & 1) + 4 * (g & 3) + 16 * (s >> 1);
+    }
+    __device__ static constexpr int offset(int r) { return group(r) * GS + slot(r) * RB; }
+    static constexpr int R16 = 16 / (D == 128 ? 16 : 8) * RB;   // 16 rows on: the same group, so many bytes on
+    static constexpr int R8 = 2 * GS;                           // 8 rows on, from a row of 0 .. 7 modulo 16
+};
 
-// K lands twice, once per padding (row reads and transposing reads of one padded copy would conflict; the
-// chunk-permuted single copy the dK/dV kernel uses needs 16 more address registers than this kernel has at two
-// workgroups per compute unit); the tile is single-buffered and the two workgroups of a compute unit cover each
-// other's gathers.
+// Two tiles: the one in use and the one on its way.
 template <int D>
 struct DqSmem : TileMeta {
-    using S = MfmaTileBufs<D, 64>;
-    unsigned char kr[S::NL * S::GSK];  // K rows, padded for row reads
-    unsigned char kt[S::NL * S::GSV];  // K rows, padded for transposing reads
-    unsigned char vr[S::NL * S::GSK];  // V rows, padded for row reads
+    struct Tile {
+        unsigned char k[RowTile<D>::BYTES];
+        unsigned char v[RowTile<D>::BYTES];
+    } t[2];
 };
 static_assert(sizeof(DqSmem<128>) <= 80 * 1024, "two workgroups per CU");
+
+typedef const unsigned char __attribute__((address_space(3)))* lds_bytes_t;
+__device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(uintptr_t)(lds_void_t*)p; }
+// The operands of a RowTile: a row read (16 bytes of one row), and a transposing read (8 + 8 bytes, rows 8 apart).
+__device__ __forceinline__ bf16x8 row_operand(uint32_t at)
+{
+    return *(const bf16x8 __attribute__((address_space(3)))*)(lds_bytes_t)(uintptr_t)at;
+}
+template <int D>
+__device__ __forceinline__ bf16x8 transposed_operand(uint32_t at)
+{
+    const i16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((i16x4 __attribute__((address_space(3)))*)(uintptr_t)at);
+    const i16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((i16x4 __attribute__((address_space(3)))*)(uintptr_t)(at + RowTile<D>::R8));
+    const bf16x4 lo = __builtin_bit_cast(bf16x4, lo4), hi = __builtin_bit_cast(bf16x4, hi4);
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+// Where in a tile a lane's operands start: row reads of rows 0 .. 31, chunk lane / 32 (+ 2 per step); transposing reads of rows
+// 4 (lane / 32) + r16 / 4 (+ 8, + 16 per step), 8 bytes at column 16 grp2 + 4 (r16 % 4) (+ 32 per step).
+template <int D>
+__device__ __forceinline__ uint32_t row_lane(int lane) { return RowTile<D>::offset(lane & 31) + 16 * (lane >> 5); }
+template <int D>
+__device__ __forceinline__ uint32_t transposed_lane(int lane)
+{
+    const int half = lane >> 5, r16 = lane & 15, grp2 = (lane >> 4) & 1;
+    return RowTile<D>::offset(4 * half + (r16 >> 2)) + (16 * grp2 + 4 * (r16 & 3)) * 2;
+}
 
 // What a lane of the dQ kernel keeps for the whole block.
 struct DqLane {
@@ -236,63 +267,56 @@ struct DqLane {
     int qi;
 };
 
-// The gather of one tile: K (twice) and V rows at the positions jp[0..63].
+// The gather of one tile: K and V rows at the positions jp[0..63].  The wave's loads are groups whose rows are neighbours, so
+// that a lane's row numbers come with one read.
 template <int D>
-__device__ __forceinline__ void dq_issue(DqSmem<D>& sm, const int32_t* jp, const unsigned char* kh,
+__device__ __forceinline__ void dq_issue(typename DqSmem<D>::Tile& t, const int32_t* jp, const unsigned char* kh,
                                          const unsigned char* vh, int wv, int lane)
 {
-    using S = MfmaTileBufs<D, 64>;
+    using S = RowTile<D>;
     constexpr int NX = S::NL / 4, LPR = S::RB / 16;
-    const TileRows<D, 64> rows = tile_rows<D, 64>(jp, wv, lane);
-    const int c = lane % LPR;
+    static_assert(S::row(4, 0) == 1 && (NX == 2 || S::row(8, 0) == 2), "the rows of groups wv, wv + 4, .. are neighbours");
+    const int32_t* src = jp + S::row(wv, 0) + S::row(0, lane / LPR);
+    int j[NX];
+    if constexpr (NX == 4) {
+        const int4 x = *(const int4*)src;
+        j[0] = x.x; j[1] = x.y; j[2] = x.z; j[3] = x.w;
+    } else {
+        const int2 x = *(const int2*)src;
+        j[0] = x.x; j[1] = x.y;
+    }
 #pragma unroll
     for (int x = 0; x < NX; x++) {
-        const int L = wv * NX + x;
-        const uint32_t off = (uint32_t)rows.j[x] * (uint32_t)S::RB + 16u * (uint32_t)c;
-        async_load_lds16(kh, off, &sm.kr[L * S::GSK]);
-        async_load_lds16(vh, off, &sm.vr[L * S::GSK]);
-        async_load_lds16(kh, off, &sm.kt[L * S::GSV]);
+        const int L = wv + 4 * x;
+        const uint32_t off = (uint32_t)j[x] * (uint32_t)S::RB + 16u * (uint32_t)(lane % LPR);
+        async_load_lds16(kh, off, &t.k[L * S::GS]);
+        async_load_lds16(vh, off, &t.v[L * S::GS]);
     }
 }
 
 // One 64-key tile for one wave.  jbase: position of the tile's first key if the key set were contiguous.
 template <int D, int MODE, int KIND>
-__device__ __forceinline__ void dq_tile_body(DqSmem<D>& sm, const int32_t* jdeath, const float* ju, int jbase,
+__device__ __forceinline__ void dq_tile_body(uint32_t rk, uint32_t tk, const int32_t* jdeath, const float* ju, int jbase,
                                              const DqLane& ln, int lane, int w, float c2,
                                              const bf16x8 (&qreg)[D / 16], const bf16x8 (&dreg)[D / 16],
                                              f32x16 (&acc_q)[D / 32])
 {
     using TT = TileTraits<MODE, KIND>;
-    using S = MfmaTileBufs<D, 64>;
+    using S = RowTile<D>;
     constexpr int DS = D / 16, DB = D / 32;
-    const int half = lane >> 5, col = lane & 31;
+    const int half = lane >> 5;
     const int qw = ln.qi - (w - 1);
     const int dqh = ln.qi - jbase - 4 * half;  // contiguous tiles: key number cst + 4*half sits dqh - cst behind the query
     const int dqw = dqh - w;                   // in the window  <=>  cst > dqw
-    // transposing reads of K^T (see the forward's V^T operand): lane -> (row, column block)
-    const int r16 = lane & 15, grp2 = (lane >> 4) & 1;
-    const int tcol = (16 * grp2 + 4 * (r16 & 3)) * 2;
-    const int trow = 4 * half + (r16 >> 2);
-    auto kt_operand = [&](int g, int x) -> bf16x8 {
-        const int row0 = 16 * g + trow, row1 = row0 + 8;
-        const unsigned char* p0 = sm.kt + (row0 % S::NL) * S::GSV + (row0 / S::NL) * S::RB + tcol + 64 * x;
-        const unsigned char* p1 = sm.kt + (row1 % S::NL) * S::GSV + (row1 / S::NL) * S::RB + tcol + 64 * x;
-        const i16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((i16x4 __attribute__((address_space(3)))*)p0);
-        const i16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((i16x4 __attribute__((address_space(3)))*)p1);
-        const bf16x4 lo = __builtin_bit_cast(bf16x4, lo4), hi = __builtin_bit_cast(bf16x4, hi4);
-        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    };
 #pragma unroll
     for (int mb = 0; mb < 2; mb++) {
-        const int trw = 32 * mb + col;
-        const int off = (trw % S::NL) * S::GSK + (trw / S::NL) * S::RB + 16 * half;
         const f32x16 zero = {0};
         f32x16 acc_s = zero, acc_d = zero;
         __builtin_amdgcn_sched_barrier(0);  // one half at a time: there are no registers for two in flight
 #pragma unroll
         for (int s = 0; s < DS; s++) {
-            const bf16x8 ka = *(const bf16x8*)(sm.kr + off + 32 * s);
-            const bf16x8 va = *(const bf16x8*)(sm.vr + off + 32 * s);
+            const bf16x8 ka = row_operand(rk + 2 * mb * S::R16 + 32 * s);
+            const bf16x8 va = row_operand(rk + S::BYTES + 2 * mb * S::R16 + 32 * s);
             acc_s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qreg[s], s == 0 ? zero : acc_s, 0, 0, 0);
             acc_d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, dreg[s], s == 0 ? zero : acc_d, 0, 0, 0);
         }
@@ -332,7 +356,7 @@ __device__ __forceinline__ void dq_tile_body(DqSmem<D>& sm, const int32_t* jdeat
         }
 #pragma unroll
         for (int i = 0; i < 2 * DB; i++)
-            acc_q[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt_operand(2 * mb + i / DB, i % DB),
+            acc_q[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(transposed_operand<D>(tk + (2 * mb + i / DB) * S::R16 + 64 * (i % DB)),
                                                                     __builtin_bit_cast(bf16x8, dsb[i / DB]),
                                                                     acc_q[i % DB], 0, 0, 0);
     }
@@ -345,16 +369,21 @@ __device__ __forceinline__ void dq_run_tiles(DqSmem<D>& sm, const StageSrc& src,
                                              const DqLane& ln, int w, float c2, const bf16x8 (&qreg)[D / 16],
                                              const bf16x8 (&dreg)[D / 16], f32x16 (&acc_q)[D / 32])
 {
+    const uint32_t rl = lds_address(&sm.t[0].k[0]) + row_lane<D>(lane), tl = lds_address(&sm.t[0].k[0]) + transposed_lane<D>(lane);
     for (; T < T_end; T++) {
         const int sg = T / TPS, lt = T - sg * TPS;
-        __syncthreads();  // everybody is done with tile T-1 (and, at the first tile of a segment, with the segment before)
-        if (lt == 0 && (sg + 1) * TPS < src.nt) stage_meta(sm, src, sg + 1, wv, lane);
-        dq_issue<D>(sm, sm.jpos[sg & 1] + lt * KT, kh, vh, wv, lane);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();  // the tile (and any metadata staged above) has landed
-        if (KIND != TILE_SKIP)
-            dq_tile_body<D, MODE, KIND>(sm, sm.jdeath[sg & 1] + lt * KT, sm.ju[sg & 1] + lt * KT, jbase0 + T * KT, ln,
+        __syncthreads();  // tile T has landed; everybody is done with tile T-1 (and, at the first tile of a segment, with the segment before)
+        if (lt == 0 && (sg + 1) * TPS < src.nt) stage_meta(sm, src, sg + 1, wv, lane);
+        if (T + 1 < src.nt) {
+            const int sn = (T + 1) / TPS;
+            dq_issue<D>(sm.t[(T + 1) & 1], sm.jpos[sn & 1] + (T + 1 - sn * TPS) * KT, kh, vh, wv, lane);
+        }
+        if (KIND != TILE_SKIP) {
+            const uint32_t tb = (uint32_t)(T & 1) * (uint32_t)sizeof(typename DqSmem<D>::Tile);
+            dq_tile_body<D, MODE, KIND>(rl + tb, tl + tb, sm.jdeath[sg & 1] + lt * KT, sm.ju[sg & 1] + lt * KT, jbase0 + T * KT, ln,
                                         lane, w, c2, qreg, dreg, acc_q);
+        }
     }
 }
 
@@ -568,8 +597,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(
 #pragma unroll
     for (int s = 0; s < DS; s++) asm volatile("" ::"v"(qreg[s]), "v"(dreg[s]));
     asm volatile("" ::"v"(ln.tau_q), "v"(ln.lse2), "v"(ln.Di));
-    // (segment 0 of the metadata is published by the first tile's barriers: each wave waits for its own copies
-    //  before the second one)
+    __syncthreads();   // segment 0 of the metadata has landed
+    if (NT > 0) dq_issue<D>(sm.t[0], sm.jpos[0], kh, vh, wv, lane);
     {
         const int jbase0 = c0 - nkl;
         int T = 0;
@@ -660,18 +689,16 @@ __device__ __forceinline__ void mfma_v(f32x16& d, const bf16x8& a, const bf16x8&
     if constexpr (FIRST) asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "v"(b));
     else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
 }
-__device__ __forceinline__ void mfma_done(f32x16& a, f32x16& b)
-{
-    asm volatile("s_nop 15\n\ts_nop 7" : "+v"(a), "+v"(b));
-}
 
-constexpr int DKV_NBUF = 2;  // tiles in LDS: one in use, one being filled
+constexpr int DKV_NBUF = 4;  // tiles in LDS: the one the products are at, the one before it, and two on their way
 template <int D>
 struct DkvSmem {
     struct Tile {
-        unsigned char q[KT * D * 2];   // Q rows of a tile
-        unsigned char g[KT * D * 2];   // dO rows
+        unsigned char q[RowTile<D>::BYTES];   // Q rows of a tile
+        unsigned char g[RowTile<D>::BYTES];   // dO rows
     } t[DKV_NBUF];
+    // per query of a tile: lse * log2(e), D_i, tau_{i-w} (and a fourth row that only keeps the loads branch-free)
+    float meta[DKV_NBUF][4][KT];
     int red[2][4];
 };
 
@@ -685,7 +712,6 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(
     uint16_t* __restrict__ dk, uint16_t* __restrict__ dv, int H, int Gu, int n, int w, float scale, int nb,
     int q_begin, int q_rows, RangesArgs ranges)
 {
-    using S = MfmaTileBufs<D, 64>;  // (tile geometry only)
     union Smem {
         __device__ Smem() {}
         DkvSmem<D> t;
@@ -699,9 +725,8 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(
         if (id < rows * per_row) mask_bwd_ranges(ranges, smem.ts, id % per_row, id / per_row);
         return;
     }
-    // per query of a tile: lse * log2(e), D_i, tau_{i-w} (and a fourth row that only keeps the loads branch-free)
-    __shared__ __align__(16) float meta[DKV_NBUF][4][KT];
-    constexpr int DS = D / 16, DB = D / 32, NX = S::NL / 4, LPR = S::RB / 16, RB = S::RB, RPL = S::RPL;
+    using S = RowTile<D>;
+    constexpr int DS = D / 16, DB = D / 32, NX = S::NL / 4, LPR = S::RB / 16, RB = S::RB;
     const int bh = blockIdx.x;
     const int b = bh / H, h = bh % H;
     const int row = b * Gu + (Gu == 1 ? 0 : h);
@@ -769,203 +794,233 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(
     const unsigned char* qh = (const unsigned char*)(q + qo * D);
     const unsigned char* gh = (const unsigned char*)(dO + qo * D);
 
-    // LDS byte offsets of this lane's operand reads (see tile_swz):
-    //   row reads: tile row 32 * run + col, chunk 2 * step + half          -> roff[run][step]
-    //   transposing reads: rows 16 g + 4 half + r16 / 4 (+ 8), chunk 4 x + 2 grp2 + (r16 % 4) / 2, 8-byte half r16 % 2
-    //                                                                      -> toff[0 / 1][x] + 16 g rows
-    const int r16 = lane & 15, grp2 = (lane >> 4) & 1;
-    int roff[2][DS], toff[2][DB];
-#pragma unroll
-    for (int run = 0; run < 2; run++) {
-        const int R = 32 * run + col, sw = tile_swz<D>(R);
-#pragma unroll
-        for (int st = 0; st < DS; st++) roff[run][st] = R * RB + (((2 * st + half) ^ sw) << 4);
-    }
-#pragma unroll
-    for (int hl = 0; hl < 2; hl++) {
-        const int R = 4 * half + (r16 >> 2) + 8 * hl, sw = tile_swz<D>(R);  // (swz has period 16 in R)
-#pragma unroll
-        for (int x = 0; x < DB; x++)
-            toff[hl][x] = R * RB + (((4 * x + 2 * grp2 + ((r16 & 3) >> 1)) ^ sw) << 4) + 8 * (r16 & 1);
-    }
-    auto t_operand = [&](const unsigned char* tbuf, int g, int x) -> bf16x8 {
-        const unsigned char* p0 = tbuf + 16 * g * RB + toff[0][x];
-        const unsigned char* p1 = tbuf + 16 * g * RB + toff[1][x];
-        const i16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((i16x4 __attribute__((address_space(3)))*)p0);
-        const i16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((i16x4 __attribute__((address_space(3)))*)p1);
-        const bf16x4 l4 = __builtin_bit_cast(bf16x4, lo4), h4 = __builtin_bit_cast(bf16x4, hi4);
-        return __builtin_shufflevector(l4, h4, 0, 1, 2, 3, 4, 5, 6, 7);
-    };
-    // The gather of one tile (64 consecutive queries from i_first, clamped to the last row): a wave-load fills RPL
-    // consecutive tile rows; lane l delivers position l % LPR of row l / LPR, i.e. chunk (l % LPR) ^ swz(row).
-    int goff[NX];  // byte offset of this lane's chunk inside a tile whose first row is at 0
-#pragma unroll
-    for (int x = 0; x < NX; x++) {
-        const int R = RPL * (wv * NX + x) + lane / LPR;
-        goff[x] = R * RB + (((lane % LPR) ^ tile_swz<D>(R)) << 4);
-    }
-    auto issue = [&](int buf, int i_first) {
-#pragma unroll
-        for (int x = 0; x < NX; x++) {
-            const int R = RPL * (wv * NX + x) + lane / LPR;
-            // rows past the end of the sequence repeat the last row (their pairs are masked)
-            const int over = max(i_first + R - (n - 1), 0);
-            const uint32_t off = (uint32_t)i_first * (uint32_t)RB + (uint32_t)(goff[x] - over * RB);
-            async_load_lds16(qh, off, &sm.t[buf].q[(wv * NX + x) * 1024]);
-            async_load_lds16(gh, off, &sm.t[buf].g[(wv * NX + x) * 1024]);
-        }
+    // The gather of one tile (64 consecutive queries from i_first, clamped to the last row): load L fills group L, lane l
+    // delivers chunk l % LPR of the row in slot l / LPR.  One step of it is the Q and the dO rows of one group.
+    const int grow = S::row(0, lane / LPR), gchunk = 16 * (lane % LPR);
+    auto issue_step = [&](int buf, int i_first, int x) {
+        const int L = wv + 4 * x;
+        // rows past the end of the sequence repeat the last row (their pairs are masked)
+        const int i = min(i_first + S::row(L, 0) + grow, n - 1);
+        const uint32_t off = (uint32_t)i * (uint32_t)RB + (uint32_t)gchunk;
+        async_load_lds16(qh, off, &sm.t[buf].q[L * S::GS]);
+        async_load_lds16(gh, off, &sm.t[buf].g[L * S::GS]);
     };
     // the tile's per-query values: waves 0, 1, 2 load one row each (wave 3 a copy of tau into the spare row)
     const float* msrc = wv == 0 ? lse2s + qo : wv == 1 ? delta + qo : tr;
     auto issue_meta = [&](int buf, int i_first) {
         const int i = min(i_first + lane, n - 1);
-        async_load_lds4(msrc, 4u * (uint32_t)(wv >= 2 ? max(i - w, 0) : i), &meta[buf][wv][0]);
+        async_load_lds4(msrc, 4u * (uint32_t)(wv >= 2 ? max(i - w, 0) : i), &sm.meta[buf][wv][0]);
     };
+    constexpr int NLOADS = 2 * NX + 1;   // a wave's loads per tile
+    auto issue = [&](int t) {   // tile t; past the last one its rows again, so that every tile has the same number of loads behind it
+        const int i_first = blo + min(t, ntiles - 1) * KT, buf = t & (DKV_NBUF - 1);
+#pragma unroll
+        for (int x = 0; x < NX; x++) issue_step(buf, i_first, x);
+        issue_meta(buf, i_first);
+    };
+    // tile t has landed (this wave's share of it; only tile t + 1 may still be under way), for every wave, and everybody is
+    // done with the tile before the one before it
+    auto landed = [&]() {
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NLOADS) : "memory");
+    };
+    // The K / V fragments must have arrived before the first load that the compiler does not know: its own wait for them would
+    // otherwise sit at their first use, inside the loop, and count the loads of every iteration too.
+    // (The first tiles' gather is under way beside them.)
     if (ntiles > 0) {
-        issue_meta(0, blo);
-        issue(0, blo);
+        issue(0);
+        issue(1);
     }
-    // The K / V fragments must have arrived before the tile loop: the compiler's own wait for them would otherwise
-    // sit at their first use, inside the loop, and count the prefetches of every iteration too.  (The first tile's
-    // gather is already in flight beside them; the loop waits for it anyway.)
 #pragma unroll
     for (int s = 0; s < DS; s++) asm volatile("" ::"v"(kreg[s]), "v"(vreg[s]));
-    // One tile for this wave, as four runs of NS MFMAs:
-    //   1: S and dO.V of queries 0..31            2: the same for queries 32..63, under it the elementwise
-    //   3: dV, dK += from queries 0..31, under        work (P, dS) of queries 0..31
-    //      it the elementwise work of 32..63       4: dV, dK += from queries 32..63
-    // Every step issues one MFMA and a slice of elementwise work, fenced so that the interleave survives the
-    // scheduler; MFMA operands come from LDS through a small ring filled DEPTH steps ahead.  GATED: the keys
-    // carry soft gates (selected keys, gate modes 0 and 1); CHECK: some (query, key) pair of the tile may lie
-    // outside the key's interval.  The softmax scale of dS is applied once, to the finished dK.
-    constexpr int NS = 2 * DS, EPM = 16 / NS, DEPTH = 4;
-    static_assert(NS == 4 * DB && EPM * NS == 16, "stage lengths");
-    const unsigned char* mbase = (const unsigned char*)&meta[0][0][0];
-    // (the buffer number is a compile-time constant, so that every LDS address is a per-lane register plus an immediate)
-    auto tile = [&](auto gated_c, auto check_c, auto buf_c, int i_first) {
-        constexpr bool GATED = decltype(gated_c)::value, CHECK = decltype(check_c)::value;
-        constexpr int buf = decltype(buf_c)::value;
-        constexpr bool GK = GATED && MODE == 0, GV = GATED && MODE != 2;
-        f32x16 s0, d0, s1, d1;
-        u32x4 pb0[2], dsb0[2], pb1[2], dsb1[2];
-        const int rel0 = i_first + 4 * half - lo_eff;
-        // operand idx of the tile's 4 * NS MFMAs, in issue order
-        auto operand = [&](auto ic) -> bf16x8 {
-            constexpr int idx = decltype(ic)::value, run = idx / NS, m = idx % NS;
-            if constexpr (run < 2) {
-                const unsigned char* base = (m & 1) ? sm.t[buf].g : sm.t[buf].q;
-                return *(const bf16x8*)(base + roff[run][m / 2]);
-            } else {
-                constexpr int qb = run - 2, i2 = m / 2, g = 2 * qb + i2 / DB, x = i2 % DB;
-                return t_operand((m & 1) ? sm.t[buf].q : sm.t[buf].g, g, x);
-            }
-        };
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+
+    // The work on 32 queries (a unit; a tile holds two) is four runs of MFMAs: S and D = dO.V, then dV += dO^T.P and
+    // dK += Q^T.dS, with the elementwise work in two parts: P from S, and dS from P and D.  One wave per SIMD has nothing else
+    // to hide behind, so the runs of neighbouring units are interleaved and every run has elementwise work of another under it:
+    //     S(m)          dV(m-1)        D(m)          dK(m-1)        S(m+1) ...
+    //     dS(m-1)       P(m)           P(m)          dS(m)          dS(m)
+    // A slot is one MFMA, the LDS read of an operand DEPTH slots on and a slice of elementwise work, fenced so that the
+    // scheduler keeps the interleave.  The first LEAD slots after S and D have no elementwise work (its input is still being
+    // computed); the next tile's gather sits there.  A tile's barrier lies DEPTH slots ahead of its first S, inside the tile
+    // before, so that nobody waits for operands behind it.  GATED: the keys carry soft gates (selected keys, gate modes 0 and
+    // 1); CHECK: some (query, key) pair of the tile may lie outside the key's interval; FIRST: nothing comes before the tile.
+    // The softmax scale of dS is applied once, to the finished dK.
+    constexpr int DEPTH = 4, LEAD = D == 128 ? 3 : 2, ESL = 2 * DS - LEAD;
+    static_assert(DS == 2 * DB && DEPTH <= DS && DS % DEPTH == 0, "run lengths");
+    static_assert(3 * LEAD >= NX + 1, "slots for the gather");
+    const uint32_t lds0 = lds_address(&sm.t[0].q[0]);
+    constexpr uint32_t TB = sizeof(typename DkvSmem<D>::Tile);
+    const uint32_t rlane = lds0 + row_lane<D>(lane), tlane = lds0 + transposed_lane<D>(lane);
+    const uint32_t mlane = lds_address(&sm.meta[0][0][0]) + 16 * half;
+    constexpr uint32_t MB = 4 * KT * 4;
+    uint32_t rcur = rlane, tcur = tlane, tprev = tlane, mcur = mlane, mprev = mlane;
+    auto values = [&](uint32_t base, int imm) -> float4 {
+        const f32x4v x = *(const f32x4v __attribute__((address_space(3)))*)(uintptr_t)(base + imm);
+        return make_float4(x[0], x[1], x[2], x[3]);
+    };
+    // operand idx of a tile: run idx / DS in the order S, dV, D, dK of the first unit, then of the second, and S of the next tile
+    auto operand = [&](auto ic) -> bf16x8 {
+        constexpr int idx = decltype(ic)::value, run = idx / DS, m = idx % DS, h = run / 4, kind = run % 4;
+        if constexpr (run == 8) return row_operand(rcur + 32 * m);   // (rcur is the next tile's by then)
+        else if constexpr (kind == 0) return row_operand(rcur + 2 * h * S::R16 + 32 * m);
+        else if constexpr (kind == 2) return row_operand(rcur + S::BYTES + 2 * h * S::R16 + 32 * m);
+        else return transposed_operand<D>((h == 0 ? tprev : tcur) + (kind == 1 ? S::BYTES : 0) + ((h == 0 ? 2 : 0) + m / DB) * S::R16 + 64 * (m % DB));
+    };
+    struct Pipe {                       // what goes from one tile to the next
+        f32x16 sacc, dacc;
+        float pv[16];                   // P of the unit whose dS is next
+        u32x4 pb[2][2], dsb[2][2];      // P and dS of the first / second unit of a tile as B operands
+        float4 L4[2], PT4[2], D4[2], DT4[2];
         bf16x8 ring[DEPTH];
-        static_for<0, DEPTH>([&](auto ic) { ring[decltype(ic)::value] = operand(ic); });
-        auto refill = [&](auto ic) {
-            constexpr int idx = decltype(ic)::value;
-            if constexpr (idx + DEPTH < 4 * NS) ring[idx % DEPTH] = operand(std::integral_constant<int, idx + DEPTH>{});
-        };
-        float4 L4, D4, T4;
-        float hold_p = 0.0f, hold_s = 0.0f;
-        auto element = [&](auto qbc, auto rc, const f32x16& sacc, const f32x16& dacc, u32x4(&pb)[2], u32x4(&dsb)[2]) {
-            constexpr int qb = decltype(qbc)::value, r = decltype(rc)::value, g4 = r / 4, e = r % 4;
-            if constexpr (e == 0) {
-                const int qo = 32 * qb + 8 * g4 + 4 * half;  // first of 4 consecutive queries of the tile
-                const unsigned char* mp = mbase + (buf * 4 * KT + qo) * 4;
-                L4 = *(const float4*)(mp);
-                D4 = *(const float4*)(mp + KT * 4);
-                if constexpr (GATED) T4 = *(const float4*)(mp + 2 * KT * 4);
+        float ds_even;
+    };
+    // per-query values of 4 elements: one group of 4 ahead
+    auto p_values = [&](Pipe& P, auto gatedc, auto hc, auto gc) {
+        constexpr int h = decltype(hc)::value, g4 = decltype(gc)::value;
+        P.L4[g4 & 1] = values(mcur, 4 * (32 * h + 8 * g4));
+        if constexpr (decltype(gatedc)::value) P.PT4[g4 & 1] = values(mcur, 4 * (32 * h + 8 * g4 + 2 * KT));
+    };
+    auto ds_values = [&](Pipe& P, auto gatedc, auto hc, auto gc, uint32_t mb) {
+        constexpr int h = decltype(hc)::value, g4 = decltype(gc)::value;
+        P.D4[g4 & 1] = values(mb, 4 * (32 * h + 8 * g4 + KT));
+        if constexpr (decltype(gatedc)::value) P.DT4[g4 & 1] = values(mb, 4 * (32 * h + 8 * g4 + 2 * KT));
+    };
+    auto part = [](const float4& x, int e) { return e == 0 ? x.x : e == 1 ? x.y : e == 2 ? x.z : x.w; };
+    auto p_element = [&](Pipe& P, auto gatedc, auto checkc, auto hc, auto rc, int rel0) {
+        constexpr bool GATED = decltype(gatedc)::value;
+        constexpr int h = decltype(hc)::value, r = decltype(rc)::value, g4 = r / 4, e = r % 4;
+        if constexpr (e == 0 && g4 < 3) p_values(P, gatedc, hc, std::integral_constant<int, g4 + 1>{});
+        float gate = 1.0f;
+        if constexpr (GATED) gate = clip01(uj - part(P.PT4[g4 & 1], e));
+        float arg = fmaf(P.sacc[r], GATED && MODE == 0 ? gate * c2 : c2, -part(P.L4[g4 & 1], e));
+        if constexpr (decltype(checkc)::value) {
+            const bool valid = (unsigned)(rel0 + (32 * h + 8 * g4 + e)) <= span;
+            arg = valid ? arg : -INFINITY;  // p = 0, and with it dS
+        }
+        const float p = __builtin_amdgcn_exp2f(arg);
+        P.pv[r] = GATED && MODE == 1 ? p : GATED ? p * gate : p;
+        if constexpr (r & 1) {
+            if constexpr (GATED && MODE == 1) {
+                const float g0 = clip01(uj - part(P.PT4[g4 & 1], e - 1));
+                P.pb[h][r >> 3][(r & 7) >> 1] = pack_bf16x2(P.pv[r - 1] * g0, P.pv[r] * gate);
+            } else P.pb[h][r >> 3][(r & 7) >> 1] = pack_bf16x2(P.pv[r - 1], P.pv[r]);
+        }
+    };
+    auto ds_element = [&](Pipe& P, auto gatedc, auto hc, auto rc, uint32_t mb) {
+        constexpr bool GATED = decltype(gatedc)::value;
+        constexpr int h = decltype(hc)::value, r = decltype(rc)::value, g4 = r / 4, e = r % 4;
+        if constexpr (e == 0 && g4 < 3) ds_values(P, gatedc, hc, std::integral_constant<int, g4 + 1>{}, mb);
+        float ds;
+        if constexpr (GATED) ds = P.pv[r] * fmaf(clip01(uj - part(P.DT4[g4 & 1], e)), P.dacc[r], -part(P.D4[g4 & 1], e));
+        else ds = P.pv[r] * (P.dacc[r] - part(P.D4[g4 & 1], e));
+        if constexpr (r & 1) P.dsb[h][r >> 3][(r & 7) >> 1] = pack_bf16x2(P.ds_even, ds);
+        else P.ds_even = ds;
+    };
+    // elements [16 e / ESL, 16 (e + 1) / ESL) in the e-th of the ESL slots of an elementwise part
+    auto p_slice = [&](Pipe& P, auto gatedc, auto checkc, auto hc, auto ec, int rel0) {
+        constexpr int e = decltype(ec)::value;
+        static_for<16 * e / ESL, 16 * (e + 1) / ESL>([&](auto rc) { p_element(P, gatedc, checkc, hc, rc, rel0); });
+    };
+    auto ds_slice = [&](Pipe& P, auto gatedc, auto hc, auto ec, uint32_t mb) {   // mb: the values of the unit's tile
+        constexpr int e = decltype(ec)::value;
+        static_for<16 * e / ESL, 16 * (e + 1) / ESL>([&](auto rc) { ds_element(P, gatedc, hc, rc, mb); });
+    };
+    // the products of a run are far enough behind: the slots between, and a few states more (all of them where nothing lies between)
+    auto settled = [](f32x16& x, auto alone) {
+        if constexpr (decltype(alone)::value) asm volatile("s_nop 15\n\ts_nop 7" : "+v"(x));
+        else asm volatile("s_nop 3" : "+v"(x));
+    };
+#define SPK_I(x) std::integral_constant<int, (x)>{}
+    // tile t; slot(idx) issues the product, refills the P.ring and does whatever lies under it
+    auto tile = [&](Pipe& P, auto gatedc, auto checkc, auto firstc, int t) {
+        constexpr bool FIRST = decltype(firstc)::value;
+        const int rel0 = blo + t * KT + 4 * half - lo_eff;
+        const int ni = blo + min(t + 2, ntiles - 1) * KT, nbuf = (t + 2) & (DKV_NBUF - 1);
+        if constexpr (FIRST) static_for<0, DEPTH>([&](auto ic) { P.ring[decltype(ic)::value] = operand(ic); });
+        static_for<0, 8 * DS>([&](auto ic) {
+            constexpr int idx = decltype(ic)::value, run = idx / DS, m = idx % DS, h = run / 4, kind = run % 4;
+            constexpr bool product = !(FIRST && h == 0 && (kind & 1));
+            const bf16x8 cur = P.ring[idx % DEPTH];
+            if constexpr (product) {
+                if constexpr (kind == 0) mfma_v<m == 0>(P.sacc, cur, kreg[m]);
+                else if constexpr (kind == 2) mfma_v<m == 0>(P.dacc, cur, vreg[m]);
+                else if constexpr (kind == 1) acc_v[m % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, __builtin_bit_cast(bf16x8, P.pb[h ^ 1][m / DB]), acc_v[m % DB], 0, 0, 0);
+                else acc_k[m % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, __builtin_bit_cast(bf16x8, P.dsb[h ^ 1][m / DB]), acc_k[m % DB], 0, 0, 0);
             }
-            const float l2 = e == 0 ? L4.x : e == 1 ? L4.y : e == 2 ? L4.z : L4.w;
-            const float Di = e == 0 ? D4.x : e == 1 ? D4.y : e == 2 ? D4.z : D4.w;
-            float gate = 1.0f;
-            if constexpr (GATED) gate = clip01(uj - (e == 0 ? T4.x : e == 1 ? T4.y : e == 2 ? T4.z : T4.w));
-            const float qk = sacc[r], dov = dacc[r];
-            float arg = GK ? fmaf(qk, gate * c2, -l2) : fmaf(qk, c2, -l2);
-            if constexpr (CHECK) {
-                const bool valid = (unsigned)(rel0 + (32 * qb + 8 * g4 + e)) <= span;
-                arg = valid ? arg : -INFINITY;  // p = 0, and with it dS
+            if constexpr (idx == 8 * DS - DEPTH) {   // the next tile's barrier; from here on its rows are read
+                landed();
+                rcur = rlane + (uint32_t)((t + 1) & (DKV_NBUF - 1)) * TB;
             }
-            const float p = __builtin_amdgcn_exp2f(arg);
-            const float pvv = GV ? p * gate : p;
-            const float tt = GV ? fmaf(gate, dov, -Di) : dov - Di;
-            const float ds = GK ? pvv * tt : p * tt;
-            if constexpr ((r & 1) == 0) {
-                hold_p = pvv;
-                hold_s = ds;
-            } else {
-                pb[r >> 3][(r & 7) >> 1] = pack_bf16x2(hold_p, pvv);
-                dsb[r >> 3][(r & 7) >> 1] = pack_bf16x2(hold_s, ds);
+            constexpr int nx = idx + DEPTH, nrun = nx / DS;
+            if constexpr (!(FIRST && nrun < 4 && (nrun & 1))) P.ring[idx % DEPTH] = operand(SPK_I(nx));
+            // the gather: a step per slot without elementwise work, in the runs dV, dK of the first unit and dV of the second
+            if constexpr ((kind & 1) && m < LEAD) {
+                constexpr int g = (run / 2) * LEAD + m;
+                if constexpr (g < NX) issue_step(nbuf, ni, g);
+                if constexpr (g == NX) issue_meta(nbuf, ni);
             }
-        };
-        static_for<0, NS>([&](auto mc) {  // run 1
-            constexpr int m = decltype(mc)::value;
-            const bf16x8 cur = ring[m % DEPTH];
-            if constexpr (m & 1) mfma_v<(m < 2)>(d0, cur, vreg[m / 2]);
-            else mfma_v<(m < 2)>(s0, cur, kreg[m / 2]);
-            if constexpr (m == NS - 1) mfma_done(s0, d0);
-            refill(mc);
-            __builtin_amdgcn_sched_barrier(0);
-        });
-        static_for<0, NS>([&](auto mc) {  // run 2
-            constexpr int m = decltype(mc)::value;
-            const bf16x8 cur = ring[(NS + m) % DEPTH];
-            if constexpr (m & 1) mfma_v<(m < 2)>(d1, cur, vreg[m / 2]);
-            else mfma_v<(m < 2)>(s1, cur, kreg[m / 2]);
-            refill(std::integral_constant<int, NS + m>{});
-            static_for<0, EPM>([&](auto ec) {
-                element(std::integral_constant<int, 0>{}, std::integral_constant<int, m * EPM + decltype(ec)::value>{}, s0, d0, pb0, dsb0);
-            });
-            __builtin_amdgcn_sched_barrier(0);
-        });
-        mfma_done(s1, d1);
-        static_for<0, NS>([&](auto mc) {  // run 3
-            constexpr int m = decltype(mc)::value, i2 = m / 2, x = i2 % DB;
-            const bf16x8 cur = ring[(2 * NS + m) % DEPTH];
-            if constexpr (m & 1) acc_k[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, __builtin_bit_cast(bf16x8, dsb0[i2 / DB]), acc_k[x], 0, 0, 0);
-            else acc_v[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, __builtin_bit_cast(bf16x8, pb0[i2 / DB]), acc_v[x], 0, 0, 0);
-            refill(std::integral_constant<int, 2 * NS + m>{});
-            static_for<0, EPM>([&](auto ec) {
-                element(std::integral_constant<int, 1>{}, std::integral_constant<int, m * EPM + decltype(ec)::value>{}, s1, d1, pb1, dsb1);
-            });
-            __builtin_amdgcn_sched_barrier(0);
-        });
-        static_for<0, NS>([&](auto mc) {  // run 4
-            constexpr int m = decltype(mc)::value, i2 = m / 2, x = i2 % DB;
-            const bf16x8 cur = ring[(3 * NS + m) % DEPTH];
-            if constexpr (m & 1) acc_k[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, __builtin_bit_cast(bf16x8, dsb1[i2 / DB]), acc_k[x], 0, 0, 0);
-            else acc_v[x] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, __builtin_bit_cast(bf16x8, pb1[i2 / DB]), acc_v[x], 0, 0, 0);
-            refill(std::integral_constant<int, 3 * NS + m>{});
+            // elementwise work
+            if constexpr (kind == 0 && m == DS - 2) p_values(P, gatedc, SPK_I(h), SPK_I(0));
+            if constexpr (kind == 2 && m == DS - 2) ds_values(P, gatedc, SPK_I(h), SPK_I(0), mcur);
+            if constexpr (kind == 1 && m == LEAD) settled(P.sacc, SPK_I(FIRST && h == 0));
+            if constexpr (kind == 3 && m == LEAD) settled(P.dacc, SPK_I(FIRST && h == 0));
+            if constexpr (kind == 1 && m >= LEAD) p_slice(P, gatedc, checkc, SPK_I(h), SPK_I(m - LEAD), rel0);
+            if constexpr (kind == 2) p_slice(P, gatedc, checkc, SPK_I(h), SPK_I(m + DS - LEAD), rel0);
+            if constexpr (kind == 3 && m >= LEAD) ds_slice(P, gatedc, SPK_I(h), SPK_I(m - LEAD), mcur);
+            if constexpr (kind == 0 && !(FIRST && h == 0)) ds_slice(P, gatedc, SPK_I(h ^ 1), SPK_I(m + DS - LEAD), h == 0 ? mprev : mcur);
             __builtin_amdgcn_sched_barrier(0);
         });
     };
-    auto step = [&](auto gated_c, auto buf_c, int t) {
-        constexpr int buf = decltype(buf_c)::value;
-        const int i_first = blo + t * KT;
-        // the dK / dV accumulators stay in the accumulation registers: only MFMAs touch them until the end
+    // what is left of the last tile: the rest of its second unit's dS, and its dV and dK
+    auto finish = [&](Pipe& P, auto gatedc) {
+        static_for<DS, 2 * DS>([&](auto ic) { if constexpr (decltype(ic)::value < DS + DEPTH) P.ring[decltype(ic)::value % DEPTH] = operand(ic); });
+        static_for<0, DS>([&](auto mc) { ds_slice(P, gatedc, SPK_I(1), SPK_I(decltype(mc)::value + DS - LEAD), mprev); });
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<0, 2 * DS>([&](auto ic) {
+            constexpr int idx = decltype(ic)::value, m = idx % DS;
+            const bf16x8 cur = P.ring[(DS + idx) % DEPTH];
+            if constexpr (idx < DS) acc_v[m % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, __builtin_bit_cast(bf16x8, P.pb[1][m / DB]), acc_v[m % DB], 0, 0, 0);
+            else acc_k[m % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, __builtin_bit_cast(bf16x8, P.dsb[1][m / DB]), acc_k[m % DB], 0, 0, 0);
+            constexpr int nx = idx + DEPTH;   // operands of dV (run 1), then of dK (run 3)
+            if constexpr (nx < 2 * DS) P.ring[(DS + idx) % DEPTH] = operand(SPK_I(nx < DS ? DS + nx : 2 * DS + nx));
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    auto tiles = [&](auto gatedc) {
+        Pipe P;
+        bool prev = false;
+        for (int t = 0; t <= ntiles; t++) {
+            // the dK / dV accumulators stay in the accumulation registers: only MFMAs touch them until the end
 #pragma unroll
-        for (int x = 0; x < DB; x++) asm volatile("" : "+a"(acc_k[x]), "+a"(acc_v[x]));
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();  // tile t landed (rows and per-query values); everybody is done with tile t-1
-        if (t + 1 < ntiles) {
-            issue_meta(buf ^ 1, i_first + KT);
-            issue(buf ^ 1, i_first + KT);
-        }
-        if (i_first <= whi && i_first + KT - 1 >= wlo) {  // some key of this wave is attended from this tile
-            const bool full = i_first >= wfull_lo && i_first + KT - 1 <= wfull_hi;
-            if (full) tile(gated_c, std::false_type{}, buf_c, i_first);
-            else tile(gated_c, std::true_type{}, buf_c, i_first);
-        }
-    };
-    auto tiles = [&](auto gated_c) {
-        for (int t = 0; t < ntiles; t += 2) {
-            step(gated_c, std::integral_constant<int, 0>{}, t);
-            if (t + 1 < ntiles) step(gated_c, std::integral_constant<int, 1>{}, t + 1);
+            for (int x = 0; x < DB; x++) asm volatile("" : "+a"(acc_k[x]), "+a"(acc_v[x]));
+            const int i_first = blo + t * KT;
+            const uint32_t cb = (uint32_t)(t & (DKV_NBUF - 1));
+            rcur = rlane + cb * TB;
+            tprev = tcur;
+            mprev = mcur;
+            tcur = tlane + cb * TB;
+            mcur = mlane + cb * MB;
+            // some key of this wave is attended from this tile
+            const bool live = t < ntiles && i_first <= whi && i_first + KT - 1 >= wlo;
+            if (live) {
+                const bool full = i_first >= wfull_lo && i_first + KT - 1 <= wfull_hi;
+                if (!prev) tile(P, gatedc, std::true_type{}, std::true_type{}, t);
+                else if (full) tile(P, gatedc, std::false_type{}, std::false_type{}, t);
+                else tile(P, gatedc, std::true_type{}, std::false_type{}, t);
+            } else {
+                if (prev) finish(P, gatedc);
+                if (t < ntiles) {
+                    issue(t + 2);
+                    landed();
+                }
+            }
+            prev = live;
         }
     };
     if (selected_kind && MODE != 2) tiles(std::true_type{});
     else tiles(std::false_type{});
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (loads past the last tile land in LDS that is still this workgroup's)
+#undef SPK_I
     // A key that is never selected gets all of its gradient here: round and store it.  The other keys' two parts
     // (window block, selected block) go to fp32 buffers and are added by the merge kernel.
     if (kreal) {
