@@ -1110,7 +1110,7 @@ static void launch_dkv_mfma(const sparsek_cfg& c, const void* q, const void* k, 
 int launch_attn_bwd(const sparsek_cfg& c, const void* q, const void* k, const void* v, const float* u,
                     const float* tau, const int32_t* death, const void* o, const float* lse, const void* dO, void* dq,
                     void* dk, void* dv, void* ws, hipStream_t st, int q_begin, const int32_t* first_valid, int q_rows,
-                    const MaskBwdPrep* prep, BwdShared* shared)
+                    const MaskBwdPrep* prep, BwdShared* shared, const FwdLists* have)
 {
     const AbwdWs W = abwd_ws(c);
     char* base = (char*)ws;
@@ -1136,7 +1136,12 @@ int launch_attn_bwd(const sparsek_cfg& c, const void* q, const void* k, const vo
         x.u = (float*)(base + W.xu);
         x.KP = (int)ext_stride(c);
     }
-    launch_block_lists_ext(c, death, lists, counts, u, x, st);
+    if (mfma && have) {
+        lists = const_cast<int32_t*>(have->lists);
+        counts = const_cast<int32_t*>(have->counts);
+        x = ExtLists{const_cast<int32_t*>(have->pos), const_cast<int32_t*>(have->death), const_cast<float*>(have->u), x.KP};
+    } else
+        launch_block_lists_ext(c, death, lists, counts, u, x, st);
     dim3 grid(nb, c.B * c.H);
     if (c.dtype == SPARSEK_F32) {
         hipLaunchKernelGGL(abwd_delta_kernel<float>, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, (const float*)o,
@@ -1196,14 +1201,15 @@ int launch_attn_bwd(const sparsek_cfg& c, const void* q, const void* k, const vo
 
 int launch_bwd(const sparsek_cfg& cfg, const void* q, const void* k, const void* v, const float* u, const float* tau,
                const int32_t* death, const void* o, const float* lse, const void* dO, void* dq, void* dk, void* dv, float* du,
-               void* attn_ws, void* mask_ws, hipStream_t st, int q_begin, const int32_t* first_valid, int q_rows, int t_min)
+               void* attn_ws, void* mask_ws, hipStream_t st, int q_begin, const int32_t* first_valid, int q_rows, int t_min,
+               const FwdLists* lists)
 {
     sparsek_cfg c = cfg;
     if (c.gate_mode == 3) c.gate_mode = 2;  // the straight-through forward has no gates on q, k, v
     const MaskBwdPrep prep = mask_bwd_prep(cfg, u, tau, mask_ws, t_min, first_valid);
     BwdShared shared{nullptr, nullptr, nullptr};
     const int rc = launch_attn_bwd(c, q, k, v, u, tau, death, o, lse, dO, dq, dk, dv, attn_ws, st, q_begin, first_valid, q_rows,
-                                   &prep, &shared);
+                                   &prep, &shared, lists);
     if (rc) return rc;
     return launch_mask_bwd(cfg, q, k, v, u, tau, death, o, lse, dO, du, mask_ws, st, q_begin, q_rows, t_min, first_valid,
                            shared.delta ? &shared : nullptr);

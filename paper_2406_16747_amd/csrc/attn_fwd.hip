@@ -11,6 +11,7 @@
 // (queries x keys) tiles.
 #include "common.hpp"
 #include "attn_tiles.hpp"
+#include "chunk_parts.hpp"
 #include <type_traits>
 
 namespace spk {
@@ -137,22 +138,36 @@ __device__ __forceinline__ int block_list(ListSmem& sm, int buf, int ncand, int 
 }
 
 // BL_REG: lifetimes per lane of a scan.  32 read a prefix of 32768 once; 8 leave room for a second workgroup on the
-// compute unit.  RUNS: a workgroup owns `run` consecutive blocks, else one.
-template <int BL_REG, bool RUNS>
+// compute unit.  RUNS: a workgroup owns `run` consecutive blocks, else one.  CHUNK: lifetimes are read as the end of a chunk has
+// them, and the first workgroup of a row clears them in memory and finds the row's survivors.
+template <int BL_REG, bool RUNS, bool CHUNK>
 __global__ __launch_bounds__(64 * BL_WAVES, RUNS ? 8 : 4) void block_lists_kernel(
     const int32_t* __restrict__ death, int n, int k, int w, int nb, int run /* consecutive blocks per workgroup */,
     int32_t* __restrict__ lists, int32_t* __restrict__ counts, const float* __restrict__ u, int32_t* __restrict__ xpos,
-    int32_t* __restrict__ xdeath, float* __restrict__ xu, int KP)
+    int32_t* __restrict__ xdeath, float* __restrict__ xu, int KP, int blk0, ChunkTail tail)
 {
     constexpr int NT = 64 * BL_WAVES;
-    __shared__ ListSmem sm;
+    union Smem {
+        __device__ Smem() {}
+        ListSmem l;
+        RetainSmem r;
+    };
+    __shared__ Smem smem;
+    ListSmem& sm = smem.l;
+    if (CHUNK && blockIdx.x == 0) {
+        chunk_clear_padding(tail, blockIdx.y, NT);
+        chunk_retain(smem.r, tail, blockIdx.y);
+        return;
+    }
+    const int wg = CHUNK ? blockIdx.x - 1 : blockIdx.x;
     const int row = blockIdx.y, nrows = gridDim.y;
     const int tid = threadIdx.x;
     const int32_t* dr = death + (size_t)row * n;
+    auto lifetime = [&](int e) { return CHUNK ? tail.lifetime(row, e) : dr[e]; };
     const float* ur = u ? u + (size_t)row * n : nullptr;
     int stayed = -1;   // entries of the list before that stayed selected; -1: no such list
     int buf = 0;
-    const int b_first = RUNS ? blockIdx.x * run : blockIdx.x, b_end = RUNS ? min(nb, b_first + run) : b_first + 1;
+    const int b_first = blk0 + (RUNS ? wg * run : wg), b_end = RUNS ? min(nb, b_first + run) : b_first + 1;
     for (int blk = b_first; blk < b_end; blk++) {
         const int T0 = blk * QB - w;
         if (T0 < 0 || k == 0) {
@@ -166,14 +181,14 @@ __global__ __launch_bounds__(64 * BL_WAVES, RUNS ? 8 : 4) void block_lists_kerne
         const ListOut out{lists + ((size_t)row * nb + blk) * (size_t)k, xpos ? xpos + xo : nullptr, xdeath + xo, xu + xo};
         int cnt, tot_s;
         if (!RUNS || stayed < 0) {
-            tot_s = block_list<BL_REG>(sm, buf, T0 + 1, T0, k, ur, out, cnt, [&](int e) { return dr[e]; },
+            tot_s = block_list<BL_REG>(sm, buf, T0 + 1, T0, k, ur, out, cnt, lifetime,
                                        [](int e) { return e; });
         } else {   // what stayed, then the positions T0 - QB + 1 .. T0: ascending again
             const int* pp = sm.pos[buf ^ 1];
             const int* pd = sm.death[buf ^ 1];
             const int first = T0 - QB + 1 - stayed;
             tot_s = block_list<2>(sm, buf, stayed + QB, T0, k, ur, out, cnt,
-                                  [&](int e) { return e < stayed ? pd[e] : dr[first + e]; },
+                                  [&](int e) { return e < stayed ? pd[e] : lifetime(first + e); },
                                   [&](int e) { return e < stayed ? pp[e] : first + e; });
         }
         if (tid == 0) {
@@ -676,14 +691,15 @@ __device__ __forceinline__ void run_tiles(FwdSmem<D>& sm, const StageSrc& src, i
     }
 }
 
-template <int D, int MODE>
+// TAIL: workgroups behind the blocks move the rows that survive a chunk (an instance of its own: the registers are all taken).
+template <int D, int MODE, bool TAIL>
 __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ kk, const uint16_t* __restrict__ v,
     const float* __restrict__ u, const float* __restrict__ tau, const int32_t* __restrict__ death,
     const int32_t* __restrict__ xpos, const int32_t* __restrict__ xdeath, const float* __restrict__ xu, int KP,
     const int32_t* __restrict__ counts, uint16_t* __restrict__ o,
     float* __restrict__ lse, int H, int Gu, int n, int k, int w, float scale, int nb, int BH, int nrows,
-    int q_begin, const int32_t* __restrict__ first_valid, int q_rows)
+    int q_begin, const int32_t* __restrict__ first_valid, int q_rows, ChunkTail tail)
 {
     __shared__ __align__(16) FwdSmem<D> sm;
     constexpr int DS = D / 16;   // MFMA k-steps over the head dim
@@ -691,6 +707,11 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, col = lane & 31;
 
+    if (TAIL && (int)blockIdx.x >= nb * BH) {
+        const int id = blockIdx.x - nb * BH, bh = id % BH;
+        chunk_retain_rows(tail, bh, bh / H * Gu + (Gu == 1 ? 0 : bh % H), id / BH);
+        return;
+    }
     // ---- block -> (head, query block): heads are dealt to the 8 XCDs so that one head's
     // blocks share an L2; late (long) blocks go first
     int bh, blk;
@@ -821,35 +842,46 @@ template <int D>
 static void launch_mfma(const sparsek_cfg& c, const void* q, const void* k, const void* v, const float* u,
                         const float* tau, const int32_t* death, const ExtLists& x, const int32_t* counts,
                         void* o, float* lse, int nb, int q_begin, const int32_t* first_valid,
-                        int q_rows, hipStream_t st)
+                        int q_rows, const ChunkTail& tail, hipStream_t st)
 {
     const int BH = c.B * c.H;
-    dim3 grid(nb * BH);
-#define SPK_LAUNCH(MODE)                                                                                          \
-    hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, MODE>), grid, dim3(256), 0, st, (const uint16_t*)q,               \
+    dim3 grid((nb + tail.wgs) * BH);
+#define SPK_LAUNCH(MODE, TAIL)                                                                                    \
+    hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, MODE, TAIL>), grid, dim3(256), 0, st, (const uint16_t*)q,         \
                        (const uint16_t*)k, (const uint16_t*)v, u, tau, death, (const int32_t*)x.pos,              \
                        (const int32_t*)x.death, (const float*)x.u, x.KP, counts, (uint16_t*)o, lse, c.H, c.Gu,    \
-                       c.n, c.k, c.w, c.softmax_scale, nb, BH, c.B * c.Gu, q_begin, first_valid, q_rows)
-    if (c.gate_mode == 0) SPK_LAUNCH(0);
-    else if (c.gate_mode == 1) SPK_LAUNCH(1);
-    else SPK_LAUNCH(2);
+                       c.n, c.k, c.w, c.softmax_scale, nb, BH, c.B * c.Gu, q_begin, first_valid, q_rows, tail)
+    if (tail.wgs) {
+        if (c.gate_mode == 0) SPK_LAUNCH(0, true);
+        else if (c.gate_mode == 1) SPK_LAUNCH(1, true);
+        else SPK_LAUNCH(2, true);
+    } else if (c.gate_mode == 0) SPK_LAUNCH(0, false);
+    else if (c.gate_mode == 1) SPK_LAUNCH(1, false);
+    else SPK_LAUNCH(2, false);
 #undef SPK_LAUNCH
 }
 
 void launch_block_lists_ext(const sparsek_cfg& c, const int32_t* death, int32_t* lists, int32_t* counts,
-                                   const float* u, const ExtLists& x, hipStream_t st)
+                            const float* u, const ExtLists& x, hipStream_t st, int q_begin, const ChunkTail* tail)
 {
-    const int nb = nblocks(c.n);
+    const int nb = nblocks(c.n), blk0 = tail ? q_begin / QB : 0, nl = nb - blk0;
     // Up to 256 blocks: a compute unit for each.  More: two workgroups per compute unit, and runs of up to 16 blocks
     // once there are several rounds of them.
-    const long long blocks = (long long)nb * c.B * c.Gu;
+    const long long blocks = (long long)nl * c.B * c.Gu;
     const int run = (int)std::max(1ll, std::min(16ll, blocks / 512));
-    if (blocks > 256)
-        hipLaunchKernelGGL((block_lists_kernel<8, true>), dim3((nb + run - 1) / run, c.B * c.Gu), dim3(64 * BL_WAVES), 0, st, death,
-                           c.n, c.k, c.w, nb, run, lists, counts, u, x.pos, x.death, x.u, x.KP);
-    else
-        hipLaunchKernelGGL((block_lists_kernel<32, false>), dim3(nb, c.B * c.Gu), dim3(64 * BL_WAVES), 0, st, death, c.n, c.k, c.w,
-                           nb, 1, lists, counts, u, x.pos, x.death, x.u, x.KP);
+    const ChunkTail t = tail ? *tail : ChunkTail{};
+#define SPK_LISTS(REG, RUNS, CHUNK)                                                                                       \
+    hipLaunchKernelGGL((block_lists_kernel<REG, RUNS, CHUNK>), dim3((RUNS ? (nl + run - 1) / run : nl) + (CHUNK ? 1 : 0), c.B * c.Gu), \
+                       dim3(64 * BL_WAVES), 0, st, death, c.n, c.k, c.w, nb, RUNS ? run : 1, lists, counts, u, x.pos, x.death, \
+                       x.u, x.KP, blk0, t)
+    if (blocks > 256) {
+        if (tail) SPK_LISTS(8, true, true);
+        else SPK_LISTS(8, true, false);
+    } else {
+        if (tail) SPK_LISTS(32, false, true);
+        else SPK_LISTS(32, false, false);
+    }
+#undef SPK_LISTS
 }
 
 void launch_block_lists(const sparsek_cfg& c, const int32_t* death, int32_t* lists, int32_t* counts,
@@ -858,25 +890,43 @@ void launch_block_lists(const sparsek_cfg& c, const int32_t* death, int32_t* lis
     launch_block_lists_ext(c, death, lists, counts, nullptr, ExtLists{nullptr, nullptr, nullptr, 0}, st);
 }
 
+bool attn_fwd_mfma(const sparsek_cfg& c)
+{
+    return c.dtype == SPARSEK_BF16 && (c.d == 64 || c.d == 128) && (uint64_t)c.n * c.d * 2 <= 0xFFFFFFFFull;
+}
+
+static ExtLists fwd_ext_lists(const sparsek_cfg& c, char* ws, size_t lb)
+{
+    const size_t xb = ext_array_bytes(c);
+    return ExtLists{(int32_t*)(ws + lb), (int32_t*)(ws + lb + xb), (float*)(ws + lb + 2 * xb), (int)ext_stride(c)};
+}
+
+FwdLists attn_fwd_lists(const sparsek_cfg& c, const void* ws)
+{
+    if (!attn_fwd_mfma(c)) return FwdLists{};
+    size_t coff = 0;
+    const size_t lb = block_lists_bytes(c, &coff);
+    const ExtLists x = fwd_ext_lists(c, (char*)ws, lb);
+    return FwdLists{(const int32_t*)ws, (const int32_t*)((const char*)ws + coff), x.pos, x.death, x.u};
+}
+
 int launch_attn_fwd(const sparsek_cfg& c, const void* q, const void* k, const void* v, const float* u,
                     const float* tau, const int32_t* death, void* o, float* lse, void* ws,
-                    hipStream_t st, int q_begin, const int32_t* first_valid, int q_rows)
+                    hipStream_t st, int q_begin, const int32_t* first_valid, int q_rows, const ChunkTail* tail)
 {
     const int nb = nblocks(c.n);
     size_t coff = 0;
     const size_t lb = block_lists_bytes(c, &coff);
     int32_t* lists = (int32_t*)ws;
     int32_t* counts = (int32_t*)((char*)ws + coff);
-    if (c.dtype == SPARSEK_BF16 && (c.d == 64 || c.d == 128) && (uint64_t)c.n * c.d * 2 <= 0xFFFFFFFFull) {
-        const size_t xb = ext_array_bytes(c);
-        ExtLists x;
-        x.pos = (int32_t*)((char*)ws + lb);
-        x.death = (int32_t*)((char*)ws + lb + xb);
-        x.u = (float*)((char*)ws + lb + 2 * xb);
-        x.KP = (int)ext_stride(c);
-        launch_block_lists_ext(c, death, lists, counts, u, x, st);
-        if (c.d == 64) launch_mfma<64>(c, q, k, v, u, tau, death, x, counts, o, lse, nb, q_begin, first_valid, q_rows, st);
-        else launch_mfma<128>(c, q, k, v, u, tau, death, x, counts, o, lse, nb, q_begin, first_valid, q_rows, st);
+    if (attn_fwd_mfma(c)) {
+        const ExtLists x = fwd_ext_lists(c, (char*)ws, lb);
+        launch_block_lists_ext(c, death, lists, counts, u, x, st, q_begin, tail);
+        ChunkTail t = tail ? *tail : ChunkTail{};
+        // a workgroup of the row copy takes 16 KB or more of each tensor; 2048 of them are four rounds of what the chip holds
+        t.wgs = tail ? (int)std::max<long long>(1, std::min<long long>(((long long)t.rcap * t.unit + 1023) / 1024, 2048 / std::max(1, c.B * c.H))) : 0;
+        if (c.d == 64) launch_mfma<64>(c, q, k, v, u, tau, death, x, counts, o, lse, nb, q_begin, first_valid, q_rows, t, st);
+        else launch_mfma<128>(c, q, k, v, u, tau, death, x, counts, o, lse, nb, q_begin, first_valid, q_rows, t, st);
         return launch_status();
     }
     launch_block_lists(c, death, lists, counts, st);

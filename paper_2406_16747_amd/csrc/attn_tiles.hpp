@@ -138,9 +138,10 @@ struct ExtLists {
     int KP;
 };
 
-// Builds the per-block lists (and, with x.pos != nullptr, their extended form) of every score row.
+// Builds the per-block lists (and, with x.pos != nullptr, their extended form) of every score row.  tail: of the blocks from query
+// q_begin on, and what the end of a chunk adds to the launch.
 void launch_block_lists_ext(const sparsek_cfg& c, const int32_t* death, int32_t* lists, int32_t* counts,
-                            const float* u, const ExtLists& x, hipStream_t st);
+                            const float* u, const ExtLists& x, hipStream_t st, int q_begin = 0, const struct ChunkTail* tail = nullptr);
 
 // Metadata (position, lifetime, score of every key of the block's key set) is staged in segments of TPS tiles, double
 // buffered: while the tiles of one segment run, the next segment is copied into the other buffer.

@@ -17,6 +17,7 @@
 // keys and gates of the unchunked run.  The mask and attention kernels are told the first real
 // position: rows start there, and the padding is kept out of every query's key set (lifetimes cleared).
 #include "common.hpp"
+#include "chunk_parts.hpp"
 
 namespace spk {
 
@@ -62,7 +63,7 @@ static sparsek_cfg virtual_cfg(const sparsek_chunk_cfg& c, int nv)
 }
 
 struct ChunkWs {
-    size_t u, tau, death, map, first, lse, k, v, mask, attn, total;
+    size_t u, tau, death, map, first, kept, lse, k, v, mask, attn, total;
 };
 static ChunkWs chunk_ws(const sparsek_chunk_cfg& c, int clen)
 {
@@ -77,6 +78,7 @@ static ChunkWs chunk_ws(const sparsek_chunk_cfg& c, int clen)
     W.death = off; off += align_up(rows * nv * 4, 256);
     W.map = off; off += align_up(rows * L.rcap * 4, 256);
     W.first = off; off += align_up(rows * 4, 256);
+    W.kept = off; off += align_up(rows * (size_t)(L.rcap / 64) * 8, 256);
     W.lse = off; off += align_up(BH * (size_t)clen * 4, 256);
     const size_t tens = align_up(BH * nv * c.d * esize(c.dtype), 256);
     W.k = off; off += tens;
@@ -94,17 +96,24 @@ __global__ void chunk_init_kernel(int32_t* count, int32_t* flags, int rows)
     if (i < rows) { count[i] = 0; flags[i] = 0; }
 }
 
-// Scores of the virtual sequence of one row: padding (-inf, nobody looks at it), retained, chunk.
+// Scores of the virtual sequence of one row: padding (-inf, nobody looks at it), retained, chunk.  kept: which of the first rcap
+// positions are neither padding nor retained for their score alone (a wave looks at 64 of them, all before rcap or none).
 __global__ __launch_bounds__(1024) void chunk_assemble_scores_kernel(const int32_t* __restrict__ count,
                                                                      const float* __restrict__ ret_u,
+                                                                     const int32_t* __restrict__ ret_sel,
                                                                      const float* __restrict__ u_chunk, int rcap,
                                                                      int clen, float* __restrict__ u_v,
-                                                                     int32_t* __restrict__ first_valid)
+                                                                     int32_t* __restrict__ first_valid,
+                                                                     unsigned long long* __restrict__ kept)
 {
     const int row = blockIdx.y;
     const int pad = rcap - count[row], nv = rcap + clen;
     const int e = blockIdx.x * 1024 + threadIdx.x;
     if (e == 0) first_valid[row] = pad;
+    if (e < rcap) {
+        const unsigned long long m = __ballot(e >= pad && ret_sel[(size_t)row * rcap + max(e - pad, 0)] != 0);
+        if ((e & 63) == 0) kept[(size_t)row * (rcap / 64) + (e >> 6)] = m;
+    }
     if (e < nv)
         u_v[(size_t)row * nv + e] = e < pad ? -INFINITY : e < rcap ? ret_u[(size_t)row * rcap + (e - pad)]
                                                                    : u_chunk[(size_t)row * clen + (e - rcap)];
@@ -120,135 +129,20 @@ static RowCopy chunk_rows(const sparsek_chunk_cfg& c, const ChunkLayout& L, char
                    (int)(c.d * esize(c.dtype) / 16), 0};
 }
 
-// Padding entries are never selected: death[e] = e.  The same holds for retained keys that were
-// kept only because their score is above the threshold: they left the top-k in an earlier chunk, at
-// a prefix whose block the mask skips, so their lifetime is still at its preset.
-__global__ void chunk_clear_padding_kernel(const int32_t* __restrict__ count, const int32_t* __restrict__ ret_sel,
-                                           int rcap, int nv, int32_t* __restrict__ death)
+// The parts of a chunk's end as launches of their own.
+__global__ __launch_bounds__(1024) void chunk_retain_kernel(ChunkTail c)
 {
-    const int row = blockIdx.y;
-    const int pad = rcap - count[row];
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= rcap) return;
-    if (e < pad || !ret_sel[(size_t)row * rcap + (e - pad)]) death[(size_t)row * nv + e] = e;
+    __shared__ RetainSmem sm;
+    chunk_retain(sm, c, blockIdx.x);
 }
 
-// The survivors of one row, in position order: the last w entries, the keys still selected for the
-// last prefix used so far (T = nv - 1 - w) and every other real key whose score is above that
-// prefix's threshold.  The first two classes always fit; if the third does not, its oldest members
-// are dropped and bit 0 of the row's flag word is set (later thresholds are then approximate).
-//
-// One workgroup per row, so what counts is the number of dependent round trips: a wave owns a contiguous run of positions,
-// fetches 8 x 64 of them at once, whatever their class, and takes counts and ranks from ballots.  Classes are formed again
-// in the second pass, from loads that are in flight together with the scores it needs anyway.
-// Rows of 14336 virtual positions: 17 -> 11 us; four chunks of 8192 tokens with their attention 1626 -> 1588 us.
-constexpr int RETAIN_UNR = 8;
-
-__global__ __launch_bounds__(1024) void chunk_retain_kernel(int32_t* __restrict__ count, int32_t* __restrict__ flags,
-                                                            const float* __restrict__ u_v,
-                                                            const float* __restrict__ tau_v,
-                                                            const int32_t* __restrict__ death_v, int rcap, int clen,
-                                                            int w, int32_t* __restrict__ map, float* __restrict__ ret_u,
-                                                            int32_t* __restrict__ ret_sel)
-{
-    __shared__ int wt[2][16];
-    const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nv = rcap + clen;
-    const int pad = rcap - count[row];
-    const int T = nv - 1 - w;  // last prefix any query has used
-    const float* ur = u_v + (size_t)row * nv;
-    const int32_t* dr = death_v + (size_t)row * nv;
-    const float thr = T >= pad ? tau_v[(size_t)row * nv + T] : -INFINITY;
-    const int groups = (nv + 63) / 64, per = (groups + 15) / 16;
-    const int g0 = min(wv * per, groups), g1 = min(g0 + per, groups);
-    // class 1: mandatory (window, or selected for prefix T); class 2: other keys above the threshold
-    float uu[RETAIN_UNR];
-    unsigned long long m1[RETAIN_UNR], m2[RETAIN_UNR];
-    auto classify = [&](int g) {
-        int dd[RETAIN_UNR];
-#pragma unroll
-        for (int x = 0; x < RETAIN_UNR; x++) {
-            const int e = min((g + x) * 64 + lane, nv - 1);
-            dd[x] = dr[e];
-            uu[x] = ur[e];
-        }
-#pragma unroll
-        for (int x = 0; x < RETAIN_UNR; x++) {
-            const int e = (g + x) * 64 + lane;
-            const bool in = g + x < g1 && e >= pad && e < nv, must = e > T || dd[x] > T;
-            m1[x] = __ballot(in && must);
-            m2[x] = __ballot(in && !must && uu[x] > thr);
-        }
-    };
-    int n1 = 0, n2 = 0;
-    for (int g = g0; g < g1; g += RETAIN_UNR) {
-        classify(g);
-#pragma unroll
-        for (int x = 0; x < RETAIN_UNR; x++) {
-            n1 += __popcll(m1[x]);
-            n2 += __popcll(m2[x]);
-        }
-    }
-    if (lane == 0) {
-        wt[0][wv] = n1;
-        wt[1][wv] = n2;
-    }
-    __syncthreads();
-    int p1 = 0, p2 = 0, t1 = 0, t2 = 0;
-#pragma unroll
-    for (int i = 0; i < 16; i++) {
-        if (i < wv) {
-            p1 += wt[0][i];
-            p2 += wt[1][i];
-        }
-        t1 += wt[0][i];
-        t2 += wt[1][i];
-    }
-    const int allowed = rcap - t1;        // >= 0: the mandatory classes hold at most k + w entries
-    const int drop = t2 > allowed ? t2 - allowed : 0;  // the oldest `drop` members of class 2 go
-    const unsigned long long below = (1ull << lane) - 1;
-    for (int g = g0; g < g1; g += RETAIN_UNR) {
-        classify(g);
-#pragma unroll
-        for (int x = 0; x < RETAIN_UNR; x++) {
-            const bool must = m1[x] >> lane & 1, above = m2[x] >> lane & 1;
-            const int before = p2 + __popcll(m2[x] & below);   // members of class 2 ahead of this entry
-            if (must || (above && before >= drop)) {
-                const size_t j = (size_t)row * rcap + p1 + __popcll(m1[x] & below) + max(before - drop, 0);
-                map[j] = (g + x) * 64 + lane;
-                ret_u[j] = uu[x];
-                ret_sel[j] = must;
-            }
-            p1 += __popcll(m1[x]);
-            p2 += __popcll(m2[x]);
-        }
-    }
-    if (tid == 0) {  // every thread has read the old count (before the barrier)
-        count[row] = t1 + t2 - drop;
-        if (drop > 0) flags[row] |= 1;
-    }
-}
-
-__global__ __launch_bounds__(256) void chunk_retain_rows_kernel(const int32_t* __restrict__ count,
-                                                                const int32_t* __restrict__ map,
-                                                                const uint4* __restrict__ k_v,
-                                                                const uint4* __restrict__ v_v, int H, int Gu, int rcap,
-                                                                int nv, int row16, uint4* __restrict__ ret_k,
-                                                                uint4* __restrict__ ret_v)
+__global__ __launch_bounds__(256) void chunk_retain_rows_kernel(ChunkTail c, int H, int Gu)
 {
     const int bh = blockIdx.y;
-    const int b = bh / H, h = bh % H;
-    const int row = b * Gu + (Gu == 1 ? 0 : h);
-    const size_t total = (size_t)count[row] * row16;
-    for (size_t x = (size_t)blockIdx.x * 256 + threadIdx.x; x < total; x += (size_t)gridDim.x * 256) {
-        const int j = (int)(x / row16), c16 = (int)(x % row16);
-        const int e = map[(size_t)row * rcap + j];
-        const size_t src = ((size_t)bh * nv + e) * row16 + c16;
-        const size_t dst = ((size_t)bh * rcap + j) * row16 + c16;
-        ret_k[dst] = k_v[src];
-        ret_v[dst] = v_v[src];
-    }
+    chunk_retain_rows(c, bh, bh / H * Gu + (Gu == 1 ? 0 : bh % H), blockIdx.x);
 }
+
+__global__ __launch_bounds__(1024) void chunk_clear_padding_kernel(ChunkTail c) { chunk_clear_padding(c, blockIdx.x, 1024); }
 
 int launch_chunk_init(const sparsek_chunk_cfg& c, void* state, hipStream_t st)
 {
@@ -258,6 +152,14 @@ int launch_chunk_init(const sparsek_chunk_cfg& c, void* state, hipStream_t st)
     hipLaunchKernelGGL(chunk_init_kernel, dim3((rows + 255) / 256), dim3(256), 0, st, (int32_t*)(s + L.count),
                        (int32_t*)(s + L.flags), rows);
     return launch_status();
+}
+
+static ChunkTail chunk_tail(const sparsek_chunk_cfg& c, const ChunkLayout& L, const ChunkWs& W, char* s, char* w, int clen)
+{
+    return ChunkTail{(const unsigned long long*)(w + W.kept), (int32_t*)(s + L.count), (int32_t*)(s + L.flags),
+                     (const float*)(w + W.u), (const float*)(w + W.tau), (int32_t*)(w + W.death), L.rcap, clen, c.w,
+                     (int32_t*)(w + W.map), (float*)(s + L.ret_u), (int32_t*)(s + L.ret_sel), (const uint4*)(w + W.k),
+                     (const uint4*)(w + W.v), (uint4*)(s + L.ret_k), (uint4*)(s + L.ret_v), 0, 0};
 }
 
 int launch_chunk_prefill(const sparsek_chunk_cfg& c, void* state, int clen, const void* q, const void* k,
@@ -271,35 +173,37 @@ int launch_chunk_prefill(const sparsek_chunk_cfg& c, void* state, int clen, cons
     char* s = (char*)state;
     char* w = (char*)ws;
     int32_t* count = (int32_t*)(s + L.count);
-    int32_t* flags = (int32_t*)(s + L.flags);
-    float* ret_u = (float*)(s + L.ret_u);
-    uint4* ret_k = (uint4*)(s + L.ret_k);
-    uint4* ret_v = (uint4*)(s + L.ret_v);
     float* u_v = (float*)(w + W.u);
     float* tau_v = (float*)(w + W.tau);
     int32_t* death_v = (int32_t*)(w + W.death);
-    int32_t* map = (int32_t*)(w + W.map);
     int32_t* first_valid = (int32_t*)(w + W.first);
     uint4* k_v = (uint4*)(w + W.k);
     uint4* v_v = (uint4*)(w + W.v);
     const sparsek_cfg cv = virtual_cfg(c, nv);
 
-    hipLaunchKernelGGL(chunk_assemble_scores_kernel, dim3((nv + 1023) / 1024, rows), dim3(1024), 0, st, count, ret_u, u, L.rcap, clen, u_v,
-                       first_valid);
+    hipLaunchKernelGGL(chunk_assemble_scores_kernel, dim3((nv + 1023) / 1024, rows), dim3(1024), 0, st, count,
+                       (const float*)(s + L.ret_u), (const int32_t*)(s + L.ret_sel), u, L.rcap, clen, u_v, first_valid, (unsigned long long*)(w + W.kept));
     const RowCopy copy = chunk_rows(c, L, s, k, v, clen, w + W.k, w + W.v);
     // thresholds are needed from prefix R_cap - w - 1 on (the last one the previous call used)
     int rc = launch_mask(cv, u_v, tau_v, death_v, w + W.mask, st, std::max(0, L.rcap - c.w - 1), first_valid, &copy);
     if (rc) return rc;
-    hipLaunchKernelGGL(chunk_clear_padding_kernel, dim3((L.rcap + 255) / 256, rows), dim3(256), 0, st, count,
-                       (const int32_t*)(s + L.ret_sel), L.rcap, nv, death_v);
+    ChunkTail tail = chunk_tail(c, L, W, s, w, clen);
+    tail.unit = row16;
+    // Where the MFMA kernels do the attention, the rest of the chunk rides on its launches: three launches less, the survivors are
+    // found beside the lists and their rows move while the attention's last blocks run.  32 heads in chunks of 8192, k = w = 1024,
+    // d = 128: 397 -> 385 us a chunk; 8 heads in chunks of 512, k = w = 64: 46 -> 39.
+    if (attn_fwd_mfma(cv)) {
+        rc = launch_attn_fwd(cv, q, k_v, v_v, u_v, tau_v, death_v, o, (float*)(w + W.lse), w + W.attn, st, L.rcap,
+                             first_valid, clen, &tail);
+        return rc ? rc : launch_status();
+    }
+    hipLaunchKernelGGL(chunk_clear_padding_kernel, dim3(rows), dim3(1024), 0, st, tail);
     rc = launch_attn_fwd(cv, q, k_v, v_v, u_v, tau_v, death_v, o, (float*)(w + W.lse), w + W.attn, st, L.rcap,
                          first_valid, clen);
     if (rc) return rc;
-    hipLaunchKernelGGL(chunk_retain_kernel, dim3(rows), dim3(1024), 0, st, count, flags, u_v, tau_v, death_v, L.rcap,
-                       clen, c.w, map, ret_u, (int32_t*)(s + L.ret_sel));
-    const int gr = (int)std::min<size_t>(((size_t)L.rcap * row16 + 255) / 256, 2048);
-    hipLaunchKernelGGL(chunk_retain_rows_kernel, dim3(gr, BH), dim3(256), 0, st, count, map, k_v, v_v, c.H, c.Gu,
-                       L.rcap, nv, row16, ret_k, ret_v);
+    hipLaunchKernelGGL(chunk_retain_kernel, dim3(rows), dim3(1024), 0, st, tail);
+    tail.wgs = (int)std::min<size_t>(((size_t)L.rcap * row16 + 1023) / 1024, 512);
+    hipLaunchKernelGGL(chunk_retain_rows_kernel, dim3(tail.wgs, BH), dim3(256), 0, st, tail, c.H, c.Gu);
     return launch_status();
 }
 
@@ -309,7 +213,7 @@ int launch_chunk_prefill(const sparsek_chunk_cfg& c, void* state, int clen, cons
 // in its workspace; the ordinary backward kernels run on it with the queries offset to the chunk, and only
 // keys from the chunk on receive dk, dv, du.
 struct ChunkBwdWs {
-    size_t du, attn, mask, total;
+    size_t attn, mask, total;
 };
 static ChunkBwdWs chunk_bwd_ws(const sparsek_chunk_cfg& c, int clen)
 {
@@ -318,7 +222,6 @@ static ChunkBwdWs chunk_bwd_ws(const sparsek_chunk_cfg& c, int clen)
     sparsek_cfg v = virtual_cfg(c, nv);
     ChunkBwdWs W;
     size_t off = 0;
-    W.du = off; off += align_up((size_t)c.B * c.Gu * nv * 4, 256);
     W.attn = off; off += align_up(attn_bwd_ws_bytes(v), 256);
     v.gate_mode = c.gate_mode;
     W.mask = off; off += align_up(mask_bwd_ws_bytes(v), 256);
@@ -327,20 +230,12 @@ static ChunkBwdWs chunk_bwd_ws(const sparsek_chunk_cfg& c, int clen)
 }
 size_t chunk_bwd_ws_bytes(const sparsek_chunk_cfg& c) { return chunk_bwd_ws(c, c.chunk_max).total; }
 
-__global__ void chunk_slice_du_kernel(const float* __restrict__ du_v, int nv, int rcap, int clen, float* __restrict__ du)
-{
-    const int row = blockIdx.y;
-    for (int x = blockIdx.x * blockDim.x + threadIdx.x; x < clen; x += gridDim.x * blockDim.x)
-        du[(size_t)row * clen + x] = du_v[(size_t)row * nv + rcap + x];
-}
-
 int launch_chunk_bwd(const sparsek_chunk_cfg& c, int clen, const void* q, const void* o, const void* dO,
                      const void* fwd_ws, void* dq, void* dk, void* dv, float* du, void* ws, hipStream_t st)
 {
     const ChunkLayout L = chunk_layout(c);
     const ChunkWs W = chunk_ws(c, clen);
     const ChunkBwdWs Bw = chunk_bwd_ws(c, clen);
-    const int rows = c.B * c.Gu;
     const int nv = L.rcap + clen;
     const char* w = (const char*)fwd_ws;
     char* b = (char*)ws;
@@ -353,12 +248,10 @@ int launch_chunk_bwd(const sparsek_chunk_cfg& c, int clen, const void* q, const 
     const void* v_v = w + W.v;
     sparsek_cfg cv = virtual_cfg(c, nv);
     cv.gate_mode = c.gate_mode;  // (the straight-through mode has its own score gradient)
-    float* du_v = (float*)(b + Bw.du);
-    const int rc = launch_bwd(cv, q, k_v, v_v, u_v, tau_v, death_v, o, lse, dO, dq, dk, dv, du_v, b + Bw.attn, b + Bw.mask, st,
-                              L.rcap, first_valid, clen, std::max(0, L.rcap - c.w - 1));
-    if (rc) return rc;
-    hipLaunchKernelGGL(chunk_slice_du_kernel, dim3((clen + 255) / 256, rows), dim3(256), 0, st, du_v, nv, L.rcap, clen, du);
-    return launch_status();
+    // (the forward's lists are those of the same lifetimes)
+    const FwdLists lists = attn_fwd_lists(virtual_cfg(c, nv), w + W.attn);
+    return launch_bwd(cv, q, k_v, v_v, u_v, tau_v, death_v, o, lse, dO, dq, dk, dv, du, b + Bw.attn, b + Bw.mask, st,
+                      L.rcap, first_valid, clen, std::max(0, L.rcap - c.w - 1), lists.pos ? &lists : nullptr);
 }
 
 // Decode state after the tokens consumed so far: the retained entries alone (no chunk) form a
@@ -385,12 +278,12 @@ int launch_chunk_to_decode(const sparsek_chunk_cfg& c, void* state, void* ws, co
     uint4* v_v = (uint4*)(w + W.v);
     const sparsek_cfg cv = virtual_cfg(c, nv);
     hipLaunchKernelGGL(chunk_assemble_scores_kernel, dim3((nv + 1023) / 1024, rows), dim3(1024), 0, st, count, (const float*)(s + L.ret_u),
-                       (const float*)nullptr, L.rcap, 0, u_v, (int32_t*)(w + W.first));
+                       (const int32_t*)(s + L.ret_sel), (const float*)nullptr, L.rcap, 0, u_v, (int32_t*)(w + W.first),
+                       (unsigned long long*)(w + W.kept));
     const RowCopy copy = chunk_rows(c, L, s, nullptr, nullptr, 0, w + W.k, w + W.v);
     int rc = launch_mask(cv, u_v, tau_v, death_v, w + W.mask, st, std::max(0, L.rcap - c.w - 1), (const int32_t*)(w + W.first), &copy);
     if (rc) return rc;
-    hipLaunchKernelGGL(chunk_clear_padding_kernel, dim3((L.rcap + 255) / 256, rows), dim3(256), 0, st, count,
-                       (const int32_t*)(s + L.ret_sel), L.rcap, nv, death_v);
+    hipLaunchKernelGGL(chunk_clear_padding_kernel, dim3(rows), dim3(1024), 0, st, chunk_tail(c, L, W, s, w, 0));
     return launch_decode_load(dc, dstate, nv, k_v, v_v, u_v, tau_v, death_v, st);
 }
 

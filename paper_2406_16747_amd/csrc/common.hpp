@@ -36,10 +36,19 @@ int launch_materialize(const sparsek_cfg& c, const float* u, const float* tau, c
 int launch_attn_fwd(const sparsek_cfg& c, const void* q, const void* k, const void* v,
                     const float* u, const float* tau, const int32_t* death, void* o, float* lse,
                     void* ws, hipStream_t st, int q_begin = 0, const int32_t* first_valid = nullptr,
-                    int q_rows = 0);
+                    int q_rows = 0, const struct ChunkTail* tail = nullptr);
 // (query blocks that end at or before q_begin are skipped; keys before first_valid[row] are never attended;
-//  q_rows != 0: q, o and lse hold q_rows rows per head, the first being query q_begin, a multiple of 128)
+//  q_rows != 0: q, o and lse hold q_rows rows per head, the first being query q_begin, a multiple of 128;
+//  tail: the end of a chunk, done in the same launches; only where attn_fwd_mfma)
+bool attn_fwd_mfma(const sparsek_cfg& c);   // the MFMA kernels do the work
 size_t attn_fwd_ws_bytes(const sparsek_cfg& c);
+// The per-block lists that launch_attn_fwd left in its workspace (pos == nullptr: none in the form the backward reads).  With
+// q_begin only those of the blocks from there on.
+struct FwdLists {
+    const int32_t *lists, *counts, *pos, *death;
+    const float* u;
+};
+FwdLists attn_fwd_lists(const sparsek_cfg& c, const void* ws);
 // What a backward of both kinds shares.  launch_attn_bwd builds the per-block lists and dO.o of every query (bf16, d = 64
 // or 128); given `prep` it also clears and fills what launch_mask_bwd starts from, in launches it makes anyway.
 struct BwdShared {
@@ -52,14 +61,15 @@ int launch_mask_bwd(const sparsek_cfg& c, const void* q, const void* k, const vo
                     const float* lse, const void* dO, float* du, void* ws, hipStream_t st, int q_begin = 0,
                     int q_rows = 0, int t_min = 0, const int32_t* first_valid = nullptr,
                     const BwdShared* shared = nullptr);
-// (q_begin, q_rows as in launch_attn_fwd, for q, o, dO and lse; thresholds of prefixes before t_min are not read, row r
+// (q_begin, q_rows as in launch_attn_fwd, for q, o, dO and lse, and du, which holds the scores from q_begin on; thresholds of prefixes before t_min are not read, row r
 //  starts at position first_valid[r]; bf16 with d = 64 or 128 only when any of them is set)
 size_t mask_bwd_ws_bytes(const sparsek_cfg& c);
 int launch_attn_bwd(const sparsek_cfg& c, const void* q, const void* k, const void* v, const float* u,
                     const float* tau, const int32_t* death, const void* o, const float* lse, const void* dO,
                     void* dq, void* dk, void* dv, void* ws, hipStream_t st, int q_begin = 0,
                     const int32_t* first_valid = nullptr, int q_rows = 0, const MaskBwdPrep* prep = nullptr,
-                    BwdShared* shared = nullptr);
+                    BwdShared* shared = nullptr, const FwdLists* lists = nullptr);
+// (lists: those of the forward, where the caller still has them)
 // (shared->delta stays null where the caller's launch_mask_bwd has to do its own preparation)
 // (q_rows != 0: q, o, dO, lse, dq and also dk, dv hold q_rows rows per head, the first being position q_begin: only
 //  keys from q_begin on receive a gradient; keys before first_valid[row] are attended by nobody; bf16, d = 64 / 128)
@@ -70,7 +80,7 @@ size_t attn_bwd_ws_bytes(const sparsek_cfg& c);
 int launch_bwd(const sparsek_cfg& c, const void* q, const void* k, const void* v, const float* u, const float* tau,
                const int32_t* death, const void* o, const float* lse, const void* dO, void* dq, void* dk, void* dv, float* du,
                void* attn_ws, void* mask_ws, hipStream_t st, int q_begin = 0, const int32_t* first_valid = nullptr,
-               int q_rows = 0, int t_min = 0);
+               int q_rows = 0, int t_min = 0, const FwdLists* lists = nullptr);
 
 inline int launch_status()
 {

@@ -617,12 +617,13 @@ constexpr int SCAN_PER = 8;
 // The same for rows of up to 1024 * PER positions: everything a thread needs is fetched at the start and G stays in LDS.
 // A chain of scans on one workgroup per row, so the two round trips of G through memory were most of its time
 // (21 -> 13 us at n = 8192, 9.6 -> 4.5 us at 2000).
+// du holds the scores from position du_begin on.
 template <int PER>
 __global__ __launch_bounds__(1024) void mask_bwd_scan_final_lds_kernel(const float* __restrict__ A,
                                                                         const int32_t* __restrict__ diff,
                                                                         const float* __restrict__ C,
                                                                         const int2* __restrict__ ab, int n,
-                                                                        float* __restrict__ du)
+                                                                        int du_begin, float* __restrict__ du)
 {
     __shared__ int cw[16];
     __shared__ double gw[16];
@@ -676,14 +677,14 @@ __global__ __launch_bounds__(1024) void mask_bwd_scan_final_lds_kernel(const flo
         const int j = 1024 * e + tid;
         const bool any = r[e].x <= r[e].y;
         const double hi = G[any ? r[e].y + 1 : 0], lo = G[any ? r[e].x : 0];
-        if (j < n) du[(size_t)row * n + j] = (float)((double)cv[e] - (hi - lo));
+        if (j < n && j >= du_begin) du[(size_t)row * (n - du_begin) + j - du_begin] = (float)((double)cv[e] - (hi - lo));
     }
 }
 
 __global__ __launch_bounds__(1024) void mask_bwd_scan_final_kernel(const float* __restrict__ A,
                                                                     const int32_t* __restrict__ diff,
                                                                     const float* __restrict__ C,
-                                                                    const int2* __restrict__ ab, int n,
+                                                                    const int2* __restrict__ ab, int n, int du_begin,
                                                                     double* __restrict__ G, float* __restrict__ du)
 {
     __shared__ int cw[16];
@@ -731,7 +732,7 @@ __global__ __launch_bounds__(1024) void mask_bwd_scan_final_kernel(const float* 
     __syncthreads();  // the row's G is complete and visible to the whole workgroup
     const int2* abr = ab + (size_t)row * n;
     const float* Cr = C + (size_t)row * n;
-    float* dur = du + (size_t)row * n;
+    float* dur = du + (size_t)row * (n - du_begin);
     for (int base = 0; base < n; base += 1024 * SCAN_PER) {
         int2 r[SCAN_PER];
         float cv[SCAN_PER];
@@ -751,7 +752,7 @@ __global__ __launch_bounds__(1024) void mask_bwd_scan_final_kernel(const float* 
 #pragma unroll
         for (int e = 0; e < SCAN_PER; e++) {
             const int j = base + 1024 * e + tid;
-            if (j < n) dur[j] = (float)((double)cv[e] - (hi[e] - lo[e]));
+            if (j < n && j >= du_begin) dur[j - du_begin] = (float)((double)cv[e] - (hi[e] - lo[e]));
         }
     }
 }
@@ -789,7 +790,7 @@ int launch_mask_bwd(const sparsek_cfg& c, const void* q, const void* k, const vo
     double* G = (double*)(base + W.G);
     int2* ab = (int2*)(base + W.ab);
     if (mask_bwd_is_zero(c)) {
-        hipLaunchKernelGGL(zero_kernel, dim3(512), dim3(256), 0, st, (uint32_t*)du, (size_t)rows * c.n);
+        hipLaunchKernelGGL(zero_kernel, dim3(512), dim3(256), 0, st, (uint32_t*)du, (size_t)rows * (c.n - q_begin));
         return launch_status();
     }
     if (sh) {   // launch_attn_bwd has built the lists, cleared A, C and diff and written the ranges
@@ -822,13 +823,13 @@ int launch_mask_bwd(const sparsek_cfg& c, const void* q, const void* k, const vo
                            lse, (const uint16_t*)dO, A, C, c.H, c.Gu, c.n, c.d, c.k, c.w, c.gate_mode,
                            c.softmax_scale, nb);
     if (c.n <= 2048)
-        hipLaunchKernelGGL(mask_bwd_scan_final_lds_kernel<2>, dim3(rows), dim3(1024), 0, st, A, diff, C, ab, c.n, du);
+        hipLaunchKernelGGL(mask_bwd_scan_final_lds_kernel<2>, dim3(rows), dim3(1024), 0, st, A, diff, C, ab, c.n, q_begin, du);
     else if (c.n <= 8192)
-        hipLaunchKernelGGL(mask_bwd_scan_final_lds_kernel<8>, dim3(rows), dim3(1024), 0, st, A, diff, C, ab, c.n, du);
+        hipLaunchKernelGGL(mask_bwd_scan_final_lds_kernel<8>, dim3(rows), dim3(1024), 0, st, A, diff, C, ab, c.n, q_begin, du);
     else if (c.n <= 16384)
-        hipLaunchKernelGGL(mask_bwd_scan_final_lds_kernel<16>, dim3(rows), dim3(1024), 0, st, A, diff, C, ab, c.n, du);
+        hipLaunchKernelGGL(mask_bwd_scan_final_lds_kernel<16>, dim3(rows), dim3(1024), 0, st, A, diff, C, ab, c.n, q_begin, du);
     else
-        hipLaunchKernelGGL(mask_bwd_scan_final_kernel, dim3(rows), dim3(1024), 0, st, A, diff, C, ab, c.n, G, du);
+        hipLaunchKernelGGL(mask_bwd_scan_final_kernel, dim3(rows), dim3(1024), 0, st, A, diff, C, ab, c.n, q_begin, G, du);
     return launch_status();
 }
 

@@ -73,6 +73,19 @@ def test_chunked_equals_unchunked(oracle, n, d, k, w, Gu, dtype, chunk):
     assert (counts <= k + w + 4 * max(k, 16) + 127).all() and (counts >= min(n, w)).all()
 
 
+# From 257 blocks of queries on the lists are built by smaller workgroups, from 1024 on each owns more than one block; the first
+# workgroup of every row finds the survivors beside them.  A row per head, a last chunk shorter than a block, and one that ends a block.
+@pytest.mark.parametrize("chunks", [[1100, 60], [4100, 60], [4096, 128]])
+def test_chunks_with_runs_of_blocks(oracle, chunks):
+    require_gpu()
+    say("chunked prefill, runs of blocks", chunks)
+    inp = synth.make(3, Gu=32, seed=sum(chunks), B=1, H=32, n=sum(chunks), d=64, k=48, w=70, qk_div=2.0)
+    o_g, counts, flags = run_chunked(inp, chunks)
+    compare(oracle, inp, o_g)
+    assert not flags.any()
+    assert (counts >= 70).all() and (counts <= 48 + 70 + 4 * 48 + 127).all()
+
+
 @pytest.mark.parametrize("gate_mode", [1, 2, 3])
 def test_chunked_gate_modes_and_uneven_chunks(oracle, gate_mode):
     require_gpu()
