@@ -8,6 +8,7 @@
 // p_ij is recomputed from q, k and the forward's lse; nothing of size n x (k + w) is stored.
 #include "common.hpp"
 #include "attn_tiles.hpp"
+#include "bwd_merge.hpp"
 #include "mask_ranges.hpp"
 
 namespace spk {
@@ -1056,34 +1057,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(
     store(acc_v, 1.0f, (selected_kind ? sv32 : dv32) + po, dv + wo);
 }
 
-// For every ever-selected key (list slot e, position j): dk_j = dk32_j + sk32_e rounded to bf16; same for dv.
-__global__ __launch_bounds__(256) void abwd_merge_kernel(const float* __restrict__ dk32, const float* __restrict__ dv32,
-                                                         const float* __restrict__ sk32, const float* __restrict__ sv32,
-                                                         const int32_t* __restrict__ elist, const int32_t* __restrict__ ecount,
-                                                         int H, int Gu, int n, int d4, uint16_t* __restrict__ dk,
-                                                         uint16_t* __restrict__ dv, int q_begin, int q_rows)
-{
-    const int bh = blockIdx.y;
-    const ptrdiff_t qo = q_rows ? (ptrdiff_t)bh * q_rows - q_begin : (ptrdiff_t)bh * n;  // rows of dk, dv
-    const int b = bh / H, h = bh % H;
-    const int row = b * Gu + (Gu == 1 ? 0 : h);
-    const size_t total = (size_t)ecount[row] * d4;  // float4 units of this head's list
-    for (size_t x = (size_t)blockIdx.x * 256 + threadIdx.x; x < total; x += (size_t)gridDim.x * 256) {
-        const int e = (int)(x / d4), c4 = (int)(x % d4);
-        const int j = elist[(size_t)row * n + e];
-        const size_t src = ((size_t)bh * n + j) * d4 + c4, s2 = ((size_t)bh * n + e) * d4 + c4;
-        float4 a = ((const float4*)dk32)[src], c = ((const float4*)dv32)[src];
-        const float4 a2 = ((const float4*)sk32)[s2], c2 = ((const float4*)sv32)[s2];
-        a.x += a2.x; a.y += a2.y; a.z += a2.z; a.w += a2.w;
-        c.x += c2.x; c.y += c2.y; c.z += c2.z; c.w += c2.w;
-        ushort4 oa, oc;
-        oa.x = f32_to_bf16(a.x); oa.y = f32_to_bf16(a.y); oa.z = f32_to_bf16(a.z); oa.w = f32_to_bf16(a.w);
-        oc.x = f32_to_bf16(c.x); oc.y = f32_to_bf16(c.y); oc.z = f32_to_bf16(c.z); oc.w = f32_to_bf16(c.w);
-        const size_t dst = (size_t)(qo + j) * d4 + c4;
-        ((ushort4*)dk)[dst] = oa;
-        ((ushort4*)dv)[dst] = oc;
-    }
-}
+__global__ __launch_bounds__(256) void abwd_merge_kernel(MergeArgs m) { abwd_merge(m, blockIdx.y, blockIdx.x); }
 
 template <int D>
 static void launch_dkv_mfma(const sparsek_cfg& c, const void* q, const void* k, const void* v, const float* u,
@@ -1110,7 +1084,7 @@ static void launch_dkv_mfma(const sparsek_cfg& c, const void* q, const void* k, 
 int launch_attn_bwd(const sparsek_cfg& c, const void* q, const void* k, const void* v, const float* u,
                     const float* tau, const int32_t* death, const void* o, const float* lse, const void* dO, void* dq,
                     void* dk, void* dv, void* ws, hipStream_t st, int q_begin, const int32_t* first_valid, int q_rows,
-                    const MaskBwdPrep* prep, BwdShared* shared, const FwdLists* have)
+                    const MaskBwdPrep* prep, BwdShared* shared, const FwdLists* have, MergeArgs* merge)
 {
     const AbwdWs W = abwd_ws(c);
     char* base = (char*)ws;
@@ -1171,7 +1145,7 @@ int launch_attn_bwd(const sparsek_cfg& c, const void* q, const void* k, const vo
                 aux.zero_blocks = (int)((prep->zero_words + ZERO_PER_BLOCK - 1) / ZERO_PER_BLOCK);
                 ranges = prep->ranges;
             }
-            if (share) *shared = BwdShared{lists, counts, delta};
+            if (share) *shared = BwdShared{lists, counts, delta, nullptr};
             if (c.d == 64) {
                 launch_dq_mfma<64>(c, q, k, v, u, tau, death, x, counts, lse, o, dO, delta, lse2, dq, nb, st, q_begin,
                                    first_valid, q_rows, aux);
@@ -1183,10 +1157,16 @@ int launch_attn_bwd(const sparsek_cfg& c, const void* q, const void* k, const vo
                 launch_dkv_mfma<128>(c, q, k, v, u, tau, death, elist, ecount, lse2, dO, delta, dk32, dv32, sk32, sv32, eslot,
                                      dk, dv, nb, st, q_begin, q_rows, ranges);
             }
-            const int d4 = c.d / 4;
-            const int gx = (int)std::min<size_t>(((size_t)c.n * d4 + 255) / 256, 1024);
-            hipLaunchKernelGGL(abwd_merge_kernel, dim3(gx, c.B * c.H), dim3(256), 0, st, dk32, dv32, sk32, sv32, elist,
-                               ecount, c.H, c.Gu, c.n, d4, (uint16_t*)dk, (uint16_t*)dv, q_begin, q_rows);
+            MergeArgs m{dk32, dv32, sk32, sv32, elist, ecount, c.H, c.Gu, c.n, c.d / 4, (uint16_t*)dk, (uint16_t*)dv, q_begin,
+                        q_rows, 0};
+            if (share && prep && prep->zero) {   // the score gradient's main kernel takes it along
+                m.parts = std::max(1, nb / 4);
+                *merge = m;
+                shared->merge = merge;
+            } else {
+                m.parts = (int)std::min<size_t>(((size_t)c.n * m.d4 + 511) / 512, 512);
+                hipLaunchKernelGGL(abwd_merge_kernel, dim3(m.parts, c.B * c.H), dim3(256), 0, st, m);
+            }
         } else {
             hipLaunchKernelGGL(attn_bwd_generic_kernel<uint16_t>, grid, dim3(256), 0, st, (const uint16_t*)q,
                                (const uint16_t*)k, (const uint16_t*)v, u, tau, death, lists, counts, lse,
@@ -1207,9 +1187,10 @@ int launch_bwd(const sparsek_cfg& cfg, const void* q, const void* k, const void*
     sparsek_cfg c = cfg;
     if (c.gate_mode == 3) c.gate_mode = 2;  // the straight-through forward has no gates on q, k, v
     const MaskBwdPrep prep = mask_bwd_prep(cfg, u, tau, mask_ws, t_min, first_valid);
-    BwdShared shared{nullptr, nullptr, nullptr};
+    BwdShared shared{nullptr, nullptr, nullptr, nullptr};
+    MergeArgs merge;
     const int rc = launch_attn_bwd(c, q, k, v, u, tau, death, o, lse, dO, dq, dk, dv, attn_ws, st, q_begin, first_valid, q_rows,
-                                   &prep, &shared, lists);
+                                   &prep, &shared, lists, &merge);
     if (rc) return rc;
     return launch_mask_bwd(cfg, q, k, v, u, tau, death, o, lse, dO, du, mask_ws, st, q_begin, q_rows, t_min, first_valid,
                            shared.delta ? &shared : nullptr);

@@ -54,6 +54,7 @@ FwdLists attn_fwd_lists(const sparsek_cfg& c, const void* ws);
 struct BwdShared {
     const int32_t *lists, *counts;
     const float* delta;
+    const struct MergeArgs* merge;   // the end of the attention's part, left to launch_mask_bwd (null: nothing is left)
 };
 struct MaskBwdPrep;
 int launch_mask_bwd(const sparsek_cfg& c, const void* q, const void* k, const void* v,
@@ -68,8 +69,8 @@ int launch_attn_bwd(const sparsek_cfg& c, const void* q, const void* k, const vo
                     const float* tau, const int32_t* death, const void* o, const float* lse, const void* dO,
                     void* dq, void* dk, void* dv, void* ws, hipStream_t st, int q_begin = 0,
                     const int32_t* first_valid = nullptr, int q_rows = 0, const MaskBwdPrep* prep = nullptr,
-                    BwdShared* shared = nullptr, const FwdLists* lists = nullptr);
-// (lists: those of the forward, where the caller still has them)
+                    BwdShared* shared = nullptr, const FwdLists* lists = nullptr, struct MergeArgs* merge = nullptr);
+// (lists: those of the forward, where the caller still has them; merge: where shared->merge may point, needed with prep and shared)
 // (shared->delta stays null where the caller's launch_mask_bwd has to do its own preparation)
 // (q_rows != 0: q, o, dO, lse, dq and also dk, dv hold q_rows rows per head, the first being position q_begin: only
 //  keys from q_begin on receive a gradient; keys before first_valid[row] are attended by nobody; bf16, d = 64 / 128)
