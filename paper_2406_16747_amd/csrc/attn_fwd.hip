@@ -229,10 +229,13 @@ __global__ __launch_bounds__(64 * BL_WAVES, RUNS ? 8 : 4) void block_lists_kerne
 //                  order of d inside a contraction is free, Q uses the same);
 //   O^T += V^T.P^T step r contracts the keys 4 g + r, g = 0..3: exactly the P values that lane group g holds.
 // Problems of this kind are small (one head of 1024 queries, k = w = 64: 31 us with a wave per query and scalar
-// products), so it is built for latency: GEN_SPLIT workgroups per query block, positions one tile ahead; 11.6 us now.
+// products), so it is built for latency: GEN_SPLIT workgroups per query block, positions one tile ahead.
 // ---------------------------------------------------------------------------------
 constexpr int GQ = 16;                 // queries per workgroup
 constexpr int GEN_SPLIT = QB / GQ;
+// Without lists (lists == nullptr) a workgroup finds the top-k of its own first prefix: one pass over up to GEN_N lifetimes, the
+// positions in LDS.  The launch in between is saved, and the key set is that of 16 queries and not of 128.
+constexpr int GEN_N = 4096, GEN_K = 1024;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 // As wide as the head dimension's multiple of 4 allows, but tensors of this kernel need no more than element alignment.
 typedef float f32x4_any __attribute__((__vector_size__(16), __aligned__(4)));
@@ -259,6 +262,7 @@ __global__ __launch_bounds__(256) void attn_fwd_generic_kernel(
     int q_begin, const int32_t* __restrict__ first_valid, int q_rows)
 {
     __shared__ float po[4][DT * 16][GQ + 1], pm[4][GQ], pl[4][GQ];
+    __shared__ int own[GEN_K], wtot[4];
     const int blk = blockIdx.x / GEN_SPLIT, sub = blockIdx.x % GEN_SPLIT, bh = blockIdx.y;
     const int b = bh / H, h = bh % H;
     const int row = b * Gu + (Gu == 1 ? 0 : h);
@@ -272,16 +276,16 @@ __global__ __launch_bounds__(256) void attn_fwd_generic_kernel(
     const T* vh = v + (size_t)bh * n * d;
     const float* ur = u + (size_t)row * n;
     const int32_t* dr = death + (size_t)row * n;
-    const int32_t* list = lists + ((size_t)row * nb + blk) * (size_t)(k > 0 ? k : 1);
+    const int32_t* list = lists ? lists + ((size_t)row * nb + blk) * (size_t)(k > 0 ? k : 1) : nullptr;
+    const int T0 = (lists ? i0 : ia) - w;          // the prefix of the listed keys
     // keys before first_valid[row] (padding of a chunked prefill) are attended by nobody
-    const int c0 = max(max(0, i0 - w + 1), first_valid ? first_valid[row] : 0);
+    const int c0 = max(max(0, T0 + 1), first_valid ? first_valid[row] : 0);
     const int i = ia + col;                        // this lane's query
     const int iq = min(i, n - 1);
     const int Tp = i - w;
     const float tauT = (Tp >= 0 && i < n) ? tau[(size_t)row * n + Tp] : 0.0f;
     const int ib = min(ia + GQ - 1, n - 1);        // last query of the workgroup
-    const int nl = ib - w >= 0 ? counts[(size_t)row * nb + blk] : 0;
-    const int total = nl + max(0, ib - c0 + 1);
+    int nl = lists && ib - w >= 0 ? counts[(size_t)row * nb + blk] : 0;
     f32x4 qf[DT], acc[DT];
 #pragma unroll
     for (int x = 0; x < DT; x++) {
@@ -290,8 +294,38 @@ __global__ __launch_bounds__(256) void attn_fwd_generic_kernel(
         if (dd < d) qf[x] = load4(q + (qo + iq) * d + dd);
         acc[x] = f32x4{0, 0, 0, 0};
     }
+    if (!lists && T0 >= 0) {   // (uniform)
+        constexpr int REG = GEN_N / 256;
+        const int per = ((T0 + 4) / 4 + 63) / 64 * 64, e_lo = wv * per, e_hi = min(T0 + 1, e_lo + per);
+        int dj[REG], mine = 0;
+#pragma unroll
+        for (int r = 0; r < REG; r++) {
+            const int e = e_lo + 64 * r + lane;
+            dj[r] = e < e_hi ? dr[e] : INT32_MIN;
+        }
+#pragma unroll
+        for (int r = 0; r < REG; r++) mine += __popcll(__ballot(dj[r] > T0));
+        if (lane == 0) wtot[wv] = mine;
+        __syncthreads();
+        int at = 0;
+#pragma unroll
+        for (int x = 0; x < 4; x++) {
+            if (x < wv) at += wtot[x];
+            nl += wtot[x];
+        }
+        nl = min(nl, k);
+#pragma unroll
+        for (int r = 0; r < REG; r++) {
+            const unsigned long long alive = __ballot(dj[r] > T0);
+            const int o = at + __popcll(alive & ((1ull << lane) - 1ull));
+            if (dj[r] > T0 && o < nl) own[o] = e_lo + 64 * r + lane;
+            at += __popcll(alive);
+        }
+        __syncthreads();
+    }
+    const int total = nl + max(0, ib - c0 + 1);
     const float c2 = scale * 1.4426950408889634f;
-    auto pos = [&](int e) { return e >= total ? -1 : e < nl ? list[e] : c0 + (e - nl); };
+    auto pos = [&](int e) { return e >= total ? -1 : e >= nl ? c0 + (e - nl) : list ? list[e] : own[e]; };
     float m_run = -INFINITY, l_run = 0.0f;
     // positions of this lane's K row and of its four P / V rows
     int jk = pos(16 * wv + col), jp[4];
@@ -929,7 +963,10 @@ int launch_attn_fwd(const sparsek_cfg& c, const void* q, const void* k, const vo
         else launch_mfma<128>(c, q, k, v, u, tau, death, x, counts, o, lse, nb, q_begin, first_valid, q_rows, t, st);
         return launch_status();
     }
-    launch_block_lists(c, death, lists, counts, st);
+    // The line lies where a workgroup's registers and LDS end.  us with the lists / without, mask and all: one head of 1024,
+    // k = w = 64, d = 64 24.7 / 21.6; 16 heads of 2048, k = w = 128, d = 128 155 / 135; 16 of 4096, k = 1024, w = 256 396 / 383.
+    if (c.n <= GEN_N && c.k <= GEN_K) lists = nullptr;
+    else launch_block_lists(c, death, lists, counts, st);
     if (c.dtype == SPARSEK_F32)
         launch_generic<float>(c, q, k, v, u, tau, death, lists, counts, o, lse, nb, q_begin, first_valid, q_rows, st);
     else

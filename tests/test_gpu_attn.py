@@ -84,6 +84,19 @@ def test_small_shapes(oracle, n, d, k, w, Gu, dtype, gate_mode):
     run_case(oracle, inp, gate_mode, qk_boost=8.0)
 
 
+# The generic kernel finds its own keys up to 4096 positions and 1024 of them; beyond, it takes the lists of blocks of 128 queries.
+# Windows that are no multiple of its 16 queries, none at all, and prefixes that start in the middle of a workgroup's queries.
+@pytest.mark.parametrize("n,d,k,w,Gu,dtype", [
+    (4096, 32, 40, 30, 1, "fp32"), (4097, 32, 40, 30, 1, "fp32"), (2100, 32, 1024, 21, 2, "fp32"),
+    (2100, 32, 1025, 21, 1, "fp32"), (17, 36, 3, 5, 1, "bf16"), (700, 64, 90, 0, 1, "fp32"), (300, 100, 0, 17, 1, "fp32"),
+    (1100, 128, 70, 16, 2, "fp32"),
+])
+def test_generic_kernel_with_and_without_lists(oracle, n, d, k, w, Gu, dtype):
+    require_gpu()
+    say("generic kernel", n, d, k, w, Gu, dtype)
+    run_case(oracle, synth.make(1, Gu=Gu, seed=n + k + w, B=1, H=2, n=n, d=d, k=k, w=w, dtype=dtype))
+
+
 @pytest.mark.parametrize("k", [4095, 4096, 4100])
 @pytest.mark.parametrize("Gu", [1, 24])   # a workgroup per block; runs of two blocks, whose lists grow past the limit
 def test_lists_longer_than_lds_holds(oracle, k, Gu):
