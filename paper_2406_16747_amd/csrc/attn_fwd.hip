@@ -726,8 +726,11 @@ __device__ __forceinline__ void run_tiles(FwdSmem<D>& sm, const StageSrc& src, i
 }
 
 // TAIL: workgroups behind the blocks move the rows that survive a chunk (an instance of its own: the registers are all taken).
+// Without gates and with 64 columns three workgroups fit a compute unit at the cost of 3 spilled registers (96 heads of 4096,
+// k = w = 256: 127.3 -> 121.5 us for the prefill; 64 heads of 8192 at k = 512, w = 700: 255 -> 242).  With gates it takes 29 of them
+// and loses (135 -> 199, 631 -> 766).
 template <int D, int MODE, bool TAIL>
-__global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(
+__global__ __launch_bounds__(256, D == 64 && MODE == 2 ? 3 : 2) void attn_fwd_mfma_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ kk, const uint16_t* __restrict__ v,
     const float* __restrict__ u, const float* __restrict__ tau, const int32_t* __restrict__ death,
     const int32_t* __restrict__ xpos, const int32_t* __restrict__ xdeath, const float* __restrict__ xu, int KP,
