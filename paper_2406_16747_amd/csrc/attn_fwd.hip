@@ -139,7 +139,7 @@ __device__ __forceinline__ int block_list(ListSmem& sm, int buf, int ncand, int 
 
 // BL_REG: lifetimes per lane of a scan.  32 read a prefix of 32768 once; 8 leave room for a second workgroup on the
 // compute unit.  RUNS: a workgroup owns `run` consecutive blocks, else one.  CHUNK: lifetimes are read as the end of a chunk has
-// them, and the first workgroup of a row clears them in memory and finds the row's survivors.
+// them; the first workgroup of a row finds its survivors, the others clear the lifetimes in memory when their lists are done.
 template <int BL_REG, bool RUNS, bool CHUNK>
 __global__ __launch_bounds__(64 * BL_WAVES, RUNS ? 8 : 4) void block_lists_kernel(
     const int32_t* __restrict__ death, int n, int k, int w, int nb, int run /* consecutive blocks per workgroup */,
@@ -155,7 +155,6 @@ __global__ __launch_bounds__(64 * BL_WAVES, RUNS ? 8 : 4) void block_lists_kerne
     __shared__ Smem smem;
     ListSmem& sm = smem.l;
     if (CHUNK && blockIdx.x == 0) {
-        chunk_clear_padding(tail, blockIdx.y, NT);
         chunk_retain(smem.r, tail, blockIdx.y);
         return;
     }
@@ -218,6 +217,7 @@ __global__ __launch_bounds__(64 * BL_WAVES, RUNS ? 8 : 4) void block_lists_kerne
         stayed = cnt <= BL_LDS && tot_s <= cnt ? tot_s : -1;
         buf ^= 1;
     }
+    if (CHUNK) chunk_clear_padding(tail, row, wg * NT + tid, (gridDim.x - 1) * NT);
 }
 
 // ---------------------------------------------------------------------------------

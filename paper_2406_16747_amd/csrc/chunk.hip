@@ -142,7 +142,7 @@ __global__ __launch_bounds__(256) void chunk_retain_rows_kernel(ChunkTail c, int
     chunk_retain_rows(c, bh, bh / H * Gu + (Gu == 1 ? 0 : bh % H), blockIdx.x);
 }
 
-__global__ __launch_bounds__(1024) void chunk_clear_padding_kernel(ChunkTail c) { chunk_clear_padding(c, blockIdx.x, 1024); }
+__global__ __launch_bounds__(1024) void chunk_clear_padding_kernel(ChunkTail c) { chunk_clear_padding(c, blockIdx.x, threadIdx.x, 1024); }
 
 int launch_chunk_init(const sparsek_chunk_cfg& c, void* state, hipStream_t st)
 {
@@ -191,7 +191,7 @@ int launch_chunk_prefill(const sparsek_chunk_cfg& c, void* state, int clen, cons
     tail.unit = row16;
     // Where the MFMA kernels do the attention, the rest of the chunk rides on its launches: three launches less, the survivors are
     // found beside the lists and their rows move while the attention's last blocks run.  32 heads in chunks of 8192, k = w = 1024,
-    // d = 128: 397 -> 385 us a chunk; 8 heads in chunks of 512, k = w = 64: 46 -> 39.
+    // d = 128: 397 -> 381 us a chunk; 8 heads in chunks of 512, k = w = 64: 46 -> 39.
     if (attn_fwd_mfma(cv)) {
         rc = launch_attn_fwd(cv, q, k_v, v_v, u_v, tau_v, death_v, o, (float*)(w + W.lse), w + W.attn, st, L.rcap,
                              first_valid, clen, &tail);

@@ -35,20 +35,22 @@ struct ChunkTail {
     // the lifetime of position e of a row
     __device__ __forceinline__ int lifetime(int row, int e) const
     {
-        const int d = death[(size_t)row * (rcap + clen) + e];
-        return e < rcap && !(kept[(size_t)row * (rcap / 64) + (e >> 6)] >> (e & 63) & 1) ? e : d;
+        // (both loads without a condition, so that a caller's loads stay in flight together)
+        const int d = death[(size_t)row * (rcap + clen) + e], c = min(e, rcap - 1);
+        const unsigned word = ((const unsigned*)kept)[(size_t)row * (rcap / 32) + (c >> 5)];
+        return (e >= rcap) | (word >> (c & 31) & 1) ? d : e;
     }
 };
 
 // Padding entries are never selected: death[e] = e.  The same holds for retained keys that were
 // kept only because their score is above the threshold: they left the top-k in an earlier chunk, at
 // a prefix whose block the mask skips, so their lifetime is still at its preset.
-// `threads` threads of one workgroup clear a row.  (Whoever reads lifetimes in the same launch goes through lifetime(): a
+// Thread `first` of `threads` that clear a row.  (Whoever reads lifetimes in the same launch goes through lifetime(): a
 // cleared one and one that is about to be come to the same.)
-__device__ __forceinline__ void chunk_clear_padding(const ChunkTail& c, int row, int threads)
+__device__ __forceinline__ void chunk_clear_padding(const ChunkTail& c, int row, int first, int threads)
 {
     const unsigned long long* kept = c.kept + (size_t)row * (c.rcap / 64);
-    for (int e = threadIdx.x; e < c.rcap; e += threads)
+    for (int e = first; e < c.rcap; e += threads)
         if (!(kept[e >> 6] >> (e & 63) & 1)) c.death[(size_t)row * (c.rcap + c.clen) + e] = e;
 }
 
