@@ -190,7 +190,7 @@ __global__ __launch_bounds__(256) void attn_bwd_generic_kernel(
 // to the block's last query) in runs of one kind per wave, so that only the tiles that need a test or a gate pay
 // for it; metadata staged in segments, tiles gathered straight into LDS one tile ahead.  Per 32-key half:
 // S^T = K.Q^T and DV^T = V.dO^T (row reads of the K and V tiles), the elementwise step to ds_ij gk_ij in bf16, then
-// dQ^T += K^T.dS^T with K^T through transposing reads of the same K tile (see tile_swz).  The softmax scale is
+// dQ^T += K^T.dS^T with K^T through transposing reads of the same K tile (see RowTile).  The softmax scale is
 // applied once, to the finished dQ.
 // ---------------------------------------------------------------------------------
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
