@@ -233,8 +233,10 @@ __global__ __launch_bounds__(64 * BL_WAVES, RUNS ? 8 : 4) void block_lists_kerne
 // ---------------------------------------------------------------------------------
 constexpr int GQ = 16;                 // queries per workgroup
 constexpr int GEN_SPLIT = QB / GQ;
-// Without lists (lists == nullptr) a workgroup finds the top-k of its own first prefix: one pass over up to GEN_N lifetimes, the
-// positions in LDS.  The launch in between is saved, and the key set is that of 16 queries and not of 128.
+// Without lists (OWN) a workgroup finds the top-k of its own first prefix: one pass over up to GEN_N lifetimes, the positions in
+// LDS.  The launch in between is saved, and the key set is that of 16 queries and not of 128.  An instance of its own: one kernel for
+// both takes 6 to 8 registers more, and up to 32 columns that is the fifth wave of a SIMD (64 heads of 4096, k = w = 64, d = 32, prefill
+// 211 us, 183 with two instances; 16 heads of 16384, which take lists, 223 and 203).
 constexpr int GEN_N = 4096, GEN_K = 1024;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 // As wide as the head dimension's multiple of 4 allows, but tensors of this kernel need no more than element alignment.
@@ -253,7 +255,7 @@ __device__ __forceinline__ float load1(const uint16_t* p) { return bf16_to_f32(*
 __device__ __forceinline__ void store1(float* p, float v) { *p = v; }
 __device__ __forceinline__ void store1(uint16_t* p, float v) { *p = f32_to_bf16(v); }
 
-template <typename T, int DT>   // DT = number of 16-column blocks of the head dimension (rounded up)
+template <typename T, int DT, bool OWN>   // DT = number of 16-column blocks of the head dimension (rounded up)
 __global__ __launch_bounds__(256) void attn_fwd_generic_kernel(
     const T* __restrict__ q, const T* __restrict__ kk, const T* __restrict__ v,
     const float* __restrict__ u, const float* __restrict__ tau, const int32_t* __restrict__ death,
@@ -262,7 +264,7 @@ __global__ __launch_bounds__(256) void attn_fwd_generic_kernel(
     int q_begin, const int32_t* __restrict__ first_valid, int q_rows)
 {
     __shared__ float po[4][DT * 16][GQ + 1], pm[4][GQ], pl[4][GQ];
-    __shared__ int own[GEN_K], wtot[4];
+    __shared__ int own[OWN ? GEN_K : 1], wtot[4];
     const int blk = blockIdx.x / GEN_SPLIT, sub = blockIdx.x % GEN_SPLIT, bh = blockIdx.y;
     const int b = bh / H, h = bh % H;
     const int row = b * Gu + (Gu == 1 ? 0 : h);
@@ -276,8 +278,8 @@ __global__ __launch_bounds__(256) void attn_fwd_generic_kernel(
     const T* vh = v + (size_t)bh * n * d;
     const float* ur = u + (size_t)row * n;
     const int32_t* dr = death + (size_t)row * n;
-    const int32_t* list = lists ? lists + ((size_t)row * nb + blk) * (size_t)(k > 0 ? k : 1) : nullptr;
-    const int T0 = (lists ? i0 : ia) - w;          // the prefix of the listed keys
+    const int32_t* list = lists + (OWN ? 0 : ((size_t)row * nb + blk) * (size_t)(k > 0 ? k : 1));
+    const int T0 = (OWN ? ia : i0) - w;          // the prefix of the listed keys
     // keys before first_valid[row] (padding of a chunked prefill) are attended by nobody
     const int c0 = max(max(0, T0 + 1), first_valid ? first_valid[row] : 0);
     const int i = ia + col;                        // this lane's query
@@ -285,7 +287,7 @@ __global__ __launch_bounds__(256) void attn_fwd_generic_kernel(
     const int Tp = i - w;
     const float tauT = (Tp >= 0 && i < n) ? tau[(size_t)row * n + Tp] : 0.0f;
     const int ib = min(ia + GQ - 1, n - 1);        // last query of the workgroup
-    int nl = lists && ib - w >= 0 ? counts[(size_t)row * nb + blk] : 0;
+    int nl = !OWN && ib - w >= 0 ? counts[(size_t)row * nb + blk] : 0;
     f32x4 qf[DT], acc[DT];
 #pragma unroll
     for (int x = 0; x < DT; x++) {
@@ -294,7 +296,7 @@ __global__ __launch_bounds__(256) void attn_fwd_generic_kernel(
         if (dd < d) qf[x] = load4(q + (qo + iq) * d + dd);
         acc[x] = f32x4{0, 0, 0, 0};
     }
-    if (!lists && T0 >= 0) {   // (uniform)
+    if (OWN && T0 >= 0) {   // (uniform)
         constexpr int REG = GEN_N / 256;
         const int per = ((T0 + 4) / 4 + 63) / 64 * 64, e_lo = wv * per, e_hi = min(T0 + 1, e_lo + per);
         int dj[REG], mine = 0;
@@ -325,7 +327,7 @@ __global__ __launch_bounds__(256) void attn_fwd_generic_kernel(
     }
     const int total = nl + max(0, ib - c0 + 1);
     const float c2 = scale * 1.4426950408889634f;
-    auto pos = [&](int e) { return e >= total ? -1 : e >= nl ? c0 + (e - nl) : list ? list[e] : own[e]; };
+    auto pos = [&](int e) { return e >= total ? -1 : e >= nl ? c0 + (e - nl) : OWN ? own[e] : list[e]; };
     float m_run = -INFINITY, l_run = 0.0f;
     // positions of this lane's K row and of its four P / V rows
     int jk = pos(16 * wv + col), jp[4];
@@ -865,13 +867,17 @@ static void launch_generic(const sparsek_cfg& c, const void* q, const void* k, c
                            float* lse, int nb, int q_begin, const int32_t* first_valid, int q_rows, hipStream_t st)
 {
     dim3 grid(nb * GEN_SPLIT, c.B * c.H);
-#define SPK_LAUNCH_G(DT)                                                                                              \
-    hipLaunchKernelGGL((attn_fwd_generic_kernel<T, DT>), grid, dim3(256), 0, st, (const T*)q, (const T*)k, (const T*)v, \
-                       u, tau, death, lists, counts, (T*)o, lse, c.H, c.Gu, c.n, c.d, c.k, c.w, c.gate_mode,            \
+#define SPK_LAUNCH_G(DT, OWN)                                                                                              \
+    hipLaunchKernelGGL((attn_fwd_generic_kernel<T, DT, OWN>), grid, dim3(256), 0, st, (const T*)q, (const T*)k, (const T*)v, \
+                       u, tau, death, lists, counts, (T*)o, lse, c.H, c.Gu, c.n, c.d, c.k, c.w, c.gate_mode,                 \
                        c.softmax_scale, nb, q_begin, first_valid, q_rows)
-    if (c.d <= 32) SPK_LAUNCH_G(2);
-    else if (c.d <= 64) SPK_LAUNCH_G(4);
-    else SPK_LAUNCH_G(8);
+    if (lists) {
+        if (c.d <= 32) SPK_LAUNCH_G(2, false);
+        else if (c.d <= 64) SPK_LAUNCH_G(4, false);
+        else SPK_LAUNCH_G(8, false);
+    } else if (c.d <= 32) SPK_LAUNCH_G(2, true);
+    else if (c.d <= 64) SPK_LAUNCH_G(4, true);
+    else SPK_LAUNCH_G(8, true);
 #undef SPK_LAUNCH_G
 }
 
@@ -966,8 +972,10 @@ int launch_attn_fwd(const sparsek_cfg& c, const void* q, const void* k, const vo
         else launch_mfma<128>(c, q, k, v, u, tau, death, x, counts, o, lse, nb, q_begin, first_valid, q_rows, t, st);
         return launch_status();
     }
-    // The line lies where a workgroup's registers and LDS end.  us with the lists / without, mask and all: one head of 1024,
-    // k = w = 64, d = 64 24.7 / 21.6; 16 heads of 2048, k = w = 128, d = 128 155 / 135; 16 of 4096, k = 1024, w = 256 396 / 383.
+    // The line lies where a workgroup's registers and LDS end; below it the lists were slower wherever both were timed (37 sizes of 4 to
+    // 256 heads).  us with the lists / without, mask and all: one head of 1024, k = w = 64, d = 64 24.7 / 21.6; 16 heads of 2048,
+    // k = w = 128, d = 64 85 / 75; the least was gained with many heads, few columns and a full scan: 256 heads of 4096, k = w = 64,
+    // d = 32 705 / 666, 32 heads of 4096, k = 64, w = 1024 348 / 332, k = 1024, w = 64 374 / 338.
     if (c.n <= GEN_N && c.k <= GEN_K) lists = nullptr;
     else launch_block_lists(c, death, lists, counts, st);
     if (c.dtype == SPARSEK_F32)
