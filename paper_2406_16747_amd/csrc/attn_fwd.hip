@@ -155,7 +155,7 @@ __global__ __launch_bounds__(64 * BL_WAVES, RUNS ? 8 : 4) void block_lists_kerne
     __shared__ Smem smem;
     ListSmem& sm = smem.l;
     if (CHUNK && blockIdx.x == 0) {
-        chunk_retain(smem.r, tail, blockIdx.y);
+        chunk_retain<false>(smem.r, tail, blockIdx.y);
         return;
     }
     const int wg = CHUNK ? blockIdx.x - 1 : blockIdx.x;

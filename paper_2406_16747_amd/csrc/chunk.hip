@@ -133,7 +133,7 @@ static RowCopy chunk_rows(const sparsek_chunk_cfg& c, const ChunkLayout& L, char
 __global__ __launch_bounds__(1024) void chunk_retain_kernel(ChunkTail c)
 {
     __shared__ RetainSmem sm;
-    chunk_retain(sm, c, blockIdx.x);
+    chunk_retain<true>(sm, c, blockIdx.x);
 }
 
 __global__ __launch_bounds__(256) void chunk_retain_rows_kernel(ChunkTail c, int H, int Gu)

@@ -58,6 +58,8 @@ struct RetainSmem {
     int wt[2][16];
 };
 
+// CLEARED: an earlier launch has cleared the lifetimes (9.9 us against 11.7 with lifetime(), a row of 9088 virtual positions).
+template <bool CLEARED>
 __device__ __forceinline__ void chunk_retain(RetainSmem& sm, const ChunkTail& c, int row)
 {
     auto& wt = sm.wt;
@@ -81,7 +83,7 @@ __device__ __forceinline__ void chunk_retain(RetainSmem& sm, const ChunkTail& c,
 #pragma unroll
         for (int x = 0; x < RETAIN_UNR; x++) {
             const int e = min((g + x) * 64 + lane, nv - 1);
-            dd[x] = c.lifetime(row, e);
+            dd[x] = CLEARED ? c.death[(size_t)row * nv + e] : c.lifetime(row, e);
             uu[x] = ur[e];
         }
 #pragma unroll
