@@ -113,6 +113,33 @@ def test_one_call_backward_equals_the_two_parts(oracle, gate_mode):
         assert rs > 0 and diff.max() <= 1e-2 * rs, (name, diff.max(), rs)
 
 
+# In the one call dK and dV are merged by groups of 8 workgroups among the score gradient's blocks.  A single block of a single head; one
+# part per head and several, with a last group that is not full; a score row per head; more parts than one batch's heads.
+@pytest.mark.parametrize("B,H,Gu,n,d,k,w", [
+    (1, 1, 1, 100, 64, 10, 9), (1, 1, 1, 2600, 128, 150, 100), (1, 5, 5, 2300, 128, 150, 100), (2, 13, 13, 600, 128, 40, 30),
+    (1, 11, 1, 2050, 64, 90, 64), (3, 7, 1, 2000, 128, 128, 128),
+])
+@pytest.mark.parametrize("gate_mode", [0, 3])
+def test_one_call_backward_merges_every_row(B, H, Gu, n, d, k, w, gate_mode):
+    """Bit for bit what sparsek_attn_bwd gives, whose merge is a launch of its own (that one against the oracle: above)."""
+    require_gpu()
+    say("one-call backward, merge", B, H, Gu, n, d, k, w, gate_mode)
+    inp = synth.make(3, Gu=Gu, seed=n + H, with_dO=True, B=B, H=H, n=n, d=d, k=k, w=w, dtype="bf16", qk_div=2.0)
+    u = dev(inp["u"])
+    Q, K, V, dO = (dev(inp[x], True) for x in ("Q", "K", "V", "dO"))
+    tau, death = spk.sparsek_mask(u, k)
+    o, lse = spk.sparsek_attn_fwd(Q, K, V, u, tau, death, k, w, gate_mode, 1.0)
+    two = spk.sparsek_attn_bwd(Q, K, V, u, tau, death, o, lse, dO, k, w, gate_mode, 1.0)
+    torch.cuda.synchronize()
+    poison = [torch.full_like(Q, float("nan")) for _ in range(4)]   # (what the results are allocated from: an unwritten row shows)
+    torch.cuda.synchronize()
+    del poison
+    one = spk.sparsek_bwd(Q, K, V, u, tau, death, o, lse, dO, k, w, gate_mode, 1.0)
+    torch.cuda.synchronize()
+    for name, a, b in zip(("dq", "dk", "dv"), two, one):
+        assert torch.isfinite(a.float()).all() and torch.equal(a, b), name
+
+
 def test_one_call_backward_fp32_generic_path(oracle):
     """sparsek_bwd on the generic (fp32) kernels against the oracle's two gradients."""
     require_gpu()

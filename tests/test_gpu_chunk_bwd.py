@@ -18,12 +18,17 @@ from gpu_util import dev, host, require_gpu, say
 pytestmark = pytest.mark.gpu
 
 
-def run_case(oracle, inp, chunks, gate_mode):
+def run_case(oracle, inp, chunks, gate_mode, heads=None):
+    """heads: those to compare (a score row each), None for all."""
     B, H, n, d, k, w, Gu = (inp[x] for x in ("B", "H", "n", "d", "k", "w", "Gu"))
     q, kk, v, dO = (dev(inp[x], True) for x in ("Q", "K", "V", "dO"))
     u = dev(inp["u"])
     st = spk.ChunkState(B, H, Gu, d, k, w, spk.BF16, max(chunks), gate_mode, inp["scale"], 0)
-    tau64, death = oracle.mask_all(inp["u"], k)
+    hs = slice(None) if heads is None else heads
+    assert heads is None or Gu == H
+    Q32, K32, V32, dO32 = (inp[x][:, hs] for x in ("Q32", "K32", "V32", "dO32"))
+    u_np = inp["u"][:, hs] if heads is not None else inp["u"]
+    tau64, death = oracle.mask_all(u_np, k)
     pos = 0
     for ci, c in enumerate(chunks):
         sl = slice(pos, pos + c)
@@ -35,11 +40,13 @@ def run_case(oracle, inp, chunks, gate_mode):
         got = {"dq": host(dq), "dk": host(dk), "dv": host(dv), "du": host(du)}
         for name, g in got.items():
             assert np.isfinite(g).all(), (name, ci)
-        dO_m = np.zeros_like(inp["dO32"])
-        dO_m[:, :, sl] = inp["dO32"][:, :, sl]
-        rq, rk, rv = oracle.attn_bwd(inp["Q32"], inp["K32"], inp["V32"], inp["u"], tau64, death, dO_m, k, w,
+        if heads is not None:
+            got = {name: g[:, hs] for name, g in got.items()}
+        dO_m = np.zeros_like(dO32)
+        dO_m[:, :, sl] = dO32[:, :, sl]
+        rq, rk, rv = oracle.attn_bwd(Q32, K32, V32, u_np, tau64, death, dO_m, k, w,
                                      2 if gate_mode == 3 else gate_mode, inp["scale"])
-        ru, _ = oracle.mask_bwd(inp["Q32"], inp["K32"], inp["V32"], inp["u"], tau64, death, dO_m, k, w, gate_mode,
+        ru, _ = oracle.mask_bwd(Q32, K32, V32, u_np, tau64, death, dO_m, k, w, gate_mode,
                                 inp["scale"])
         ref = {"dq": rq[:, :, sl], "dk": rk[:, :, sl], "dv": rv[:, :, sl], "du": ru[:, :, sl]}
         common = max(np.abs(ref[x]).max() for x in ("dq", "dk", "dv"))
@@ -74,3 +81,26 @@ def test_chunk_bwd_equals_masked_full_backward(oracle, n, d, k, w, Gu, chunks, g
     inp = synth.make(3, Gu=Gu, seed=n + k + w, with_dO=True, B=1, H=2, n=n, d=d, k=k, w=w, dtype="bf16",
                      qk_div=float(np.sqrt(d)) / 4)
     run_case(oracle, inp, chunks, gate_mode)
+
+
+# The backward reads the lists that the forward left, from the first block of the chunk on.  More than 256 blocks of queries over all
+# score rows: smaller workgroups build them; from 1024 on a workgroup owns 2 blocks and more and takes each list from the one before.
+@pytest.mark.parametrize("H,chunks", [(32, [1100, 60]), (32, [4100, 60]), (64, [130, 4100])])
+def test_chunk_bwd_reads_lists_built_in_runs(oracle, H, chunks):
+    require_gpu()
+    say("chunk bwd, lists in runs", H, chunks)
+    n = sum(chunks)
+    inp = synth.make(3, Gu=H, seed=n + 3, with_dO=True, B=1, H=H, n=n, d=64, k=48, w=70, dtype="bf16", qk_div=2.0)
+    run_case(oracle, inp, chunks, 0, heads=[0, H // 2 - 1, H - 1])
+
+
+# The last scan of the score gradient has a kernel for up to 2048, 8192 and 16384 virtual positions (256 retained ones and the chunk) and
+# one beyond; each writes the chunk's scores only.  (Seeds: no score lies within 1e-7 of a threshold that decides whether its gate is soft.)
+@pytest.mark.parametrize("chunks", [[1792, 40], [1793, 40], [7937, 40], [16129, 300]])
+@pytest.mark.parametrize("Gu", [1, 2])
+def test_chunk_bwd_score_gradient_of_long_chunks(oracle, chunks, Gu):
+    require_gpu()
+    say("chunk bwd, long chunks", chunks, Gu)
+    n = sum(chunks)
+    inp = synth.make(3, Gu=Gu, seed=n, with_dO=True, B=1, H=2, n=n, d=64, k=40, w=50, dtype="bf16", qk_div=2.0)
+    run_case(oracle, inp, chunks, 0)
