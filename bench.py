@@ -185,10 +185,10 @@ def prefill_leg(config, iters=20, warm=3, with_cpu=True):
     else:
         roof = {"bound": "alu", "achieved": flops / t_attn / 1e12, "peak": FP32_VECTOR_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "algorithmic_flops": flops, "traffic": None,
-                "note": "31 MFLOP in all: the two launches are latency-bound; microseconds are the figure to read"}
+                "note": "31 MFLOP in all: mask and attention are latency-bound; microseconds are the figure to read"}
     roof["frac"] = roof["achieved"] / roof["peak"]
     roof["kernel"] = ("attn_fwd_mfma_kernel<%d> (+ block_lists_kernel, inside the timed call)" % d) if bf16 else \
-        "attn_fwd_generic_kernel<float> (+ block_lists_kernel, inside the timed call)"
+        "attn_fwd_generic_kernel<float> (finds its own lists)"
     roof["ms_per_launch"] = attn_ms["mean"]
     out = {
         "workload": "config %d: prefill fwd, B=%d H=%d n=%d d=%d k=%d w=%d %s, Gu=%d, gate_mode=0, mask+select+attention "

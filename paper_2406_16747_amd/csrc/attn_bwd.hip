@@ -496,10 +496,10 @@ __device__ __forceinline__ void dq_aux(ElistSmem& sm, const DqAux& a, int id, co
     for (size_t i = w0 + threadIdx.x; i < min(a.zero_words, w0 + ZERO_PER_BLOCK); i += 256) a.zero[i] = 0u;
 }
 
-// (Three workgroups per compute unit where the registers allow it, as in the forward: 48 heads of 2000, k = w = 128, straight-through
-// 159.0 -> 152.1 us for forward and backward, both kernels.)
-template <int D, int MODE>
-__global__ __launch_bounds__(256, D == 64 && MODE == 2 ? 3 : 2) void attn_bwd_dq_kernel(
+// WGS: workgroups per compute unit, three where the registers allow it and there are blocks for them, as in the forward (48 heads of
+// 2000, k = w = 128, straight-through, forward and backward: 152.7 -> 147.7 us by this kernel, 152.1 -> 147.5 by the forward's).
+template <int D, int MODE, int WGS>
+__global__ __launch_bounds__(256, WGS) void attn_bwd_dq_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ kk, const uint16_t* __restrict__ v,
     const float* __restrict__ u, const float* __restrict__ tau, const int32_t* __restrict__ death,
     const int32_t* __restrict__ xpos, const int32_t* __restrict__ xdeath, const float* __restrict__ xu, int KP,
@@ -639,15 +639,16 @@ static void launch_dq_mfma(const sparsek_cfg& c, const void* q, const void* k, c
 {
     const int BH = c.B * c.H;
     dim3 grid(nb * BH + aux.rows + aux.zero_blocks);
-#define SPK_LAUNCH_DQ(MODE)                                                                                        \
-    hipLaunchKernelGGL((attn_bwd_dq_kernel<D, MODE>), grid, dim3(256), 0, st, (const uint16_t*)q, (const uint16_t*)k, \
+#define SPK_LAUNCH_DQ(MODE, WGS)                                                                                   \
+    hipLaunchKernelGGL((attn_bwd_dq_kernel<D, MODE, WGS>), grid, dim3(256), 0, st, (const uint16_t*)q, (const uint16_t*)k, \
                        (const uint16_t*)v, u, tau, death, (const int32_t*)x.pos, (const int32_t*)x.death,          \
                        (const float*)x.u, x.KP, counts, lse, (const uint16_t*)o, (const uint16_t*)dO, delta, lse2, \
                        (uint16_t*)dq, c.H, c.Gu, c.n, c.k, c.w, c.softmax_scale, nb, BH, c.B * c.Gu, q_begin,      \
                        first_valid, q_rows, aux)
-    if (c.gate_mode == 0) SPK_LAUNCH_DQ(0);
-    else if (c.gate_mode == 1) SPK_LAUNCH_DQ(1);
-    else SPK_LAUNCH_DQ(2);
+    if (c.gate_mode == 0) SPK_LAUNCH_DQ(0, 2);
+    else if (c.gate_mode == 1) SPK_LAUNCH_DQ(1, 2);
+    else if (D == 64 && three_per_cu(c, q_begin, aux.rows)) SPK_LAUNCH_DQ(2, (D == 64 ? 3 : 2));
+    else SPK_LAUNCH_DQ(2, 2);
 #undef SPK_LAUNCH_DQ
 }
 
@@ -665,7 +666,7 @@ static void launch_dq_mfma(const sparsek_cfg& c, const void* q, const void* k, c
 // Every key belongs to exactly one window block and at most one selected block, so nothing needs an
 // atomic: a window block stores the final dk, dv rows of the keys that are never selected, and its
 // fp32 part of the others into dk32 / dv32 by position; a selected block stores into sk32 / sv32 at
-// the key's slot of the list; abwd_merge_kernel adds the two parts and rounds.
+// the key's slot of the list; abwd_merge adds the two parts and rounds, in the score gradient's launch or in one of its own.
 // With q_rows != 0 the queries are offset (a chunk attending retained keys): q, dO, lse, delta, dk, dv
 // hold q_rows rows per head from position q_begin, and only keys from q_begin on are processed.
 // ---------------------------------------------------------------------------------
@@ -681,11 +682,13 @@ __device__ __forceinline__ int wave_min_i32(int x) { return ~wave_max_i32(~x); }
 __device__ __forceinline__ int b_row(int bh, int H, int Gu) { return (bh / H) * Gu + (Gu == 1 ? 0 : bh % H); }
 
 // S and dO.V go straight to vector registers: the compiler, given accumulation registers, puts every product there, and the
-// elementwise work then reads each value with an instruction of its own (64 of the 224 vector instructions of a tile without
-// gates).  It does not know the latency of these products (8 passes: behind the builtin form it leaves 12 states):
-// mfma_done waits for 24 before anything else looks at them.  Their operands come from LDS and from registers that are
-// loaded once, never from a vector instruction just ahead.  The build reads the generated code and refuses any in which a
-// result or an operand is touched too early (check_products).  64 heads of 8192 at k = w = 512: the backward -18 us of 930.
+// elementwise work then reads each value with an instruction of its own (64 per tile).  It does not know the latency of these
+// products (8 passes: behind the builtin form it leaves 12 states).  What keeps the distance is the schedule below: between the
+// last product into a sum and its first reader lie the LEAD + 1 slots of another run, each a product of 8 passes with an LDS read,
+// and the 4 states of settled(); where nothing lies between (a wave's first unit) settled() waits 24 states.  Their operands come
+// from LDS and from registers that are loaded once, never from a vector instruction just ahead.  The build reads the generated
+// code and refuses any in which a result is touched within 12 states or an operand within 2 (check_products), so whoever changes
+// LEAD or a slot's contents finds out.  64 heads of 8192 at k = w = 512: the backward -18 us of 930.
 template <bool FIRST>
 __device__ __forceinline__ void mfma_v(f32x16& d, const bf16x8& a, const bf16x8& b)
 {
@@ -928,7 +931,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(
         constexpr int e = decltype(ec)::value;
         static_for<16 * e / ESL, 16 * (e + 1) / ESL>([&](auto rc) { ds_element(P, gatedc, hc, rc, mb); });
     };
-    // the products of a run are far enough behind: the slots between, and a few states more (all of them where nothing lies between)
+    // the products of a run are far enough behind: LEAD + 1 slots, and 4 states more (24 where nothing lies between; see mfma_v)
     auto settled = [](f32x16& x, auto alone) {
         if constexpr (decltype(alone)::value) asm volatile("s_nop 15\n\ts_nop 7" : "+v"(x));
         else asm volatile("s_nop 3" : "+v"(x));
@@ -1025,7 +1028,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (loads past the last tile land in LDS that is still this workgroup's)
 #undef SPK_I
     // A key that is never selected gets all of its gradient here: round and store it.  The other keys' two parts
-    // (window block, selected block) go to fp32 buffers and are added by the merge kernel.
+    // (window block, selected block) go to fp32 buffers and are added by abwd_merge.
     // A lane holds one key's row: stored from there, every instruction touches 32 rows, 32 bytes of each (64 such instructions a
     // wave took longer than a tile).  The rows go through LDS, a wave's 32 at a time, and are stored whole.  16 heads in chunks of
     // 4096, k = w = 512: 1455 -> 1418 us for the document's forward and backward; 48 heads of 2000, k = w = 128: 164 -> 162.7.

@@ -728,11 +728,11 @@ __device__ __forceinline__ void run_tiles(FwdSmem<D>& sm, const StageSrc& src, i
 }
 
 // TAIL: workgroups behind the blocks move the rows that survive a chunk (an instance of its own: the registers are all taken).
-// Without gates and with 64 columns three workgroups fit a compute unit at the cost of 3 spilled registers (96 heads of 4096,
-// k = w = 256: 127.3 -> 121.5 us for the prefill; 64 heads of 8192 at k = 512, w = 700: 255 -> 242).  With gates it takes 29 of them
-// and loses (135 -> 199, 631 -> 766).
-template <int D, int MODE, bool TAIL>
-__global__ __launch_bounds__(256, D == 64 && MODE == 2 ? 3 : 2) void attn_fwd_mfma_kernel(
+// WGS: workgroups per compute unit.  Without gates and with 64 columns three fit at the cost of 3 spilled registers (96 heads of 4096,
+// k = w = 256: 125.3 -> 114.5 us for the prefill; 64 heads of 8192 at k = 512, w = 700: 249.0 -> 232.7; see three_per_cu for where they
+// lose).  With gates it takes 29 of them and loses (135 -> 199, 631 -> 766).
+template <int D, int MODE, bool TAIL, int WGS>
+__global__ __launch_bounds__(256, WGS) void attn_fwd_mfma_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ kk, const uint16_t* __restrict__ v,
     const float* __restrict__ u, const float* __restrict__ tau, const int32_t* __restrict__ death,
     const int32_t* __restrict__ xpos, const int32_t* __restrict__ xdeath, const float* __restrict__ xu, int KP,
@@ -889,18 +889,22 @@ static void launch_mfma(const sparsek_cfg& c, const void* q, const void* k, cons
 {
     const int BH = c.B * c.H;
     dim3 grid((nb + tail.wgs) * BH);
-#define SPK_LAUNCH(MODE, TAIL)                                                                                    \
-    hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, MODE, TAIL>), grid, dim3(256), 0, st, (const uint16_t*)q,         \
+#define SPK_LAUNCH(MODE, TAIL, WGS)                                                                               \
+    hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, MODE, TAIL, WGS>), grid, dim3(256), 0, st, (const uint16_t*)q,         \
                        (const uint16_t*)k, (const uint16_t*)v, u, tau, death, (const int32_t*)x.pos,              \
                        (const int32_t*)x.death, (const float*)x.u, x.KP, counts, (uint16_t*)o, lse, c.H, c.Gu,    \
                        c.n, c.k, c.w, c.softmax_scale, nb, BH, c.B * c.Gu, q_begin, first_valid, q_rows, tail)
+    constexpr int MOST = D == 64 ? 3 : 2;
+    const bool most = D == 64 && three_per_cu(c, q_begin);
     if (tail.wgs) {
-        if (c.gate_mode == 0) SPK_LAUNCH(0, true);
-        else if (c.gate_mode == 1) SPK_LAUNCH(1, true);
-        else SPK_LAUNCH(2, true);
-    } else if (c.gate_mode == 0) SPK_LAUNCH(0, false);
-    else if (c.gate_mode == 1) SPK_LAUNCH(1, false);
-    else SPK_LAUNCH(2, false);
+        if (c.gate_mode == 0) SPK_LAUNCH(0, true, 2);
+        else if (c.gate_mode == 1) SPK_LAUNCH(1, true, 2);
+        else if (most) SPK_LAUNCH(2, true, MOST);
+        else SPK_LAUNCH(2, true, 2);
+    } else if (c.gate_mode == 0) SPK_LAUNCH(0, false, 2);
+    else if (c.gate_mode == 1) SPK_LAUNCH(1, false, 2);
+    else if (most) SPK_LAUNCH(2, false, MOST);
+    else SPK_LAUNCH(2, false, 2);
 #undef SPK_LAUNCH
 }
 

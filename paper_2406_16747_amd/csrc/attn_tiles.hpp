@@ -177,6 +177,22 @@ struct TileTraits {
     static constexpr bool MASKC = KIND == TILE_CONT || KIND == TILE_DIAG;
 };
 
+// The forward and dQ without gates at 64 columns have an instance with room for three workgroups on a compute unit and one with room for
+// two.  Three help where there are more blocks than places for two each (512), but not below: a compute unit that gets three long blocks
+// then ends later (a document in chunks with 256 blocks each, k = w = 896: 477 us against 444).  Blocks that start before k + w have
+// shorter key sets and free their places early; where a full key set is long, two still end sooner as long as the tiles those blocks
+// lack outweigh the tiles of the blocks beyond 512 (about 7 for what every block does besides; 5/6 fits both sides of the line at 13 to 32
+// tiles).  Prefill, us with two / three: 36 heads of 2048, k = w = 128 39.5 / 36.1, 448 47.2 / 49.7, 1024 60.6 / 73.4; 38 of 2048, 512
+// 55.1 / 51.9; 48 of 2048, 700 66.9 / 62.6, 1024 68.7 / 74.7; 17 of 4096, 512 51.4 / 55.3; 20 of 4096, 1024 85.5 / 80.1.  Training moves
+// the same way.  (From 769 to 1024 blocks both take two rounds: within 3 % of each other up to 16 tiles, three up to 14 % ahead beyond.)
+// others: workgroups ahead of the blocks that hold a place for long.
+inline bool three_per_cu(const sparsek_cfg& c, int q_begin, int others = 0)
+{
+    const double BH = (double)c.B * c.H, excess = BH * (nblocks(c.n) - q_begin / QB) + others - 512;
+    const double keys = std::min((double)c.k + c.w, (double)c.n), tiles = keys / KT, lacking = q_begin ? 0 : BH * tiles * tiles / 4;
+    return excess > 0 && (keys <= 800 || excess * (tiles + 7) > lacking * 5 / 6);
+}
+
 // Workgroup -> (head, query block).  Workgroups go to the chip's 8 partitions in turn: of every 8 heads each partition gets
 // one, so that a head's blocks share an L2; late (long) blocks go first.  The blocks of up to 7 heads that are left over are
 // dealt to all partitions (dealing all blocks so where the number of heads is no multiple of 8: 25 heads of 20000 at

@@ -12,7 +12,7 @@ struct MergeArgs {
     int H, Gu, n, d4;       // d4: units of 4 columns per row
     uint16_t *dk, *dv;
     int q_begin, q_rows;    // dk and dv hold q_rows rows per head from position q_begin (0: all n)
-    int parts;              // workgroups per head (0: nothing to do here)
+    int parts;              // workgroups per head (at least 1)
 };
 
 // Workgroup `part` of m.parts on head bh.  Bound by memory: two units of each of the four parts are under way per thread.
