@@ -10,6 +10,7 @@
 #include "attn_tiles.hpp"
 #include "bwd_merge.hpp"
 #include "mask_ranges.hpp"
+#include <cmath>
 
 namespace spk {
 
@@ -1064,6 +1065,21 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dkv_kernel(
 
 __global__ __launch_bounds__(256) void abwd_merge_kernel(MergeArgs m) { abwd_merge(m, blockIdx.y, blockIdx.x); }
 
+// Workgroups per head for the merge among the score gradient's blocks.  Each holds a place of a block for some 5 us and 12 or fewer turns
+// of two units per thread: one for every four blocks, more where that many turns do not suffice for the keys that k makes selected
+// (random scores), and where blocks with a gradient leave half of the chip's 512 places free as many as fill them.  Training,
+// d = 128, us at a quarter of the blocks / now: 8 heads of 1000, k = 800, w = 900 149 / 118; 128 of 600, k = w = 100 229 / 216;
+// 50 of 700, k = 200, w = 100 168 / 144; 32 of 2048, k = w = 1024 333 / 317.  Always 512 in all: 48 of 2000, k = w = 128, d = 64,
+// straight-through 149 / 155, 12 of 8192, k = 1024, w = 64 570 / 590.
+static int merge_parts(const sparsek_cfg& c, int nb, int q_begin)
+{
+    const double BH = (double)c.B * c.H, rows = c.n - q_begin;
+    const double busy = BH * (q_begin ? nb - q_begin / QB : std::max(0, nb - (c.k + c.w) / QB));   // blocks with a gradient
+    const double selected = c.k >= rows ? rows : std::min(rows, c.k * (1.0 + std::log(rows / c.k)));
+    const double units = selected * c.d / 4, parts = std::max(nb / 4, (int)std::ceil(units / 6144));
+    return (int)std::max(1.0, std::min(busy < 256 ? std::max(parts, (512 - busy) / BH) : parts, std::ceil(units / 512)));
+}
+
 template <int D>
 static void launch_dkv_mfma(const sparsek_cfg& c, const void* q, const void* k, const void* v, const float* u,
                             const float* tau, const int32_t* death, const int32_t* elist, const int32_t* ecount,
@@ -1165,7 +1181,7 @@ int launch_attn_bwd(const sparsek_cfg& c, const void* q, const void* k, const vo
             MergeArgs m{dk32, dv32, sk32, sv32, elist, ecount, c.H, c.Gu, c.n, c.d / 4, (uint16_t*)dk, (uint16_t*)dv, q_begin,
                         q_rows, 0};
             if (share && prep && prep->zero) {   // the score gradient's main kernel takes it along
-                m.parts = std::max(1, nb / 4);
+                m.parts = merge_parts(c, nb, q_begin);
                 *merge = m;
                 shared->merge = merge;
             } else {

@@ -344,7 +344,9 @@ __device__ __forceinline__ void bwd_step(MfmaSmem<D, 16>& sm, float* colsum_prev
 
 // MERGE: every (merge_every + 1)-th group of 8 workgroups, as long as there are merge_groups of them, adds up dK and dV of the
 // attention's backward: that is bound by memory, the blocks are not.  64 heads of 8192, k = w = 512: forward and backward 1957 -> 1936 us
-// against a launch of its own; 48 heads of 2000, k = w = 128, straight-through: 163.6 -> 157.8.  (Groups of 8 leave every block on the partition it is dealt to.)
+// against a launch of its own; 48 heads of 2000, k = w = 128, straight-through: 163.6 -> 157.8.  (Groups of 8 leave every block on the partition it is dealt to.
+// merge_every is even: workgroups go to a partition's shader engines in turn, and merging ones at a period of 2, 4 or 6 groups all land on the
+// same of them.  100 heads of 1300, k = 300, w = 200, d = 128, forward and backward: 511 us at 4 groups, 505 at 6, 477 at 3.)
 template <int D, int MODE, bool MERGE>
 __global__ __launch_bounds__(256, 2) void mask_bwd_mfma_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ kk, const uint16_t* __restrict__ v,
@@ -580,9 +582,9 @@ static void launch_bwd_mfma(const sparsek_cfg& c, const void* q, const void* k, 
 {
     const int BH = c.B * c.H;
     const int groups = (nb * BH + 7) / 8, merge_groups = merge ? (merge->parts * BH + 7) / 8 : 0;
-    const int every = merge ? std::max(1, groups / merge_groups) : 1;
+    const int every = merge ? std::max(2, groups / merge_groups & ~1) : 2;
     const MergeArgs m = merge ? *merge : MergeArgs{};
-    // (the merging groups come after `every` others each: there are at least that many workgroups in all)
+    // (the merging groups come after `every` others each, an even number: there are at least that many workgroups in all)
     dim3 grid(merge ? 8 * std::max(groups + merge_groups, merge_groups * (every + 1)) : nb * BH);
 #define SPK_LAUNCH_B(MODE, MERGE)                                                                             \
     hipLaunchKernelGGL((mask_bwd_mfma_kernel<D, MODE, MERGE>), grid, dim3(256), 0, st, (const uint16_t*)q,    \
