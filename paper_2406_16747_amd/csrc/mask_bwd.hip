@@ -643,8 +643,9 @@ constexpr int SCAN_PER = 8;
 // The same for rows of up to 1024 * PER positions: everything a thread needs is fetched at the start and G stays in LDS.
 // A chain of scans on one workgroup per row, so the two round trips of G through memory were most of its time
 // (21 -> 13 us at n = 8192, 9.6 -> 4.5 us at 2000).
-// du holds the scores from position du_begin on.
-template <int PER>
+// du holds the scores from position du_begin on (0 without OFF: the offset costs the largest form 14 more spilled registers,
+// 26.8 -> 31.0 us for a row of 14336).
+template <int PER, bool OFF = true>
 __global__ __launch_bounds__(1024) void mask_bwd_scan_final_lds_kernel(const float* __restrict__ A,
                                                                         const int32_t* __restrict__ diff,
                                                                         const float* __restrict__ C,
@@ -658,6 +659,7 @@ __global__ __launch_bounds__(1024) void mask_bwd_scan_final_lds_kernel(const flo
     int* const sd = (int*)G;
     float* const sa = (float*)G + 1024 * PER;
     const int row = blockIdx.x, tid = threadIdx.x;
+    if (!OFF) du_begin = 0;
     const float* Ar = A + (size_t)row * n;
     const int32_t* dr = diff + (size_t)row * (n + 1);
     int dv[PER];
@@ -703,7 +705,7 @@ __global__ __launch_bounds__(1024) void mask_bwd_scan_final_lds_kernel(const flo
         const int j = 1024 * e + tid;
         const bool any = r[e].x <= r[e].y;
         const double hi = G[any ? r[e].y + 1 : 0], lo = G[any ? r[e].x : 0];
-        if (j < n && j >= du_begin) du[(size_t)row * (n - du_begin) + j - du_begin] = (float)((double)cv[e] - (hi - lo));
+        if (j < n && (!OFF || j >= du_begin)) du[(size_t)row * (n - du_begin) + j - du_begin] = (float)((double)cv[e] - (hi - lo));
     }
 }
 
@@ -852,8 +854,10 @@ int launch_mask_bwd(const sparsek_cfg& c, const void* q, const void* k, const vo
         hipLaunchKernelGGL(mask_bwd_scan_final_lds_kernel<2>, dim3(rows), dim3(1024), 0, st, A, diff, C, ab, c.n, q_begin, du);
     else if (c.n <= 8192)
         hipLaunchKernelGGL(mask_bwd_scan_final_lds_kernel<8>, dim3(rows), dim3(1024), 0, st, A, diff, C, ab, c.n, q_begin, du);
-    else if (c.n <= 16384)
+    else if (c.n <= 16384 && q_begin)
         hipLaunchKernelGGL(mask_bwd_scan_final_lds_kernel<16>, dim3(rows), dim3(1024), 0, st, A, diff, C, ab, c.n, q_begin, du);
+    else if (c.n <= 16384)
+        hipLaunchKernelGGL((mask_bwd_scan_final_lds_kernel<16, false>), dim3(rows), dim3(1024), 0, st, A, diff, C, ab, c.n, 0, du);
     else
         hipLaunchKernelGGL(mask_bwd_scan_final_kernel, dim3(rows), dim3(1024), 0, st, A, diff, C, ab, c.n, q_begin, G, du);
     return launch_status();
