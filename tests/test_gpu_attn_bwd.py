@@ -140,6 +140,37 @@ def test_one_call_backward_merges_every_row(B, H, Gu, n, d, k, w, gate_mode):
         assert torch.isfinite(a.float()).all() and torch.equal(a, b), name
 
 
+# Gate modes 2 and 3 at 64 columns have an instance for three workgroups per compute unit, taken with more than 512 blocks of queries
+# (here 48 heads of 12 blocks, and of 11 in a chunk), and one for two, which the smaller tests hold against the oracle: the same bits.
+@pytest.mark.parametrize("Gu,gate_mode", [(1, 2), (1, 3), (48, 3)])
+def test_many_blocks_without_gates_equal_few(Gu, gate_mode):
+    require_gpu()
+    say("three workgroups per compute unit", Gu, gate_mode)
+    H, n, d, k, w = 48, 1500, 64, 70, 90
+    inp = synth.make(3, Gu=Gu, seed=1500 + Gu, with_dO=True, B=1, H=H, n=n, d=d, k=k, w=w, dtype="bf16", qk_div=2.0)
+    Q, K, V, dO = (dev(inp[x], True) for x in ("Q", "K", "V", "dO"))
+    u = dev(inp["u"])
+
+    def run(hs):
+        q, kk, v, g = (x[:, hs].contiguous() for x in (Q, K, V, dO))
+        us = u if Gu == 1 else u[:, hs].contiguous()
+        tau, death = spk.sparsek_mask(us, k)
+        o, lse = spk.sparsek_attn_fwd(q, kk, v, us, tau, death, k, w, gate_mode, 1.0)
+        out = [o, lse, *spk.sparsek_bwd(q, kk, v, us, tau, death, o, lse, g, k, w, gate_mode, 1.0)[:3]]
+        st = spk.ChunkState(1, q.shape[1], us.shape[1], d, k, w, spk.BF16, 1400, gate_mode, 1.0, 0)
+        for sl in (slice(0, 100), slice(100, n)):
+            qc, kc, vc, gc, uc = (x[:, :, sl].contiguous() for x in (q, kk, v, g, us))
+            oc = spk.sparsek_chunk_prefill(st, qc, kc, vc, uc)
+            out += [oc, *spk.sparsek_chunk_bwd(st, qc, oc, gc)[:3]]
+        return out
+
+    many = run(slice(0, H))
+    few = [torch.cat(pair, dim=1) for pair in zip(run(slice(0, H // 2)), run(slice(H // 2, H)))]
+    torch.cuda.synchronize()
+    for i, (a, b) in enumerate(zip(many, few)):
+        assert torch.isfinite(a.float()).all() and torch.equal(a, b), i
+
+
 def test_one_call_backward_fp32_generic_path(oracle):
     """sparsek_bwd on the generic (fp32) kernels against the oracle's two gradients."""
     require_gpu()

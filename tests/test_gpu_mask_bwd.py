@@ -64,6 +64,15 @@ def test_mask_bwd_small(oracle, n, d, k, w, Gu, dtype, gate_mode):
         assert scale == 0.0
 
 
+@pytest.mark.parametrize("n", [2048, 2049, 8192, 8193, 16385])
+def test_mask_bwd_at_the_edges_of_the_last_scan(oracle, n):
+    """The last scan has a kernel for up to 2048, 8192 and 16384 positions and one beyond."""
+    require_gpu()
+    say("mask_bwd, last scan", n)
+    inp = synth.make(3, seed=n, with_dO=True, B=1, H=2, n=n, d=64, k=40, w=50, dtype="bf16", qk_div=2.0)
+    run_bwd(oracle, inp, 0)
+
+
 def test_mask_bwd_config3_recipe_reduced(oracle):
     """Config 3 recipe (drifting scores, k=w=512 at n=8192 scaled down 4x), one batch, 2 heads."""
     require_gpu()
